@@ -19,6 +19,7 @@ namespace {
 
 constexpr int kMaxSplits = 128;
 constexpr int kPrefillChunk = 16;   // caches dequantized per prefill-attention pass (two per XCD)
+constexpr int kPrefillSlots = 512; // partial results of prefill attention: two pieces of a query tile per compute unit (68 MB)
 constexpr int kWindowWeight = 6;   // cost of a chunk (<= 32 tokens) of the fp16 window in a split's share, in packed blocks
 constexpr size_t kAlign = 256;
 
@@ -67,6 +68,7 @@ struct LayerPlan {
 struct Plan {
     std::vector<LayerPlan> layer;
     size_t part_o, part_ml, prefill_scratch, prefill_select, total;
+    int prefill_slots;      // pieces of query tiles whose partial results the prefill attention may keep (at part_o)
     int NB, RC;
     int prefill_chunk;      // (batch, kv head) caches whose dequantized units the prefill scratch holds at a time
 };
@@ -94,6 +96,13 @@ Plan make_plan(const kvq_config *c)
     const size_t rows = (size_t)c->batch * c->n_q_heads;
     p.part_o = off; off = align_up(off + rows * kMaxSplits * kvq::kD * sizeof(float));
     p.part_ml = off; off = align_up(off + rows * kMaxSplits * 2 * sizeof(float));
+    // The prefill attention's partial results share that area with the decode splits': the two kinds of calls follow each
+    // other on the context's stream.  A prompt of max_tokens has `tiles` query tiles per head; they are cut (into pieces of
+    // 12 units or more, so only where there are 24) when they are too few to fill the GPU, and a cut of up to kPrefillSlots pieces is enough for that.
+    const size_t tiles = ((size_t)c->max_tokens + 255) / 256;
+    const size_t slots = p.NB < 24 ? 0 : rows * tiles * (p.NB / 12);
+    p.prefill_slots = slots < (size_t)kPrefillSlots ? (int)slots : kPrefillSlots;
+    if (off < p.part_o + p.prefill_slots * kvq::prefill_piece_bytes()) off = align_up(p.part_o + p.prefill_slots * kvq::prefill_piece_bytes());
     p.prefill_chunk = BH < (size_t)kPrefillChunk ? (int)BH : kPrefillChunk;
     p.prefill_scratch = off; off = align_up(off + (size_t)p.prefill_chunk * p.NB * kvq::prefill_unit_bytes());
     p.prefill_select = off; off = align_up(off + BH * kvq::prefill_select_bytes());       // (a pass may take all caches)
@@ -431,6 +440,9 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
     a.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)kvq::kD));
     a.scratch = c->ws + c->plan.prefill_scratch;
     a.select = nullptr;
+    a.part_o = ws_part_o(c);
+    a.part_ml = a.part_o + (size_t)c->plan.prefill_slots * 256 * kvq::kD;
+    a.part_slots = c->plan.prefill_slots;
     const bool timed = c->ev_begin && c->ev_end;
     const int BH = a.B * a.Hkv;
     // The caches are taken a chunk at a time: dequantize the chunk's packed units into the scratch area, attend.

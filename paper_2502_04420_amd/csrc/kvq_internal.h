@@ -87,6 +87,10 @@ struct PrefillArgs {
     // one record of prefill_select_bytes() per cache of the launch (written and read by the launch's kernels): which 32
     // key channels keep the remainders of their fp16 rounding, or that all do
     uint8_t *select;
+    // partial results of the pieces that a launch of few query tiles is cut into: part_slots records of 256 queries, each 128
+    // un-normalised outputs (part_o) and a pair (reference, sum) (part_ml)
+    float *part_o, *part_ml;
+    int part_slots;
 };
 
 // Work units [u0, u1) of a split: units are the quantized blocks, then the chunks of <= 32 fp16 window tokens.  The
@@ -111,6 +115,7 @@ hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);
 // ev_begin / ev_end (both or neither): receive the start and stop time stamps of the kernel's own dispatch
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
+size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache
 // decides for the caches [bh0, bh0 + n_bh) which key channels keep their low parts (a.select: their records; layers with
 // packed, per-channel quantized keys only); ev_begin (may be null) receives the kernel's start

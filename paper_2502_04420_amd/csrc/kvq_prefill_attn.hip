@@ -501,7 +501,8 @@ __device__ __forceinline__ bool softmax_unit(const float4v (&S)[2][kQT], float c
         float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
         mx = fmaxf(mx, xor_lanes(mx, 16));
         mx = fmaxf(mx, xor_lanes(mx, 32));
-        // unit 0 holds token 0, which every query sees: the reference is finite from the start
+        // a tile's first unit holds token 0, and a piece starts with a unit that lies before all of its tile's queries:
+        // every query sees a token of it, so the reference is finite from the start
         const float top = PRE ? mx + base[qt] : fmaf(mx, c, base[qt]);
         const float mn = top > m[qt] + kCalm ? top : m[qt];              // m = -inf at the start: moves
         moved |= mn != m[qt];
@@ -737,23 +738,35 @@ __device__ __forceinline__ void wait_fetches() { asm volatile("s_waitcnt vmcnt(0
 // on each other), instead of waiting for each product's result in turn.
 constexpr int kBuffers = 5;
 
+// What one work-group attends to: piece `index` of the `count` pieces that the packed units of query tile `tile` are cut
+// into (the fp16 window goes with the last one); slot: where its partial results go (count > 1).
+struct Piece { int tile, index, count, slot; };
+
+// How the tiles of a query head are cut into pieces (plan_pieces).  One word per tile, the tiles with the longest pieces
+// first: tile | pieces << 8 | pieces in front of it << 16 (whole words: the kernel reads them through the scalar unit).
+// pieces = 0: every tile is one piece.
+constexpr int kMaxCutTiles = 128;
+constexpr int kMaxPieces = 255;          // of a tile
+struct PieceTable {
+    int pieces;                          // of a query head
+    uint32_t entry[kMaxCutTiles];
+};
+
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
 // kLoCompact).
 template <int LO>
-__device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, int jq, int rank)
+__device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, int jq, const Piece &pc)
 {
     constexpr bool KLO = LO != kLoNone;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, rq = lane >> 4;
-    const int tiles = (a.n_q + kQB - 1) / kQB;
     const int gq = a.Hq / a.Hkv;
     const int bh = a.bh0 + local;
-    const int tile = tiles - 1 - rank;                           // the longest rows start first
     const int head = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + jq;   // b * Hq + query head
     const int T = 32 * a.n_blocks + a.n_res;
     const int p0 = T - a.n_q;                                    // absolute position of query 0
-    const int i0 = tile * kQB;
+    const int i0 = pc.tile * kQB;
     const int ilast = (i0 + kQB < a.n_q ? i0 + kQB : a.n_q) - 1;
     const int units = (p0 + ilast) / 32 + 1;                     // units the work-group walks through
     const int iw = i0 + kQW * wave;                              // first query of this wave
@@ -823,18 +836,19 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         for (int ct = 0; ct < 8; ct++) O[ct][qt] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
-    // ---- packed units [0, nb).  Unit u lives in buffer u % 5.  Per trip: the wave issues its fetches of units u + 3 and
+    // ---- packed units [ub, nb): the tile's, or a piece of them.  Unit u lives in buffer (u - ub) % 5.  Per trip: the wave issues its fetches of units u + 3 and
     // u + 4 (into the buffers of units u - 2 and u - 1, which everybody left at the last barrier), uses units u and u + 1
     // (taking the scores of the following unit ahead each time), then waits until its fetches have landed, and the
     // barrier makes everybody's visible.  Past the end the last unit is fetched again, into a buffer nobody reads.
-    const int nb = a.n_blocks < units ? a.n_blocks : units;
-    if (nb > 0) {
+    const int nbt = a.n_blocks < units ? a.n_blocks : units;     // the tile's
+    const int ub = nbt * pc.index / pc.count, nb = nbt * (pc.index + 1) / pc.count;
+    if (nb > ub) {
         const uint8_t *mine = a.scratch + (size_t)local * a.n_blocks * sizeof(Tiles);
         const int last = nb - 1;
         auto unit_at = [&](int u) { return mine + (size_t)(u < last ? u : last) * sizeof(Tiles); };
-        fetch_unit<LO>(unit_at(0), L[0], wave, lane);
-        fetch_unit<LO>(unit_at(1), L[1], wave, lane);
-        fetch_unit<LO>(unit_at(2), L[2], wave, lane);
+        fetch_unit<LO>(unit_at(ub), L[0], wave, lane);
+        fetch_unit<LO>(unit_at(ub + 1), L[1], wave, lane);
+        fetch_unit<LO>(unit_at(ub + 2), L[2], wave, lane);
         // The queries are first used under a condition; without this the compiler would keep their loads on its list
         // of pending ones inside the loop and wait there for everything in flight, the fetches just issued included.
 #pragma unroll
@@ -845,7 +859,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 #pragma unroll
             for (int qt = 0; qt < kQT; qt++) asm volatile("" ::"v"(Qlo[qt]));
         }
-        wait_fetches();                                         // units 0, 1 and 2 are there
+        wait_fetches();                                         // the first three units are there
         __syncthreads();
         float4v S[2][kQT], Sn[2][kQT];
         // base[qt]: what the scores waiting in S / Sn are relative to (KLO only: the reference as it stood when their
@@ -860,11 +874,11 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
             }
         };
         set_base();
-        if (0 <= wlast) score_unit<LO>(L[0], Qf, Qlo, S, n, rq, init);
+        if (ub <= wlast) score_unit<LO>(L[0], Qf, Qlo, S, n, rq, init);
         // one unit: its scores come in Sin, those of the next unit leave in Sout (the two arrays swap roles from unit to
         // unit).  Whether a unit may take the calm form is decided one unit ahead, right after its scores were issued:
         // the test then sits next to the output products of the unit before, which need nothing from it.
-        bool calm = false;                                       // unit 0 never is: the references start at -inf
+        bool calm = false;                                       // the first unit never is: the references start at -inf
         auto step = [&](int u, const Tiles &X0, const Tiles &X1, const float4v (&Sin)[2][kQT], float4v (&Sout)[2][kQT]) {
             if (u <= wlast) {
                 const bool ahead = u + 1 < nb && u + 1 <= wlast;
@@ -906,7 +920,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         };
         auto after = [](int x) { return x + 1 < kBuffers ? x + 1 : 0; };
         int b0 = 0;                                              // buffer of unit u
-        for (int u = 0; u < nb; u += 2) {
+        for (int u = ub; u < nb; u += 2) {
             const int b1 = after(b0), b2 = after(b1), b3 = after(b2), b4 = after(b3);
             fetch_unit<LO>(unit_at(u + 3), L[b3], wave, lane);  // buffers of units u - 2 and u - 1: all are done with them
             fetch_unit<LO>(unit_at(u + 4), L[b4], wave, lane);
@@ -917,8 +931,9 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
             b0 = b2;
         }
     }
-    // ---- chunks of the fp16 window, staged by the first four waves straight from the ring
-    for (int u = nb; u < units; u++) {
+    // ---- chunks of the fp16 window (with the tile's last piece), staged by the first four waves straight from the ring
+    const int uend = pc.index + 1 == pc.count ? units : nbt;
+    for (int u = nbt; u < uend; u++) {
         if (wave < kStagers) stage_window(a, bh, u, T, tid, L[0]);
         __syncthreads();
         if (u <= wlast) {
@@ -943,7 +958,13 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         l += xor_lanes(l, 16);
         l += xor_lanes(l, 32);
         const int i = iw + 16 * qt + n;
-        if (i < a.n_q) {
+        if (i < a.n_q && pc.count > 1) {
+            // a piece: un-normalised outputs and (reference, sum) of the query, for prefill_merge
+            float *o = a.part_o + (size_t)(pc.slot * kQB + (i - i0)) * kD;
+            if (rq == 0) *reinterpret_cast<float2 *>(a.part_ml + (size_t)(pc.slot * kQB + (i - i0)) * 2) = make_float2(m[qt], l);
+#pragma unroll
+            for (int ct = 0; ct < 8; ct++) *reinterpret_cast<float4v *>(o + 16 * ct + 4 * rq) = O[ct][qt];
+        } else if (i < a.n_q) {
             const float inv = 1.0f / l;
             uint16_t *row = a.out + ((size_t)head * a.n_q + i) * kD;
 #pragma unroll
@@ -957,35 +978,196 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 // KQ: the layer's keys are quantized.  Each cache of such a layer is attended in the form its selection record names
 // (without records: low parts of all channels).
 template <bool KQ>
-__global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a)
+__global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a, PieceTable pt)
 {
     const int tiles = (a.n_q + kQB - 1) / kQB;
+    const int pieces = pt.pieces ? pt.pieces : tiles;            // work-groups per query head
     const int gq = a.Hq / a.Hkv;
     // Work-groups go to the 8 XCDs in turn by their index, and each XCD has an L2 of its own: all query heads and
     // query tiles that read one (batch, kv head) cache are given to one XCD (when the count divides), so that its
-    // units are fetched from memory once and then served by that L2.
+    // units are fetched from memory once and then served by that L2.  Otherwise the pieces of all heads start in the order
+    // of their length, and as many neighbouring heads as possible share an XCD.
     int local, jq, rank;                                         // cache within this launch, query head within its group, order
+    const int heads = a.n_bh * gq;
     if (a.n_bh % 8 == 0) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3, per = gq * tiles;
+        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3, per = gq * pieces;
         local = 8 * (k / per) + xcd;
         jq = (k % per) % gq;
         rank = (k % per) / gq;
     } else {
-        local = blockIdx.x / (gq * tiles);
-        jq = (blockIdx.x / tiles) % gq;
-        rank = blockIdx.x % tiles;
+        int head = blockIdx.x % heads;
+        rank = blockIdx.x / heads;
+        if (heads % 8 == 0) head = (head & 7) * (heads >> 3) + (head >> 3);
+        local = head / gq;
+        jq = head % gq;
+    }
+    Piece pc = {tiles - 1 - rank, 0, 1, 0};                      // the longest rows start first
+    if (pt.pieces) {
+        uint32_t w = pt.entry[0];
+        for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) w = pt.entry[r];
+        pc.tile = (int)(w & 255u);
+        pc.index = rank - (int)(w >> 16);
+        pc.count = (int)((w >> 8) & 255u);
+        pc.slot = (local * gq + jq) * pieces + rank;
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact>(a, rec, local, jq, rank);
-        else attend<kLoAll>(a, rec, local, jq, rank);
+        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact>(a, rec, local, jq, pc);
+        else attend<kLoAll>(a, rec, local, jq, pc);
     } else {
-        attend<kLoNone>(a, nullptr, local, jq, rank);
+        attend<kLoNone>(a, nullptr, local, jq, pc);
     }
+}
+
+// ---- pass 3, only behind a pass 2 whose tiles were cut: merges the pieces of every tile that has more than one.  32 lanes
+// per query row, 16 bytes per lane and piece, up to eight pieces in flight.  Bound by the traffic of the partial results.
+constexpr int kMergeRows = 8;
+
+__global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, PieceTable pt)
+{
+    const uint32_t w = pt.entry[blockIdx.y];
+    const int tile = (int)(w & 255u), count = (int)((w >> 8) & 255u);
+    const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 5), lane = threadIdx.x & 31;
+    const int i = tile * kQB + row;
+    if (count < 2 || i >= a.n_q) return;
+    const int head = blockIdx.z;                                 // query head of the launch: local * gq + jq
+    const int gq = a.Hq / a.Hkv, bh = a.bh0 + head / gq;
+    const size_t row0 = ((size_t)head * pt.pieces + (w >> 16)) * kQB + row;
+    const float *po = a.part_o + row0 * kD + 4 * lane, *pm = a.part_ml + row0 * 2;
+    float M = -INFINITY, Lsum = 0.0f;
+    float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k0 = 0; k0 < count; k0 += 8) {
+        float2 ml[8];
+        float4v o[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int kk = k0 + k < count ? k0 + k : k0;         // past the end: a valid record again, weight zero
+            ml[k] = *reinterpret_cast<const float2 *>(pm + (size_t)kk * kQB * 2);
+            o[k] = *reinterpret_cast<const float4v *>(po + (size_t)kk * kQB * kD);
+        }
+        float Mn = M;
+#pragma unroll
+        for (int k = 0; k < 8; k++) Mn = fmaxf(Mn, ml[k].x);
+        const float f0 = __builtin_amdgcn_exp2f(M - Mn);         // M = -inf on the first pass: factor 0 on empty sums
+        Lsum *= f0;
+        O *= f0;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const float f = k0 + k < count ? __builtin_amdgcn_exp2f(ml[k].x - Mn) : 0.0f;
+            Lsum = fmaf(ml[k].y, f, Lsum);
+            O += o[k] * f;
+        }
+        M = Mn;
+    }
+    const float inv = 1.0f / Lsum;
+    uint16_t *out = a.out + ((size_t)((bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + head % gq) * a.n_q + i) * kD + 4 * lane;
+    __builtin_nontemporal_store(u32x2{pack2(O[0] * inv, O[1] * inv), pack2(O[2] * inv, O[3] * inv)}, reinterpret_cast<u32x2 *>(out));
+}
+
+// ---- how many pieces each tile is cut into (host).
+//
+// A compute unit holds one attention work-group (its five tile buffers fill the LDS), so a launch of few tiles leaves the
+// chip idle, and one whose longest tiles take longer than an even share of all units waits for them.  The plan compares
+// the uncut launch with cuts of the one to four longest tiles only and with cuts into pieces of 1/2, 1/3 .. 1/16 of the
+// longest tile, each by the time its pieces take when the compute units pick them up longest first.  In units of 32 tokens: kPieceCost more per piece for its queries,
+// first fetches and results; behind a cut kMergeCost for the launch that merges, and one per kPartialsPerUnit partial
+// results (130 KiB each, written and read once).  Measured on the Llama shape (K4V2, whole call in us, uncut / cut as
+// planned): 512 queries over 24576 tokens 833 / 292, 300 over 8000 297 / 129, a 2000-token prompt of 2 kv heads
+// 92 / 63, of 8 kv heads 106 / 100 (finer cuts 106..122: the partial results outweigh the even load).
+constexpr int kCUs = 256;
+constexpr int kPieceCost = 4;
+constexpr int kMergeCost = 4;
+constexpr int kPartialsPerUnit = 20;
+constexpr int kMinPiece = 12;            // units: more than a tile's diagonal and one unit in front of it (9 + 1), so that every query of the
+                                         // tile sees the whole first unit of its last piece (softmax_unit relies on it)
+
+struct Tiling { int tiles, n_blocks, p0, n_q; };
+
+int tile_units(const Tiling &g, int tile)
+{
+    const int last = (tile + 1) * kQB < g.n_q ? (tile + 1) * kQB - 1 : g.n_q - 1;
+    const int units = (g.p0 + last) / 32 + 1;
+    return g.n_blocks < units ? g.n_blocks : units;
+}
+
+int tile_pieces(int units, int length)
+{
+    const int most = units / kMinPiece < kMaxPieces ? units / kMinPiece : kMaxPieces, want = (units + length - 1) / length;
+    return want < 1 || most < 1 ? 1 : want < most ? want : most;
+}
+
+// Fills t for pieces of at most `length` units; returns the time by the rule above for `heads` query heads.
+long long cut(const Tiling &g, int heads, int length, PieceTable &t)
+{
+    // tiles by falling length of their pieces
+    int len[kMaxCutTiles], num[kMaxCutTiles], id[kMaxCutTiles];
+    for (int i = 0; i < g.tiles; i++) {
+        const int tile = g.tiles - 1 - i, units = tile_units(g, tile), count = tile_pieces(units, length);
+        const int each = (units + count - 1) / count;
+        int at = i;
+        for (; at > 0 && len[at - 1] < each; at--) { len[at] = len[at - 1]; num[at] = num[at - 1]; id[at] = id[at - 1]; }
+        len[at] = each; num[at] = count; id[at] = tile;
+    }
+    int pieces = 0, partials = 0;
+    for (int r = 0; r < g.tiles; r++) {
+        t.entry[r] = (uint32_t)(id[r] | num[r] << 8 | pieces << 16);
+        pieces += num[r];
+        partials += num[r] > 1 ? num[r] : 0;
+    }
+    t.pieces = pieces;
+    // compute units grouped by when they are free, soonest first; equal pieces go to whole groups at a time
+    struct { long long free; int count; } cu[kMaxCutTiles + 2];
+    int groups = 1;
+    cu[0] = {0, kCUs};
+    for (int r = 0; r < g.tiles; r++) {
+        long long left = (long long)num[r] * heads;
+        const int cost = len[r] + kPieceCost;
+        const long long rounds = left / kCUs;                    // whole rounds over all compute units
+        for (int i = 0; i < groups; i++) cu[i].free += rounds * cost;
+        left -= rounds * kCUs;
+        while (left > 0) {
+            const int take = left < cu[0].count ? (int)left : cu[0].count;
+            const long long until = cu[0].free + cost;
+            left -= take;
+            if (take < cu[0].count) cu[0].count -= take;
+            else { for (int i = 1; i < groups; i++) cu[i - 1] = cu[i]; groups--; }
+            int at = groups;
+            while (at > 0 && cu[at - 1].free > until) { cu[at] = cu[at - 1]; at--; }
+            if (at > 0 && cu[at - 1].free == until) {            // joins a group: close the gap again
+                cu[at - 1].count += take;
+                for (int i = at; i < groups; i++) cu[i] = cu[i + 1];
+            } else {
+                cu[at] = {until, take};
+                groups++;
+            }
+        }
+    }
+    return cu[groups - 1].free + (partials ? kMergeCost + (long long)partials * heads / kPartialsPerUnit : 0);
+}
+
+// slots: partial results the scratch area has room for
+PieceTable plan_pieces(const Tiling &g, int heads, int slots)
+{
+    PieceTable best;
+    best.pieces = 0;
+    if (g.tiles > kMaxCutTiles || g.n_blocks < 2 * kMinPiece || (long long)heads * g.tiles >= slots) return best;
+    const int longest = tile_units(g, g.tiles - 1);
+    PieceTable t;
+    long long least = cut(g, heads, longest, t);
+    auto consider = [&](int length) {
+        if (length < kMinPiece || length >= longest) return;
+        const long long time = cut(g, heads, length, t);
+        if ((long long)t.pieces * heads <= slots && time < least) { least = time; best = t; }
+    };
+    for (int k = 1; k <= 4 && k < g.tiles; k++) consider(tile_units(g, g.tiles - 1 - k));
+    for (int parts = 2; parts <= 16 && longest / parts >= kMinPiece; parts++) consider((longest + parts - 1) / parts);
+    return best;
 }
 
 }  // namespace
 
+
+size_t prefill_piece_bytes() { return kQB * (kD + 2) * sizeof(float); }
 
 size_t prefill_unit_bytes() { return sizeof(Tiles); }
 size_t prefill_select_bytes() { return sizeof(Select); }
@@ -1008,7 +1190,10 @@ hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t
 hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
     const long long tiles = (a.n_q + kQB - 1) / kQB;
-    const long long groups = tiles * a.n_bh * (a.Hq / a.Hkv);
+    const int heads = a.n_bh * (a.Hq / a.Hkv);                   // query heads of the launch
+    const Tiling tiling = {(int)tiles, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q};
+    const PieceTable pt = plan_pieces(tiling, heads, a.part_slots);
+    const long long groups = (pt.pieces ? pt.pieces : tiles) * heads;
     if (groups < 1 || groups > 0x7fffffffLL || a.n_bh < 1 || a.n_bh > 65535) return hipErrorInvalidConfiguration;
     const bool kq = a.lv.kbits < 16, vq = a.lv.vbits < 16;
     // selection records only exist where launch_prefill_select could write them
@@ -1037,11 +1222,18 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
         // a host-side setting, negligible next to a launch of milliseconds, and no process-wide state to keep
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        if (begin || ev_end) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, begin, ev_end, 0, a);
-        else hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
+        hipEvent_t end = pt.pieces ? nullptr : ev_end;           // stamped by the end of the last kernel
+        if (begin || end) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, begin, end, 0, a, pt);
+        else hipLaunchKernelGGL(kernel, grid, block, lds, s, a, pt);
         return hipGetLastError();
     };
-    return kq ? attend_launch(prefill_attention<true>) : attend_launch(prefill_attention<false>);
+    const hipError_t e = kq ? attend_launch(prefill_attention<true>) : attend_launch(prefill_attention<false>);
+    if (e != hipSuccess || !pt.pieces) return e;
+    // pass 3
+    const dim3 mgrid(kQB / kMergeRows, (unsigned)tiles, (unsigned)heads), mblock(32 * kMergeRows);
+    if (ev_end) hipExtLaunchKernelGGL(prefill_merge, mgrid, mblock, 0, s, nullptr, ev_end, 0, a, pt);
+    else hipLaunchKernelGGL(prefill_merge, mgrid, mblock, 0, s, a, pt);
+    return hipGetLastError();
 }
 
 }  // namespace kvq

@@ -107,6 +107,31 @@ def test_ragged_lengths_and_query_counts(kvq_mod, oracle_mod, T, n_q):
     g.close()
 
 
+@pytest.mark.parametrize("T,n_q,batch,hq,hkv,residual,kb", [
+    (800, 800, 1, 4, 1, 32, 4),          # 24 units: the shortest tile that is cut in two
+    (799, 640, 1, 4, 1, 0, 2),           # diagonal units among the packed ones, up to the last
+    (1500, 1500, 1, 8, 2, 32, 4),        # tiles of different piece counts
+    (2300, 300, 1, 7, 1, 32, 8),         # two tiles, many pieces each; heads that do not divide by 8
+    (2048 + 5, 257, 2, 8, 4, 32, 4),     # a tile of one query; caches that divide by 8
+    (3000, 1, 1, 2, 1, 32, 4),           # a single query
+    (1700, 900, 1, 4, 2, 500, 4),        # a window of 15 chunks, which the last pieces take along
+    (1200, 1200, 1, 4, 1, 32, 16),       # fp16 keys (raw scores)
+])
+def test_query_tiles_cut_into_pieces(kvq_mod, oracle_mod, T, n_q, batch, hq, hkv, residual, kb):
+    """Few query tiles: their packed units are attended in pieces by several work-groups and merged."""
+    w = W.Workload("pieces", 1, batch, hq, hkv, 128, T, [kb], [4], seed=700 + T, outlier_channels=3)
+    g = kvq_mod.KVQ(1, batch, hq, hkv, 128, T, [kb], [4], residual=residual)
+    o = oracle_mod.OracleCache(1, batch, hq, hkv, 128, [kb], [4], residual=residual)
+    K, V = W.kv_tokens(w, 0, 0, T)
+    g.quantize_append(0, K.cuda(), V.cuda())
+    o.quantize_append(0, K.numpy(), V.numpy())
+    q = W.prefill_queries(w, 0, n_q)
+    out = g.prefill_attention(0, q.cuda())
+    assert_prefill_close(out, o.prefill_attention(0, q.numpy())[1], "T%d nq%d" % (T, n_q))
+    assert torch.equal(out, g.prefill_attention(0, q.cuda()))            # the pieces and their order are fixed
+    g.close()
+
+
 @pytest.mark.parametrize("hq,hkv", [(1, 1), (7, 1), (8, 1), (6, 3), (28, 4)])
 def test_head_ratios(kvq_mod, oracle_mod, hq, hkv):
     w = W.Workload("heads", 1, 2, hq, hkv, 128, 32 * 5 + 9, [4], [4], seed=500 + hq, outlier_channels=2)
