@@ -597,59 +597,76 @@ __device__ __forceinline__ void output_rescale(const float (&alpha)[kQT], float4
 // (the case the per-channel grouping is made for, Section 3.2) qualify, and so do keys with a large offset on every
 // channel (the offsets are centred away); keys that are large and widely spread on many channels do not.
 constexpr float kSelectBudget = 300.0f;
-constexpr int kSelectParts = 8;
+// One work-group per cache.  Bound by the latency of its loads, so as many as fit are in flight: a wave takes a block's
+// metadata (a query's row) at a time, lane = two neighbouring channels, kSelectAhead of them outstanding.  Measured per
+// launch (8 caches): 2027 tokens 15.5 -> 10.6 us, 24576 tokens 40 -> 22 us, against four blocks in flight per thread and
+// serial loops over the 128 channels at the end.
+constexpr int kSelectWaves = 16;
+constexpr int kSelectAhead = 16;
 
 template <bool NARROW>
-__global__ __launch_bounds__(kD * kSelectParts) void prefill_select(PrefillArgs a)
+__global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs a)
 {
-    const int d = threadIdx.x & (kD - 1), part = threadIdx.x >> 7, local = blockIdx.x, bh = a.bh0 + local;
-    __shared__ float k1[kSelectParts][kD], k2[kSelectParts][kD], q2[kSelectParts][kD], w[kD], rest[kD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, local = blockIdx.x, bh = a.bh0 + local;
+    __shared__ __attribute__((aligned(16))) float k1[kSelectWaves][kD], k2[kSelectWaves][kD], q2[kSelectWaves][kD], w[kD];
+    __shared__ int above[8][kD];
+    __shared__ float rest[2];
     const float top = (float)((1 << a.lv.kbits) - 1);
-    float sk = 0.0f, sm = 0.0f;
-    for (int u0 = part; u0 < a.n_blocks; u0 += 4 * kSelectParts) {
-        float sc[4], zp[4];
-#pragma unroll
-        for (int k = 0; k < 4; k++) {                            // four blocks in flight
-            const int u = u0 + kSelectParts * k < a.n_blocks ? u0 + kSelectParts * k : u0;
-            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
-            sc[k] = NARROW ? half_bits(meta_scales16(meta)[d]) : meta[d];
-            zp[k] = half_bits(meta_zeros(meta, NARROW)[d]);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            if (u0 + kSelectParts * k < a.n_blocks) {
-                const float lo = zp[k], hi = fmaf(sc[k], top, lo);
-                sk += (lo * lo + lo * hi + hi * hi) * (1.0f / 3.0f);        // mean of x^2 over [lo, hi]
-                sm += 0.5f * (lo + hi);
-            }
-        }
-    }
     const int gq = a.Hq / a.Hkv, stride = (a.n_q + 63) / 64;
     const int head0 = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq;
     const int per_head = (a.n_q + stride - 1) / stride, samples = gq * per_head;
-    float sq = 0.0f;
-    for (int i0 = part; i0 < samples; i0 += 8 * kSelectParts) {
-        uint16_t x[8];
+    float sq[2] = {0.0f, 0.0f}, sk[2] = {0.0f, 0.0f}, sm[2] = {0.0f, 0.0f};
+    for (int i0 = wave; i0 < samples; i0 += kSelectAhead * kSelectWaves) {
+        uint32_t x[kSelectAhead];
 #pragma unroll
-        for (int k = 0; k < 8; k++) {                            // eight samples in flight
-            const int i = i0 + kSelectParts * k < samples ? i0 + kSelectParts * k : i0;
-            x[k] = a.q[((size_t)(head0 + i / per_head) * a.n_q + (size_t)(i % per_head) * stride) * kD + d];
+        for (int k = 0; k < kSelectAhead; k++) {
+            const int i = i0 + kSelectWaves * k < samples ? i0 + kSelectWaves * k : i0;
+            x[k] = *reinterpret_cast<const uint32_t *>(a.q + ((size_t)(head0 + i / per_head) * a.n_q + (size_t)(i % per_head) * stride) * kD + 2 * lane);
         }
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const float v = i0 + kSelectParts * k < samples ? half_bits(x[k]) : 0.0f;
-            sq = fmaf(v, v, sq);
+        for (int k = 0; k < kSelectAhead; k++) {
+            if (i0 + kSelectWaves * k < samples) {
+                const float v0 = half_bits(x[k] & 0xffffu), v1 = half_bits(x[k] >> 16);
+                sq[0] = fmaf(v0, v0, sq[0]);
+                sq[1] = fmaf(v1, v1, sq[1]);
+            }
         }
     }
-    k1[part][d] = sm;
-    k2[part][d] = sk;
-    q2[part][d] = sq;
+    for (int u0 = wave; u0 < a.n_blocks; u0 += kSelectAhead * kSelectWaves) {
+        u32x2 sc[kSelectAhead];                                  // (fp16 scales: one word, the other one is not used)
+        uint32_t zp[kSelectAhead];
+#pragma unroll
+        for (int k = 0; k < kSelectAhead; k++) {
+            const int u = u0 + kSelectWaves * k < a.n_blocks ? u0 + kSelectWaves * k : u0;
+            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
+            if constexpr (NARROW) sc[k][0] = *reinterpret_cast<const uint32_t *>(meta_scales16(meta) + 2 * lane);
+            else sc[k] = *reinterpret_cast<const u32x2 *>(meta + 2 * lane);
+            zp[k] = *reinterpret_cast<const uint32_t *>(meta_zeros(meta, NARROW) + 2 * lane);
+        }
+#pragma unroll
+        for (int k = 0; k < kSelectAhead; k++) {
+            if (u0 + kSelectWaves * k < a.n_blocks) {
+                const uint32_t s0 = sc[k][0], s1 = sc[k][1];
+#pragma unroll
+                for (int e = 0; e < 2; e++) {
+                    const float s = NARROW ? half_bits(e ? s0 >> 16 : s0 & 0xffffu) : __builtin_bit_cast(float, e ? s1 : s0);
+                    const float lo = half_bits(e ? zp[k] >> 16 : zp[k] & 0xffffu), hi = fmaf(s, top, lo);
+                    sk[e] += (lo * lo + lo * hi + hi * hi) * (1.0f / 3.0f);      // mean of x^2 over [lo, hi]
+                    sm[e] += 0.5f * (lo + hi);
+                }
+            }
+        }
+    }
+    *reinterpret_cast<float2 *>(&k1[wave][2 * lane]) = make_float2(sm[0], sm[1]);
+    *reinterpret_cast<float2 *>(&k2[wave][2 * lane]) = make_float2(sk[0], sk[1]);
+    *reinterpret_cast<float2 *>(&q2[wave][2 * lane]) = make_float2(sq[0], sq[1]);
     __syncthreads();
     Select *sel = reinterpret_cast<Select *>(a.select) + local;
-    if (part == 0) {
+    const int d = tid & (kD - 1), slice = tid >> 7;              // 8 slices of 16 channels for the ranks
+    if (tid < kD) {
         float tm = 0.0f, tk = 0.0f, tq = 0.0f;
 #pragma unroll
-        for (int k = 0; k < kSelectParts; k++) { tm += k1[k][d]; tk += k2[k][d]; tq += q2[k][d]; }
+        for (int k = 0; k < kSelectWaves; k++) { tm += k1[k][d]; tk += k2[k][d]; tq += q2[k][d]; }
         // the channel's centre: the mean of its blocks' midpoints, as an fp16 number (the zero-points are fp16 numbers, so
         // zero-point minus centre is exact in fp32).  What counts from here on is the keys' spread about it.
         const float centre = (float)(_Float16)(tm / (float)a.n_blocks);
@@ -659,44 +676,69 @@ __global__ __launch_bounds__(kD * kSelectParts) void prefill_select(PrefillArgs 
         w[d] = spread * (tq / (float)samples);
     }
     __syncthreads();
-    if (part == 0) {
-        const float mine = w[d];
+    const float mine = w[d];
+    int over = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const float4 o4 = *reinterpret_cast<const float4 *>(&w[16 * slice + 4 * k]);
+        const float o[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++) over += (o[e] > mine || (o[e] == mine && 16 * slice + 4 * k + e < d)) ? 1 : 0;
+    }
+    above[slice][d] = over;
+    __syncthreads();
+    if (tid < kD) {
         int rank = 0;
-        for (int o = 0; o < kD; o++) rank += (w[o] > mine || (w[o] == mine && o < d)) ? 1 : 0;
+#pragma unroll
+        for (int k = 0; k < 8; k++) rank += above[k][d];
         sel->pos[d] = rank < 32 ? (uint8_t)rank : (uint8_t)255;
         if (rank < 32) sel->chan[rank] = (uint8_t)d;
-        rest[d] = rank < 32 && mine == mine ? 0.0f : mine;       // (not a number: stays one, and the sum below with it)
+        float r = rank < 32 && mine == mine ? 0.0f : mine;       // (not a number: stays one, and the sum below with it)
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) r += xor_lanes(r, m);
+        if (lane == 0) rest[wave] = r;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float r = 0.0f;
-        for (int o = 0; o < kD; o++) r += rest[o];
-        sel->compact = r < kSelectBudget ? 1u : 0u;              // (a sum that is not a number compares false: all channels)
-    }
+    if (tid == 0) sel->compact = rest[0] + rest[1] < kSelectBudget ? 1u : 0u;    // (a sum that is not a number compares false: all channels)
 }
 
 // ---- pass 1: every packed unit of the (batch, kv head) caches [bh0, bh0 + n_bh) is dequantized once into the scratch
 // area, in the very layout the attention kernel keeps a unit in LDS (struct Tiles), so that pass 2 fetches plain copies.
 // KQ / VQ: the layer's keys / values are quantized (else fp16 rows in the code area).
+//
+// The unit is put together in LDS and goes out as whole KiB, 16 bytes per lane at consecutive addresses: bound by the writes
+// (27 KiB per unit, 21 in the compact form; its code and metadata reads are a tenth of that).  Stored to the scratch area
+// straight from the registers that hold the values (64-byte pieces of rows, 8-byte pieces of the transposed values, 2-byte
+// low parts, row padding left out) the lines were written in parts.  Measured (K4V2, compact): 16 caches of 255 units
+// 40 -> 31.5 us, 8 caches of 767 units 60 -> 45 us (4.0 TB/s of reads and writes).
+constexpr int kTileKiB = 9;
+static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * kVStride == kTileKiB * 1024 &&
+              sizeof(Tiles) == 3 * kTileKiB * 1024, "tiles of a unit are whole KiB");
+
 template <bool KQ, bool VQ>
 __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs a)
 {
     const int tid = threadIdx.x, u = blockIdx.x, local = blockIdx.y;
     const int T = 32 * a.n_blocks + a.n_res;
     __shared__ __attribute__((aligned(16))) MetaSlab M[kStagers];
+    __shared__ __attribute__((aligned(16))) Tiles tile;
     Stage st;
     load_packed<KQ, VQ>(a, a.bh0 + local, u, T, tid, st);
     const Select *rec = KQ && a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-    Tiles &dst = *reinterpret_cast<Tiles *>(a.scratch + ((size_t)local * a.n_blocks + u) * sizeof(Tiles));
-    store_packed<KQ, VQ>(a, tid, st, dst, M[tid >> 6], rec);
+    store_packed<KQ, VQ>(a, tid, st, tile, M[tid >> 6], rec);
+    __syncthreads();
+    const int lo_pieces = !KQ ? 0 : rec && rec->compact != 0 ? kLoPieces : kTileKiB;
+    uint8_t *dst = a.scratch + ((size_t)local * a.n_blocks + u) * sizeof(Tiles);
+    const uint8_t *src = reinterpret_cast<const uint8_t *>(&tile);
+    for (int p = tid >> 6; p < 2 * kTileKiB + lo_pieces; p += kStagers) {
+        const int off = 1024 * (p < kTileKiB + lo_pieces ? p : p - lo_pieces + kTileKiB) + 16 * (tid & 63);      // K^, low parts, then V^
+        *reinterpret_cast<u32x4 *>(dst + off) = *reinterpret_cast<const u32x4 *>(src + off);
+    }
 }
 
 // A unit goes from the scratch area into an LDS buffer without passing through registers: a wave issues
 // global-to-LDS loads of 1 KiB each (64 lanes x 16 bytes, which land at consecutive LDS addresses from the base
 // that M0 holds).  The three tiles of a unit are 9 KiB each, so a piece never straddles two of them.
-constexpr int kTileKiB = 9;
-static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * kVStride == kTileKiB * 1024 &&
-              sizeof(Tiles) == 3 * kTileKiB * 1024, "tiles of a unit are whole KiB");
 
 __device__ __forceinline__ void fetch_piece(const uint8_t *unit, uint32_t offset_of_lane, uint32_t lds_base)
 {
@@ -1177,7 +1219,7 @@ size_t prefill_select_bytes() { return sizeof(Select); }
 hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin)
 {
     if (!a.select || a.lv.kbits >= 16 || a.lv.kpt || a.n_blocks < 1 || a.n_bh < 1) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)a.n_bh), block(kD * kSelectParts);
+    const dim3 grid((unsigned)a.n_bh), block(64 * kSelectWaves);
     auto launch = [&](auto kernel) {
         if (ev_begin) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev_begin, nullptr, 0, a);
         else hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
