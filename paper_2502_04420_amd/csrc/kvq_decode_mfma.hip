@@ -278,6 +278,10 @@ __device__ __forceinline__ void await_loads_either(CodeRegs<BITS> &r, int more_b
 #undef KVQ_EITHER
 }
 
+// The (empty) loads of a group without blocks have landed.  The registers are not named: naming them on a second code path
+// would make the compiler copy them while the loads are still writing.
+__device__ __forceinline__ void drain_unused() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // a block outside the streaming loop: issue and wait for everything
 template <int BITS, bool NARROW>
 __device__ __forceinline__ void load_block_now(const BlockStream &S, int blk, CodeRegs<BITS> &r)
@@ -375,7 +379,6 @@ struct KeyState {
 template <int GQ>
 struct ValueState {
     float4v O[8];                  // un-normalised output tile per 16-channel block (scaled by 2^(14 - ev - shift))
-    float oF[GQ][2];               // fp16-row contributions, channels 2*lane, 2*lane+1
     float accz[GQ];                // sum_t p_t z_tg for group rq, tokens 2n, 2n+1
     int ev;                        // largest value-scale exponent so far
 };
@@ -493,21 +496,126 @@ __device__ __forceinline__ void scores_packed_per_token(const CodeRegs<KB> &blk,
     wave_lds_sync();          // the metadata tile is rewritten for the next block
 }
 
-// scores of up to 32 fp16 rows (16-bit region or window ring); rows 2j and 2j + 1 of the query tile are equal
+// ---- fp16 rows (16-bit layers, window chunks): 32 tokens of a wave's tensor in registers
+
+// keys: tokens n and 16 + n, channels 32 cb + 8 rq .. + 7
+struct KeyRows { u32x4 lo[4], hi[4]; };
+// values: tokens 16 half + i, channels 4 (lane & 31) .. + 3 (half = lane >> 5): one load fetches two whole rows
+struct ValueRows { u32x2 row[16]; };
+
+// One unit (32 rows of 256 bytes) of a 16-bit layer.  Issued unconditionally, past the end of a range through a resource
+// with no bytes in range (no traffic, zeros): the number of loads behind a unit is then the same on every path, and the
+// compiler's waits leave the next unit's loads in flight.
+typedef __amdgpu_buffer_rsrc_t RowStream;
+__device__ __forceinline__ RowStream row_stream(const uint8_t *base, bool real, int unit)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base) + (size_t)unit * block_code_bytes(16), 0, real ? block_code_bytes(16) : 0, 0x00020000);
+}
+constexpr int kNonTemporal = 2;          // cache policy bit of the buffer loads: 16-bit layers stream by like the packed codes
+
+__device__ __forceinline__ void fetch_unit(const uint8_t *base, bool real, int unit, int lane, KeyRows &x)
+{
+    const RowStream r = row_stream(base, real, unit);
+    const int off = (lane & 15) * (kD * 2) + (lane >> 4) * 16;
+#pragma unroll
+    for (int cb = 0; cb < 4; cb++) {
+        x.lo[cb] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 64 * cb, 0, kNonTemporal);
+        x.hi[cb] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * kD * 2 + 64 * cb, 0, kNonTemporal);
+    }
+}
+__device__ __forceinline__ void fetch_unit(const uint8_t *base, bool real, int unit, int lane, ValueRows &x)
+{
+    const RowStream r = row_stream(base, real, unit);
+    const int off = (lane >> 5) * (16 * kD * 2) + (lane & 31) * 8;
+#pragma unroll
+    for (int i = 0; i < 16; i++) x.row[i] = __builtin_amdgcn_raw_buffer_load_b64(r, off + i * (kD * 2), 0, kNonTemporal);
+}
+
+// A chunk of nt <= 32 window tokens from position pos0 on: rows of the ring of RC >= 32 slots, except for the token of a fused
+// append (the chunk's last one: new_row), which is not in the ring yet.  Rows past the end are the last one again.
+struct WindowChunk {
+    const uint16_t *ring, *new_row;      // new_row: null unless the chunk's last token is the appended one
+    int slot0, RC, nt;
+    __device__ __forceinline__ const uint16_t *row(int t) const
+    {
+        const int tc = t < nt ? t : nt - 1;
+        int slot = slot0 + tc;
+        slot = slot >= RC ? slot - RC : slot;
+        const uint16_t *p = ring + (size_t)slot * kD;
+        return new_row && tc == nt - 1 ? new_row : p;
+    }
+};
+
+__device__ __forceinline__ WindowChunk window_chunk(const DecodeArgs &a, bool values, int bh, int chunk)
+{
+    WindowChunk w;
+    const int pos0 = a.n_blocks * kG + chunk * 32, left = a.n_res - chunk * 32;
+    const uint16_t *fresh = values ? a.v_new : a.k_new;
+    w.nt = left < 32 ? left : 32;
+    w.ring = (values ? a.lv.vres : a.lv.kres) + (size_t)bh * a.RC * kD;
+    w.RC = a.RC;
+    w.slot0 = pos0 % a.RC;
+    w.new_row = fresh && a.new_pos == pos0 + w.nt - 1 ? fresh + (size_t)bh * kD : nullptr;
+    return w;
+}
+
+// the chunk's appended row goes into the ring for later launches (nothing reads that slot in this launch)
+__device__ __forceinline__ void keep_new_row(const WindowChunk &w, int lane)
+{
+    if (w.new_row) {
+        int slot = w.slot0 + w.nt - 1;
+        slot = slot >= w.RC ? slot - w.RC : slot;
+        reinterpret_cast<uint32_t *>(const_cast<uint16_t *>(w.ring) + (size_t)slot * kD)[lane] = reinterpret_cast<const uint32_t *>(w.new_row)[lane];
+    }
+}
+
+__device__ __forceinline__ void fetch_chunk(const WindowChunk &w, int lane, KeyRows &x)
+{
+    asm volatile("" : "+v"(lane));                               // (nothing of the addresses is worked out ahead or kept)
+    const uint16_t *row0 = w.row(lane & 15) + 8 * (lane >> 4), *row1 = w.row(16 + (lane & 15)) + 8 * (lane >> 4);
+#pragma unroll
+    for (int cb = 0; cb < 4; cb++) {
+        x.lo[cb] = *reinterpret_cast<const u32x4 *>(row0 + 32 * cb);
+        x.hi[cb] = *reinterpret_cast<const u32x4 *>(row1 + 32 * cb);
+    }
+}
+// values: the ring's rows by 32-bit offsets; the appended row comes in `fresh` and takes its place in settle_chunk
+__device__ __forceinline__ void fetch_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x2 &fresh)
+{
+    const uint8_t *ring = reinterpret_cast<const uint8_t *>(w.ring);
+    asm volatile("" : "+v"(lane));
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int t = 16 * (lane >> 5) + i, tc = t < w.nt ? t : w.nt - 1;
+        int slot = w.slot0 + tc;
+        slot = slot >= w.RC ? slot - w.RC : slot;
+        x.row[i] = *reinterpret_cast<const u32x2 *>(ring + (uint32_t)(slot * (kD * 2) + 8 * (lane & 31)));
+    }
+    fresh = *reinterpret_cast<const u32x2 *>((w.new_row ? w.new_row : w.ring + (size_t)w.slot0 * kD) + 4 * (lane & 31));
+}
+__device__ __forceinline__ void settle_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x2 fresh)
+{
+    if (w.new_row) {
+        asm volatile("" : "+v"(lane));
+#pragma unroll
+        for (int i = 0; i < 16; i++) {                           // (rows past the end too: the ring's may never have been written)
+            const bool mine = 16 * (lane >> 5) + i >= w.nt - 1;
+            x.row[i] = u32x2{mine ? fresh[0] : x.row[i][0], mine ? fresh[1] : x.row[i][1]};
+        }
+    }
+}
+
+// scores of nt fp16 rows; rows 2j and 2j + 1 of the query tile are equal
 template <int GQ>
-__device__ __forceinline__ void scores_rows(const uint16_t *row0, const uint16_t *row1, int nt, const QueryRegs<GQ> &Q,
-                                            int lane, float (&s)[2][2])
+__device__ __forceinline__ void scores_rows(const KeyRows &x, int nt, const QueryRegs<GQ> &Q, int lane, float (&s)[2][2])
 {
     const int n = lane & 15, rq = lane >> 4;
     float4v S0 = {0.0f, 0.0f, 0.0f, 0.0f}, S1 = S0;
 #pragma unroll
     for (int cb = 0; cb < 4; cb++) {
-        uint4 x0 = make_uint4(0, 0, 0, 0), x1 = x0;
-        if (n < nt) x0 = *reinterpret_cast<const uint4 *>(row0 + 32 * cb + 8 * rq);
-        if (16 + n < nt) x1 = *reinterpret_cast<const uint4 *>(row1 + 32 * cb + 8 * rq);
         const half8 Aop = *reinterpret_cast<const half8 *>(Q.Aq + n * (kD + 8) + 32 * cb + 8 * rq);
-        S0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, as_half8(x0.x, x0.y, x0.z, x0.w), S0, 0, 0, 0);
-        S1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, as_half8(x1.x, x1.y, x1.z, x1.w), S1, 0, 0, 0);
+        S0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, __builtin_bit_cast(half8, x.lo[cb]), S0, 0, 0, 0);
+        S1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, __builtin_bit_cast(half8, x.hi[cb]), S1, 0, 0, 0);
     }
 #pragma unroll
     for (int hh = 0; hh < 2; hh++) {
@@ -562,7 +670,7 @@ __device__ __forceinline__ void apply_rescale(ValueState<GQ> &W, const PairLds<G
 #pragma unroll
         for (int j = 0; j < GQ; j++) {
             const float aj = L.alpha[buf][j];
-            W.oF[j][0] *= aj; W.oF[j][1] *= aj; W.accz[j] *= aj;
+            W.accz[j] *= aj;
         }
     }
 }
@@ -607,32 +715,44 @@ __device__ __forceinline__ void output_packed(const CodeRegs<VB> &blk, uint32_t 
     }
 }
 
-// output contribution of nt fp16 rows: lane owns channels 2*lane, 2*lane+1
+// output contribution of 32 fp16 rows (numerators of rows past the end are zero): this lane's 4 channels over the 16 tokens
+// of its half; the halves are added at the end (add_row_outputs)
 template <int GQ>
-__device__ __forceinline__ void output_rows(const uint16_t *base, int pos0, int nt, int ring, const uint16_t *new_row, int new_pos,
-                                            ValueState<GQ> &W, const PairLds<GQ> &L, int buf, int lane)
+__device__ __forceinline__ void output_rows(const ValueRows &x, float (&oF)[GQ][4], const PairLds<GQ> &L, int buf, int lane)
 {
-    // eight rows are fetched at a time with independent loads (a token-by-token loop pays one memory latency per token)
-    for (int t0 = 0; t0 < nt; t0 += 8) {
-        uint32_t x[8];
+    const int half = lane >> 5;
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            const int pos = pos0 + (t0 + k < nt ? t0 + k : t0);        // past the end: a valid row again, not used
-            const uint16_t *row = base + (size_t)(ring ? pos % ring : pos) * kD;
-            if (new_row && pos == new_pos) row = new_row;              // the token of a fused append is not in the ring yet
-            x[k] = *reinterpret_cast<const uint32_t *>(row + 2 * lane);
-        }
+    for (int i0 = 0; i0 < 16; i0 += 4) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            if (t0 + k < nt) {
-                const float v0 = half_lo(x[k]), v1 = half_hi(x[k]);
+        for (int j = 0; j < GQ; j++) {
+            const float4 p4 = *reinterpret_cast<const float4 *>(&L.P[buf][j][16 * half + i0]);
+            const float p[4] = {p4.x, p4.y, p4.z, p4.w};
 #pragma unroll
-                for (int j = 0; j < GQ; j++) {
-                    const float pj = L.P[buf][j][t0 + k];
-                    W.oF[j][0] = fmaf(pj, v0, W.oF[j][0]);
-                    W.oF[j][1] = fmaf(pj, v1, W.oF[j][1]);
-                }
+            for (int k = 0; k < 4; k++) {
+                const uint32_t w0 = x.row[i0 + k][0], w1 = x.row[i0 + k][1];
+                oF[j][0] = fmaf(p[k], half_lo(w0), oF[j][0]);
+                oF[j][1] = fmaf(p[k], half_hi(w0), oF[j][1]);
+                oF[j][2] = fmaf(p[k], half_lo(w1), oF[j][2]);
+                oF[j][3] = fmaf(p[k], half_hi(w1), oF[j][3]);
             }
+            // (left alone, the compiler fetches all numerators up front, puts the sums off until after the next loads and spills)
+            asm volatile("" : "+v"(oF[j][0]), "+v"(oF[j][1]), "+v"(oF[j][2]), "+v"(oF[j][3]));
+            if (j % 4 == 3) asm volatile("" ::: "memory");
+        }
+    }
+}
+
+// shrink: what the outputs of the blocks before the rows (already out of the registers) are to be multiplied by
+template <int GQ>
+__device__ __forceinline__ void rescale_rows(float (&oF)[GQ][4], float (&shrink)[GQ], const PairLds<GQ> &L, int buf)
+{
+    if (__builtin_amdgcn_readfirstlane(L.rescale[buf][0])) {
+#pragma unroll
+        for (int j = 0; j < GQ; j++) {
+            const float aj = L.alpha[buf][j];
+            shrink[j] *= aj;
+#pragma unroll
+            for (int k = 0; k < 4; k++) oF[j][k] *= aj;
         }
     }
 }
@@ -641,8 +761,8 @@ __device__ __forceinline__ void output_rows(const uint16_t *base, int pos0, int 
 
 // Waves per SIMD the register allocation must leave room for: the host plans 2048 groups (4 waves per SIMD) for code
 // widths up to 8 bits per key + value element and 1024 (2) beyond; the wider instantiations may
-// use the registers that fewer resident waves leave free instead of spilling.
-template <int KB, int VB> constexpr int resident_waves() { return (KB < 16 && VB < 16) ? (KB + VB <= 8 ? 4 : 2) : 4; }
+// use the registers that fewer resident waves leave free instead of spilling (16-bit layers: two units of rows).
+template <int KB, int VB> constexpr int resident_waves() { return KB + VB <= 8 ? 4 : 2; }
 
 template <int KB, int VB, int GQ, bool NARROW, bool KPT>
 __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(DecodeArgs a)
@@ -654,6 +774,9 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     // tokens: two or three blocks behind are 3-5 % slower for 4- and 2-bit codes and no faster for 8-bit ones: the
     // memory system is the queue here, more requests in it only wait longer).
     constexpr int DK = 2, DV = 2;
+    // a group without blocks asks for its window rows before anything else (not where a tile of 8 heads has to make do with a
+    // quarter of a SIMD's registers: it would spill)
+    constexpr bool kEarlyRows = !(kFast && GQ == 8 && resident_waves<KB, VB>() == 4);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
     const int n = lane & 15, rq = lane >> 4;
@@ -678,6 +801,7 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     const int f1 = kFast ? (u1 < a.n_blocks ? u1 : a.n_blocks) : u0;     // phase 1 = [u0, f1), phase 2 = [f1, u1)
     const int f1c = f1 > u0 ? f1 : u0;
     const int n1 = f1c - u0, n2 = u1 - f1c;
+    const int n2p = !kFast && f1c < a.n_blocks ? (u1 < a.n_blocks ? u1 : a.n_blocks) - f1c : 0;      // blocks among phase 2's units
     const size_t blk0 = (size_t)bh * a.NB;       // first block of this cache in the layer's arrays
     // cache block number of the i-th phase-1 unit (0 <= i < n1).
     // Every group starts its sweep at a different place of its range and wraps around: groups advance at the
@@ -686,6 +810,12 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     auto blk1 = [&](int i) {
         const int r = i + rot;
         return u0 + (r < n1 ? r : r - n1);
+    };
+    // cache block number of the i-th of phase 2's blocks (16-bit tensors), with the same rotation
+    const int rot2 = n2p > 0 ? (int)(((uint32_t)bh * 40503u + (uint32_t)split * 9973u) % (uint32_t)n2p) : 0;
+    auto blk2 = [&](int i) {
+        const int r = i + rot2;
+        return f1c + (r < n2p ? r : r - n2p);
     };
     auto blk1c = [&](int i) { return i < n1 ? blk1(i) : 0; };     // past the range: any number, the load is an empty one
     // byte offset, in the cache's exponent array, of the word this lane holds for the chunk that starts at step c0
@@ -795,6 +925,11 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
                     reinterpret_cast<uint4 *>(&L.Ak[row0][0])[i] = make_uint4(0, 0, 0, 0);
             }
         }
+        // fp16 rows this wave starts with: a group without packed blocks asks for them here, one with packed blocks behind
+        // those (16-bit keys: a pipeline of their own)
+        KeyRows rows;
+        const int first_chunk = f1c + n2p - a.n_blocks, chunks = n2 - n2p;
+        if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);
         wg_barrier();                                   // the value wave has written the exact-fp16 query tile
         KeyState<GQ> W;
 #pragma unroll
@@ -804,85 +939,101 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
             // DK register stages in rotation: stage d is consumed while the loads of the next DK - 1 units (as far as
             // there are any) are in flight.
             // The sweep goes in chunks of kChunk steps (one register of exponent words each); a chunk starts at stage 0.
-            await_exponents<(DK - 1) * NLK>(kexp);                         // the first chunk's: issued ahead of the first blocks
-            const PrioritySteps prio = priority_steps(n1);
-            if (n1 > 0) __builtin_amdgcn_s_setprio(3);
-            for (int c0 = 0; c0 < n1; c0 += kChunk) {
-                if (c0 > 0) {
-                    issue_exponents(kexp, KS, exp_offset(c0));
-                    await_exponents<0>(kexp);
-                }
-                const int cend = c0 + kChunk < n1 ? c0 + kChunk : n1;
-                for (int z0 = c0; z0 < cend; z0 += kZChunk) {
-                    const int zend = z0 + kZChunk < cend ? z0 + kZChunk : cend;
-                    if constexpr (kZB) {
-                        // The chunk's zero-points were asked for a chunk ago (the first chunk's ahead of the first
-                        // blocks): they are older than every load still allowed to be pending here.  Form the chunk's
-                        // terms, then ask for the next chunk's; those four loads go out in front of the first step's
-                        // block loads, so that step alone waits with four more loads allowed behind its block.
-                        await_zero_points<(DK - 1) * NLK>(zb);
-                        zero_point_terms<GQ>(zb, Q, L, lane);
-                        wave_lds_sync();
-                        issue_zero_points(zb, KS, z0 + kZChunk < n1, zero_point_offset(z0 + kZChunk));
-                    }
-                    bool more = true;
-                    for (int i = z0; more;) {
+            auto drain = [&]() {
+                // the empty loads past the end of the range, before their registers go back to the compiler
 #pragma unroll
-                        for (int d = 0; d < DK; d++) {
-                            if (more) {
-                                priority_at_step(i, prio);
-                                issue_block<KB, NARROW, !kZB>(KS, i + DK - 1 < n1, blk1c(i + DK - 1), kr[(d + DK - 1) % DK]);
-                                if constexpr (kZB) await_loads_either<(DK - 1) * NLK, 4, KB>(kr[d], __builtin_amdgcn_readfirstlane(i == z0 ? 1 : 0));
-                                else await_block<KB, DK>(kr[d]);
-                                const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)kexp, i - c0);
-                                if constexpr (KPT) scores_packed_per_token<KB, GQ, NARROW>(kr[d], Q, L, lane, s);
-                                else if constexpr (kZB)
-                                    scores_packed<KB, GQ, NARROW, true>(kr[d], ew, Q, L, lane, s, *reinterpret_cast<const float2 *>(&L.Zt[i - z0][rq][0]));
-                                else scores_packed<KB, GQ, NARROW>(kr[d], ew, Q, L, lane, s);
-                                softmax_publish<GQ>(s, W, L, i & 1, lane);
-                                wg_barrier();
-                                more = ++i < zend;
+                for (int d = 0; d < DK; d++) await_loads<0, KB>(kr[d]);
+                await_exponents<0>(kexp);
+                if constexpr (kZB) await_zero_points<0>(zb);
+            };
+            if (n1 > 0) {
+                await_exponents<(DK - 1) * NLK>(kexp);                         // the first chunk's: issued ahead of the first blocks
+                const PrioritySteps prio = priority_steps(n1);
+                __builtin_amdgcn_s_setprio(3);
+                for (int c0 = 0; c0 < n1; c0 += kChunk) {
+                    if (c0 > 0) {
+                        issue_exponents(kexp, KS, exp_offset(c0));
+                        await_exponents<0>(kexp);
+                    }
+                    const int cend = c0 + kChunk < n1 ? c0 + kChunk : n1;
+                    for (int z0 = c0; z0 < cend; z0 += kZChunk) {
+                        const int zend = z0 + kZChunk < cend ? z0 + kZChunk : cend;
+                        if constexpr (kZB) {
+                            // The chunk's zero-points were asked for a chunk ago (the first chunk's ahead of the first
+                            // blocks): they are older than every load still allowed to be pending here.  Form the chunk's
+                            // terms, then ask for the next chunk's; those four loads go out in front of the first step's
+                            // block loads, so that step alone waits with four more loads allowed behind its block.
+                            await_zero_points<(DK - 1) * NLK>(zb);
+                            zero_point_terms<GQ>(zb, Q, L, lane);
+                            wave_lds_sync();
+                            issue_zero_points(zb, KS, z0 + kZChunk < n1, zero_point_offset(z0 + kZChunk));
+                        }
+                        bool more = true;
+                        for (int i = z0; more;) {
+#pragma unroll
+                            for (int d = 0; d < DK; d++) {
+                                if (more) {
+                                    priority_at_step(i, prio);
+                                    issue_block<KB, NARROW, !kZB>(KS, i + DK - 1 < n1, blk1c(i + DK - 1), kr[(d + DK - 1) % DK]);
+                                    if constexpr (kZB) await_loads_either<(DK - 1) * NLK, 4, KB>(kr[d], __builtin_amdgcn_readfirstlane(i == z0 ? 1 : 0));
+                                    else await_block<KB, DK>(kr[d]);
+                                    const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)kexp, i - c0);
+                                    if constexpr (KPT) scores_packed_per_token<KB, GQ, NARROW>(kr[d], Q, L, lane, s);
+                                    else if constexpr (kZB)
+                                        scores_packed<KB, GQ, NARROW, true>(kr[d], ew, Q, L, lane, s, *reinterpret_cast<const float2 *>(&L.Zt[i - z0][rq][0]));
+                                    else scores_packed<KB, GQ, NARROW>(kr[d], ew, Q, L, lane, s);
+                                    softmax_publish<GQ>(s, W, L, i & 1, lane);
+                                    wg_barrier();
+                                    more = ++i < zend;
+                                }
                             }
                         }
                     }
                 }
+                __builtin_amdgcn_s_setprio(0);
+                drain();
+                if (chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);    // (here: on no path is `rows` held over the loop)
+            } else {
+                drain_unused();
+                if (!kEarlyRows && chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);
             }
-            __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-            for (int d = 0; d < DK; d++) await_loads<0, KB>(kr[d]);      // the empty loads past the end of the range, before
-            await_exponents<0>(kexp);                                    // their registers go back to the compiler
-            if constexpr (kZB) await_zero_points<0>(zb);
         }
-        for (int i = 0; i < n2; i++) {
-            const int u = f1c + i;
-            const bool packed = u < a.n_blocks;
-            const int pos0 = packed ? u * kG : a.n_blocks * kG + (u - a.n_blocks) * 32;
-            const int nt = packed ? 32 : (a.n_res - (u - a.n_blocks) * 32 < 32 ? a.n_res - (u - a.n_blocks) * 32 : 32);
-            bool k_rows = true;
-            if constexpr (KB < 16) if (packed) {
-                k_rows = false;
+        if constexpr (KB == 16) {
+            // 16-bit keys: a unit's rows are on their way while the one before is worked on
+            const uint8_t *base = a.lv.kcode + blk0 * block_code_bytes(16);
+            KeyRows next;
+            if (n2p > 0) fetch_unit(base, true, blk2(0), lane, rows);
+            auto step = [&](int i, const KeyRows &x, KeyRows &y) {
+                fetch_unit(base, i + 1 < n2p, blk2(i + 1), lane, y);
+                scores_rows<GQ>(x, 32, Q, lane, s);
+                softmax_publish<GQ>(s, W, L, i & 1, lane);
+                wg_barrier();
+            };
+            for (int i = 0; i < n2p; i += 2) {
+                step(i, rows, next);
+                if (i + 1 < n2p) step(i + 1, next, rows);
+            }
+        } else {
+            // quantized keys next to 16-bit values
+            for (int i = 0; i < n2p; i++) {
+                const int u = blk2(i);
                 CodeRegs<KB> r;
                 clear_regs(r);
                 load_block_now<KB, NARROW>(KS, u, r);
                 if constexpr (KPT) scores_packed_per_token<KB, GQ, NARROW>(r, Q, L, lane, s);
                 else scores_packed<KB, GQ, NARROW>(r, a.lv.bexp[blk0 + u], Q, L, lane, s);
+                softmax_publish<GQ>(s, W, L, i & 1, lane);
+                wg_barrier();
             }
-            if (k_rows) {
-                const uint16_t *kbase = packed ? reinterpret_cast<const uint16_t *>(a.lv.kcode) + (size_t)bh * a.NB * kG * kD
-                                               : a.lv.kres + (size_t)bh * a.RC * kD;
-                const int p0 = pos0 + n, p1 = pos0 + 16 + n;
-                const uint16_t *row0 = kbase + (size_t)(packed ? p0 : p0 % a.RC) * kD, *row1 = kbase + (size_t)(packed ? p1 : p1 % a.RC) * kD;
-                if (!packed && a.k_new && a.new_pos >= pos0 && a.new_pos < pos0 + nt) {
-                    // fused append: this chunk holds the new token.  Read its row from the caller's tensor and
-                    // put it into the window ring for later launches (nothing reads that slot in this launch).
-                    const uint16_t *src = a.k_new + (size_t)bh * kD;
-                    if (p0 == a.new_pos) row0 = src;
-                    if (p1 == a.new_pos) row1 = src;
-                    reinterpret_cast<uint32_t *>(a.lv.kres + ((size_t)bh * a.RC + a.new_pos % a.RC) * kD)[lane] = reinterpret_cast<const uint32_t *>(src)[lane];
-                }
-                scores_rows<GQ>(row0, row1, nt, Q, lane, s);
-            }
-            softmax_publish<GQ>(s, W, L, (n1 + i) & 1, lane);
+        }
+        if (n2p > 0 && chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);
+#pragma unroll 1
+        for (int i = 0; i < chunks; i++) {
+            const WindowChunk w = window_chunk(a, false, bh, first_chunk + i);
+            keep_new_row(w, lane);
+            scores_rows<GQ>(rows, w.nt, Q, lane, s);
+            if (i + 1 < chunks) fetch_chunk(window_chunk(a, false, bh, first_chunk + i + 1), lane, rows);
+            softmax_publish<GQ>(s, W, L, (n1 + n2p + i) & 1, lane);
             wg_barrier();
         }
         wg_barrier();                                   // the value wave consumes the last unit
@@ -917,6 +1068,9 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
 #pragma unroll
             for (int d = 0; d < DV - 1; d++) issue_block<VB, NARROW>(VS, d < n1, blk1c(d), vr[d]);
         }
+        ValueRows rows;                                 // (as in the key wave)
+        u32x2 fresh;
+        if constexpr (VB == 16) fetch_unit(a.lv.vcode + blk0 * block_code_bytes(16), n2p > 0, n2p > 0 ? blk2(0) : 0, lane, rows);
 #pragma unroll
         for (int pass = 0; pass < 4; pass++) *reinterpret_cast<uint4 *>(&aq_lds[4 * pass + rq][8 * n]) = qx[pass];
         {
@@ -927,103 +1081,149 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         }
         Q.vw0 = code_weight_inv<VB < 16 ? VB : 8>((2 * n) & 7);
         Q.vw1 = code_weight_inv<VB < 16 ? VB : 8>((2 * n + 1) & 7);
+        const int first_chunk = f1c + n2p - a.n_blocks, chunks = n2 - n2p;
+        if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
         wg_barrier();                                   // query tile handed to the key wave
         ValueState<GQ> W;
 #pragma unroll
         for (int cblk = 0; cblk < 8; cblk++) W.O[cblk] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int j = 0; j < GQ; j++) { W.oF[j][0] = W.oF[j][1] = 0.0f; W.accz[j] = 0.0f; }
+        for (int j = 0; j < GQ; j++) W.accz[j] = 0.0f;
         W.ev = -100;
         wg_barrier();                                   // the key wave has produced the first unit
         if constexpr (kFast) {
-            await_exponents<(DV - 1) * block_loads<VB>()>(vexp);
-            const PrioritySteps prio = priority_steps(n1);
-            if (n1 > 0) __builtin_amdgcn_s_setprio(3);
-            for (int c0 = 0; c0 < n1; c0 += kChunk) {
-                if (c0 > 0) {
-                    issue_exponents(vexp, VS, exp_offset(c0));
-                    await_exponents<0>(vexp);
-                }
-                const int cend = c0 + kChunk < n1 ? c0 + kChunk : n1;
-                bool more = true;
-                for (int i = c0; more;) {
+            auto drain = [&]() {
 #pragma unroll
-                    for (int d = 0; d < DV; d++) {
-                        if (more) {
-                            priority_at_step(i, prio);
-                            issue_block<VB, NARROW>(VS, i + DV - 1 < n1, blk1c(i + DV - 1), vr[(d + DV - 1) % DV]);
-                            await_block<VB, DV>(vr[d]);
-                            const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)vexp, i - c0);
-                            // (always true here; as a run-time test it keeps the rarely taken re-base and rescale
-                            // paths out of line, without it the register count of the loop grows by half)
-                            if (i < n1) {
-                                apply_rescale<GQ>(W, L, i & 1, lane);
-                                output_packed<VB, GQ, NARROW>(vr[d], ew, Q, W, L, i & 1, lane);
+                for (int d = 0; d < DV; d++) await_loads<0, VB>(vr[d]);
+                await_exponents<0>(vexp);
+            };
+            if (n1 > 0) {
+                await_exponents<(DV - 1) * block_loads<VB>()>(vexp);
+                const PrioritySteps prio = priority_steps(n1);
+                __builtin_amdgcn_s_setprio(3);
+                for (int c0 = 0; c0 < n1; c0 += kChunk) {
+                    if (c0 > 0) {
+                        issue_exponents(vexp, VS, exp_offset(c0));
+                        await_exponents<0>(vexp);
+                    }
+                    const int cend = c0 + kChunk < n1 ? c0 + kChunk : n1;
+                    bool more = true;
+                    for (int i = c0; more;) {
+#pragma unroll
+                        for (int d = 0; d < DV; d++) {
+                            if (more) {
+                                priority_at_step(i, prio);
+                                issue_block<VB, NARROW>(VS, i + DV - 1 < n1, blk1c(i + DV - 1), vr[(d + DV - 1) % DV]);
+                                await_block<VB, DV>(vr[d]);
+                                const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)vexp, i - c0);
+                                // (always true here; as a run-time test it keeps the rarely taken re-base and rescale
+                                // paths out of line, without it the register count of the loop grows by half)
+                                if (i < n1) {
+                                    apply_rescale<GQ>(W, L, i & 1, lane);
+                                    output_packed<VB, GQ, NARROW>(vr[d], ew, Q, W, L, i & 1, lane);
+                                }
+                                wg_barrier();
+                                more = ++i < cend;
                             }
-                            wg_barrier();
-                            more = ++i < cend;
                         }
                     }
                 }
+                __builtin_amdgcn_s_setprio(0);
+                drain();
+                if (chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
+            } else {
+                drain_unused();
+                if (!kEarlyRows && chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
             }
-            __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-            for (int d = 0; d < DV; d++) await_loads<0, VB>(vr[d]);
-            await_exponents<0>(vexp);
         }
-        for (int i = 0; i < n2; i++) {
-            const int u = f1c + i, buf = (n1 + i) & 1;
-            const bool packed = u < a.n_blocks;
-            const int pos0 = packed ? u * kG : a.n_blocks * kG + (u - a.n_blocks) * 32;
-            const int nt = packed ? 32 : (a.n_res - (u - a.n_blocks) * 32 < 32 ? a.n_res - (u - a.n_blocks) * 32 : 32);
-            apply_rescale<GQ>(W, L, buf, lane);
-            bool v_rows = true;
-            if constexpr (VB < 16) if (packed) {
-                v_rows = false;
+        if constexpr (VB < 16) {
+            // quantized values next to 16-bit keys
+            for (int i = 0; i < n2p; i++) {
+                const int u = blk2(i);
+                apply_rescale<GQ>(W, L, i & 1, lane);
                 CodeRegs<VB> r;
                 clear_regs(r);
                 load_block_now<VB, NARROW>(VS, u, r);
-                output_packed<VB, GQ, NARROW>(r, a.lv.bexp[blk0 + u], Q, W, L, buf, lane);
+                output_packed<VB, GQ, NARROW>(r, a.lv.bexp[blk0 + u], Q, W, L, i & 1, lane);
+                wg_barrier();
             }
-            if (v_rows) {
-                const uint16_t *vbase = packed ? reinterpret_cast<const uint16_t *>(a.lv.vcode) + (size_t)bh * a.NB * kG * kD
-                                               : a.lv.vres + (size_t)bh * a.RC * kD;
-                const uint16_t *new_row = nullptr;
-                if (!packed && a.v_new && a.new_pos >= pos0 && a.new_pos < pos0 + nt) {
-                    new_row = a.v_new + (size_t)bh * kD;
-                    reinterpret_cast<uint32_t *>(a.lv.vres + ((size_t)bh * a.RC + a.new_pos % a.RC) * kD)[lane] = reinterpret_cast<const uint32_t *>(new_row)[lane];
-                }
-                output_rows<GQ>(vbase, pos0, nt, packed ? 0 : a.RC, new_row, a.new_pos, W, L, buf, lane);
-            }
-            wg_barrier();
         }
-        // ---- result of the value wave: un-normalised output per head and channel.  The tile layout (lane =
-        // channel 16 cblk + n, rows of heads 2 rq, 2 rq + 1) is turned into (lane = channels 2 lane, 2 lane + 1,
-        // all heads) through the A-tile memory, which is no longer needed.
+        // ---- un-normalised outputs of the blocks per head and channel.  The tile layout (lane = channel 16 cblk + n, rows of
+        // heads 2 rq, 2 rq + 1) is turned into (lane = channels 2 lane, 2 lane + 1, all heads) through the A-tile memory, which
+        // is no longer needed; they stay there while the window is taken, which needs their registers.
         static_assert(sizeof(L.Av) >= GQ * kD * sizeof(float), "output staging fits the A tiles");
         float *o_lds = reinterpret_cast<float *>(&L.Av[0].at[0][0]);
-        constexpr int vshift = CodeShift<VB < 16 ? VB : 8>::value;
-        const float wO = ldexpf(1.0f, vshift + W.ev - 14);       // high and low parts carry the same weight
-        wave_lds_sync();
+        if constexpr (VB < 16) {
+            constexpr int vshift = CodeShift<VB>::value;
+            const float wO = ldexpf(1.0f, vshift + W.ev - 14);   // high and low parts carry the same weight
+            wave_lds_sync();
 #pragma unroll
-        for (int hh = 0; hh < 2; hh++) {
-            const int j = 2 * rq + hh;
-            if (j < GQ) {
+            for (int hh = 0; hh < 2; hh++) {
+                const int j = 2 * rq + hh;
+                if (j < GQ) {
 #pragma unroll
-                for (int cblk = 0; cblk < 8; cblk++) o_lds[j * kD + 16 * cblk + n] = wO * (W.O[cblk][2 * hh] + W.O[cblk][2 * hh + 1]);
+                    for (int cblk = 0; cblk < 8; cblk++) o_lds[j * kD + 16 * cblk + n] = wO * (W.O[cblk][2 * hh] + W.O[cblk][2 * hh + 1]);
+                }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int j = 0; j < GQ; j++) {
+                // sum_t p_t z_tg of this lane's channel group (lane >> 4), over the 16 lanes that hold its tokens
+                const float az = row_sum16(W.accz[j]);
+                float2 *t = reinterpret_cast<float2 *>(&o_lds[j * kD + 2 * lane]);
+                *t = make_float2(t->x + az, t->y + az);
+            }
+            wave_lds_sync();
+        }
+        float oF[GQ][4], shrink[GQ];                    // contributions of fp16 rows: see output_rows, rescale_rows
+#pragma unroll
+        for (int j = 0; j < GQ; j++) { oF[j][0] = oF[j][1] = oF[j][2] = oF[j][3] = 0.0f; shrink[j] = 1.0f; }
+        if constexpr (VB == 16) {
+            const uint8_t *base = a.lv.vcode + blk0 * block_code_bytes(16);
+            ValueRows next;
+            auto step = [&](int i, const ValueRows &x, ValueRows &y) {
+                fetch_unit(base, i + 1 < n2p, blk2(i + 1), lane, y);
+                rescale_rows<GQ>(oF, shrink, L, i & 1);
+                output_rows<GQ>(x, oF, L, i & 1, lane);
+                wg_barrier();
+            };
+            for (int i = 0; i < n2p; i += 2) {
+                step(i, rows, next);
+                if (i + 1 < n2p) step(i + 1, next, rows);
             }
         }
-        wave_lds_sync();
-#pragma unroll
-        for (int j = 0; j < GQ; j++) {
-            // sum_t p_t z_tg of this lane's channel group (lane >> 4), over the 16 lanes that hold its tokens
-            const float az = row_sum16(W.accz[j]);
-            if (j < nvalid) {
-                const float2 t = *reinterpret_cast<const float2 *>(&o_lds[j * kD + 2 * lane]);
-                const size_t prow = (qrow0 + j) * a.splits + split;
-                store_through(a.part_o + prow * kD + 2 * lane, make_float2(t.x + W.oF[j][0] + az, t.y + W.oF[j][1] + az));
-            }
+        if (n2p > 0 && chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
+#pragma unroll 1
+        for (int i = 0; i < chunks; i++) {
+            const int buf = (n1 + n2p + i) & 1;
+            const WindowChunk w = window_chunk(a, true, bh, first_chunk + i);
+            keep_new_row(w, lane);
+            settle_chunk(w, lane, rows, fresh);
+            rescale_rows<GQ>(oF, shrink, L, buf);
+            output_rows<GQ>(rows, oF, L, buf, lane);
+            if (i + 1 < chunks) fetch_chunk(window_chunk(a, true, bh, first_chunk + i + 1), lane, rows, fresh);
+            wg_barrier();
         }
+        // ---- result of the value wave: un-normalised output per head and channel
+        if (n2 > 0) {
+            // the fp16 rows' part: the two halves of the wave hold the same channels over different tokens
+#pragma unroll
+            for (int j = 0; j < GQ; j++) {
+                float r[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) r[k] = oF[j][k] + __shfl_xor(oF[j][k], 32, 64);
+                if (lane < 32) {
+                    float4 *o = reinterpret_cast<float4 *>(&o_lds[j * kD + 4 * lane]);
+                    const float4 t = VB < 16 ? *o : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    *o = make_float4(fmaf(t.x, shrink[j], r[0]), fmaf(t.y, shrink[j], r[1]), fmaf(t.z, shrink[j], r[2]), fmaf(t.w, shrink[j], r[3]));
+                }
+            }
+            wave_lds_sync();
+        }
+#pragma unroll
+        for (int j = 0; j < GQ; j++)
+            if (j < nvalid)
+                store_through(a.part_o + ((qrow0 + j) * a.splits + split) * kD + 2 * lane, *reinterpret_cast<const float2 *>(&o_lds[j * kD + 2 * lane]));
     }
 }
 

@@ -274,6 +274,29 @@ def test_one_group_sweeps_many_chunks(kvq_mod, oracle_mod, kb, vb, gq, splits):
         assert_outputs_close(g.decode_attention(0, q.cuda()), o16, o64, "K%dV%d gq %d splits %d" % (kb, vb, gq, splits))
 
 
+@pytest.mark.parametrize("gq,residual,splits", [(4, 150, 0), (7, 32, 1), (8, 0, 2), (3, 90, 3)])
+@pytest.mark.parametrize("kb,vb", [(16, 16), (16, 4), (4, 16), (4, 2)])
+def test_fp16_row_units_and_window_chunks(kvq_mod, oracle_mod, kb, vb, gq, residual, splits):
+    """fp16 rows of the matrix-core kernel: 16-bit units of which the next is in flight (odd and even numbers of them, one
+    group or several), windows of one to six chunks that wrap around the ring, the appended row in the last of them."""
+    w = W.Workload("rows", 1, 2, gq * 2, 2, 128, 32 * 9 + residual + 21, [kb], [vb], seed=660 + kb + vb + gq, outlier_channels=2)
+    g, o = _pair(kvq_mod, oracle_mod, w, w.context + 20, residual=residual)
+    K, V = W.kv_tokens(w, 0, 0, w.context)
+    g.quantize_append(0, K.cuda(), V.cuda())
+    o.quantize_append(0, K.numpy(), V.numpy())
+    g.set_decode_options(2, splits)
+    Kn, Vn = W.kv_tokens(w, 0, 0, 14, stream=1, total=14)
+    for step in range(14):                                   # 21 + 14 > 32: one flush on the way
+        k1, v1, q = Kn[:, :, step:step + 1].contiguous(), Vn[:, :, step:step + 1].contiguous(), W.query(w, 0, step)
+        out = g.append_decode_attention(0, k1.cuda(), v1.cuda(), q.cuda())
+        o.quantize_append(0, k1.numpy(), v1.numpy())
+        if step in (0, 9, 10, 11, 13):
+            o16, o64 = o.decode_attention(0, q.numpy())
+            assert_outputs_close(out, o16, o64, "step %d" % step)
+            assert torch.equal(out, g.decode_attention(0, q.cuda()))
+    assert_export_equal(g.debug_export(0), o.export(0), "after the steps")
+
+
 def test_biased_keys_gq7_mixed_layers(kvq_mod, oracle_mod, variant):
     """Shape of the Qwen configuration in small: g_q = 7, keys with a large per-channel offset, K8V2 / K4V2 layers."""
     w = W.config4(batch=2, context=32 * 20 + 32)
