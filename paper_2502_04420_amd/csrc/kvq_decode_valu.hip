@@ -302,55 +302,70 @@ __global__ __launch_bounds__(256) void decode_valu(DecodeArgs a)
 }
 
 // Merge the splits of one (batch, query head) by log-sum-exp and store fp16 (round to nearest even).
-// 512 threads: thread = (quarter g, channel d).  Quarter g merges the splits g, g + 4, g + 8, .., fetching
-// W partial records at a time with independent loads (a plain loop would pay one memory latency per
-// split; W = 16 for more than 32 splits, so that up to 64 splits are one round trip); the four quarter results are
-// merged through LDS.  The order of all sums is fixed.
-template <int W>
-__global__ __launch_bounds__(512) void combine_splits(DecodeArgs a)
+// 32 lanes hold a record (16 bytes of outputs each), so a wave takes two splits at a time; W records per half wave are in
+// flight at once and one round trip fetches all of up to 2 * WAVES * W splits.  The halves of a wave are merged by a lane
+// exchange, the waves through LDS.  The order of all sums is fixed.  Bound by its launch and that round trip, hence few
+// waves and few loads per thread where there are few splits.  Measured (whole decode call, us per call, 512 threads with a
+// channel each and 8 or 16 records in turn -> this): 7 splits 11.3 -> 10.6 (batch 4, 760 tokens), 16 splits 32.9 -> 32.6
+// (batch 16, 8192 tokens), 33 splits 11.7 -> 11.1 (one sequence of 4133 tokens).
+template <int WAVES, int W>
+__global__ __launch_bounds__(64 * WAVES) void combine_splits(DecodeArgs a)
 {
     const size_t row = blockIdx.x;
-    const int d = threadIdx.x & 127, g = threadIdx.x >> 7;
-    const float *ml = a.part_ml + row * a.splits * 2;
-    const float *po = a.part_o + row * a.splits * kD + d;
-    __shared__ float Mq[4], Lq[4], Oq[4][kD];
-    float M = -INFINITY, L = 0.0f, O = 0.0f;
-    for (int s0 = g; s0 < a.splits; s0 += 4 * W) {
-        float m8[W], l8[W], o8[W];
+    const int lane = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row * a.splits;
+    const float4 *po = reinterpret_cast<const float4 *>(a.part_o + row * a.splits * kD) + lane;
+    float2 r[W];
+    float4 x[W];
 #pragma unroll
-        for (int k = 0; k < W; k++) {
-            const int sp = s0 + 4 * k;
-            const bool ok = sp < a.splits;
-            m8[k] = ok ? ml[sp * 2] : -INFINITY;
-            l8[k] = ok ? ml[sp * 2 + 1] : 0.0f;
-            o8[k] = ok ? po[(size_t)sp * kD] : 0.0f;
-        }
-        float Mn = M;
-#pragma unroll
-        for (int k = 0; k < W; k++) Mn = fmaxf(Mn, m8[k]);
-        const float fo = exp2f(M - Mn);          // M = -inf on the first pass: factor 0 on empty sums
-        L *= fo; O *= fo;
-#pragma unroll
-        for (int k = 0; k < W; k++) {
-            const float f = exp2f(m8[k] - Mn);   // an absent split has m = -inf: factor 0
-            L = fmaf(l8[k], f, L);
-            O = fmaf(o8[k], f, O);
-        }
-        M = Mn;
+    for (int k = 0; k < W; k++) {
+        const int sp = g + 2 * WAVES * k, spc = sp < a.splits ? sp : 0;
+        r[k] = ml[spc];
+        x[k] = po[(size_t)spc * (kD / 4)];
     }
-    Oq[g][d] = O;
-    if (d == 0) { Mq[g] = M; Lq[g] = L; }
-    __syncthreads();
-    if (g == 0) {
-        const float Mt = fmaxf(fmaxf(Mq[0], Mq[1]), fmaxf(Mq[2], Mq[3]));      // quarter 0 always holds split 0: finite
-        float Lt = 0.0f, Ot = 0.0f;
+    float M = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const float f = exp2f(Mq[k] - Mt);   // an empty quarter has M = -inf: factor 0
-            Lt = fmaf(Lq[k], f, Lt);
-            Ot = fmaf(Oq[k][d], f, Ot);
+    for (int k = 0; k < W; k++) {
+        if (g + 2 * WAVES * k >= a.splits) r[k].x = -INFINITY;   // no such split: weight zero
+        M = fmaxf(M, r[k].x);
+    }
+    M = fmaxf(M, __shfl_xor(M, 32, 64));                         // (-inf in a wave without splits)
+    float L = 0.0f;
+    float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int k = 0; k < W; k++) {
+        const float f = r[k].x == -INFINITY ? 0.0f : exp2f(r[k].x - M);
+        L = fmaf(r[k].y, f, L);
+        O.x = fmaf(x[k].x, f, O.x); O.y = fmaf(x[k].y, f, O.y); O.z = fmaf(x[k].z, f, O.z); O.w = fmaf(x[k].w, f, O.w);
+    }
+    L += __shfl_xor(L, 32, 64);
+    O.x += __shfl_xor(O.x, 32, 64); O.y += __shfl_xor(O.y, 32, 64); O.z += __shfl_xor(O.z, 32, 64); O.w += __shfl_xor(O.w, 32, 64);
+    if constexpr (WAVES > 1) {
+        __shared__ float Mw[WAVES], Lw[WAVES];
+        __shared__ __attribute__((aligned(16))) float Ow[WAVES][kD];
+        const int wave = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) < 32) *reinterpret_cast<float4 *>(&Ow[wave][4 * lane]) = O;
+        if ((threadIdx.x & 63) == 0) { Mw[wave] = M; Lw[wave] = L; }
+        __syncthreads();
+        if (threadIdx.x >= 32) return;
+        M = Mw[0];                                               // wave 0 holds split 0: finite
+#pragma unroll
+        for (int k = 1; k < WAVES; k++) M = fmaxf(M, Mw[k]);
+        L = 0.0f;
+        O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int k = 0; k < WAVES; k++) {
+            const float f = exp2f(Mw[k] - M);                    // (a wave without splits: factor 0)
+            const float4 t = *reinterpret_cast<const float4 *>(&Ow[k][4 * lane]);
+            L = fmaf(Lw[k], f, L);
+            O.x = fmaf(t.x, f, O.x); O.y = fmaf(t.y, f, O.y); O.z = fmaf(t.z, f, O.z); O.w = fmaf(t.w, f, O.w);
         }
-        a.out[row * kD + d] = __builtin_bit_cast(uint16_t, (_Float16)(Ot / Lt));
+    }
+    if (g == 0) {
+        uint2 h;
+        h.x = __builtin_bit_cast(uint16_t, (_Float16)(O.x / L)) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(O.y / L)) << 16);
+        h.y = __builtin_bit_cast(uint16_t, (_Float16)(O.z / L)) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(O.w / L)) << 16);
+        __builtin_memcpy(a.out + row * kD + 4 * lane, &h, sizeof h);    // (the caller's tensor: fp16 alignment is all it owes)
     }
 }
 
@@ -404,10 +419,22 @@ hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s)
     }
 }
 
+template <int WAVES, int W>
+static void launch_merge(const DecodeArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL((combine_splits<WAVES, W>), dim3(a.B * a.Hq), dim3(64 * WAVES), 0, s, a);
+}
+
 hipError_t launch_combine(const DecodeArgs &a, hipStream_t s)
 {
-    if (a.splits > 32) hipLaunchKernelGGL(combine_splits<16>, dim3(a.B * a.Hq), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL(combine_splits<8>, dim3(a.B * a.Hq), dim3(512), 0, s, a);
+    // the fewest waves and records per thread that fetch all splits (at most 128) in one round trip
+    if (a.splits <= 4) launch_merge<1, 2>(a, s);
+    else if (a.splits <= 8) launch_merge<1, 4>(a, s);
+    else if (a.splits <= 16) launch_merge<4, 2>(a, s);
+    else if (a.splits <= 32) launch_merge<4, 4>(a, s);
+    else if (a.splits <= 64) launch_merge<8, 4>(a, s);
+    else if (a.splits <= 128) launch_merge<8, 8>(a, s);
+    else return hipErrorInvalidConfiguration;
     return hipGetLastError();
 }
 
