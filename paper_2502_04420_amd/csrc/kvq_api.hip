@@ -19,7 +19,7 @@ namespace {
 
 constexpr int kMaxSplits = 128;
 constexpr int kPrefillChunk = 16;   // caches dequantized per prefill-attention pass (two per XCD)
-constexpr int kPrefillSlots = 512; // partial results of prefill attention: two pieces of a query tile per compute unit (68 MB)
+constexpr size_t kPrefillSlots = 512;  // partial results of prefill attention: two pieces of a query tile per compute unit (68 MB)
 constexpr int kWindowWeight = 6;   // cost of a chunk (<= 32 tokens) of the fp16 window in a split's share, in packed blocks
 constexpr size_t kAlign = 256;
 
@@ -97,12 +97,17 @@ Plan make_plan(const kvq_config *c)
     p.part_o = off; off = align_up(off + rows * kMaxSplits * kvq::kD * sizeof(float));
     p.part_ml = off; off = align_up(off + rows * kMaxSplits * 2 * sizeof(float));
     // The prefill attention's partial results share that area with the decode splits': the two kinds of calls follow each
-    // other on the context's stream.  A prompt of max_tokens has `tiles` query tiles per head; they are cut (into pieces of
-    // 12 units or more, so only where there are 24) when they are too few to fill the GPU, and a cut of up to kPrefillSlots pieces is enough for that.
+    // other on the context's stream.  They belong to pieces of query tiles (tiles are cut where they are too few to fill the
+    // GPU, into pieces of 12 units or more, so only where there are 24).  A piece per compute unit is enough for most
+    // launches; where the splits' area does not hold that many, it grows to hold two.
     const size_t tiles = ((size_t)c->max_tokens + 255) / 256;
-    const size_t slots = p.NB < 24 ? 0 : rows * tiles * (p.NB / 12);
-    p.prefill_slots = slots < (size_t)kPrefillSlots ? (int)slots : kPrefillSlots;
-    if (off < p.part_o + p.prefill_slots * kvq::prefill_piece_bytes()) off = align_up(p.part_o + p.prefill_slots * kvq::prefill_piece_bytes());
+    const size_t most = p.NB < 24 ? 0 : rows * tiles * (p.NB / 12);
+    size_t slots = (off - p.part_o) / kvq::prefill_piece_bytes();
+    if (slots < kPrefillSlots / 2) slots = kPrefillSlots;
+    if (slots > most) slots = most;
+    if (slots > kPrefillSlots) slots = kPrefillSlots;
+    p.prefill_slots = (int)slots;
+    if (off < p.part_o + slots * kvq::prefill_piece_bytes()) off = align_up(p.part_o + slots * kvq::prefill_piece_bytes());
     p.prefill_chunk = BH < (size_t)kPrefillChunk ? (int)BH : kPrefillChunk;
     p.prefill_scratch = off; off = align_up(off + (size_t)p.prefill_chunk * p.NB * kvq::prefill_unit_bytes());
     p.prefill_select = off; off = align_up(off + BH * kvq::prefill_select_bytes());       // (a pass may take all caches)

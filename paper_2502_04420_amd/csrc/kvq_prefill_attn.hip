@@ -791,8 +791,15 @@ constexpr int kMaxCutTiles = 128;
 constexpr int kMaxPieces = 255;          // of a tile
 struct PieceTable {
     int pieces;                          // of a query head
+    int partials;                        // those of tiles with more than one piece: their results go through memory
     uint32_t entry[kMaxCutTiles];
 };
+
+__device__ __forceinline__ int piece_partials(uint32_t entry)
+{
+    const int count = (int)((entry >> 8) & 255u);
+    return count > 1 ? count : 0;
+}
 
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
 // kLoCompact).
@@ -1046,11 +1053,15 @@ __global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs 
     Piece pc = {tiles - 1 - rank, 0, 1, 0};                      // the longest rows start first
     if (pt.pieces) {
         uint32_t w = pt.entry[0];
-        for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) w = pt.entry[r];
+        int before = 0;                                          // partial results of the tiles in front of this one
+        for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) {
+            before += piece_partials(w);
+            w = pt.entry[r];
+        }
         pc.tile = (int)(w & 255u);
         pc.index = rank - (int)(w >> 16);
         pc.count = (int)((w >> 8) & 255u);
-        pc.slot = (local * gq + jq) * pieces + rank;
+        pc.slot = (local * gq + jq) * pt.partials + before + pc.index;
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
@@ -1072,9 +1083,11 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
     const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 5), lane = threadIdx.x & 31;
     const int i = tile * kQB + row;
     if (count < 2 || i >= a.n_q) return;
+    int before = 0;
+    for (int r = 0; r < (int)blockIdx.y; r++) before += piece_partials(pt.entry[r]);
     const int head = blockIdx.z;                                 // query head of the launch: local * gq + jq
     const int gq = a.Hq / a.Hkv, bh = a.bh0 + head / gq;
-    const size_t row0 = ((size_t)head * pt.pieces + (w >> 16)) * kQB + row;
+    const size_t row0 = ((size_t)head * pt.partials + before) * kQB + row;
     const float *po = a.part_o + row0 * kD + 4 * lane, *pm = a.part_ml + row0 * 2;
     float M = -INFINITY, Lsum = 0.0f;
     float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1157,6 +1170,7 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
         partials += num[r] > 1 ? num[r] : 0;
     }
     t.pieces = pieces;
+    t.partials = partials;
     // compute units grouped by when they are free, soonest first; equal pieces go to whole groups at a time
     struct { long long free; int count; } cu[kMaxCutTiles + 2];
     int groups = 1;
@@ -1191,15 +1205,16 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
 PieceTable plan_pieces(const Tiling &g, int heads, int slots)
 {
     PieceTable best;
-    best.pieces = 0;
-    if (g.tiles > kMaxCutTiles || g.n_blocks < 2 * kMinPiece || (long long)heads * g.tiles >= slots) return best;
+    best.pieces = best.partials = 0;
+    // (with three work-groups and more for every compute unit the longest tiles start early enough)
+    if (g.tiles > kMaxCutTiles || g.n_blocks < 2 * kMinPiece || (long long)heads * g.tiles >= 3 * kCUs || slots < 2) return best;
     const int longest = tile_units(g, g.tiles - 1);
     PieceTable t;
     long long least = cut(g, heads, longest, t);
     auto consider = [&](int length) {
         if (length < kMinPiece || length >= longest) return;
         const long long time = cut(g, heads, length, t);
-        if ((long long)t.pieces * heads <= slots && time < least) { least = time; best = t; }
+        if ((long long)t.partials * heads <= slots && time < least) { least = time; best = t; }
     };
     for (int k = 1; k <= 4 && k < g.tiles; k++) consider(tile_units(g, g.tiles - 1 - k));
     for (int parts = 2; parts <= 16 && longest / parts >= kMinPiece; parts++) consider((longest + parts - 1) / parts);
