@@ -218,6 +218,10 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
     const int np_old = packed_tokens(c, t_old), np_new = packed_tokens(c, t_new);
     const int BH = c->cfg.batch * c->cfg.n_kv_heads;
 
+    // new tokens that stay in the window go to the ring
+    const int pos0 = np_new > t_old ? np_new : t_old;
+    bool copy = copy_window && t_new > pos0;
+
     // 1. quantize the groups that leave the fp16 window: positions [np_old, np_new)
     if (np_new > np_old) {
         kvq::QuantArgs a;
@@ -231,12 +235,20 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
         a.BH = BH;
         a.NB = c->plan.NB;
         a.RC = c->plan.RC;
+        a.copy_pos0 = a.copy_pos1 = a.copy_groups = 0;
+        // The same launch fills the ring, unless a new token's slot still holds a token that this launch quantizes: slots are
+        // positions modulo RC, so the first such token would be RC behind the last new one.  (Never the case in a prompt's
+        // first append, which quantizes nothing from the ring, or when one token is appended.)
+        if (copy && (np_old >= t_old || t_new - 1 < np_old + c->plan.RC)) {
+            a.copy_pos0 = pos0;
+            a.copy_pos1 = t_new;
+            copy = false;
+        }
         hipError_t e = kvq::launch_quantize(a, c->stream);
         if (e != hipSuccess) return launch_failed("quantize kernel", e);
     }
-    // 2. new tokens that stay in the window go to the ring (after step 1 has read the old slots)
-    const int pos0 = np_new > t_old ? np_new : t_old;
-    if (copy_window && t_new > pos0) {
+    // 2. the ring, if step 1 has not filled it: after it has read the old slots
+    if (copy) {
         kvq::ResidualCopyArgs a;
         a.lv = view(c, layer);
         a.k_in = static_cast<const uint16_t *>(k_device);

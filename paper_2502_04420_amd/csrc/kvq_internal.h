@@ -31,6 +31,8 @@ struct QuantArgs {
     int BH;                        // batch * kv heads
     int NB;                        // block capacity per (b, h)
     int RC;                        // ring capacity (R + G)
+    int copy_pos0, copy_pos1;      // absolute positions of this append that go into the ring in the same launch (none: equal)
+    int copy_groups;               // waves per tensor that copy them (set by launch_quantize)
 };
 
 struct ResidualCopyArgs {
@@ -108,7 +110,7 @@ __device__ __forceinline__ void split_range(const DecodeArgs &a, int split, int 
     if (split == a.splits - 1) u1 = a.n_blocks + (a.n_res + 31) / 32;
 }
 
-hipError_t launch_quantize(const QuantArgs &a, hipStream_t s);
+hipError_t launch_quantize(QuantArgs a, hipStream_t s);
 hipError_t launch_residual_copy(const ResidualCopyArgs &a, hipStream_t s);
 hipError_t launch_export(const ExportArgs &a, hipStream_t s);
 hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);

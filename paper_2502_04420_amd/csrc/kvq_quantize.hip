@@ -228,16 +228,47 @@ __device__ __forceinline__ float wave_max64(float xf)
 // 16 different 16-byte bank groups.
 __device__ __forceinline__ int value_row(int ch) { return (ch & 0x70) | ((ch ^ (ch >> 3)) & 15); }
 
-// One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values.  The statistics are
+// Window rows taken along by the quantize launch (QuantArgs::copy_groups): new tokens [copy_pos0, copy_pos1) of one tensor,
+// input rows -> ring slots, kCopyRows rows per wave (16 lanes per row, four rows in flight per lane).
+constexpr int kCopyRows = 16;
+
+__device__ __forceinline__ void copy_window_rows(const QuantArgs &a, int group, bool values, int lane)
+{
+    const int n_tok = a.copy_pos1 - a.copy_pos0, c16 = lane & 15;
+    const uint16_t *in = values ? a.v_in : a.k_in;
+    uint16_t *ring = values ? a.lv.vres : a.lv.kres;
+    const long long rows = (long long)a.BH * n_tok, row0 = (long long)group * kCopyRows + (lane >> 4);
+    uint4 x[kCopyRows / 4];
+    size_t dst[kCopyRows / 4];
+#pragma unroll
+    for (int i = 0; i < kCopyRows / 4; i++) {
+        const long long r = row0 + 4 * i < rows ? row0 + 4 * i : rows - 1;       // past the end: the last row once more
+        const int bh = (int)(r / n_tok), pos = a.copy_pos0 + (int)(r % n_tok);
+        x[i] = *reinterpret_cast<const uint4 *>(in + ((size_t)bh * a.n_in + (pos - a.t_old)) * kD + 8 * c16);
+        dst[i] = ((size_t)bh * a.RC + pos % a.RC) * kD + 8 * c16;
+    }
+#pragma unroll
+    for (int i = 0; i < kCopyRows / 4; i++) *reinterpret_cast<uint4 *>(ring + dst[i]) = x[i];
+}
+
+// One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values; in front of them copy_groups waves per
+// tensor that put the tokens which stay in the window into the ring (a launch of its own for those took 4-5 us behind every
+// append: a 2027-token prompt, append and attention of 4 layers, 418 -> 409 us without it; 16 x 8192 tokens, append and
+// first token of 2 layers, 323 -> 319 us).  The statistics are
 // taken in the arrangement the rows are loaded in (16 bytes = 8 channels of a token per lane), the tile
 // goes through LDS, and each lane encodes exactly the 64 codes it stores.
 template <int KB, int VB, bool NARROW>
 __global__ __launch_bounds__(64) void quantize_blocks(QuantArgs a)
 {
     const int lane = threadIdx.x;
-    const int bh = blockIdx.x / a.n_blocks;
-    const int blk = a.first_block + blockIdx.x % a.n_blocks;
     const bool values = blockIdx.y != 0;
+    if ((int)blockIdx.x < a.copy_groups) {
+        copy_window_rows(a, blockIdx.x, values, lane);
+        return;
+    }
+    const int item = blockIdx.x - a.copy_groups;
+    const int bh = item / a.n_blocks;
+    const int blk = a.first_block + item % a.n_blocks;
     const int r = lane >> 4, c16 = lane & 15;
     const int n = lane & 15, kq = lane >> 4;
 
@@ -613,7 +644,7 @@ __global__ void export_rows(ExportArgs a, int which)
 template <int KB, bool NARROW>
 hipError_t launch_quantize_vb(const QuantArgs &a, hipStream_t s)
 {
-    const dim3 grid((unsigned)a.n_blocks * (unsigned)a.BH, 2), block(64);
+    const dim3 grid((unsigned)a.copy_groups + (unsigned)a.n_blocks * (unsigned)a.BH, 2), block(64);
     switch (a.lv.vbits) {
     case 2: hipLaunchKernelGGL((quantize_blocks<KB, 2, NARROW>), grid, block, 0, s, a); break;
     case 4: hipLaunchKernelGGL((quantize_blocks<KB, 4, NARROW>), grid, block, 0, s, a); break;
@@ -638,10 +669,12 @@ unsigned blocks_for(long long total, int threads) { return (unsigned)((total + t
 
 }  // namespace
 
-hipError_t launch_quantize(const QuantArgs &a, hipStream_t s)
+hipError_t launch_quantize(QuantArgs a, hipStream_t s)
 {
     if (a.n_blocks < 1 || a.BH < 1) return hipSuccess;
-    if ((long long)a.n_blocks * a.BH > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const long long rows = (long long)a.BH * (a.copy_pos1 - a.copy_pos0), groups = rows > 0 ? (rows + kCopyRows - 1) / kCopyRows : 0;
+    if ((long long)a.n_blocks * a.BH + groups > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    a.copy_groups = (int)groups;
     return a.lv.narrow ? launch_quantize_kb<true>(a, s) : launch_quantize_kb<false>(a, s);
 }
 

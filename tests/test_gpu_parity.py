@@ -218,6 +218,23 @@ def test_chunked_appends_match_oracle_bulk(kvq_mod, oracle_mod, chunks, residual
     assert_outputs_close(out, o16, o64, "chunks")
 
 
+@pytest.mark.parametrize("residual", [0, 32, 100])
+@pytest.mark.parametrize("chunks", [[63, 40, 90], [40, 24, 1, 128], [50, 45, 98], [95, 1, 97]])
+def test_append_that_flushes_and_fills_the_window(kvq_mod, oracle_mod, chunks, residual):
+    """Appends that quantize groups and put new tokens into the ring: in one launch, or in two where a new token takes the
+    slot of one that is being quantized (63 + 40 tokens at a window of 32: positions 64.. over 0..).  State after each."""
+    w = W.Workload("ring", 1, 3, 4, 2, 128, sum(chunks), [4], [4], seed=450 + len(chunks), outlier_channels=2)
+    g, o = _pair(kvq_mod, oracle_mod, w, 256, residual=residual)
+    K, V = W.kv_tokens(w, 0, 0, w.context)
+    t = 0
+    for n in chunks:
+        k1, v1 = K[:, :, t:t + n].contiguous(), V[:, :, t:t + n].contiguous()
+        g.quantize_append(0, k1.cuda(), v1.cuda())
+        o.quantize_append(0, k1.numpy(), v1.numpy())
+        t += n
+        assert_export_equal(g.debug_export(0), o.export(0), "after %d tokens" % t)
+
+
 def test_decode_loop_with_flushes(kvq_mod, oracle_mod, variant):
     """Prefill, then 70 decode steps that append one token each (two window flushes), checked every step."""
     w = W.Workload("loop", 2, 2, 8, 2, 128, 100, [4, 8], [2, 4], seed=500, outlier_channels=3)
