@@ -21,6 +21,7 @@ constexpr int kMaxSplits = 128;
 constexpr int kPrefillChunk = 16;   // caches dequantized per prefill-attention pass (two per XCD)
 constexpr size_t kPrefillSlots = 512;  // partial results of prefill attention: two pieces of a query tile per compute unit (68 MB)
 constexpr int kWindowWeight = 6;   // cost of a chunk (<= 32 tokens) of the fp16 window in a split's share, in packed blocks
+constexpr int kCUs = 256;          // compute units of the GPU
 constexpr size_t kAlign = 256;
 
 thread_local char g_last_error[256] = "";
@@ -285,7 +286,14 @@ SplitPlan plan_splits(int BH, int width, int n_blocks, int n_res, int forced, in
         const int groups = variant != 2 ? 1024 : width <= 8 ? 2048 : 1024;
         const int min_units = variant == 2 ? 4 : 8;
         splits = (groups + BH - 1) / BH;
-        const int cap = (n_blocks + min_units - 1) / min_units + (n_res > 0 ? 1 : 0);
+        int cap = (n_blocks + min_units - 1) / min_units + (n_res > 0 ? 1 : 0);
+        // Short caches of a small batch: where 4 blocks per group make a few more groups than there are compute units, 5 per
+        // group give each a unit of its own (one sequence, 8 kv heads of 4133 tokens, 264 or 216 groups: 11.1 or 10.7 us a
+        // call; 4 kv heads of 8200 tokens, 260 or 208: 14.3 or 12.7.  With two groups per unit and more it is the other way
+        // round: 24 caches of 2500 tokens, 480 or 384 groups: 11.5 or 12.4).
+        // With very few caches 2 blocks per group: 2 kv heads of 512 tokens, 5 or 9 splits: 9.2 or 8.4 us (8 kv heads: alike).
+        if (variant == 2 && BH * cap > kCUs && BH * cap <= kCUs + kCUs / 4) cap = (n_blocks + 4) / 5 + (n_res > 0 ? 1 : 0);
+        else if (variant == 2 && BH * (n_blocks / 2 + 1) <= kCUs / 4) cap = (n_blocks + 1) / 2 + (n_res > 0 ? 1 : 0);
         if (splits > cap) splits = cap;
     }
     if (splits > kMaxSplits) splits = kMaxSplits;
@@ -301,8 +309,15 @@ SplitPlan plan_splits(int BH, int width, int n_blocks, int n_res, int forced, in
     const int most = n_blocks + (window ? 1 : 0);                // no more splits than blocks (+ one for the window)
     if (splits > most) splits = most;
     if (splits < 1) splits = 1;
-    // (never more than a split's share of blocks: with many small splits the window's split simply takes no blocks)
-    if (window > (n_blocks + splits - 1) / splits) window = (n_blocks + splits - 1) / splits;
+    // (never more than the share of a split in front of the window's: with many small splits the window's split takes no
+    // blocks, not even the odd one that is left over.  One sequence, 23 blocks: 11.1 us a call with a block in front of the
+    // window in the same group, 9.1 without)
+    if (splits > 1) {
+        const int share = (n_blocks + splits - 2) / (splits - 1);
+        if (window > share) window = share;
+    } else if (window > n_blocks) {
+        window = n_blocks;
+    }
     if (n_res > 0 && window < 1) window = 1;
     SplitPlan p;
     for (;;) {

@@ -1153,7 +1153,8 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         // is no longer needed; they stay there while the window is taken, which needs their registers.
         static_assert(sizeof(L.Av) >= GQ * kD * sizeof(float), "output staging fits the A tiles");
         float *o_lds = reinterpret_cast<float *>(&L.Av[0].at[0][0]);
-        if constexpr (VB < 16) {
+        const bool staged = VB < 16 && n1 + n2p > 0;             // (a group with nothing but the window has no such outputs)
+        if constexpr (VB < 16) if (staged) {
             constexpr int vshift = CodeShift<VB>::value;
             const float wO = ldexpf(1.0f, vshift + W.ev - 14);   // high and low parts carry the same weight
             wave_lds_sync();
@@ -1214,7 +1215,7 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
                 for (int k = 0; k < 4; k++) r[k] = oF[j][k] + __shfl_xor(oF[j][k], 32, 64);
                 if (lane < 32) {
                     float4 *o = reinterpret_cast<float4 *>(&o_lds[j * kD + 4 * lane]);
-                    const float4 t = VB < 16 ? *o : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    const float4 t = staged ? *o : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     *o = make_float4(fmaf(t.x, shrink[j], r[0]), fmaf(t.y, shrink[j], r[1]), fmaf(t.z, shrink[j], r[2]), fmaf(t.w, shrink[j], r[3]));
                 }
             }
