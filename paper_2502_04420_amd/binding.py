@@ -121,7 +121,7 @@ class KVQ:
                  device="cuda:0", stream=None, meta_dtype: int = META_FP32, key_mode: int = KEYS_PER_CHANNEL):
         import torch
 
-        self._torch = torch
+        self._torch, self._Tensor, self._fp16 = torch, torch.Tensor, torch.float16
         self._lib = load_library()
         if len(kbits) != n_layers or len(vbits) != n_layers:
             raise ValueError("need one (key bits, value bits) pair per layer")
@@ -129,6 +129,8 @@ class KVQ:
         self.head_dim, self.max_tokens, self.group, self.residual = head_dim, max_tokens, group, residual
         self.kbits, self.vbits = list(kbits), list(vbits)
         self.device = torch.device(device)
+        self._q_shape = (batch, n_q_heads, head_dim)
+        self._token_shape = (batch, n_kv_heads, 1, head_dim)
         cfg, self._keep = make_config(n_layers, batch, n_q_heads, n_kv_heads, head_dim, max_tokens, self.kbits,
                                       self.vbits, group, residual, meta_dtype, key_mode)
         self.meta_dtype, self.key_mode = meta_dtype, key_mode
@@ -146,14 +148,16 @@ class KVQ:
                                        need, c_void_p(s.cuda_stream)))
 
     # -- helpers
-    def _dev_ptr(self, t, shape, dtype, name):
-        torch = self._torch
-        if not isinstance(t, torch.Tensor) or t.device != self.device:
+    def _dev_ptr(self, t, shape, name):
+        """Address of a contiguous fp16 tensor of this shape (a tuple) on the cache's device; the address goes to the
+        library as a plain integer.  A decode call passes two to five tensors through here and takes the GPU about
+        8 us when the cache is short, so the order is: what nearly always holds, cheapest first (7.9 -> 6.5 us of host
+        time per decode call)."""
+        if isinstance(t, self._Tensor) and t.shape == shape and t.dtype is self._fp16 and t.device == self.device and t.is_contiguous():
+            return t.data_ptr()
+        if not isinstance(t, self._Tensor) or t.device != self.device:
             raise ValueError("%s must be a tensor on %s" % (name, self.device))
-        if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
-            raise ValueError("%s must be contiguous %s of shape %s, got %s %s" % (name, dtype, tuple(shape), t.dtype,
-                                                                                  tuple(t.shape)))
-        return c_void_p(t.data_ptr())
+        raise ValueError("%s must be contiguous %s of shape %s, got %s %s" % (name, self._fp16, shape, t.dtype, tuple(t.shape)))
 
     def close(self):
         if getattr(self, "_h", None):
@@ -169,60 +173,55 @@ class KVQ:
     # -- the three calls of the path
     def quantize_append(self, layer: int, K, V):
         """K, V: fp16 [batch, n_kv_heads, n_tokens, head_dim] on the device."""
-        torch = self._torch
         n = int(K.shape[2]) if K.dim() == 4 else -1
         shape = (self.batch, self.n_kv_heads, n, self.head_dim)
-        kp = self._dev_ptr(K, shape, torch.float16, "K")
-        vp = self._dev_ptr(V, shape, torch.float16, "V")
-        _check(self._lib.kvq_quantize_append(self._h, layer, kp, vp, n))
+        rc = self._lib.kvq_quantize_append(self._h, layer, self._dev_ptr(K, shape, "K"), self._dev_ptr(V, shape, "V"), n)
+        if rc:
+            _check(rc)
 
     def decode_attention(self, layer: int, q, out=None):
         """q: fp16 [batch, n_q_heads, head_dim]; returns out of the same shape (allocated if not given)."""
-        torch = self._torch
-        shape = (self.batch, self.n_q_heads, self.head_dim)
-        qp = self._dev_ptr(q, shape, torch.float16, "q")
+        shape = self._q_shape
+        qp = self._dev_ptr(q, shape, "q")
         if out is None:
-            out = torch.empty(shape, dtype=torch.float16, device=self.device)
-        op = self._dev_ptr(out, shape, torch.float16, "out")
-        _check(self._lib.kvq_decode_attention(self._h, layer, qp, op))
+            out = self._torch.empty(shape, dtype=self._fp16, device=self.device)
+        rc = self._lib.kvq_decode_attention(self._h, layer, qp, self._dev_ptr(out, shape, "out"))
+        if rc:
+            _check(rc)
         return out
 
     def decode_attention_noalloc(self, layer: int, q, out):
         """kvq_decode_attention_noalloc: the splits' partial results live in the library's built-in device array.  The
         output tensor is the caller's (nothing is allocated on the way)."""
-        torch = self._torch
-        shape = (self.batch, self.n_q_heads, self.head_dim)
-        qp = self._dev_ptr(q, shape, torch.float16, "q")
-        op = self._dev_ptr(out, shape, torch.float16, "out")
-        _check(self._lib.kvq_decode_attention_noalloc(self._h, layer, qp, op))
+        shape = self._q_shape
+        rc = self._lib.kvq_decode_attention_noalloc(self._h, layer, self._dev_ptr(q, shape, "q"), self._dev_ptr(out, shape, "out"))
+        if rc:
+            _check(rc)
         return out
 
     def append_decode_attention(self, layer: int, K, V, q, out=None):
         """One decode step: append one token per sequence (K, V: fp16 [batch, n_kv_heads, 1, head_dim]) and attend."""
-        torch = self._torch
-        kshape = (self.batch, self.n_kv_heads, 1, self.head_dim)
-        kp = self._dev_ptr(K, kshape, torch.float16, "K")
-        vp = self._dev_ptr(V, kshape, torch.float16, "V")
-        shape = (self.batch, self.n_q_heads, self.head_dim)
-        qp = self._dev_ptr(q, shape, torch.float16, "q")
+        kshape, shape = self._token_shape, self._q_shape
+        kp, vp, qp = self._dev_ptr(K, kshape, "K"), self._dev_ptr(V, kshape, "V"), self._dev_ptr(q, shape, "q")
         if out is None:
-            out = torch.empty(shape, dtype=torch.float16, device=self.device)
-        op = self._dev_ptr(out, shape, torch.float16, "out")
-        _check(self._lib.kvq_append_decode_attention(self._h, layer, kp, vp, qp, op))
+            out = self._torch.empty(shape, dtype=self._fp16, device=self.device)
+        rc = self._lib.kvq_append_decode_attention(self._h, layer, kp, vp, qp, self._dev_ptr(out, shape, "out"))
+        if rc:
+            _check(rc)
         return out
 
     def prefill_attention(self, layer: int, q, out=None):
         """Causal attention of the last n_q tokens over the layer's cache as it stands.
         q: fp16 [batch, n_q_heads, n_q, head_dim]; returns out of the same shape (allocated if not given)."""
-        torch = self._torch
         if q.dim() != 4:
             raise ValueError("q must be [batch, n_q_heads, n_q, head_dim]")
         shape = (self.batch, self.n_q_heads, int(q.shape[2]), self.head_dim)
-        qp = self._dev_ptr(q, shape, torch.float16, "q")
+        qp = self._dev_ptr(q, shape, "q")
         if out is None:
-            out = torch.empty(shape, dtype=torch.float16, device=self.device)
-        op = self._dev_ptr(out, shape, torch.float16, "out")
-        _check(self._lib.kvq_prefill_attention(self._h, layer, qp, shape[2], op))
+            out = self._torch.empty(shape, dtype=self._fp16, device=self.device)
+        rc = self._lib.kvq_prefill_attention(self._h, layer, qp, shape[2], self._dev_ptr(out, shape, "out"))
+        if rc:
+            _check(rc)
         return out
 
     # -- bookkeeping and debugging
