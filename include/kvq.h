@@ -188,7 +188,7 @@ int kvq_append_decode_attention(kvq_ctx *ctx, int32_t layer, const void *k_devic
  * numbers); accumulation is fp32.  The cache is not modified.  With n_q = 1 the result is that
  * of kvq_decode_attention up to rounding.  The call enqueues two kernels per pass over a group
  * of (batch, kv head) caches: one dequantizes their packed tokens once into a scratch area
- * inside the workspace (16 * floor(max_tokens / 32) * 27 KiB, counted by kvq_workspace_bytes:
+ * inside the workspace (16 * floor(max_tokens / 32) * 26 KiB, counted by kvq_workspace_bytes:
  * 16 caches per pass at full length, more when the layer holds fewer tokens), one attends.  For
  * keys quantized per channel, one kernel in front of the passes finds, per cache and from the
  * stored scales and zero-points, the centre of every channel's keys, which is taken off the

@@ -54,13 +54,19 @@ constexpr int kQW = 16 * kQT;            // queries per wave
 constexpr int kQB = kQW * kWaves;       // queries per work-group
 constexpr int kKStride = kD + 16;       // halves per K^ row: 288 bytes.  Measured with a probe kernel: the 16-byte operand reads of a wave
                                         // (16 rows x 4 pieces) take 3.9 LDS cycles at this stride, like a linear read; 7.8 + 3.9 conflict cycles at 272
-constexpr int kVStride = 32 + 4;        // halves per V^ channel row (72 bytes = 18 banks: the 16 rows of an 8-byte read fall on different banks)
 
 struct Tiles {
     _Float16 K[32][kKStride];           // K^[token][channel], rounded to fp16
     _Float16 Klo[32][kKStride];         // what the rounding left over (quantized keys only)
-    _Float16 Vt[kD][kVStride];          // V^[channel][token]
+    _Float16 Vt[kD][32];                // V^[channel][value_place(channel, token)]
 };
+
+// Place of a token in the V^ row of a channel.  A lane's operand of the output product (tokens 4 rq .. + 3 and 16 + 4 rq .. + 3, the
+// rows of the scores' result tile that it holds) is one piece of 16 bytes; the four pieces of a row are rotated by
+// channel / 4, so that 16 lanes with neighbouring channels and the same rq meet 16 different groups of four banks although
+// rows follow each other without padding (64 bytes).  Before, two pieces of 8 bytes in rows of 72: half the bytes per LDS
+// cycle and a KiB more to fetch per unit (4 x 8192-token prompts 2508 -> 2477 us, a 2027-token prompt, 4 layers, 414 -> 407).
+__host__ __device__ constexpr int value_place(int channel, int t) { return 8 * ((((t >> 2) & 3) + (channel >> 2)) & 3) + 4 * (t >> 4) + (t & 3); }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -156,7 +162,7 @@ __device__ __forceinline__ void store_value_piece(Tiles &L, int idx, u32x4 x, in
 #pragma unroll
     for (int e = 0; e < 8; e++) {
         const uint32_t w = x[e >> 1];
-        L.Vt[8 * c16 + e][t] = __builtin_bit_cast(_Float16, (uint16_t)(live ? ((e & 1) ? w >> 16 : w & 0xffffu) : 0u));
+        L.Vt[8 * c16 + e][value_place(8 * c16 + e, t)] = __builtin_bit_cast(_Float16, (uint16_t)(live ? ((e & 1) ? w >> 16 : w & 0xffffu) : 0u));
     }
 }
 
@@ -303,10 +309,10 @@ __device__ __forceinline__ void store_value_codes(const LayerView &lv, Tiles &L,
         float x[8];
 #pragma unroll
         for (int e = 0; e < 8; e++) x[e] = fmaf(code_of<BITS>(w0, w1, mm, e), s[e], z[e]);
-        const u32x4 h = pack8(x);                          // rows are 8-byte aligned only
-        uint2 *dst = reinterpret_cast<uint2 *>(&L.Vt[16 * (2 * g + mm) + n][8 * kq]);
-        dst[0] = make_uint2(h[0], h[1]);
-        dst[1] = make_uint2(h[2], h[3]);
+        const u32x4 h = pack8(x);
+        const int ch = 16 * (2 * g + mm) + n;
+        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq)]) = make_uint2(h[0], h[1]);
+        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq + 4)]) = make_uint2(h[2], h[3]);
     }
 }
 
@@ -388,9 +394,7 @@ __device__ __forceinline__ float xor_lanes(float x, int mask) { return __shfl_xo
 // the A operand of the output product for channel tile ct: V^T rows 16 ct + n, tokens {4 rq .. + 3, 16 + 4 rq .. + 3}
 __device__ __forceinline__ half8 value_operand(const Tiles &X, int ct, int n, int rq)
 {
-    const half4 v0 = *reinterpret_cast<const half4 *>(&X.Vt[16 * ct + n][4 * rq]);
-    const half4 v1 = *reinterpret_cast<const half4 *>(&X.Vt[16 * ct + n][16 + 4 * rq]);
-    return half8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+    return *reinterpret_cast<const half8 *>(&X.Vt[16 * ct + n][8 * ((rq + (n >> 2)) & 3)]);
 }
 
 struct NoSlice { __device__ __forceinline__ void operator()(int) const {} };
@@ -707,13 +711,13 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
 // KQ / VQ: the layer's keys / values are quantized (else fp16 rows in the code area).
 //
 // The unit is put together in LDS and goes out as whole KiB, 16 bytes per lane at consecutive addresses: bound by the writes
-// (27 KiB per unit, 21 in the compact form; its code and metadata reads are a tenth of that).  Stored to the scratch area
+// (26 KiB per unit, 20 in the compact form; its code and metadata reads are a tenth of that).  Stored to the scratch area
 // straight from the registers that hold the values (64-byte pieces of rows, 8-byte pieces of the transposed values, 2-byte
 // low parts, row padding left out) the lines were written in parts.  Measured (K4V2, compact): 16 caches of 255 units
 // 40 -> 31.5 us, 8 caches of 767 units 60 -> 45 us (4.0 TB/s of reads and writes).
-constexpr int kTileKiB = 9;
-static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * kVStride == kTileKiB * 1024 &&
-              sizeof(Tiles) == 3 * kTileKiB * 1024, "tiles of a unit are whole KiB");
+constexpr int kTileKiB = 9, kValuesKiB = 8;
+static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * 32 == kValuesKiB * 1024 &&
+              sizeof(Tiles) == (2 * kTileKiB + kValuesKiB) * 1024, "tiles of a unit are whole KiB");
 
 template <bool KQ, bool VQ>
 __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs a)
@@ -730,7 +734,7 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
     const int lo_pieces = !KQ ? 0 : rec && rec->compact != 0 ? kLoPieces : kTileKiB;
     uint8_t *dst = a.scratch + ((size_t)local * a.n_blocks + u) * sizeof(Tiles);
     const uint8_t *src = reinterpret_cast<const uint8_t *>(&tile);
-    for (int p = tid >> 6; p < 2 * kTileKiB + lo_pieces; p += kStagers) {
+    for (int p = tid >> 6; p < kTileKiB + lo_pieces + kValuesKiB; p += kStagers) {
         const int off = 1024 * (p < kTileKiB + lo_pieces ? p : p - lo_pieces + kTileKiB) + 16 * (tid & 63);      // K^, low parts, then V^
         *reinterpret_cast<u32x4 *>(dst + off) = *reinterpret_cast<const u32x4 *>(src + off);
     }
@@ -738,7 +742,7 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
 
 // A unit goes from the scratch area into an LDS buffer without passing through registers: a wave issues
 // global-to-LDS loads of 1 KiB each (64 lanes x 16 bytes, which land at consecutive LDS addresses from the base
-// that M0 holds).  The three tiles of a unit are 9 KiB each, so a piece never straddles two of them.
+// that M0 holds).  The tiles of a unit are whole KiB, so a piece never straddles two of them.
 
 __device__ __forceinline__ void fetch_piece(const uint8_t *unit, uint32_t offset_of_lane, uint32_t lds_base)
 {
@@ -755,7 +759,7 @@ template <int LO>
 __device__ __forceinline__ void fetch_unit(const uint8_t *unit, Tiles &L, int wave, int lane)
 {
     constexpr int lo_pieces = LO == kLoAll ? kTileKiB : LO == kLoCompact ? kLoPieces : 0;
-    constexpr int pieces = 2 * kTileKiB + lo_pieces;
+    constexpr int pieces = kTileKiB + lo_pieces + kValuesKiB;
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)reinterpret_cast<uint8_t *>(&L);
 #pragma unroll
     for (int i = 0; i < (pieces + kWaves - 1) / kWaves; i++) {
