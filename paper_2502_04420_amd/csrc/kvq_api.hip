@@ -270,9 +270,9 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
 // How a decode launch divides the tokens of a (batch, kv head) cache among its groups.
 struct SplitPlan { int splits, units_per_split, split_rem; };
 
-// BH caches, code width = key bits + value bits, n_blocks packed blocks and n_res fp16 window tokens per cache;
+// BH caches of gq query heads, code width = key bits + value bits, n_blocks packed blocks and n_res fp16 window tokens per cache;
 // forced: the caller's split count (0 = choose); variant: 1 vector-ALU kernel, 2 matrix-core kernel.
-SplitPlan plan_splits(int BH, int width, int n_blocks, int n_res, int forced, int variant)
+SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int forced, int variant)
 {
     int splits = forced;
     if (splits <= 0) {
@@ -292,18 +292,19 @@ SplitPlan plan_splits(int BH, int width, int n_blocks, int n_res, int forced, in
         // call; 4 kv heads of 8200 tokens, 260 or 208: 14.3 or 12.7.  With two groups per unit and more it is the other way
         // round: 24 caches of 2500 tokens, 480 or 384 groups: 11.5 or 12.4).
         // With very few caches 2 blocks per group: 2 kv heads of 512 tokens, 5 or 9 splits: 9.2 or 8.4 us (8 kv heads: alike).
-        if (variant == 2 && BH * cap > kCUs && BH * cap <= kCUs + kCUs / 4) cap = (n_blocks + 4) / 5 + (n_res > 0 ? 1 : 0);
-        else if (variant == 2 && BH * (n_blocks / 2 + 1) <= kCUs / 4) cap = (n_blocks + 1) / 2 + (n_res > 0 ? 1 : 0);
+        // (Counted in work-groups: a split is one per 8 query heads of a cache.)
+        const long long groups_per_split = (long long)BH * ((gq + 7) / 8);
+        if (variant == 2 && groups_per_split * cap > kCUs && groups_per_split * cap <= kCUs + kCUs / 4) cap = (n_blocks + 4) / 5 + (n_res > 0 ? 1 : 0);
+        else if (variant == 2 && groups_per_split * (n_blocks / 2 + 1) <= kCUs / 4) cap = (n_blocks + 1) / 2 + (n_res > 0 ? 1 : 0);
         if (splits > cap) splits = cap;
     }
     if (splits > kMaxSplits) splits = kMaxSplits;
     if (splits < 1) splits = 1;
-    // The fp16 window rides on the last split.  Its rows are fetched and used after the split's blocks, chunk by chunk
-    // and the values after the keys: memory round trips in a row, which cost about as much as kWindowWeight packed
-    // blocks per chunk.  The window counts as that many units behind the blocks, and the units are dealt out evenly
-    // (the last split gets that many blocks fewer, none at all when its share is smaller than that).  Measured at
-    // batch 16, 8192..8223 tokens: weights 6..10 for one chunk and 10..16 for two are alike; with 4 a two-chunk window
-    // makes its split the straggler (36.5 us against 30.4).
+    // The fp16 window rides on the last split, behind the split's blocks and chunk by chunk: a chunk's key and value rows are
+    // each asked for at once, about the time of a few packed blocks.  The window counts as kWindowWeight units per chunk behind
+    // the blocks, and the units are dealt out evenly (the last split gets that many blocks fewer, none at all when its share
+    // is smaller than that).  Measured, batch 16, 8192 tokens, 8 layers: weights 3, 4 and 6 are alike (266..267 us), 1 and 2
+    // make the window's split the straggler (273).
     int window = kWindowWeight * ((n_res + 31) / 32);
     if (n_blocks == 0) splits = 1;
     const int most = n_blocks + (window ? 1 : 0);                // no more splits than blocks (+ one for the window)
@@ -362,7 +363,7 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
     a.v_new = static_cast<const uint16_t *>(v_new);
     a.new_pos = T - 1;
     const int variant = decode_variant(c);
-    const SplitPlan sp = plan_splits(a.B * a.Hkv, a.lv.kbits + a.lv.vbits, a.n_blocks, a.n_res, c->splits, variant);
+    const SplitPlan sp = plan_splits(a.B * a.Hkv, a.Hq / a.Hkv, a.lv.kbits + a.lv.vbits, a.n_blocks, a.n_res, c->splits, variant);
     const int splits = sp.splits;
     a.units_per_split = sp.units_per_split;
     a.split_rem = sp.split_rem;
@@ -564,7 +565,7 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
         return KVQ_EINVAL;
     const int over = n_tokens - cfg->residual;
     const int np = over > 0 ? kvq::kG * (over / kvq::kG) : 0;
-    const SplitPlan p = plan_splits(cfg->batch * cfg->n_kv_heads, cfg->kbits[layer] + cfg->vbits[layer], np / kvq::kG, n_tokens - np,
+    const SplitPlan p = plan_splits(cfg->batch * cfg->n_kv_heads, cfg->n_q_heads / cfg->n_kv_heads, cfg->kbits[layer] + cfg->vbits[layer], np / kvq::kG, n_tokens - np,
                                     forced_splits, variant == 0 ? 2 : variant);
     *splits = p.splits;
     *units_per_split = p.units_per_split;

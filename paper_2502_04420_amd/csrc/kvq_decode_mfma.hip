@@ -497,6 +497,11 @@ __device__ __forceinline__ void scores_packed_per_token(const CodeRegs<KB> &blk,
 }
 
 // ---- fp16 rows (16-bit layers, window chunks): 32 tokens of a wave's tensor in registers
+//
+// A 16-bit layer is bound by memory, a window chunk by the latency of its rows, so all 32 rows of a tensor (8 KiB) are asked
+// for at once, and of a 16-bit layer two units at a time.  Measured against one unit at a time with the value rows in four
+// batches of eight: K16V16, batch 8, 4519 tokens (296 MB) 52.6 -> 33.4 us a call = 4.4 TB/s; one layer of 512 tokens
+// 11.4 -> 9.2 us; batch 4, 760 tokens 14.4 -> 11.3 us.
 
 // keys: tokens n and 16 + n, channels 32 cb + 8 rq .. + 7
 struct KeyRows { u32x4 lo[4], hi[4]; };
