@@ -189,7 +189,9 @@ int kvq_append_decode_attention(kvq_ctx *ctx, int32_t layer, const void *k_devic
  * of kvq_decode_attention up to rounding.  The call enqueues two kernels per pass over a group
  * of (batch, kv head) caches: one dequantizes their packed tokens once into a scratch area
  * inside the workspace (16 * floor(max_tokens / 32) * 26 KiB, counted by kvq_workspace_bytes:
- * 16 caches per pass at full length, more when the layer holds fewer tokens), one attends.  For
+ * 16 caches per pass at full length, more when the layer holds fewer tokens), one attends; where a
+ * pass has too few query tiles to fill the GPU, they are attended in pieces and a third kernel
+ * merges these (partial results in the area of the decode splits).  For
  * keys quantized per channel, one kernel in front of the passes finds, per cache and from the
  * stored scales and zero-points, the centre of every channel's keys, which is taken off the
  * dequantized keys before they are rounded (a constant per channel moves all scores of a query

@@ -34,6 +34,8 @@
 //      reference is shared by the four lanes that hold a query and only moves when a score exceeds it by more than 8
 //      in the exponent; the score products of quantized keys start from minus the reference, so that in the common
 //      case their results are the exponents themselves), fp32 accumulation, one division at the end.
+//   3. prefill_merge, only where a launch has too few query tiles for the GPU: the units of a tile are then attended in pieces by
+//      several work-groups (plan_pieces), and this kernel merges their un-normalised results.
 #include <hip/hip_ext.h>
 
 #include <type_traits>
@@ -44,7 +46,6 @@ namespace kvq {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;                // waves of an attention work-group
