@@ -240,7 +240,7 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
         // The same launch fills the ring, unless a new token's slot still holds a token that this launch quantizes: slots are
         // positions modulo RC, so the first such token would be RC behind the last new one.  (Never the case in a prompt's
         // first append, which quantizes nothing from the ring, or when one token is appended.)
-        if (copy && (np_old >= t_old || t_new - 1 < np_old + c->plan.RC)) {
+        if (copy && (np_old >= t_old || t_new - 1 < np_old + c->plan.RC) && kvq::quantize_takes_window(a.n_blocks, BH, t_new - pos0)) {
             a.copy_pos0 = pos0;
             a.copy_pos1 = t_new;
             copy = false;

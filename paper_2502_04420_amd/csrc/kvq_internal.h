@@ -111,6 +111,9 @@ __device__ __forceinline__ void split_range(const DecodeArgs &a, int split, int 
 }
 
 hipError_t launch_quantize(QuantArgs a, hipStream_t s);
+// whether a launch that quantizes n_blocks blocks of BH caches has work items left (32 bits of them) for the waves that copy
+// n_copy window tokens per cache
+bool quantize_takes_window(int n_blocks, int BH, int n_copy);
 hipError_t launch_residual_copy(const ResidualCopyArgs &a, hipStream_t s);
 hipError_t launch_export(const ExportArgs &a, hipStream_t s);
 hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);

@@ -229,26 +229,28 @@ __device__ __forceinline__ float wave_max64(float xf)
 __device__ __forceinline__ int value_row(int ch) { return (ch & 0x70) | ((ch ^ (ch >> 3)) & 15); }
 
 // Window rows taken along by the quantize launch (QuantArgs::copy_groups): new tokens [copy_pos0, copy_pos1) of one tensor,
-// input rows -> ring slots, kCopyRows rows per wave (16 lanes per row, four rows in flight per lane).
+// input rows -> ring slots, kCopyRows rows per wave (16 lanes per row, four rows in flight per lane).  Row numbers fit 32 bits
+// (quantize_takes_window).  The rows in flight are vector-extension values: an array of the runtime's uint4 was kept in scratch
+// memory, or in LDS by the instantiation that has none else (K16V16, 16 caches of 300 tokens: 10.4 us a launch, 4.3 so).
 constexpr int kCopyRows = 16;
 
 __device__ __forceinline__ void copy_window_rows(const QuantArgs &a, int group, bool values, int lane)
 {
-    const int n_tok = a.copy_pos1 - a.copy_pos0, c16 = lane & 15;
-    const uint16_t *in = values ? a.v_in : a.k_in;
-    uint16_t *ring = values ? a.lv.vres : a.lv.kres;
-    const long long rows = (long long)a.BH * n_tok, row0 = (long long)group * kCopyRows + (lane >> 4);
-    uint4 x[kCopyRows / 4];
+    const uint32_t n_tok = (uint32_t)(a.copy_pos1 - a.copy_pos0), rows = (uint32_t)a.BH * n_tok, c16 = lane & 15;
+    const uint32_t row0 = (uint32_t)group * kCopyRows + (lane >> 4);
+    const uint16_t *in = (values ? a.v_in : a.k_in) + 8 * c16;
+    uint16_t *ring = (values ? a.lv.vres : a.lv.kres) + 8 * c16;
+    u32x4 x[kCopyRows / 4];
     size_t dst[kCopyRows / 4];
 #pragma unroll
     for (int i = 0; i < kCopyRows / 4; i++) {
-        const long long r = row0 + 4 * i < rows ? row0 + 4 * i : rows - 1;       // past the end: the last row once more
-        const int bh = (int)(r / n_tok), pos = a.copy_pos0 + (int)(r % n_tok);
-        x[i] = *reinterpret_cast<const uint4 *>(in + ((size_t)bh * a.n_in + (pos - a.t_old)) * kD + 8 * c16);
-        dst[i] = ((size_t)bh * a.RC + pos % a.RC) * kD + 8 * c16;
+        const uint32_t r = row0 + 4 * i < rows ? row0 + 4 * i : rows - 1;        // past the end: the last row once more
+        const uint32_t bh = r / n_tok, pos = (uint32_t)a.copy_pos0 + (r - bh * n_tok);
+        x[i] = *reinterpret_cast<const u32x4 *>(in + ((size_t)bh * a.n_in + (pos - a.t_old)) * kD);
+        dst[i] = ((size_t)bh * a.RC + pos % (uint32_t)a.RC) * kD;
     }
 #pragma unroll
-    for (int i = 0; i < kCopyRows / 4; i++) *reinterpret_cast<uint4 *>(ring + dst[i]) = x[i];
+    for (int i = 0; i < kCopyRows / 4; i++) *reinterpret_cast<u32x4 *>(ring + dst[i]) = x[i];
 }
 
 // One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values; in front of them copy_groups waves per
@@ -669,12 +671,20 @@ unsigned blocks_for(long long total, int threads) { return (unsigned)((total + t
 
 }  // namespace
 
+static long long copy_groups(int BH, int n_copy) { return ((long long)BH * n_copy + kCopyRows - 1) / kCopyRows; }
+
+bool quantize_takes_window(int n_blocks, int BH, int n_copy)
+{
+    return ((long long)n_blocks * BH + copy_groups(BH, n_copy)) * 64 <= 0xffffffffLL;
+}
+
 hipError_t launch_quantize(QuantArgs a, hipStream_t s)
 {
     if (a.n_blocks < 1 || a.BH < 1) return hipSuccess;
-    const long long rows = (long long)a.BH * (a.copy_pos1 - a.copy_pos0), groups = rows > 0 ? (rows + kCopyRows - 1) / kCopyRows : 0;
-    if ((long long)a.n_blocks * a.BH + groups > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    a.copy_groups = (int)groups;
+    if ((long long)a.n_blocks * a.BH > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const int n_copy = a.copy_pos1 - a.copy_pos0;
+    if (n_copy > 0 && !quantize_takes_window(a.n_blocks, a.BH, n_copy)) return hipErrorInvalidConfiguration;
+    a.copy_groups = n_copy > 0 ? (int)copy_groups(a.BH, n_copy) : 0;
     return a.lv.narrow ? launch_quantize_kb<true>(a, s) : launch_quantize_kb<false>(a, s);
 }
 

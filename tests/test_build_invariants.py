@@ -61,6 +61,23 @@ def test_quantize_kernel_keeps_the_fused_widen_and_subtract(tmp_path):
     assert len(re.findall(r"^\s*v_fma_mix_f32 ", kernels[0], re.M)) >= 128      # 2 tensors x 64 elements per lane
 
 
+def test_quantize_kernels_keep_their_tokens_in_registers(tmp_path):
+    """No quantize kernel uses scratch memory, and the one that stores fp16 rows as they are uses no LDS: an array the
+    compiler cannot keep in registers (the window rows a launch takes along) ends up in the one or the other without any
+    message, and the launch takes two to four times as long."""
+    asm = _assembly("kvq_quantize.hip", tmp_path, extra=("-ffp-contract=off",))
+    kernels = 0
+    for block in re.split(r"\n  - \.agpr_count", asm)[1:]:
+        name = re.findall(r"\.name:\s+(_Z\S+)", block)[-1]
+        size = {k: int(v) for k, v in re.findall(r"\.(private_segment_fixed_size|group_segment_fixed_size):\s+(\d+)", block)}
+        if "quantize_blocks" in name:
+            kernels += 1
+            assert size["private_segment_fixed_size"] == 0, name
+            if "ILi16ELi16E" in name:
+                assert size["group_segment_fixed_size"] == 0, name
+    assert kernels == 32                                          # 4 x 4 bit widths, two scale precisions
+
+
 def test_builtin_scratch_array_is_visible_to_the_loader():
     """kvq_decode_attention_noalloc asks the runtime for the device address of the library's built-in scratch array.
     That only works if the device code object exports the array as a global symbol (an attribute such as `used` keeps
