@@ -65,8 +65,8 @@ def check_prefill_attention_code(asm: str) -> None:
     is only linked if, in the generated code, every M0 write is the one in front of such a fetch, nothing else reads or
     writes M0, and no kernel of the file spills registers (two waves per SIMD is what its pipelining assumes)."""
     kernels = kernel_bodies(asm, "prefill_attention")
-    if len(kernels) != 2:                                                  # keys quantized / fp16
-        raise RuntimeError("expected 2 prefill_attention kernels in the generated code, found %d" % len(kernels))
+    if len(kernels) != 4:                                                  # keys quantized / fp16, tiles cut / whole
+        raise RuntimeError("expected 4 prefill_attention kernels in the generated code, found %d" % len(kernels))
     for name, body in kernels:
         lines = [l.strip() for l in body.splitlines()]
         code = [l for l in lines if l and not l.startswith((";", ".", "_Z")) and not l.endswith(":")]

@@ -798,7 +798,7 @@ struct Piece { int tile, index, count, slot; };
 
 // How the tiles of a query head are cut into pieces (plan_pieces).  One word per tile, the tiles with the longest pieces
 // first: tile | pieces << 8 | pieces in front of it << 16 (whole words: the kernel reads them through the scalar unit).
-// pieces = 0: every tile is one piece.
+// pieces = 0: no tile is cut, the launch takes no table.
 constexpr int kMaxCutTiles = 128;
 constexpr int kMaxPieces = 255;          // of a tile
 struct PieceTable {
@@ -807,6 +807,9 @@ struct PieceTable {
     uint32_t entry[kMaxCutTiles];
 };
 
+// in place of the table where no tile is cut
+struct WholeTiles {};
+
 __device__ __forceinline__ int piece_partials(uint32_t entry)
 {
     const int count = (int)((entry >> 8) & 255u);
@@ -814,8 +817,8 @@ __device__ __forceinline__ int piece_partials(uint32_t entry)
 }
 
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
-// kLoCompact).
-template <int LO>
+// kLoCompact); CUT: the launch's tiles may be cut (else pc.tile alone counts).
+template <int LO, bool CUT>
 __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, int jq, const Piece &pc)
 {
     constexpr bool KLO = LO != kLoNone;
@@ -902,7 +905,11 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     // (taking the scores of the following unit ahead each time), then waits until its fetches have landed, and the
     // barrier makes everybody's visible.  Past the end the last unit is fetched again, into a buffer nobody reads.
     const int nbt = a.n_blocks < units ? a.n_blocks : units;     // the tile's
-    const int ub = nbt * pc.index / pc.count, nb = nbt * (pc.index + 1) / pc.count;
+    int ub = 0, nb = nbt;
+    if constexpr (CUT) {
+        ub = nbt * pc.index / pc.count;
+        nb = nbt * (pc.index + 1) / pc.count;
+    }
     if (nb > ub) {
         const uint8_t *mine = a.scratch + (size_t)local * a.n_blocks * sizeof(Tiles);
         const int last = nb - 1;
@@ -993,7 +1000,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         }
     }
     // ---- chunks of the fp16 window (with the tile's last piece), staged by the first four waves straight from the ring
-    const int uend = pc.index + 1 == pc.count ? units : nbt;
+    const int uend = !CUT || pc.index + 1 == pc.count ? units : nbt;
     for (int u = nbt; u < uend; u++) {
         if (wave < kStagers) stage_window(a, bh, u, T, tid, L[0]);
         __syncthreads();
@@ -1019,7 +1026,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         l += xor_lanes(l, 16);
         l += xor_lanes(l, 32);
         const int i = iw + 16 * qt + n;
-        if (i < a.n_q && pc.count > 1) {
+        if (CUT && i < a.n_q && pc.count > 1) {
             // a piece: un-normalised outputs and (reference, sum) of the query, for prefill_merge
             float *o = a.part_o + (size_t)(pc.slot * kQB + (i - i0)) * kD;
             if (rq == 0) *reinterpret_cast<float2 *>(a.part_ml + (size_t)(pc.slot * kQB + (i - i0)) * 2) = make_float2(m[qt], l);
@@ -1038,11 +1045,17 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 
 // KQ: the layer's keys are quantized.  Each cache of such a layer is attended in the form its selection record names
 // (without records: low parts of all channels).
-template <bool KQ>
-__global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a, PieceTable pt)
+//
+// PT: PieceTable, or WholeTiles where the plan cuts none: a kernel of its own because reading the table and dividing by piece
+// counts that are all 1 costs a work-group about 0.14 us, which shows in window-only prompts (call of one layer with / without:
+// 32 sequences of 22 tokens, 32 / 8 heads 15.6 / 15.1 us, of 33 tokens, 28 / 4 heads 21.0 / 20.4 us).
+template <bool KQ, class PT>
+__global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a, PT pt)
 {
+    constexpr bool CUT = std::is_same<PT, PieceTable>::value;
     const int tiles = (a.n_q + kQB - 1) / kQB;
-    const int pieces = pt.pieces ? pt.pieces : tiles;            // work-groups per query head
+    int pieces = tiles;                                          // work-groups per query head
+    if constexpr (CUT) pieces = pt.pieces;
     const int gq = a.Hq / a.Hkv;
     // Work-groups go to the 8 XCDs in turn by their index, and each XCD has an L2 of its own: all query heads and
     // query tiles that read one (batch, kv head) cache are given to one XCD (when the count divides), so that its
@@ -1063,7 +1076,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs 
         jq = head % gq;
     }
     Piece pc = {tiles - 1 - rank, 0, 1, 0};                      // the longest rows start first
-    if (pt.pieces) {
+    if constexpr (CUT) {
         uint32_t w = pt.entry[0];
         int before = 0;                                          // partial results of the tiles in front of this one
         for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) {
@@ -1077,10 +1090,10 @@ __global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs 
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact>(a, rec, local, jq, pc);
-        else attend<kLoAll>(a, rec, local, jq, pc);
+        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact, CUT>(a, rec, local, jq, pc);
+        else attend<kLoAll, CUT>(a, rec, local, jq, pc);
     } else {
-        attend<kLoNone>(a, nullptr, local, jq, pc);
+        attend<kLoNone, CUT>(a, nullptr, local, jq, pc);
     }
 }
 
@@ -1286,18 +1299,19 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
     // pass 2 (kBuffers tile buffers: more LDS than a kernel may declare statically)
     const dim3 grid((unsigned)groups), block(64 * kWaves);
     const size_t lds = kBuffers * sizeof(Tiles);
-    auto attend_launch = [&](auto kernel) -> hipError_t {
+    auto attend_launch = [&](auto kernel, auto table) -> hipError_t {
         // the larger dynamic LDS size is asked for at every launch of either kernel, on whichever device is current:
         // a host-side setting, negligible next to a launch of milliseconds, and no process-wide state to keep
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         hipEvent_t end = pt.pieces ? nullptr : ev_end;           // stamped by the end of the last kernel
-        if (begin || end) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, begin, end, 0, a, pt);
-        else hipLaunchKernelGGL(kernel, grid, block, lds, s, a, pt);
+        if (begin || end) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, begin, end, 0, a, table);
+        else hipLaunchKernelGGL(kernel, grid, block, lds, s, a, table);
         return hipGetLastError();
     };
-    const hipError_t e = kq ? attend_launch(prefill_attention<true>) : attend_launch(prefill_attention<false>);
-    if (e != hipSuccess || !pt.pieces) return e;
+    if (!pt.pieces) return kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
+    const hipError_t e = kq ? attend_launch(prefill_attention<true, PieceTable>, pt) : attend_launch(prefill_attention<false, PieceTable>, pt);
+    if (e != hipSuccess) return e;
     // pass 3
     const dim3 mgrid(kQB / kMergeRows, (unsigned)tiles, (unsigned)heads), mblock(32 * kMergeRows);
     if (ev_end) hipExtLaunchKernelGGL(prefill_merge, mgrid, mblock, 0, s, nullptr, ev_end, 0, a, pt);

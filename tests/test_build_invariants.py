@@ -51,6 +51,21 @@ def test_prefill_attention_writes_m0_only_for_its_own_fetches(tmp_path):
         B.check_prefill_attention_code(planted)
 
 
+def test_uncut_prefill_launches_take_no_piece_table():
+    """A prefill launch whose query tiles are not cut runs a kernel that knows no pieces: its arguments are a few pointers and
+    sizes, not the 520 bytes of the table, whose reading shows in the time of prompts of a few dozen tokens."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    asm = B.device_assembly("kvq_prefill_attn.hip")
+    sizes = []
+    for block in re.split(r"\n  - \.agpr_count", asm)[1:]:
+        if "prefill_attention" in re.findall(r"\.name:\s+(_Z\S+)", block)[-1]:
+            sizes.append(int(re.search(r"\.kernarg_segment_size:\s+(\d+)", block).group(1)))
+    assert len(sizes) == 4 and sorted(s > 512 for s in sizes) == [False, False, True, True], sizes
+
+
 def test_quantize_kernel_keeps_the_fused_widen_and_subtract(tmp_path):
     """x - z is meant to be one mixed-precision instruction per element (both fp16 operands widened inside it); the
     multiplier 1.0 is hidden from the optimiser for that.  If a compiler folds it after all, the code is still right
