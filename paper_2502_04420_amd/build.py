@@ -13,6 +13,8 @@ import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
 
+from .decode_check import check_decode_code, kernel_bodies
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libkvq.so")
@@ -55,11 +57,6 @@ def device_assembly(src: str, extra=()) -> str:
         return f.read()
 
 
-def kernel_bodies(asm: str, name: str):
-    """(mangled name, text) of the kernels whose mangled name contains `name`."""
-    return [(m.group(1), m.group(0)) for m in re.finditer(r"^(_Z\w*%s\w*):.*?^\.Lfunc_end\d+:" % name, asm, re.S | re.M)]
-
-
 def check_prefill_attention_code(asm: str) -> None:
     """The prefill attention kernels set M0 in inline assembly (LDS base of their global-to-LDS fetches).  The library
     is only linked if, in the generated code, every M0 write is the one in front of such a fetch, nothing else reads or
@@ -83,90 +80,6 @@ def check_prefill_attention_code(asm: str) -> None:
     spills = re.findall(r"\.vgpr_spill_count:\s+(\d+)", asm)
     if not spills or any(int(x) for x in spills):
         raise RuntimeError("kvq_prefill_attn.hip: register spills %s" % spills)
-
-
-def _vregs(text: str):
-    out = set()
-    for a, b in re.findall(r"\bv\[(\d+):(\d+)\]", text):
-        out.update(range(int(a), int(b) + 1))
-    out.update(int(a) for a in re.findall(r"\bv(\d+)\b", text))
-    return out
-
-
-def check_decode_code(asm: str) -> int:
-    """The matrix-core decode kernels issue the block loads of their streaming loop in inline assembly and wait for them
-    with hand-written counts; the compiler does not know that the destination registers are being written until the
-    wait.  The library is only linked if, in the generated code, no instruction of the compiler's own touches such a
-    register between the issue of a load and a wait that covers it.  Model: loads return in order, so after
-    `s_waitcnt vmcnt(N)` only the N youngest loads are pending.  The code is followed in layout order; a backward
-    conditional branch (a loop) is followed once more from its target with the state at the branch; the state is
-    dropped after an unconditional branch (what follows in the layout is reached from elsewhere).  A statement that
-    holds two waits (await_loads_either: the count depends on whether the zero-points of the next blocks were asked
-    for in this step) is taken with the larger count if at least that many loads were issued since the last wait,
-    else with the smaller.  Returns the number of hand-issued loads seen."""
-    seen = 0
-    for name, body in kernel_bodies(asm, "decode_mfma"):
-        lines = body.split("\n")
-        labels = {}
-        for i, l in enumerate(lines):
-            m = re.match(r"^(\.LBB\d+_\d+):", l)
-            if m:
-                labels[m.group(1)] = i
-
-        def run(start, stop, pending, follow):
-            nonlocal seen
-            in_asm = False
-            asm_waits = []
-            issued = 0                      # hand-issued loads since the last wait on the load counter
-            i = start
-            while i < stop:
-                t = lines[i].strip()
-                i += 1
-                if t.startswith(";;#ASMSTART"):
-                    in_asm = True
-                    asm_waits = []
-                    continue
-                if t.startswith(";;#ASMEND"):
-                    in_asm = False
-                    if asm_waits:
-                        # A statement that holds two waits takes one of them at run time: the larger count when further
-                        # loads (the zero-points of the next blocks) went out behind the awaited block's in this step,
-                        # which shows in the number of loads issued since the last wait; otherwise the smaller one.
-                        n = max(asm_waits) if issued >= max(asm_waits) else min(asm_waits)
-                        pending = pending[len(pending) - n:] if n else []
-                        issued = 0
-                    continue
-                if not t or t[0] in ";." or t.endswith(":"):
-                    continue
-                w = re.match(r"s_waitcnt\b.*vmcnt\((\d+)\)", t)
-                if w:
-                    n = int(w.group(1))
-                    if in_asm and re.match(r"s_waitcnt\s+vmcnt\(\d+\)$", t):
-                        asm_waits.append(n)
-                    else:
-                        pending = pending[len(pending) - n:] if n else []
-                        issued = 0
-                    continue
-                if in_asm:
-                    if t.startswith("buffer_load"):
-                        pending = pending + [_vregs(t.split(",")[0])]
-                        issued += 1
-                        if follow:
-                            seen += 1
-                    continue
-                used = _vregs(t)
-                for regs in pending:
-                    if used & regs:
-                        raise RuntimeError("%s: `%s` touches v%s while a hand-issued load may still be writing it"
-                                           % (name, t, sorted(used & regs)))
-                b = re.match(r"s_cbranch_\w+\s+(\.LBB\d+_\d+)", t)
-                if b and follow and labels.get(b.group(1), i) < i - 1:
-                    run(labels[b.group(1)], i - 1, list(pending), False)       # the loop once more, entered with this state
-                if t.startswith("s_branch") or t.startswith("s_endpgm"):
-                    pending = []
-
-        run(0, len(lines), [], True)
-    return seen
 
 
 def _check_generated_code() -> None:

@@ -279,7 +279,8 @@ __device__ __forceinline__ void await_loads_either(CodeRegs<BITS> &r, int more_b
 }
 
 // The (empty) loads of a group without blocks have landed.  The registers are not named: naming them on a second code path
-// would make the compiler copy them while the loads are still writing.
+// would make the compiler copy them while the loads are still writing.  That nothing else is put into them on the way here is
+// for the build to check (decode_check.py follows this path too).
 __device__ __forceinline__ void drain_unused() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // a block outside the streaming loop: issue and wait for everything

@@ -132,3 +132,37 @@ def test_decode_kernels_leave_hand_issued_loads_alone():
     planted = body[:m.end()] + "\tv_mov_b32_e32 v200, v%s\n" % m.group(2) + body[m.end():]
     with pytest.raises(RuntimeError):
         B.check_decode_code(asm.replace(body, planted, 1))
+
+
+def test_decode_check_follows_every_path_to_the_streaming_loop():
+    """The loads issued in front of the streaming loop are pending on both ways out of the prologue: into the loop, and past
+    it (a group without packed blocks).  A copy over one of their registers is refused wherever it is planted: behind the
+    last of them; in the key wave, whose queries are fetched first, also in front of the loop and in front of the wait of
+    the other way (the value wave waits for its queries, and with them for everything, before the two part)."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    asm = B.device_assembly("kvq_decode_mfma.hip")
+    plants = 0
+    for tag in ("ILi4ELi2ELi4ELb0ELb0E", "ILi8ELi8ELi4ELb1ELb0E", "ILi4ELi2ELi8ELb0ELb0E", "ILi2ELi4ELi4ELb0ELb1E"):
+        lines = [kb for kb in B.kernel_bodies(asm, "decode_mfma") if tag in kb[0]][0][1].split("\n")
+        by_hand = lambda i, start: lines[i].strip().startswith(start) and "ASMSTART" in lines[i - 1]     # noqa: E731
+        assert B.check_decode_code("\n".join(lines)) > 0
+        loops = [i for i, l in enumerate(lines) if l.strip() == "s_setprio 3"]
+        assert len(loops) == 2                                           # the value wave's, then the key wave's
+        for k, loop in enumerate(loops):
+            first = loops[0] if k else 0
+            waits = [i for i in range(first, loop) if re.search(r"vmcnt\(0\)", lines[i])]
+            drain = [i for i in waits if by_hand(i, "s_waitcnt vmcnt(0)")][-1]      # of a group without packed blocks
+            issued = [i for i in range(max(i for i in waits if i < drain) if k else 0, drain) if by_hand(i, "buffer_load")]
+            regs = [re.search(r"v\[?(\d+)", lines[i]).group(1) for i in issued]
+            assert len(regs) >= 3
+            spots = [(issued[-1] + 2, r) for r in regs]
+            if k:
+                spots += [(drain - 1, r) for r in regs] + [(loop, r) for r in regs[-2:]]
+            for spot, r in spots:
+                plants += 1
+                with pytest.raises(RuntimeError, match="hand-issued load"):
+                    B.check_decode_code("\n".join(lines[:spot] + ["\tv_mov_b32_e32 v%s, 0" % r] + lines[spot:]))
+    assert plants >= 4 * (3 + 3 + 3 + 2)
