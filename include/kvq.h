@@ -100,13 +100,19 @@ typedef struct kvq_config {
     int32_t key_mode;      /* a kvq_key_mode: axis along which keys are grouped (see there)      */
 } kvq_config;
 
-/* Bytes of device workspace kvq_configure needs for this configuration; 0 if it is invalid. */
+/*
+ * Bytes of device workspace that serve this configuration in full; 0 if it is invalid.  Where the area of the decode
+ * splits (66.6 KB per query head and sequence) holds fewer than 256 records of 133 KB and max_tokens is 768 or more, that
+ * includes up to 512 such records (68 MB) for the partial results of kvq_prefill_attention.  kvq_configure takes a workspace that is smaller
+ * by no more than that part, too: calls give the same results within rounding, and prefill attention of few queries cuts its tiles
+ * into fewer pieces, or into none, and takes longer.
+ */
 size_t kvq_workspace_bytes(const kvq_config *cfg);
 
 /*
  * Create a context (Section 5.1: the offline-searched table is loaded once, no online
  * decision remains).  `workspace_device` must be 256-byte aligned, at least
- * kvq_workspace_bytes(cfg) long and stay valid and untouched by the caller until
+ * kvq_workspace_bytes(cfg) long (see there for what may be missing) and stay valid and untouched by the caller until
  * kvq_destroy.  The kbits / vbits arrays are copied.  All layers start empty.
  */
 int kvq_configure(kvq_ctx **out, const kvq_config *cfg, void *workspace_device, size_t workspace_bytes,
@@ -186,12 +192,12 @@ int kvq_append_decode_attention(kvq_ctx *ctx, int32_t layer, const void *k_devic
  * Query head h attends kv head h / (n_q_heads / n_kv_heads).  The dequantized operands and the
  * softmax weights are rounded to fp16 for the matrix cores (keys as the sum of two fp16
  * numbers); accumulation is fp32.  The cache is not modified.  With n_q = 1 the result is that
- * of kvq_decode_attention up to rounding.  The call enqueues two kernels per pass over a group
+ * of kvq_decode_attention up to rounding.  The call enqueues two or three kernels per pass over a group
  * of (batch, kv head) caches: one dequantizes their packed tokens once into a scratch area
  * inside the workspace (16 * floor(max_tokens / 32) * 26 KiB, counted by kvq_workspace_bytes:
  * 16 caches per pass at full length, more when the layer holds fewer tokens), one attends; where a
  * pass has too few query tiles to fill the GPU, they are attended in pieces and a third kernel
- * merges these (partial results in the area of the decode splits).  For
+ * merges these (partial results in the area of the decode splits, which kvq_workspace_bytes enlarges for it).  For
  * keys quantized per channel, one kernel in front of the passes finds, per cache and from the
  * stored scales and zero-points, the centre of every channel's keys, which is taken off the
  * dequantized keys before they are rounded (a constant per channel moves all scores of a query

@@ -74,7 +74,8 @@ struct Plan {
     int prefill_chunk;      // (batch, kv head) caches whose dequantized units the prefill scratch holds at a time
 };
 
-Plan make_plan(const kvq_config *c)
+// bytes: what the caller's workspace holds
+Plan make_plan(const kvq_config *c, size_t bytes = SIZE_MAX)
 {
     Plan p;
     const size_t BH = (size_t)c->batch * c->n_kv_heads;
@@ -100,18 +101,24 @@ Plan make_plan(const kvq_config *c)
     // The prefill attention's partial results share that area with the decode splits': the two kinds of calls follow each
     // other on the context's stream.  They belong to pieces of query tiles (tiles are cut where they are too few to fill the
     // GPU, into pieces of 12 units or more, so only where there are 24).  A piece per compute unit is enough for most
-    // launches; where the splits' area does not hold that many, it grows to hold two.
+    // launches; where the splits' area does not hold that many, it grows to hold two, or as many as the workspace has
+    // room for: with fewer slots the tiles are cut less, or not at all.
+    p.prefill_chunk = BH < (size_t)kPrefillChunk ? (int)BH : kPrefillChunk;
+    const size_t scratch = align_up((size_t)p.prefill_chunk * p.NB * kvq::prefill_unit_bytes());
+    const size_t select = align_up(BH * kvq::prefill_select_bytes());                     // (a pass may take all caches)
+    const size_t least = off + scratch + select, piece = kvq::prefill_piece_bytes();
     const size_t tiles = ((size_t)c->max_tokens + 255) / 256;
     const size_t most = p.NB < 24 ? 0 : rows * tiles * (p.NB / 12);
-    size_t slots = (off - p.part_o) / kvq::prefill_piece_bytes();
+    size_t slots = (off - p.part_o) / piece;
     if (slots < kPrefillSlots / 2) slots = kPrefillSlots;
     if (slots > most) slots = most;
     if (slots > kPrefillSlots) slots = kPrefillSlots;
+    const size_t room = (off - p.part_o + (bytes > least ? bytes - least : 0)) / piece;   // (piece: a multiple of kAlign)
+    if (slots > room) slots = room;
     p.prefill_slots = (int)slots;
-    if (off < p.part_o + slots * kvq::prefill_piece_bytes()) off = align_up(p.part_o + slots * kvq::prefill_piece_bytes());
-    p.prefill_chunk = BH < (size_t)kPrefillChunk ? (int)BH : kPrefillChunk;
-    p.prefill_scratch = off; off = align_up(off + (size_t)p.prefill_chunk * p.NB * kvq::prefill_unit_bytes());
-    p.prefill_select = off; off = align_up(off + BH * kvq::prefill_select_bytes());       // (a pass may take all caches)
+    if (off < p.part_o + slots * piece) off = p.part_o + slots * piece;
+    p.prefill_scratch = off; off += scratch;
+    p.prefill_select = off; off += select;
     p.total = off;
     return p;
 }
@@ -185,7 +192,7 @@ int kvq_configure(kvq_ctx **out, const kvq_config *cfg, void *workspace_device, 
     if (!out) return KVQ_EINVAL;
     *out = nullptr;
     if (!config_ok(cfg)) return KVQ_EINVAL;
-    Plan plan = make_plan(cfg);
+    Plan plan = make_plan(cfg, workspace_bytes);
     if (!workspace_device || (reinterpret_cast<uintptr_t>(workspace_device) % kAlign) || workspace_bytes < plan.total)
         return KVQ_EWORKSPACE;
     kvq_ctx *c = new (std::nothrow) kvq_ctx();

@@ -132,6 +132,40 @@ def test_query_tiles_cut_into_pieces(kvq_mod, oracle_mod, T, n_q, batch, hq, hkv
     g.close()
 
 
+@pytest.mark.parametrize("slots", [0, 1, 3, 7, 40])
+def test_workspace_with_room_for_few_pieces_or_none(kvq_mod, oracle_mod, slots):
+    """kvq_configure takes a workspace without the room kvq_workspace_bytes counts for partial results of pieces: the call then
+    cuts its tiles into fewer pieces or none.  One query head, whose split records hold no piece; 60 units, 5 tiles."""
+    import ctypes
+
+    from paper_2502_04420_amd.binding import make_config
+
+    T, n_q = 1940, 1100
+    w = W.Workload("few pieces", 1, 1, 1, 1, 128, T, [4], [4], seed=77, outlier_channels=3)
+    g = kvq_mod.KVQ(1, 1, 1, 1, 128, T, [4], [4])
+    o = oracle_mod.OracleCache(1, 1, 1, 1, 128, [4], [4])
+    lib, cfg, keep = g._lib, *make_config(1, 1, 1, 1, 128, T, [4], [4])
+    record = 256 * 130 * 4
+    # kvq_workspace_bytes without the records: rows * tiles * (units / 12) of them
+    least = lib.kvq_workspace_bytes(ctypes.byref(cfg)) - 8 * 5 * record + 128 * 130 * 4
+    ws = torch.full((least + slots * record + 256,), 0x5a, dtype=torch.uint8, device="cuda:0")
+    base = (ws.data_ptr() + 255) // 256 * 256
+    lib.kvq_destroy(g._h)
+    h = ctypes.c_void_p()
+    assert lib.kvq_configure(ctypes.byref(h), ctypes.byref(cfg), ctypes.c_void_p(base), least - 1, None) == -4
+    assert lib.kvq_configure(ctypes.byref(h), ctypes.byref(cfg), ctypes.c_void_p(base), least + slots * record, None) == 0
+    g._h = h
+    K, V = W.kv_tokens(w, 0, 0, T)
+    g.quantize_append(0, K.cuda(), V.cuda())
+    o.quantize_append(0, K.numpy(), V.numpy())
+    q = W.prefill_queries(w, 0, n_q)
+    out = g.prefill_attention(0, q.cuda())
+    assert_prefill_close(out, o.prefill_attention(0, q.numpy())[1], "%d slots" % slots)
+    end = base - ws.data_ptr() + least + slots * record
+    assert torch.all(ws[end:] == 0x5a) and torch.all(ws[:base - ws.data_ptr()] == 0x5a)
+    g.close()
+
+
 @pytest.mark.parametrize("hq,hkv", [(1, 1), (7, 1), (8, 1), (6, 3), (28, 4)])
 def test_head_ratios(kvq_mod, oracle_mod, hq, hkv):
     w = W.Workload("heads", 1, 2, hq, hkv, 128, 32 * 5 + 9, [4], [4], seed=500 + hq, outlier_channels=2)

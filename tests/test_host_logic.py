@@ -99,6 +99,36 @@ def test_configure_and_call_errors_without_gpu(lib):
     assert lib.kvq_last_error() is not None
 
 
+def _bytes_without_pieces(layers, batch, hq, hkv, tokens, kb, vb, unit, residual=32):
+    """The workspace without room for partial results of prefill pieces, worked out from the layout that DESIGN lists:
+    packed blocks, window rings, split records, dequantized units of `unit` bytes, one selection record per cache."""
+    up = lambda x: -(-x // 256) * 256                                    # noqa: E731
+    caches, blocks, rows = batch * hkv, tokens // 32, batch * hq
+    total = 0
+    for bits in (kb, vb):
+        total += layers * (up(caches * blocks * 512 * bits) + up(caches * blocks * (768 if bits < 16 else 0)) + up(caches * (residual + 32) * 256))
+    total += layers * up(caches * blocks * 4)
+    total += up(rows * 128 * 128 * 4) + up(rows * 128 * 2 * 4)
+    return total + up(min(caches, 16) * blocks * unit) + up(caches * 768)
+
+
+@pytest.mark.parametrize("layers,batch,hq,hkv,tokens,kb,vb", [
+    (28, 1, 28, 4, 4096, 4, 2), (32, 1, 32, 8, 4133, 4, 2), (1, 1, 8, 2, 800, 4, 2), (4, 1, 32, 8, 24576, 16, 16),
+    (2, 8, 32, 8, 2048, 8, 4), (2, 64, 32, 8, 2048, 4, 4), (1, 1, 1, 1, 700, 2, 2)])
+def test_workspace_of_the_former_size_is_accepted(lib, layers, batch, hq, hkv, tokens, kb, vb):
+    """Room for the partial results of prefill pieces is asked for but not insisted on: a workspace of the size that was
+    enough before there were any (27 KiB per dequantized unit, no records) is taken, down to the layout without them."""
+    cfg, keep = _cfg(n_layers=layers, batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=tokens, kbits=[kb] * layers, vbits=[vb] * layers)
+    need = lib.kvq_workspace_bytes(ctypes.byref(cfg))
+    former = _bytes_without_pieces(layers, batch, hq, hkv, tokens, kb, vb, 27 * 1024)
+    least = _bytes_without_pieces(layers, batch, hq, hkv, tokens, kb, vb, 26 * 1024)
+    assert least <= need <= least + 512 * 256 * 130 * 4
+    for have, expected in ((former, 0), (least, 0), (least + 133120, 0), (need, 0), (need + 4096, 0), (least - 1, -4)):
+        h = ctypes.c_void_p()
+        assert lib.kvq_configure(ctypes.byref(h), ctypes.byref(cfg), ctypes.c_void_p(256), have, None) == expected, (have - least, need - least)
+        lib.kvq_destroy(h)
+
+
 def test_library_load_brings_torch_first():
     """The library must bind to the HIP runtime that torch ships (the one that owns torch's streams and allocations):
     loading it in a fresh interpreter, before anything imported torch, has to import torch on the way."""
