@@ -293,16 +293,27 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
         const int groups = variant != 2 ? 1024 : width <= 8 ? 2048 : 1024;
         const int min_units = variant == 2 ? 4 : 8;
         splits = (groups + BH - 1) / BH;
-        int cap = (n_blocks + min_units - 1) / min_units + (n_res > 0 ? 1 : 0);
-        // Short caches of a small batch: where 4 blocks per group make a few more groups than there are compute units, 5 per
-        // group give each a unit of its own (one sequence, 8 kv heads of 4133 tokens, 264 or 216 groups: 11.1 or 10.7 us a
-        // call; 4 kv heads of 8200 tokens, 260 or 208: 14.3 or 12.7.  With two groups per unit and more it is the other way
-        // round: 24 caches of 2500 tokens, 480 or 384 groups: 11.5 or 12.4).
-        // With very few caches 2 blocks per group: 2 kv heads of 512 tokens, 5 or 9 splits: 9.2 or 8.4 us (8 kv heads: alike).
-        // (Counted in work-groups: a split is one per 8 query heads of a cache.)
-        const long long groups_per_split = (long long)BH * ((gq + 7) / 8);
-        if (variant == 2 && groups_per_split * cap > kCUs && groups_per_split * cap <= kCUs + kCUs / 4) cap = (n_blocks + 4) / 5 + (n_res > 0 ? 1 : 0);
-        else if (variant == 2 && groups_per_split * (n_blocks / 2 + 1) <= kCUs / 4) cap = (n_blocks + 1) / 2 + (n_res > 0 ? 1 : 0);
+        // most splits where each takes `blocks` blocks and one the window, and the work-groups they make (one per split, cache and 8 query heads)
+        auto cap_at = [&](int blocks) { return (n_blocks + blocks - 1) / blocks + (n_res > 0 ? 1 : 0); };
+        const long long per_split = (long long)BH * ((gq + 7) / 8);
+        const int chunks = (n_res + 31) / 32;
+        int cap = cap_at(min_units);
+        if (variant == 2) {
+            // Few groups leave every compute unit one group or none, and a call takes as long as its longest group.  Measured
+            // (8, 4 and 2 kv heads, batch 1 to 12, K4V2 and K8V8, us a call, 4 blocks per group / the other):
+            // - 5 blocks, where 4 make more groups than there are compute units and 5 do not: one sequence, 8 kv heads, a window of two
+            //   chunks, 264..320 groups 11.1..11.4 / 10.6..10.8, 4 kv heads 13.9 / 12.2; 50 such shapes gain 0..16 %.  Where 5
+            //   still make more (312 / 264 groups, 336 / 272 and up) most lose 2..5 %, but not with a window of three
+            //   chunks and more, which is the longest group and slower beside another one (24 caches of 47 blocks, five chunks:
+            //   15.3 / 14.2; -4..+5 %, +1 % on average, up to 320 groups).  A window of one chunk or none is the
+            //   shorter group, and with less than 32 groups over, half of the shapes lose (264 groups -5..+4 %); from 32 over
+            //   they gain 0..7 % (but 12 x 4 kv heads, 288 groups: -4 %).
+            // - 2 blocks, up to 64 groups, where the window is one chunk at most: 9.2 / 8.4 (2 kv heads, 512 tokens), 5..15 % on all shapes.
+            //   A group with two chunks of window takes as long as one with 4 blocks: there 2 blocks are 1 % faster to 4 % slower.
+            const long long with4 = per_split * cap_at(4), with5 = per_split * cap_at(5);
+            if (with4 >= kCUs + (chunks > 1 ? 1 : 32) && (with5 <= kCUs || (chunks > 2 && with4 <= kCUs + kCUs / 4))) cap = cap_at(5);
+            else if (chunks <= 1 && per_split * (n_blocks / 2 + 1) <= kCUs / 4) cap = cap_at(2);
+        }
         if (splits > cap) splits = cap;
     }
     if (splits > kMaxSplits) splits = kMaxSplits;

@@ -226,3 +226,31 @@ def test_split_plan_covers_every_unit_once_and_leaves_no_split_empty(lib):
     for bad in ((5, 10, 2, 0), (0, 0, 2, 0), (0, 257, 2, 0), (0, 10, 3, 0), (0, 10, 2, 129), (-1, 10, 2, 0)):
         assert lib.kvq_debug_split_plan(ctypes.byref(cfg), bad[0], bad[1], bad[2], bad[3], ctypes.byref(s), ctypes.byref(u), ctypes.byref(r)) == -1, bad
     assert lib.kvq_debug_split_plan(ctypes.byref(cfg), 0, 10, 2, 0, None, ctypes.byref(u), ctypes.byref(r)) == -1
+
+
+@pytest.mark.parametrize("batch,hq,hkv,residual,T,expected", [
+    # (work-groups with 4 / 5 blocks per group; a split is one per cache and 8 query heads)
+    (1, 32, 8, 32, 128 * 32 + 37, 27),       # 264 / 216, two chunks of window: 5 blocks
+    (1, 32, 8, 32, 155 * 32 + 60, 32),       # 320 / 256
+    (1, 32, 8, 32, 156 * 32 + 60, 40),       # 320 / 264: 5 blocks are too many groups as well
+    (1, 32, 8, 32, 124 * 32 + 60, 32),       # 256: one group per compute unit with 4 blocks
+    (3, 32, 8, 32, 46 * 32 + 60, 13),        # 312 / 264
+    (3, 32, 8, 128, 47 * 32 + 137, 11),      # 312 / 264, five chunks of window: 5 blocks all the same
+    (3, 32, 8, 128, 52 * 32 + 137, 14),      # 336 / 288
+    (1, 28, 4, 32, 255 * 32 + 41, 52),       # 260 / 208
+    (1, 32, 8, 32, 127 * 32 + 32, 33),       # 264 / 216, one chunk: less than 32 groups over
+    (1, 32, 8, 32, 139 * 32 + 32, 29),       # 288 / 232, one chunk
+    (1, 32, 8, 0, 143 * 32, 29),             # 288 / 232, no window
+    (1, 8, 2, 32, 15 * 32 + 32, 9),          # 2 blocks per group: one chunk, 16 groups
+    (1, 8, 2, 32, 15 * 32 + 41, 5),          # two chunks: 4 blocks
+    (1, 8, 2, 32, 62 * 32 + 32, 32),         # 64 groups with 2 blocks
+    (1, 8, 2, 32, 64 * 32 + 32, 17),         # 66
+    (2, 8, 1, 128, 20 * 32 + 137, 6),        # five chunks
+])
+def test_split_plan_of_short_caches(lib, batch, hq, hkv, residual, T, expected):
+    """Blocks per group of short caches on either side of the lines that measurements drew."""
+    i32 = ctypes.c_int32
+    cfg, keep = _cfg(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=40000, kbits=[4], vbits=[2], residual=residual)
+    s, u, r = i32(), i32(), i32()
+    assert lib.kvq_debug_split_plan(ctypes.byref(cfg), 0, T, 2, 0, ctypes.byref(s), ctypes.byref(u), ctypes.byref(r)) == 0
+    assert s.value == expected
