@@ -47,6 +47,7 @@ def _compile(src: str) -> str:
 
 def device_assembly(src: str, extra=()) -> str:
     """The gfx950 assembly hipcc generates for one source file with the library's flags."""
+    os.makedirs(OBJ, exist_ok=True)
     out = os.path.join(OBJ, src.replace(".hip", ".s"))
     cmd = (["hipcc"] + COMMON + ["-w"] + PER_FILE.get(src, []) + list(extra)
            + ["-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", out])

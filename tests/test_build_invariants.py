@@ -51,6 +51,15 @@ def test_prefill_attention_writes_m0_only_for_its_own_fetches(tmp_path):
         B.check_prefill_attention_code(planted)
 
 
+def test_assembly_can_be_taken_before_anything_is_built(tmp_path, monkeypatch):
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    monkeypatch.setattr(B, "OBJ", str(tmp_path / "not there yet"))
+    assert "amdgcn" in B.device_assembly("kvq_api.hip")
+
+
 def test_uncut_prefill_launches_take_no_piece_table():
     """A prefill launch whose query tiles are not cut runs a kernel that knows no pieces: its arguments are a few pointers and
     sizes, not the 520 bytes of the table, whose reading shows in the time of prompts of a few dozen tokens."""
