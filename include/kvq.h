@@ -247,6 +247,17 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
                          int32_t *splits, int32_t *units_per_split, int32_t *split_rem);
 
 /*
+ * How a kvq_prefill_attention call would be divided (host only, no GPU work): on a context configured with *cfg and a workspace
+ * of workspace_bytes, a layer that holds n_tokens tokens, n_q queries.  Pass number `pass` (0, 1, ..) attends to *caches (batch, kv
+ * head) caches, 0 when there is no such pass; in it query tile `tile` (queries 256 tile .. 256 tile + 255) is attended in
+ * *pieces pieces (1: it stays whole): piece i of p takes the units [u i / p, u (i + 1) / p) of the u packed blocks up to the
+ * tile's last query, the last piece the fp16 window as well.  For tests and tuning;
+ * KVQ_EINVAL on invalid arguments, KVQ_EWORKSPACE where kvq_configure would return it.
+ */
+int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t tile,
+                           int32_t *caches, int32_t *pieces);
+
+/*
  * Tuning knobs (optional).  variant: 0 = choose automatically, 1 = vector-ALU kernel,
  * 2 = matrix-core kernel.  splits: 0 = automatic, else the number of token-range splits
  * per (batch, kv head) used to fill the GPU (at most 128).  Returns KVQ_EINVAL for unknown

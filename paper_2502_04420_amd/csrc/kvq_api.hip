@@ -466,6 +466,26 @@ int kvq_append_decode_attention(kvq_ctx *c, int32_t layer, const void *k_device,
     return rc;
 }
 
+namespace {
+
+// The caches are taken a chunk at a time: dequantize the chunk's packed units into the scratch area, attend.
+// The scratch area holds prefill_chunk caches of NB units; a shorter prompt leaves room for more caches per
+// pass (kept a multiple of the 8 XCDs, which the attention kernel's placement wants): fewer, larger launches.
+int prefill_pass_caches(const Plan &plan, int BH, int n_blocks)
+{
+    int chunk = plan.prefill_chunk;
+    if (n_blocks > 0 && chunk < BH) {
+        const long long fit = (long long)plan.prefill_chunk * plan.NB / n_blocks;
+        if (fit >= BH) chunk = BH;
+        else if (fit / 8 * 8 > chunk) chunk = (int)(fit / 8 * 8);
+    } else if (n_blocks == 0) {
+        chunk = BH;                                             // window only: nothing goes through the scratch area
+    }
+    return chunk;
+}
+
+}  // namespace
+
 int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32_t n_q, void *out_device)
 {
     if (!c || layer < 0 || layer >= c->cfg.n_layers || !q_device || !out_device) return KVQ_EINVAL;
@@ -496,17 +516,7 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
     a.part_slots = c->plan.prefill_slots;
     const bool timed = c->ev_begin && c->ev_end;
     const int BH = a.B * a.Hkv;
-    // The caches are taken a chunk at a time: dequantize the chunk's packed units into the scratch area, attend.
-    // The scratch area holds prefill_chunk caches of NB units; a shorter prompt leaves room for more caches per
-    // pass (kept a multiple of the 8 XCDs, which the attention kernel's placement wants): fewer, larger launches.
-    int chunk = c->plan.prefill_chunk;
-    if (a.n_blocks > 0 && chunk < BH) {
-        const long long fit = (long long)c->plan.prefill_chunk * c->plan.NB / a.n_blocks;
-        if (fit >= BH) chunk = BH;
-        else if (fit / 8 * 8 > chunk) chunk = (int)(fit / 8 * 8);
-    } else if (a.n_blocks == 0) {
-        chunk = BH;                                             // window only: nothing goes through the scratch area
-    }
+    const int chunk = prefill_pass_caches(c->plan, BH, a.n_blocks);
     // Keys quantized per channel: one kernel in front decides for every cache which channels keep the low parts of
     // their keys (one record per cache), unless the caller wants them kept for all.
     uint8_t *select = nullptr;
@@ -588,6 +598,30 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
     *splits = p.splits;
     *units_per_split = p.units_per_split;
     *split_rem = p.split_rem;
+    return KVQ_OK;
+}
+
+int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t tile,
+                           int32_t *caches, int32_t *pieces)
+{
+    if (!config_ok(cfg) || n_tokens < 1 || n_tokens > cfg->max_tokens || n_q < 1 || n_q > n_tokens || pass < 0 || tile < 0 || tile > (n_q - 1) / 256 ||
+        !caches || !pieces)
+        return KVQ_EINVAL;
+    const Plan plan = make_plan(cfg, workspace_bytes);
+    if (workspace_bytes < plan.total) return KVQ_EWORKSPACE;
+    const int over = n_tokens - cfg->residual, np = over > 0 ? kvq::kG * (over / kvq::kG) : 0, BH = cfg->batch * cfg->n_kv_heads;
+    const int chunk = prefill_pass_caches(plan, BH, np / kvq::kG);
+    const long long bh0 = (long long)pass * chunk;
+    kvq::PrefillArgs a = {};
+    a.Hq = cfg->n_q_heads;
+    a.Hkv = cfg->n_kv_heads;
+    a.n_blocks = np / kvq::kG;
+    a.n_res = n_tokens - np;
+    a.n_q = n_q;
+    a.n_bh = bh0 >= BH ? 0 : BH - bh0 < chunk ? (int)(BH - bh0) : chunk;
+    a.part_slots = plan.prefill_slots;
+    *caches = a.n_bh;
+    *pieces = a.n_bh > 0 ? kvq::prefill_tile_pieces(a, tile) : 0;
     return KVQ_OK;
 }
 

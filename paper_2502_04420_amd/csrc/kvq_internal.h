@@ -119,6 +119,8 @@ hipError_t launch_export(const ExportArgs &a, hipStream_t s);
 hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);
 // ev_begin / ev_end (both or neither): receive the start and stop time stamps of the kernel's own dispatch
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+// pieces that launch_prefill_attention(a) cuts query tile `tile` into (host only; 1: it stays whole)
+int prefill_tile_pieces(const PrefillArgs &a, int tile);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache

@@ -1246,8 +1246,21 @@ PieceTable plan_pieces(const Tiling &g, int heads, int slots)
     return best;
 }
 
+PieceTable plan_pieces(const PrefillArgs &a)
+{
+    const Tiling tiling = {(a.n_q + kQB - 1) / kQB, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q};
+    return plan_pieces(tiling, a.n_bh * (a.Hq / a.Hkv), a.part_slots);
+}
+
 }  // namespace
 
+int prefill_tile_pieces(const PrefillArgs &a, int tile)
+{
+    const PieceTable t = plan_pieces(a);
+    for (int r = 0; t.pieces && r < (a.n_q + kQB - 1) / kQB; r++)
+        if ((int)(t.entry[r] & 255u) == tile) return (int)((t.entry[r] >> 8) & 255u);
+    return 1;
+}
 
 size_t prefill_piece_bytes() { return kQB * (kD + 2) * sizeof(float); }
 
@@ -1273,8 +1286,7 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
 {
     const long long tiles = (a.n_q + kQB - 1) / kQB;
     const int heads = a.n_bh * (a.Hq / a.Hkv);                   // query heads of the launch
-    const Tiling tiling = {(int)tiles, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q};
-    const PieceTable pt = plan_pieces(tiling, heads, a.part_slots);
+    const PieceTable pt = plan_pieces(a);
     const long long groups = (pt.pieces ? pt.pieces : tiles) * heads;
     if (groups < 1 || groups > 0x7fffffffLL || a.n_bh < 1 || a.n_bh > 65535) return hipErrorInvalidConfiguration;
     const bool kq = a.lv.kbits < 16, vq = a.lv.vbits < 16;

@@ -107,28 +107,76 @@ def test_ragged_lengths_and_query_counts(kvq_mod, oracle_mod, T, n_q):
     g.close()
 
 
-@pytest.mark.parametrize("T,n_q,batch,hq,hkv,residual,kb", [
-    (800, 800, 1, 4, 1, 32, 4),          # 24 units: the shortest tile that is cut in two
-    (799, 640, 1, 4, 1, 0, 2),           # diagonal units among the packed ones, up to the last
-    (1500, 1500, 1, 8, 2, 32, 4),        # tiles of different piece counts
-    (2300, 300, 1, 7, 1, 32, 8),         # two tiles, many pieces each; heads that do not divide by 8
-    (2048 + 5, 257, 2, 8, 4, 32, 4),     # a tile of one query; caches that divide by 8
-    (3000, 1, 1, 2, 1, 32, 4),           # a single query
-    (1700, 900, 1, 4, 2, 500, 4),        # a window of 15 chunks, which the last pieces take along
-    (1200, 1200, 1, 4, 1, 32, 16),       # fp16 keys (raw scores)
+def _most_pieces(g, n_q, T):
+    """Per pass of a prefill-attention call, the most pieces one of its tiles is cut into."""
+    import ctypes
+
+    from paper_2502_04420_amd.binding import make_config
+
+    cfg, keep = make_config(1, g.batch, g.n_q_heads, g.n_kv_heads, 128, g.max_tokens, g.kbits, g.vbits, residual=g.residual,
+                            meta_dtype=g.meta_dtype, key_mode=g.key_mode)
+    c, n, most = ctypes.c_int32(), ctypes.c_int32(), []
+    while True:
+        row = []
+        for tile in range((n_q + 255) // 256):
+            assert g._lib.kvq_debug_prefill_plan(ctypes.byref(cfg), g.workspace.numel(), T, n_q, len(most), tile, ctypes.byref(c), ctypes.byref(n)) == 0
+            row.append(n.value)
+        if c.value == 0:
+            return most
+        most.append(max(row))
+
+
+@pytest.mark.parametrize("T,n_q,batch,hq,hkv,residual,kb,pieces", [
+    (800, 800, 1, 4, 1, 32, 4, [2]),         # 24 units: the shortest tile that is cut in two
+    (799, 640, 1, 4, 1, 0, 2, [1]),          # diagonal units among the packed ones, up to the last but one; not worth a cut
+    (1600, 900, 1, 4, 1, 0, 2, [4]),         # diagonal units among the packed ones, up to the last: no window at all
+    (1500, 1500, 1, 8, 2, 32, 4, [3]),       # tiles of different piece counts
+    (2300, 300, 1, 7, 1, 32, 8, [5]),        # two tiles, many pieces each; heads that do not divide by 8
+    (2048 + 5, 257, 2, 8, 4, 32, 4, [5]),    # a tile of one query; caches that divide by 8
+    (3000, 1, 1, 2, 1, 32, 4, [7]),          # a single query
+    (3496, 7, 1, 1, 1, 32, 4, [9]),          # nine pieces: the merge takes eight at a time, then one
+    (3800, 300, 1, 1, 1, 32, 2, [9]),
+    (6300, 257, 1, 1, 1, 32, 4, [15]),       # a full and a ragged second round of the merge
+    (6700, 300, 1, 1, 1, 32, 8, [16]),       # two full rounds
+    (1700, 900, 1, 4, 2, 500, 4, [3]),       # a window of 15 chunks, which the last pieces take along
+    (1200, 1200, 1, 4, 1, 32, 16, [3]),      # fp16 keys (raw scores)
+    (900, 300, 5, 4, 4, 32, 4, [2, 2]),      # two passes over 16 + 4 caches, which use the partial results' area in turn
+    (900, 64, 17, 2, 1, 32, 4, [2, 2]),      # 16 + 1 caches
 ])
-def test_query_tiles_cut_into_pieces(kvq_mod, oracle_mod, T, n_q, batch, hq, hkv, residual, kb):
-    """Few query tiles: their packed units are attended in pieces by several work-groups and merged."""
+def test_query_tiles_cut_into_pieces(kvq_mod, oracle_mod, T, n_q, batch, hq, hkv, residual, kb, pieces):
+    """Few query tiles: their packed units are attended in pieces by several work-groups and merged.  pieces: the most that a
+    tile of each pass is cut into."""
     w = W.Workload("pieces", 1, batch, hq, hkv, 128, T, [kb], [4], seed=700 + T, outlier_channels=3)
     g = kvq_mod.KVQ(1, batch, hq, hkv, 128, T, [kb], [4], residual=residual)
     o = oracle_mod.OracleCache(1, batch, hq, hkv, 128, [kb], [4], residual=residual)
     K, V = W.kv_tokens(w, 0, 0, T)
     g.quantize_append(0, K.cuda(), V.cuda())
     o.quantize_append(0, K.numpy(), V.numpy())
+    assert _most_pieces(g, n_q, T) == pieces
     q = W.prefill_queries(w, 0, n_q)
     out = g.prefill_attention(0, q.cuda())
     assert_prefill_close(out, o.prefill_attention(0, q.numpy())[1], "T%d nq%d" % (T, n_q))
     assert torch.equal(out, g.prefill_attention(0, q.cuda()))            # the pieces and their order are fixed
+    g.close()
+
+
+@pytest.mark.parametrize("form", ["low parts of all channels", "wide keys", "offset on every channel", "fp16 scales", "per-token keys", "fp16 scales, per-token keys",
+                                  "fp16 values", "fp16 keys and values"])
+@pytest.mark.parametrize("kb", [8, 2])
+def test_cut_tiles_in_every_form_of_the_units(kvq_mod, oracle_mod, form, kb):
+    """Pieces of tiles (1500 tokens, two kv heads, 600 queries: three) in each form that dequantized units come in."""
+    T, n_q, vb = 1500, 600, 4
+    if "values" in form:
+        vb = 16
+    if "keys and values" in form:
+        kb = 16
+    n, mult, offs = {"wide keys": (128, 12.0, 0.0), "offset on every channel": (0, 1.0, 20.0)}.get(form, (3, 12.0, 0.0))
+    meta = kvq_mod.META_FP16 if "fp16 scales" in form else kvq_mod.META_FP32
+    keys = kvq_mod.KEYS_PER_TOKEN if "per-token" in form else kvq_mod.KEYS_PER_CHANNEL
+    w = W.Workload("cut forms", 1, 1, 8, 2, 128, T, [kb], [vb], seed=950 + kb, outlier_channels=n, outlier_scale=mult, key_bias_std=offs)
+    out, o64, g, o, q = _run(kvq_mod, oracle_mod, w, n_q, meta=meta, keys=keys, max_tokens=T, low_parts=1 if form.startswith("low") else None)
+    assert _most_pieces(g, n_q, T) == [3]
+    assert_prefill_close(out, o64, "%s K%d" % (form, kb))
     g.close()
 
 

@@ -129,6 +129,58 @@ def test_workspace_of_the_former_size_is_accepted(lib, layers, batch, hq, hkv, t
         lib.kvq_destroy(h)
 
 
+def _prefill_passes(lib, cfg, have, T, n_q):
+    """[(caches, [pieces of each query tile])] of the passes of a prefill-attention call."""
+    i32 = ctypes.c_int32
+    passes = []
+    while True:
+        c, n, row = i32(), i32(), []
+        for tile in range((n_q + 255) // 256):
+            assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), have, T, n_q, len(passes), tile, ctypes.byref(c), ctypes.byref(n)) == 0
+            row.append(n.value)
+        if c.value == 0:
+            assert row == [0] * len(row)
+            return passes
+        passes.append((c.value, row))
+
+
+@pytest.mark.parametrize("batch,hq,hkv", [(1, 1, 1), (1, 2, 1), (1, 7, 1), (1, 32, 8), (2, 8, 4), (3, 28, 4), (17, 1, 1), (20, 2, 1)])
+@pytest.mark.parametrize("residual", [0, 32, 500])
+def test_prefill_plan_covers_every_tile_within_the_slots(lib, batch, hq, hkv, residual):
+    """kvq_debug_prefill_plan over lengths, query counts and workspaces: the passes cover the caches; every piece of a cut
+    tile holds at least 12 units and begins with one that lies in front of the tile's first query (so that every query sees a
+    token of it); the partial results fit the records the workspace has room for."""
+    seen = set()
+    for T in (5, 700, 799, 800, 801, 1600, 2027, 3000, 6700, 24576, 33000):
+        cfg, keep = _cfg(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=T, kbits=[4], vbits=[2], residual=residual)
+        need = lib.kvq_workspace_bytes(ctypes.byref(cfg))
+        least = _bytes_without_pieces(1, batch, hq, hkv, T, 4, 2, 26 * 1024, residual)
+        area = batch * hq * 128 * 130 * 4                                # split records: their room counts as well
+        n_blocks = max(T - residual, 0) // 32
+        for n_q in {1, min(T, 30), min(T, 257), min(T, 900), T}:
+            for have in (need, least, min(need, least + 5 * 133120)):
+                slots = min(512, (area + have - least) // 133120)
+                passes = _prefill_passes(lib, cfg, have, T, n_q)
+                assert sum(c for c, _ in passes) == batch * hkv
+                for caches, row in passes:
+                    heads = caches * (hq // hkv)
+                    assert sum(n for n in row if n > 1) * heads <= slots, (T, n_q, have - least)
+                    for tile, n in enumerate(row):
+                        first, last = T - n_q + 256 * tile, T - n_q + min(256 * tile + 255, n_q - 1)
+                        units = min(n_blocks, last // 32 + 1)
+                        assert n >= 1 and (n == 1 or units >= 24), (T, n_q, tile, n)
+                        for i in range(n if n > 1 else 0):
+                            u0, u1 = units * i // n, units * (i + 1) // n
+                            assert u1 - u0 >= 12 and 32 * u0 + 31 <= first, (T, n_q, tile, n)
+                        seen.add(n)
+    assert len(seen) >= 3
+    c, n = ctypes.c_int32(), ctypes.c_int32()
+    for bad in ((0, 1, 0, 0), (T + 1, 1, 0, 0), (T, 0, 0, 0), (T, T + 1, 0, 0), (T, 5, -1, 0), (T, 5, 0, 1), (T, 5, 0, -1)):
+        assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), need, *bad, ctypes.byref(c), ctypes.byref(n)) == -1, bad
+    assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), need, T, 5, 0, 0, None, ctypes.byref(n)) == -1
+    assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), least - 1, T, 5, 0, 0, ctypes.byref(c), ctypes.byref(n)) == -4
+
+
 def test_library_load_brings_torch_first():
     """The library must bind to the HIP runtime that torch ships (the one that owns torch's streams and allocations):
     loading it in a fresh interpreter, before anything imported torch, has to import torch on the way."""
