@@ -7,6 +7,7 @@ paper_2502_04420_amd/_build/.  hipcc cross-compiles, so no GPU is needed to buil
 """
 from __future__ import annotations
 
+import functools
 import os
 import re
 import subprocess
@@ -45,8 +46,9 @@ def _compile(src: str) -> str:
     return obj
 
 
+@functools.lru_cache(maxsize=None)
 def device_assembly(src: str, extra=()) -> str:
-    """The gfx950 assembly hipcc generates for one source file with the library's flags."""
+    """The gfx950 assembly hipcc generates for one source file with the library's flags (once per process and source)."""
     os.makedirs(OBJ, exist_ok=True)
     out = os.path.join(OBJ, src.replace(".hip", ".s"))
     cmd = (["hipcc"] + COMMON + ["-w"] + PER_FILE.get(src, []) + list(extra)

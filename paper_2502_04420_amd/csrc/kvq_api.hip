@@ -21,7 +21,7 @@ constexpr int kMaxSplits = 128;
 constexpr int kPrefillChunk = 16;   // caches dequantized per prefill-attention pass (two per XCD)
 constexpr size_t kPrefillSlots = 512;  // partial results of prefill attention: two pieces of a query tile per compute unit (68 MB)
 constexpr int kWindowWeight = 6;   // cost of a chunk (<= 32 tokens) of the fp16 window in a split's share, in packed blocks
-constexpr int kCUs = 256;          // compute units of the GPU
+using kvq::kCUs;
 constexpr size_t kAlign = 256;
 
 thread_local char g_last_error[256] = "";
@@ -107,7 +107,7 @@ Plan make_plan(const kvq_config *c, size_t bytes = SIZE_MAX)
     const size_t scratch = align_up((size_t)p.prefill_chunk * p.NB * kvq::prefill_unit_bytes());
     const size_t select = align_up(BH * kvq::prefill_select_bytes());                     // (a pass may take all caches)
     const size_t least = off + scratch + select, piece = kvq::prefill_piece_bytes();
-    const size_t tiles = ((size_t)c->max_tokens + 255) / 256;
+    const size_t tiles = ((size_t)c->max_tokens + kvq::kQueryTile - 1) / kvq::kQueryTile;
     const size_t most = p.NB < 24 ? 0 : rows * tiles * (p.NB / 12);
     size_t slots = (off - p.part_o) / piece;
     if (slots < kPrefillSlots / 2) slots = kPrefillSlots;
@@ -512,7 +512,7 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
     a.scratch = c->ws + c->plan.prefill_scratch;
     a.select = nullptr;
     a.part_o = ws_part_o(c);
-    a.part_ml = a.part_o + (size_t)c->plan.prefill_slots * 256 * kvq::kD;
+    a.part_ml = a.part_o + (size_t)c->plan.prefill_slots * kvq::kQueryTile * kvq::kD;
     a.part_slots = c->plan.prefill_slots;
     const bool timed = c->ev_begin && c->ev_end;
     const int BH = a.B * a.Hkv;
@@ -604,7 +604,7 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
 int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t tile,
                            int32_t *caches, int32_t *pieces)
 {
-    if (!config_ok(cfg) || n_tokens < 1 || n_tokens > cfg->max_tokens || n_q < 1 || n_q > n_tokens || pass < 0 || tile < 0 || tile > (n_q - 1) / 256 ||
+    if (!config_ok(cfg) || n_tokens < 1 || n_tokens > cfg->max_tokens || n_q < 1 || n_q > n_tokens || pass < 0 || tile < 0 || tile > (n_q - 1) / kvq::kQueryTile ||
         !caches || !pieces)
         return KVQ_EINVAL;
     const Plan plan = make_plan(cfg, workspace_bytes);

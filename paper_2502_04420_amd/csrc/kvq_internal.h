@@ -21,6 +21,9 @@ struct LayerView {
     int kpt;              // 1: keys grouped per token over 32 channels (metadata laid out like the values')
 };
 
+constexpr int kCUs = 256;          // compute units of the GPU
+constexpr int kQueryTile = 256;    // queries that a work-group of the prefill attention kernel takes
+
 struct QuantArgs {
     LayerView lv;
     const uint16_t *k_in, *v_in;   // fp16 [BH][n_in][128], the tokens of this append

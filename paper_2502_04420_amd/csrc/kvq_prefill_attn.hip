@@ -53,6 +53,7 @@ constexpr int kStagers = 4;              // waves that turn a unit into tiles (2
 constexpr int kQT = 2;                   // tiles of 16 queries per wave
 constexpr int kQW = 16 * kQT;            // queries per wave
 constexpr int kQB = kQW * kWaves;       // queries per work-group
+static_assert(kQB == kQueryTile, "the host counts query tiles");
 constexpr int kKStride = kD + 16;       // halves per K^ row: 288 bytes.  Measured with a probe kernel: the 16-byte operand reads of a wave
                                         // (16 rows x 4 pieces) take 3.9 LDS cycles at this stride, like a linear read; 7.8 + 3.9 conflict cycles at 272
 
@@ -798,7 +799,7 @@ struct Piece { int tile, index, count, slot; };
 
 // How the tiles of a query head are cut into pieces (plan_pieces).  One word per tile, the tiles with the longest pieces
 // first: tile | pieces << 8 | pieces in front of it << 16 (whole words: the kernel reads them through the scalar unit).
-// pieces = 0: no tile is cut, the launch takes no table.
+// pieces = 0: every tile is one piece.
 constexpr int kMaxCutTiles = 128;
 constexpr int kMaxPieces = 255;          // of a tile
 struct PieceTable {
@@ -807,7 +808,7 @@ struct PieceTable {
     uint32_t entry[kMaxCutTiles];
 };
 
-// in place of the table where no tile is cut
+// in place of the table where no tile can be cut
 struct WholeTiles {};
 
 __device__ __forceinline__ int piece_partials(uint32_t entry)
@@ -817,7 +818,7 @@ __device__ __forceinline__ int piece_partials(uint32_t entry)
 }
 
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
-// kLoCompact); CUT: the launch's tiles may be cut (else pc.tile alone counts).
+// kLoCompact); CUT: the tile may be cut (else pc.tile alone counts).
 template <int LO, bool CUT>
 __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, int jq, const Piece &pc)
 {
@@ -1046,16 +1047,17 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 // KQ: the layer's keys are quantized.  Each cache of such a layer is attended in the form its selection record names
 // (without records: low parts of all channels).
 //
-// PT: PieceTable, or WholeTiles where the plan cuts none: a kernel of its own because reading the table and dividing by piece
-// counts that are all 1 costs a work-group about 0.14 us, which shows in window-only prompts (call of one layer with / without:
-// 32 sequences of 22 tokens, 32 / 8 heads 15.6 / 15.1 us, of 33 tokens, 28 / 4 heads 21.0 / 20.4 us).
+// PT: PieceTable, or WholeTiles where the units are too few for a cut: reading the table and dividing by piece counts that are all 1
+// costs a work-group about 0.14 us, which shows in short prompts (call of one layer with / without: 32 sequences of 22
+// tokens, 32 / 8 heads 15.6 / 15.1 us, of 33 tokens, 28 / 4 heads 21.0 / 20.4 us).  Long prompts of whole tiles keep the kernel
+// that knows the table: its loop is compiled a little better (4 x 8192 tokens 2436 us; without 2454).
 template <bool KQ, class PT>
 __global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a, PT pt)
 {
     constexpr bool CUT = std::is_same<PT, PieceTable>::value;
     const int tiles = (a.n_q + kQB - 1) / kQB;
     int pieces = tiles;                                          // work-groups per query head
-    if constexpr (CUT) pieces = pt.pieces;
+    if constexpr (CUT) pieces = pt.pieces ? pt.pieces : tiles;
     const int gq = a.Hq / a.Hkv;
     // Work-groups go to the 8 XCDs in turn by their index, and each XCD has an L2 of its own: all query heads and
     // query tiles that read one (batch, kv head) cache are given to one XCD (when the count divides), so that its
@@ -1077,16 +1079,18 @@ __global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs 
     }
     Piece pc = {tiles - 1 - rank, 0, 1, 0};                      // the longest rows start first
     if constexpr (CUT) {
-        uint32_t w = pt.entry[0];
-        int before = 0;                                          // partial results of the tiles in front of this one
-        for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) {
-            before += piece_partials(w);
-            w = pt.entry[r];
+        if (pt.pieces) {
+            uint32_t w = pt.entry[0];
+            int before = 0;                                      // partial results of the tiles in front of this one
+            for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) {
+                before += piece_partials(w);
+                w = pt.entry[r];
+            }
+            pc.tile = (int)(w & 255u);
+            pc.index = rank - (int)(w >> 16);
+            pc.count = (int)((w >> 8) & 255u);
+            pc.slot = (local * gq + jq) * pt.partials + before + pc.index;
         }
-        pc.tile = (int)(w & 255u);
-        pc.index = rank - (int)(w >> 16);
-        pc.count = (int)((w >> 8) & 255u);
-        pc.slot = (local * gq + jq) * pt.partials + before + pc.index;
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
@@ -1149,17 +1153,19 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
 // A compute unit holds one attention work-group (its five tile buffers fill the LDS), so a launch of few tiles leaves the
 // chip idle, and one whose longest tiles take longer than an even share of all units waits for them.  The plan compares
 // the uncut launch with cuts of the one to four longest tiles only and with cuts into pieces of 1/2, 1/3 .. 1/16 of the
-// longest tile, each by the time its pieces take when the compute units pick them up longest first.  In units of 32 tokens: kPieceCost more per piece for its queries,
-// first fetches and results; behind a cut kMergeCost for the launch that merges, and one per kPartialsPerUnit partial
-// results (130 KiB each, written and read once).  Measured on the Llama shape (K4V2, whole call in us, uncut / cut as
+// longest tile, each by the time its pieces take when the compute units pick them up longest first.  In units of 32 tokens:
+// kPieceCost more per piece for its queries, first fetches and results; behind a cut kMergeCost for the launch that merges, and
+// one per kPartialsPerUnit partial results (130 KiB each, written and read once).  Measured on the Llama shape (K4V2, whole call in us, uncut / cut as
 // planned): 512 queries over 24576 tokens 833 / 292, 300 over 8000 297 / 129, a 2000-token prompt of 2 kv heads
-// 92 / 63, of 8 kv heads 106 / 100 (finer cuts 106..122: the partial results outweigh the even load).
-constexpr int kCUs = 256;
+// 92 / 63, of 8 kv heads 106 / 100 (finer cuts 106..122: the partial results outweigh the even load).  The constants are those
+// of compact units (36 products); units with all low parts (48) or fp16 keys (32) count the same.  Of 163 calls of all forms,
+// 17 to 30000 tokens, 8 queries and more, none takes longer than with whole tiles.
 constexpr int kPieceCost = 4;
 constexpr int kMergeCost = 4;
 constexpr int kPartialsPerUnit = 20;
 constexpr int kMinPiece = 12;            // units: more than a tile's diagonal and one unit in front of it (9 + 1), so that every query of the
                                          // tile sees the whole first unit of its last piece (softmax_unit relies on it)
+constexpr int kLeastCut = 2 * kMinPiece; // units of a cache that can be cut
 
 struct Tiling { int tiles, n_blocks, p0, n_q; };
 
@@ -1232,7 +1238,7 @@ PieceTable plan_pieces(const Tiling &g, int heads, int slots)
     PieceTable best;
     best.pieces = best.partials = 0;
     // (with three work-groups and more for every compute unit the longest tiles start early enough)
-    if (g.tiles > kMaxCutTiles || g.n_blocks < 2 * kMinPiece || (long long)heads * g.tiles >= 3 * kCUs || slots < 2) return best;
+    if (g.tiles > kMaxCutTiles || g.n_blocks < kLeastCut || (long long)heads * g.tiles >= 3 * kCUs || slots < 2) return best;
     const int longest = tile_units(g, g.tiles - 1);
     PieceTable t;
     long long least = cut(g, heads, longest, t);
@@ -1321,9 +1327,10 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
         else hipLaunchKernelGGL(kernel, grid, block, lds, s, a, table);
         return hipGetLastError();
     };
-    if (!pt.pieces) return kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
+    if (a.n_blocks < kLeastCut)
+        return kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
     const hipError_t e = kq ? attend_launch(prefill_attention<true, PieceTable>, pt) : attend_launch(prefill_attention<false, PieceTable>, pt);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || !pt.pieces) return e;
     // pass 3
     const dim3 mgrid(kQB / kMergeRows, (unsigned)tiles, (unsigned)heads), mblock(32 * kMergeRows);
     if (ev_end) hipExtLaunchKernelGGL(prefill_merge, mgrid, mblock, 0, s, nullptr, ev_end, 0, a, pt);

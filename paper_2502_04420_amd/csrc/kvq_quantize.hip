@@ -255,8 +255,8 @@ __device__ __forceinline__ void copy_window_rows(const QuantArgs &a, int group, 
 
 // One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values; in front of them copy_groups waves per
 // tensor that put the tokens which stay in the window into the ring (a launch of its own for those took 4-5 us behind every
-// append: a 2027-token prompt, append and attention of 4 layers, 418 -> 409 us without it; 16 x 8192 tokens, append and
-// first token of 2 layers, 323 -> 319 us).  The statistics are
+// append: a 2027-token prompt, append and attention of 4 layers, 418 -> 409 us without it; behind 16 x 8192 tokens, append and
+// first token of 2 layers, it is lost in what the placement of the buffers does, 2.5 % of 320 us).  The statistics are
 // taken in the arrangement the rows are loaded in (16 bytes = 8 channels of a token per lane), the tile
 // goes through LDS, and each lane encodes exactly the 64 codes it stores.
 template <int KB, int VB, bool NARROW>

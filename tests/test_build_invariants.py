@@ -61,8 +61,8 @@ def test_assembly_can_be_taken_before_anything_is_built(tmp_path, monkeypatch):
 
 
 def test_uncut_prefill_launches_take_no_piece_table():
-    """A prefill launch whose query tiles are not cut runs a kernel that knows no pieces: its arguments are a few pointers and
-    sizes, not the 520 bytes of the table, whose reading shows in the time of prompts of a few dozen tokens."""
+    """A prefill launch too short for a cut of its query tiles runs a kernel that knows no pieces: its arguments are a few pointers
+    and sizes, not the 520 bytes of the table, whose reading shows in the time of prompts of a few dozen tokens."""
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
     from paper_2502_04420_amd import build as B
