@@ -154,9 +154,10 @@ int kvq_decode_attention(kvq_ctx *ctx, int32_t layer, const void *q_device, void
  * array's address there (make that first call outside a stream capture; every later call only
  * launches kernels and can be recorded into a graph and replayed).
  *   Limit: batch * n_q_heads * splits <= 16384 records, else KVQ_ESCRATCH and nothing is
- *   enqueued (kvq_last_error has the numbers).  With automatic splits (at most 2048 token
- *   ranges over all (batch, kv head) caches) every shape with at most 8 query heads per kv head
- *   fits; splits forced through kvq_set_decode_options may not.
+ *   enqueued (kvq_last_error has the numbers).  Automatic splits are at most 128 per cache and at most ceil(2048 / (batch *
+ *   n_kv_heads)), so a shape fits at every length if batch * n_q_heads times that is no more than 16384: with up to 292
+ *   caches always for at most 7 query heads per kv head, for 8 where batch * n_kv_heads divides 2048.  Splits forced
+ *   through kvq_set_decode_options may not fit.
  *   All contexts and streams on one GPU share that GPU's array.  Nothing in it has to start at
  *   zero (each call writes every record it later reads), but two such calls that overlap in time
  *   on one GPU race on it: keep them on one stream or order them yourself.
