@@ -100,7 +100,7 @@ def test_configure_and_call_errors_without_gpu(lib):
 
 
 def _bytes_without_pieces(layers, batch, hq, hkv, tokens, kb, vb, unit, residual=32):
-    """The workspace without room for partial results of prefill pieces, worked out from the layout that DESIGN lists:
+    """The workspace without room for partial results of prefill pieces, worked out from the layout:
     packed blocks, window rings, split records, dequantized units of `unit` bytes, one selection record per cache."""
     up = lambda x: -(-x // 256) * 256                                    # noqa: E731
     caches, blocks, rows = batch * hkv, tokens // 32, batch * hq
