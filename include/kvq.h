@@ -279,7 +279,8 @@ int kvq_set_prefill_options(kvq_ctx *ctx, int32_t low_parts);
  * caller (created with timing enabled), or both NULL to switch the hook off.  While set,
  * every decode call makes its main kernel (the fused dequantize-and-attend kernel) stamp
  * begin_event with the start and end_event with the end of that kernel's own execution on the
- * context's stream (the small kernel that merges the token-range splits runs after end_event);
+ * context's stream (the small kernel that merges the token-range splits runs after end_event; calls on short
+ * caches have none, their main kernel merges);
  * a kvq_prefill_attention call stamps them with the start of its first and the end of its last
  * kernel; the caller synchronises and reads hipEventElapsedTime.  The events must outlive the hook.
  * Returns KVQ_EINVAL when exactly one of the two is NULL.

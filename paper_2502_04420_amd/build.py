@@ -85,19 +85,25 @@ def check_prefill_attention_code(asm: str) -> None:
         raise RuntimeError("kvq_prefill_attn.hip: register spills %s" % spills)
 
 
-def _check_generated_code() -> None:
+def _check_prefill() -> None:
     check_prefill_attention_code(device_assembly("kvq_prefill_attn.hip"))
-    if check_decode_code(device_assembly("kvq_decode_mfma.hip")) == 0:
-        raise RuntimeError("kvq_decode_mfma.hip: no hand-issued loads found in the generated code")
+
+
+def _check_decode(src: str) -> None:
+    if check_decode_code(device_assembly(src)) == 0:
+        raise RuntimeError("%s: no hand-issued loads found in the generated code" % src)
 
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
-        checked = ex.submit(_check_generated_code)          # alongside the compiles; a failure refuses the link
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        # alongside the compiles; a failure refuses the link
+        checked = [ex.submit(_check_decode, src) for src in srcs if src.startswith(("kvq_decode_mfma", "kvq_decode_short"))]
         objs = list(ex.map(_compile, srcs))
-        checked.result()
+        checked.append(ex.submit(_check_prefill))
+        for c in checked:
+            c.result()
     tmp = OUT + ".tmp.%d" % os.getpid()
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs,
                        capture_output=True, text=True)

@@ -170,6 +170,13 @@ float *ws_part_o(const kvq_ctx *c) { return reinterpret_cast<float *>(c->ws + c-
 float *ws_part_ml(const kvq_ctx *c) { return reinterpret_cast<float *>(c->ws + c->plan.part_ml); }
 size_t ws_part_records(const kvq_ctx *c) { return (size_t)c->cfg.batch * c->cfg.n_q_heads * kMaxSplits; }
 
+// Arrival counters of the decode kernel: in the selection records of the prefill attention, one record per cache.  A cache's
+// counters start at zero when its first block is quantized (only calls with packed blocks have more than one split) and are zero
+// again after every call.
+uint32_t *ws_tickets(const kvq_ctx *c) { return reinterpret_cast<uint32_t *>(c->ws + c->plan.prefill_select + kvq::prefill_ticket_offset()); }
+int ticket_stride() { return (int)(kvq::prefill_select_bytes() / sizeof(uint32_t)); }
+int tickets_per_cache(const kvq_ctx *c) { return (c->cfg.n_q_heads / c->cfg.n_kv_heads + 7) / 8; }
+
 int launch_failed(const char *what, hipError_t e)
 {
     snprintf(g_last_error, sizeof g_last_error, "%s: %s", what, hipGetErrorString(e));
@@ -244,6 +251,9 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
         a.NB = c->plan.NB;
         a.RC = c->plan.RC;
         a.copy_pos0 = a.copy_pos1 = a.copy_groups = 0;
+        a.tickets = ws_tickets(c);
+        a.ticket_stride = ticket_stride();
+        a.counters = tickets_per_cache(c) <= kvq::kMaxTickets ? tickets_per_cache(c) : 0;
         // The same launch fills the ring, unless a new token's slot still holds a token that this launch quantizes: slots are
         // positions modulo RC, so the first such token would be RC behind the last new one.  (Never the case in a prompt's
         // first append, which quantizes nothing from the ring, or when one token is appended.)
@@ -392,17 +402,30 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
                  (size_t)a.B * a.Hq * (size_t)splits, a.B * a.Hq, splits, part_records);
         return KVQ_ESCRATCH;
     }
+    // Two pairs of waves per work-group as long as the work-groups are all resident at once (three per compute unit for codes up to 8
+    // bits per key + value element, whose kernels leave room for that many, else two).  Measured, us a call (32 / 8 heads, one pair
+    // / two): K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups 12.6 / 15.6; K8V8 256 groups 9.9 / 8.9,
+    // 544 groups 11.3 / 11.5, 1024 groups 13.7 / 17.4; K16V16 256 groups 12.2 / 10.8, 520 groups 14.6 / 15.7.  A single split saves the
+    // merge at any number: 512 groups 11.0 / 8.0, 2048 groups 19.8 / 19.1.
+    // The last work-group merges up to 64 splits of 4 heads (48 splits 9.6 behind a launch / 9.2) or 16 of 8 heads, whose records
+    // it fetches in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
+    const long long groups = (long long)a.B * a.Hkv * tickets_per_cache(c) * splits;
+    const bool paired = variant == 2 && (splits == 1 || groups <= (a.lv.kbits + a.lv.vbits <= 8 ? 3 : 2) * kCUs);
+    const bool merged = paired && splits <= (a.Hq / a.Hkv <= 4 ? kvq::kMergeSplits : 16) && tickets_per_cache(c) <= kvq::kMaxTickets;
+    a.tickets = merged ? ws_tickets(c) : nullptr;
+    a.ticket_stride = ticket_stride();
     const bool timed = c->ev_begin && c->ev_end;
     hipError_t e;
     if (variant == 2) {
         // the matrix-core kernel's dispatch stamps the two events itself (its own start and end, no marker in between)
-        e = kvq::launch_decode_mfma(a, c->stream, timed ? c->ev_begin : nullptr, timed ? c->ev_end : nullptr);
+        e = (paired ? kvq::launch_decode_short : kvq::launch_decode_mfma)(a, c->stream, timed ? c->ev_begin : nullptr, timed ? c->ev_end : nullptr);
     } else {
         if (timed && hipEventRecord(c->ev_begin, c->stream) != hipSuccess) return launch_failed("event record", hipGetLastError());
         e = kvq::launch_decode_valu(a, c->stream);
         if (e == hipSuccess && timed && hipEventRecord(c->ev_end, c->stream) != hipSuccess) return launch_failed("event record", hipGetLastError());
     }
     if (e != hipSuccess) return launch_failed("decode kernel", e);
+    if (merged || (paired && splits == 1)) return KVQ_OK;
     e = kvq::launch_combine(a, c->stream);
     if (e != hipSuccess) return launch_failed("combine kernel", e);
     return KVQ_OK;

@@ -22,9 +22,18 @@
 // neighbouring blocks overlap on different SIMDs and each wave carries only half of the state
 // (which is what lets 4 waves share a SIMD and hide the memory latency).  Each wave writes its
 // part of the split's partial result itself; the splits are merged by combine_splits.
+//
+// Short caches give few work-groups, each of which takes its blocks one after the other, and a call takes as long as that
+// chain (0.6 us per block, on two of a compute unit's four SIMDs) and two launches.  There a work-group has two such pairs (KVQ_DECODE_PAIRS 2,
+// kvq_decode_short.hip): each takes half of the split's units, or one the blocks and one the window, their results meet in LDS, a
+// single split writes the outputs, and of several splits the work-group that finishes last merges the records (merge_pairs).
 #include <hip/hip_ext.h>
 
 #include "kvq_internal.h"
+
+#ifndef KVQ_DECODE_PAIRS
+#define KVQ_DECODE_PAIRS 1
+#endif
 
 namespace kvq {
 namespace {
@@ -763,15 +772,154 @@ __device__ __forceinline__ void rescale_rows(float (&oF)[GQ][4], float (&shrink)
     }
 }
 
+// ------------------------------------------------------------------ merge of a work-group's pairs, and of the splits
+
+static_assert(kMergeSplits == 64, "two records' maxima and sums per lane");
+
+// the maximum / sum over the 32 lanes of a half wave, in every lane
+__device__ __forceinline__ float half_max32(float x) { x = row_max16(x); return fmaxf(x, __shfl_xor(x, 16, 64)); }
+__device__ __forceinline__ float half_sum32(float x) { x = row_sum16(x); return x + __shfl_xor(x, 16, 64); }
+
+__device__ __forceinline__ void store_through(float *p, float4v v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
+}
+
+// o / l as fp16 to four channels of the output row (the caller's tensor: fp16 alignment is all it owes)
+__device__ __forceinline__ void store_output(uint16_t *out, float4v o, float l)
+{
+    const half2v h0 = {(_Float16)(o[0] / l), (_Float16)(o[1] / l)}, h1 = {(_Float16)(o[2] / l), (_Float16)(o[3] / l)};
+    const u32x2 h = {__builtin_bit_cast(uint32_t, h0), __builtin_bit_cast(uint32_t, h1)};
+    __builtin_memcpy(out, &h, sizeof h);
+}
+
+// The records of all splits (at most kMergeSplits) of the tile's heads -> outputs, by the whole work-group: 32 lanes per head and
+// subset of the splits, the subsets' sums meet in LDS.  The order of all sums is fixed, whichever work-group comes last.
+// The records come from work-groups on all XCDs: they are read past the caches (sc0 sc1), as they were written.
+// Bound by the latency of the reads (0.45 us), so as many as there are registers for go out at once.
+template <int GQ, int PAIRS>
+__device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid)
+{
+    constexpr int kBeyond = 17;                                  // cache policy bits: sc0, sc1
+    constexpr int kSubsets = 4 * PAIRS / GQ;
+    constexpr int kAhead = GQ == 8 ? 16 : 8;                     // records on their way per thread
+    float (*sums)[kD] = reinterpret_cast<float (*)[kD]>(&Ls[0].Ak[0][0]);                   // [subset * GQ + head][channel]
+    static_assert(sizeof(PairLds<GQ>) * (PAIRS - 1) >= sizeof(float) * kD * kSubsets * GQ, "the sums fit the first pairs' memory");
+    static_assert(sizeof(PairLds<GQ>) >= sizeof(float) * kSubsets * GQ * kMergeSplits, "the weights fit the last pair's");
+    const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, head = half % GQ, subset = half / GQ;
+    float *weights = reinterpret_cast<float *>(&Ls[PAIRS - 1].Ak[0][0]) + half * kMergeSplits;
+    const RowStream po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + qrow0 * a.splits * kD, 0, nvalid * a.splits * (int)(kD * sizeof(float)), 0x00020000);
+    const RowStream pm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + qrow0 * a.splits * 2, 0, nvalid * a.splits * (int)(2 * sizeof(float)), 0x00020000);
+    const int first = (head < nvalid ? head : nvalid - 1) * a.splits;
+    u32x2 ml[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) ml[k] = __builtin_amdgcn_raw_buffer_load_b64(pm, (first + (lane + 32 * k < a.splits ? lane + 32 * k : 0)) * 8, 0, kBeyond);
+    u32x4 x[kAhead];
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const int sp = s0 + subset + kSubsets * k;
+            x[k] = __builtin_amdgcn_raw_buffer_load_b128(po, (first + (sp < a.splits ? sp : 0)) * (int)(kD * sizeof(float)) + 16 * lane, 0, kBeyond);
+        }
+    };
+    fetch(0);
+    float m[2], l[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const uint32_t mw = ml[k][0], lw = ml[k][1];
+        m[k] = lane + 32 * k < a.splits ? __builtin_bit_cast(float, mw) : -INFINITY;
+        l[k] = __builtin_bit_cast(float, lw);
+    }
+    const float M = half_max32(fmaxf(m[0], m[1]));
+    float sum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const float f = m[k] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m[k] - M);       // (no such split: weight zero)
+        weights[lane + 32 * k] = f;
+        sum = fmaf(f, l[k], sum);
+    }
+    sum = half_sum32(sum);
+    wave_lds_sync();
+    float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s0 = 0; s0 < a.splits; s0 += kSubsets * kAhead) {
+        if (s0 > 0) fetch(s0);
+#pragma unroll
+        for (int k = 0; k < kAhead; k++) {
+            const int sp = s0 + subset + kSubsets * k;
+            const float f = sp < a.splits ? weights[sp] : 0.0f;
+            const uint32_t w0 = x[k][0], w1 = x[k][1], w2 = x[k][2], w3 = x[k][3];
+            O += f * float4v{__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1), __builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)};
+        }
+    }
+    *reinterpret_cast<float4v *>(&sums[half][4 * lane]) = O;
+    wg_barrier();
+    if (subset == 0 && head < nvalid) {
+#pragma unroll
+        for (int k = 1; k < kSubsets; k++) O += *reinterpret_cast<const float4v *>(&sums[k * GQ + head][4 * lane]);
+        store_output(a.out + (qrow0 + head) * kD + 4 * lane, O, sum);
+    }
+}
+
+// The pairs' results, from LDS, to the record of the split (or, with a single split, to the outputs).  With arrival counters the
+// work-group that is the last of its cache and tile to count itself merges the splits: it waits for nobody.  A record is written
+// through to memory and its stores are complete before the work-group counts itself, the counter is in memory too (device
+// scope), and the last one reads past the caches, so it sees every record.  It leaves the counter at zero for the next call.
+// Stores, count and reads are one memory round trip each (0.6, 0.4, 0.45 us) and take the place of a launch (2.6 us from kernel to
+// kernel).  Measured, us a call (launches of this kernel and combine_splits with one pair / with two / merged here): 8 kv heads, K4V2, 200 tokens
+// 9.0 / 7.9 / 7.6, 1100 tokens 9.1 / 8.4 / 7.8, 4133 tokens 10.1 / 9.5 / 9.2, 60 tokens (a single split) 9.0 / 6.0.
+template <int GQ, int PAIRS>
+__device__ __forceinline__ void merge_pairs(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid, int split, int bh)
+{
+    wg_barrier();                                                // all pairs' results are in LDS
+    const int head = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    if (head < nvalid) {
+        float m[PAIRS], l[PAIRS], M = -INFINITY, L = 0.0f;
+#pragma unroll
+        for (int p = 0; p < PAIRS; p++) {
+            const float2 ml = *reinterpret_cast<const float2 *>(&Ls[p].Zt[head][0][0]);
+            m[p] = ml.x;
+            l[p] = ml.y;
+            M = fmaxf(M, ml.x);
+        }
+        float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int p = 0; p < PAIRS; p++) {
+            if (m[p] == -INFINITY) continue;                     // a pair without units: nothing of it is in LDS
+            const float f = __builtin_amdgcn_exp2f(m[p] - M);
+            L = fmaf(f, l[p], L);
+            O += f * *reinterpret_cast<const float4v *>(reinterpret_cast<const float *>(&Ls[p].Av[0].at[0][0]) + head * kD + 4 * lane);
+        }
+        const size_t row = qrow0 + head;
+        if (a.splits == 1) {
+            store_output(a.out + row * kD + 4 * lane, O, L);
+        } else {
+            store_through(a.part_o + (row * a.splits + split) * kD + 4 * lane, O);
+            if (lane == 0) store_through(a.part_ml + (row * a.splits + split) * 2, make_float2(M, L));
+        }
+    }
+    if (a.splits == 1 || !a.tickets) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wave's part of the record has reached memory
+    wg_barrier();
+    if (threadIdx.x == 0) {
+        uint32_t *t = a.tickets + (size_t)bh * a.ticket_stride + blockIdx.z;
+        const bool last = (int)__hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.splits - 1;
+        if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        Ls[0].rescale[0][0] = last ? 1 : 0;
+    }
+    wg_barrier();
+    if (__builtin_amdgcn_readfirstlane(Ls[0].rescale[0][0])) merge_splits<GQ, PAIRS>(a, Ls, qrow0, nvalid);
+}
+
 // ------------------------------------------------------------------ kernel
 
 // Waves per SIMD the register allocation must leave room for: the host plans 2048 groups (4 waves per SIMD) for code
 // widths up to 8 bits per key + value element and 1024 (2) beyond; the wider instantiations may
 // use the registers that fewer resident waves leave free instead of spilling (16-bit layers: two units of rows).
-template <int KB, int VB> constexpr int resident_waves() { return KB + VB <= 8 ? 4 : 2; }
+// Work-groups of two pairs: up to three per compute unit for the narrow widths, two beyond (kPairedGroups in the host plan).
+template <int KB, int VB, int PAIRS> constexpr int resident_waves() { return KB + VB <= 8 ? (PAIRS > 1 ? 3 : 4) : 2; }
 
-template <int KB, int VB, int GQ, bool NARROW, bool KPT>
-__global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(DecodeArgs a)
+template <int KB, int VB, int GQ, bool NARROW, bool KPT, int PAIRS>
+__global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) void decode_mfma(DecodeArgs a)
 {
     static_assert(GQ == 4 || GQ == 8, "rows 2j and 2j + 1 of a 16-row tile");
     constexpr bool kFast = KB < 16 && VB < 16;
@@ -782,7 +930,7 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     constexpr int DK = 2, DV = 2;
     // a group without blocks asks for its window rows before anything else (not where a tile of 8 heads has to make do with a
     // quarter of a SIMD's registers: it would spill)
-    constexpr bool kEarlyRows = !(kFast && GQ == 8 && resident_waves<KB, VB>() == 4);
+    constexpr bool kEarlyRows = !(kFast && GQ == 8 && resident_waves<KB, VB, PAIRS>() == 4);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
     const int n = lane & 15, rq = lane >> 4;
@@ -794,20 +942,41 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     const size_t qrow0 = (size_t)b * a.Hq + (size_t)h * gq_total + head0;
     // wave 0 / wave 1 take the key / value role in even work-groups and the other way round in odd ones,
     // so that both kinds of wave land on every SIMD
+    const int pair = PAIRS > 1 ? wave >> 1 : 0;
     const bool key_wave = ((wave ^ (split + bh)) & 1) == 0;
 
-    __shared__ PairLds<GQ> L;
+    __shared__ PairLds<GQ> Ls[PAIRS];
+    PairLds<GQ> &L = Ls[pair];
     __shared__ __attribute__((aligned(16))) _Float16 aq_lds[16][kD + 8];
 
-    // ---- work of this group: units [u0, u1) = quantized blocks, then chunks of <= 32 fp16 window tokens.
+    // ---- work of this group: units [u0, u1) = quantized blocks, then chunks of <= 32 fp16 window tokens; of this pair: `blocks`
+    // blocks from block u0 on, then `chunks` chunks from first_chunk on.
     // Phase 1 covers the fully quantized blocks (only when both tensors are quantized), phase 2 the rest.
-    // Unit number it (counted from u0) is handed over through buffer it & 1.
+    // Unit number it (counted from the pair's first) is handed over through buffer it & 1.
     int u0, u1;
     split_range(a, split, u0, u1);
-    const int f1 = kFast ? (u1 < a.n_blocks ? u1 : a.n_blocks) : u0;     // phase 1 = [u0, f1), phase 2 = [f1, u1)
-    const int f1c = f1 > u0 ? f1 : u0;
-    const int n1 = f1c - u0, n2 = u1 - f1c;
-    const int n2p = !kFast && f1c < a.n_blocks ? (u1 < a.n_blocks ? u1 : a.n_blocks) - f1c : 0;      // blocks among phase 2's units
+    int blocks = (u1 < a.n_blocks ? u1 : a.n_blocks) - u0, first_chunk = 0, chunks = u1 > a.n_blocks ? u1 - a.n_blocks : 0;
+    int steps = blocks + chunks;                  // of the pair with most units: every wave meets that many barriers
+    if constexpr (PAIRS > 1) {
+        // the window's chunks go to the last pairs (to all, where there are no blocks), the blocks to those in front: a chunk
+        // takes as long as two blocks or three, and the window's split has few blocks or none
+        const int wp = blocks == 0 ? PAIRS : chunks < PAIRS - 1 ? chunks : PAIRS - 1, bp = PAIRS - wp;
+        const int most_b = bp ? (blocks + bp - 1) / bp : 0, most_c = wp ? (chunks + wp - 1) / wp : 0;
+        steps = most_b > most_c ? most_b : most_c;
+        if (pair < bp) {
+            const int b0 = blocks * pair / bp, b1 = blocks * (pair + 1) / bp;
+            u0 += b0;
+            blocks = b1 - b0;
+            chunks = 0;
+        } else {
+            const int i = pair - bp;
+            first_chunk = chunks * i / wp;
+            chunks = chunks * (i + 1) / wp - first_chunk;
+            blocks = 0;
+        }
+    }
+    const int n1 = kFast ? blocks : 0, n2p = kFast ? 0 : blocks;      // the blocks of phase 1, of phase 2
+    const int n2 = n2p + chunks;
     const size_t blk0 = (size_t)bh * a.NB;       // first block of this cache in the layer's arrays
     // cache block number of the i-th phase-1 unit (0 <= i < n1).
     // Every group starts its sweep at a different place of its range and wraps around: groups advance at the
@@ -821,7 +990,7 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
     const int rot2 = n2p > 0 ? (int)(((uint32_t)bh * 40503u + (uint32_t)split * 9973u) % (uint32_t)n2p) : 0;
     auto blk2 = [&](int i) {
         const int r = i + rot2;
-        return f1c + (r < n2p ? r : r - n2p);
+        return u0 + (r < n2p ? r : r - n2p);
     };
     auto blk1c = [&](int i) { return i < n1 ? blk1(i) : 0; };     // past the range: any number, the load is an empty one
     // byte offset, in the cache's exponent array, of the word this lane holds for the chunk that starts at step c0
@@ -934,7 +1103,6 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         // fp16 rows this wave starts with: a group without packed blocks asks for them here, one with packed blocks behind
         // those (16-bit keys: a pipeline of their own)
         KeyRows rows;
-        const int first_chunk = f1c + n2p - a.n_blocks, chunks = n2 - n2p;
         if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);
         wg_barrier();                                   // the value wave has written the exact-fp16 query tile
         KeyState<GQ> W;
@@ -1048,7 +1216,9 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         for (int hh = 0; hh < 2; hh++) {
             const float lsum = row_sum16(W.l[hh]);
             const int j = 2 * rq + hh;
-            if (n == 0 && j < nvalid) {
+            if constexpr (PAIRS > 1) {
+                if (n == 0) *reinterpret_cast<float2 *>(&L.Zt[j][0][0]) = make_float2(W.m[hh], lsum);
+            } else if (n == 0 && j < nvalid) {
                 const size_t prow = (qrow0 + j) * a.splits + split;
                 store_through(a.part_ml + prow * 2, make_float2(W.m[hh], lsum));
             }
@@ -1077,8 +1247,10 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         ValueRows rows;                                 // (as in the key wave)
         u32x2 fresh;
         if constexpr (VB == 16) fetch_unit(a.lv.vcode + blk0 * block_code_bytes(16), n2p > 0, n2p > 0 ? blk2(0) : 0, lane, rows);
+        if (PAIRS == 1 || pair == 0) {
 #pragma unroll
-        for (int pass = 0; pass < 4; pass++) *reinterpret_cast<uint4 *>(&aq_lds[4 * pass + rq][8 * n]) = qx[pass];
+            for (int pass = 0; pass < 4; pass++) *reinterpret_cast<uint4 *>(&aq_lds[4 * pass + rq][8 * n]) = qx[pass];
+        }
         {
             const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
             const int per = (16 - row0) * (32 + 8) / 8;              // 16-byte pieces of the unused rows per channel group
@@ -1087,7 +1259,6 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
         }
         Q.vw0 = code_weight_inv<VB < 16 ? VB : 8>((2 * n) & 7);
         Q.vw1 = code_weight_inv<VB < 16 ? VB : 8>((2 * n + 1) & 7);
-        const int first_chunk = f1c + n2p - a.n_blocks, chunks = n2 - n2p;
         if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
         wg_barrier();                                   // query tile handed to the key wave
         ValueState<GQ> W;
@@ -1227,12 +1398,20 @@ __global__ __launch_bounds__(128, (resident_waves<KB, VB>())) void decode_mfma(D
             }
             wave_lds_sync();
         }
+        if constexpr (PAIRS == 1) {
 #pragma unroll
-        for (int j = 0; j < GQ; j++)
-            if (j < nvalid)
-                store_through(a.part_o + ((qrow0 + j) * a.splits + split) * kD + 2 * lane, *reinterpret_cast<const float2 *>(&o_lds[j * kD + 2 * lane]));
+            for (int j = 0; j < GQ; j++)
+                if (j < nvalid)
+                    store_through(a.part_o + ((qrow0 + j) * a.splits + split) * kD + 2 * lane, *reinterpret_cast<const float2 *>(&o_lds[j * kD + 2 * lane]));
+        }
+    }
+    if constexpr (PAIRS > 1) {
+        for (int i = n1 + n2; i < steps; i++) wg_barrier();      // pairs with fewer units
+        merge_pairs<GQ, PAIRS>(a, Ls, qrow0, nvalid, split, bh);
     }
 }
+
+constexpr int kPairs = KVQ_DECODE_PAIRS;
 
 struct LaunchEvents { hipEvent_t begin, end; };
 
@@ -1241,16 +1420,16 @@ hipError_t launch_gq(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
 {
     const int gq = a.Hq / a.Hkv;
     const int BH = a.B * a.Hkv;
-    const dim3 block(128);
+    const dim3 block(128 * kPairs);
     const dim3 grid(a.splits, BH, gq <= 4 ? 1 : (gq + 7) / 8);
     if (ev.begin && ev.end) {
         // measurement: the runtime's extended launch stamps the events with the dispatch's own start and end times
-        if (gq <= 4) hipExtLaunchKernelGGL((decode_mfma<KB, VB, 4, NARROW, KPT>), grid, block, 0, s, ev.begin, ev.end, 0, a);
-        else hipExtLaunchKernelGGL((decode_mfma<KB, VB, 8, NARROW, KPT>), grid, block, 0, s, ev.begin, ev.end, 0, a);
+        if (gq <= 4) hipExtLaunchKernelGGL((decode_mfma<KB, VB, 4, NARROW, KPT, kPairs>), grid, block, 0, s, ev.begin, ev.end, 0, a);
+        else hipExtLaunchKernelGGL((decode_mfma<KB, VB, 8, NARROW, KPT, kPairs>), grid, block, 0, s, ev.begin, ev.end, 0, a);
     } else if (gq <= 4) {
-        hipLaunchKernelGGL((decode_mfma<KB, VB, 4, NARROW, KPT>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((decode_mfma<KB, VB, 4, NARROW, KPT, kPairs>), grid, block, 0, s, a);
     } else {
-        hipLaunchKernelGGL((decode_mfma<KB, VB, 8, NARROW, KPT>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((decode_mfma<KB, VB, 8, NARROW, KPT, kPairs>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
@@ -1288,7 +1467,11 @@ hipError_t launch_kb(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
 
 }  // namespace
 
+#if KVQ_DECODE_PAIRS == 1
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
+#else
+hipError_t launch_decode_short(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
+#endif
 {
     if (a.B * a.Hkv > 65535) return hipErrorInvalidConfiguration;
     const LaunchEvents ev = {ev_begin, ev_end};

@@ -36,6 +36,10 @@ struct QuantArgs {
     int RC;                        // ring capacity (R + G)
     int copy_pos0, copy_pos1;      // absolute positions of this append that go into the ring in the same launch (none: equal)
     int copy_groups;               // waves per tensor that copy them (set by launch_quantize)
+    // the launch that writes a layer's first block clears the arrival counters of the decode kernel (DecodeArgs):
+    // `counters` of them at tickets + bh * ticket_stride
+    uint32_t *tickets;
+    int ticket_stride, counters;
 };
 
 struct ResidualCopyArgs {
@@ -73,6 +77,10 @@ struct DecodeArgs {
     // window ring; the kernel reads them from here and stores them into the ring for later launches.  NULL: none.
     const uint16_t *k_new, *v_new;
     int new_pos;           // absolute position of that token
+    // launch_decode_short only: its last work-group of a cache and tile of query heads merges the splits (at most kMergeSplits); one
+    // arrival counter per cache and tile, zero between calls, cache bh's at tickets + bh * ticket_stride.  NULL: launch_combine merges.
+    uint32_t *tickets;
+    int ticket_stride;
 };
 
 struct PrefillArgs {
@@ -122,10 +130,16 @@ hipError_t launch_export(const ExportArgs &a, hipStream_t s);
 hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);
 // ev_begin / ev_end (both or neither): receive the start and stop time stamps of the kernel's own dispatch
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+// the same with two pairs of waves per work-group, for launches of few work-groups; a single split or a.tickets: no
+// launch_combine behind it
+hipError_t launch_decode_short(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 // pieces that launch_prefill_attention(a) cuts query tile `tile` into (host only; 1: it stays whole)
 int prefill_tile_pieces(const PrefillArgs &a, int tile);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
+constexpr int kMergeSplits = 64; // most splits that a work-group of launch_decode_short merges
+constexpr int kMaxTickets = 23;   // arrival counters (DecodeArgs::tickets) that a selection record has room for
+size_t prefill_ticket_offset();  // where in a selection record they are: bytes that the record itself leaves unused
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache
 // decides for the caches [bh0, bh0 + n_bh) which key channels keep their low parts (a.select: their records; layers with
 // packed, per-channel quantized keys only); ev_begin (may be null) receives the kernel's start

@@ -38,6 +38,7 @@
 //      several work-groups (plan_pieces), and this kernel merges their un-normalised results.
 #include <hip/hip_ext.h>
 
+#include <cstddef>
 #include <type_traits>
 
 #include "kvq_internal.h"
@@ -81,7 +82,7 @@ struct Select {
     uint8_t pos[kD];          // slot (0..31) of a channel's remainders in the compact tile, 255 = none kept
     uint8_t chan[32];         // the channel of a slot
     uint32_t compact;         // 0: every channel keeps its remainder (Tiles::Klo as declared)
-    uint8_t pad[92];
+    uint32_t tickets[kMaxTickets];      // not the prefill kernels': the decode kernel's arrival counters of this cache
     float centre[kD];         // per channel: subtracted from every dequantized key of the cache before it is rounded
 };
 static_assert(sizeof(Select) == 768, "one record per cache");
@@ -1272,6 +1273,7 @@ size_t prefill_piece_bytes() { return kQB * (kD + 2) * sizeof(float); }
 
 size_t prefill_unit_bytes() { return sizeof(Tiles); }
 size_t prefill_select_bytes() { return sizeof(Select); }
+size_t prefill_ticket_offset() { return offsetof(Select, tickets); }
 
 // Pass 0 for the caches [bh0, bh0 + n_bh) (a.select = their first record); only for layers whose keys are quantized
 // per channel and hold packed blocks.  ev_begin (may be null) receives the kernel's start.

@@ -273,6 +273,7 @@ __global__ __launch_bounds__(64) void quantize_blocks(QuantArgs a)
     const int blk = a.first_block + item % a.n_blocks;
     const int r = lane >> 4, c16 = lane & 15;
     const int n = lane & 15, kq = lane >> 4;
+    if (blk == 0 && !values && lane < a.counters) a.tickets[(size_t)bh * a.ticket_stride + lane] = 0;
 
     // keys [token][channel] with rows of kD + 8 halves, or values [row of channel][token] with rows of 32 + 8 halves
     __shared__ __attribute__((aligned(16))) uint16_t tile[kD * (32 + 8)];
