@@ -64,9 +64,10 @@ def check_prefill_attention_code(asm: str) -> None:
     """The prefill attention kernels set M0 in inline assembly (LDS base of their global-to-LDS fetches).  The library
     is only linked if, in the generated code, every M0 write is the one in front of such a fetch, nothing else reads or
     writes M0, and no kernel of the file spills registers (two waves per SIMD is what its pipelining assumes)."""
-    kernels = kernel_bodies(asm, "prefill_attention")
-    if len(kernels) != 4:                                                  # keys quantized / fp16, tiles cut / whole
-        raise RuntimeError("expected 4 prefill_attention kernels in the generated code, found %d" % len(kernels))
+    # keys quantized / fp16; 4 waves: tiles cut / whole, 8 waves: rows of one head / of several
+    kernels = kernel_bodies(asm, "prefill_attention") + kernel_bodies(asm, "prefill_attend_long")
+    if len(kernels) != 8:
+        raise RuntimeError("expected 8 prefill attention kernels in the generated code, found %d" % len(kernels))
     for name, body in kernels:
         lines = [l.strip() for l in body.splitlines()]
         code = [l for l in lines if l and not l.startswith((";", ".", "_Z")) and not l.endswith(":")]

@@ -104,6 +104,11 @@ struct PrefillArgs {
     // un-normalised outputs (part_o) and a pair (reference, sum) (part_ml)
     float *part_o, *part_ml;
     int part_slots;
+    // set by launch_prefill_attention
+    int row_heads;         // query heads that share a work-group's rows: row r of them is query r / row_heads of head r % row_heads
+    int row_groups;        // of a cache's query heads
+    uint32_t row_magic;    // for divisions by row_heads
+    int order;             // in which the work-groups start
 };
 
 // Work units [u0, u1) of a split: units are the quantized blocks, then the chunks of <= 32 fp16 window tokens.  The

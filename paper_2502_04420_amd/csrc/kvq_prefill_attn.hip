@@ -23,9 +23,9 @@
 //      Dequantizing inside the attention
 //      kernel instead repeats this work for every query head of the group and every query tile (256 times per unit at
 //      8192 queries) and made that kernel bound by its vector instructions.
-//   2. prefill_attention: a work-group of 8 waves owns 256 consecutive queries of one query head, 32 per wave (two
-//      16-query tiles).  The units are fetched from the scratch area straight into LDS (fp16 window chunks: from the
-//      ring, through registers), five tile buffers, two units per barrier, so that the score products of the next
+//   2. prefill_attention: a work-group of 8 or 4 waves owns 256 or 128 rows (queries of one query head or of several of the
+//      group's), 32 per wave (two 16-row tiles).  The units are fetched from the scratch area straight into LDS (fp16 window chunks:
+//      from the ring, through registers), five or three tile buffers, so that the score products of the next
 //      unit can be issued next to the softmax weights of the current one.  Scores are computed transposed, S^T = K^ Q^T
 //      (16x16x32 f16 instructions, tokens along the rows): a lane then holds, for its query, the scores of tokens
 //      {4 rq .. 4 rq + 3} and {16 + 4 rq ..}, which is exactly a B operand of O^T += V^T P^T when the A operand (V^T
@@ -49,12 +49,10 @@ namespace {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;                // waves of an attention work-group
 constexpr int kStagers = 4;              // waves that turn a unit into tiles (256 threads: the thread -> code maps below)
 constexpr int kQT = 2;                   // tiles of 16 queries per wave
 constexpr int kQW = 16 * kQT;            // queries per wave
-constexpr int kQB = kQW * kWaves;       // queries per work-group
-static_assert(kQB == kQueryTile, "the host counts query tiles");
+constexpr int kQB = kQueryTile;         // rows of a query tile
 constexpr int kKStride = kD + 16;       // halves per K^ row: 288 bytes.  Measured with a probe kernel: the 16-byte operand reads of a wave
                                         // (16 rows x 4 pieces) take 3.9 LDS cycles at this stride, like a linear read; 7.8 + 3.9 conflict cycles at 272
 
@@ -754,29 +752,31 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
 // global-to-LDS loads of 1 KiB each (64 lanes x 16 bytes, which land at consecutive LDS addresses from the base
 // that M0 holds).  The tiles of a unit are whole KiB, so a piece never straddles two of them.
 
-__device__ __forceinline__ void fetch_piece(const uint8_t *unit, uint32_t offset_of_lane, uint32_t lds_base)
+__device__ __forceinline__ void fetch_piece(const uint8_t *piece, uint32_t lane_offset, uint32_t lds_base)
 {
     // The compiler does not see this load: the waits for it are written out below (wait_fetches).  Loads it does not
     // know of can only make its own waits longer, never too short.  M0 is declared as clobbered, so a use of its own the compiler
     // might make of M0 (it sets M0 right before an instruction that reads it) stays correct.
-    // Address = the unit's (wave-uniform, scalar registers) + a 32-bit offset per lane that is the same for every unit.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(offset_of_lane), "s"(unit) : "memory", "m0");
+    // Address = a wave-uniform one (scalar registers) + a 32-bit offset per lane that is the same for every unit.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_offset), "s"(piece) : "memory", "m0");
 }
 
-// Wave `wave` fetches the pieces wave, wave + 8, ... of a unit.  Of the keys' low parts: none, the whole tile, or the
+// Wave `wave` of WAVES fetches the pieces wave, wave + WAVES, ... of a unit.  Of the keys' low parts: none, the whole tile, or the
 // first kLoPieces KiB of it (the compact tile).
-template <int LO>
+template <int LO, int WAVES>
 __device__ __forceinline__ void fetch_unit(const uint8_t *unit, Tiles &L, int wave, int lane)
 {
     constexpr int lo_pieces = LO == kLoAll ? kTileKiB : LO == kLoCompact ? kLoPieces : 0;
     constexpr int pieces = kTileKiB + lo_pieces + kValuesKiB;
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)reinterpret_cast<uint8_t *>(&L);
 #pragma unroll
-    for (int i = 0; i < (pieces + kWaves - 1) / kWaves; i++) {
-        const int p = wave + kWaves * i;                          // the same for all lanes of the wave
+    for (int i = 0; i < (pieces + WAVES - 1) / WAVES; i++) {
+        const int p = wave + WAVES * i;                           // the same for all lanes of the wave
         if (p < pieces) {
             const int off = 1024 * (p < kTileKiB + lo_pieces ? p : p - lo_pieces + kTileKiB);     // K^, low parts, then V^
-            fetch_piece(unit, (uint32_t)(off + 16 * lane), lds + off);
+            // (eight waves have registers for a lane offset per piece, four add the piece's to the scalar address)
+            if constexpr (WAVES == 8) fetch_piece(unit, (uint32_t)(off + 16 * lane), lds + off);
+            else fetch_piece(unit + off, (uint32_t)(16 * lane), lds + off);
         }
     }
 }
@@ -784,19 +784,32 @@ __device__ __forceinline__ void fetch_unit(const uint8_t *unit, Tiles &L, int wa
 // Returns once all fetches of this wave have landed in LDS.
 __device__ __forceinline__ void wait_fetches() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// ---- pass 2: the attention itself.  One work-group per 256 consecutive queries of one query head; every wave attends
-// 32 queries and fetches its share of each unit from the scratch area into LDS.  KLO: the keys are quantized (they come
-// as two fp16 numbers).
+// Order in which an XCD's work-groups of whole tiles start: cache by cache, the longest of each first; all of them by length; those that
+// find a compute unit for themselves by length, then the shortest of the others first (two per compute unit: long and short together).
+enum { kByCache, kByLength, kPaired };
+
+// r / row_heads, exactly: row_magic = ceil(2^32 / row_heads), and r * row_heads < 2^32 (plan_launch sees to it).  Divided by the compiler's
+// sequence instead a window-only prompt of packed rows takes 0.5 us longer.
+__device__ __forceinline__ int row_query(const PrefillArgs &a, int r) { return a.row_heads == 1 ? r : (int)__umulhi((uint32_t)r, a.row_magic); }
+
+// ---- pass 2: the attention itself.  A work-group has 8 waves and 256 rows or 4 waves and 128 (see plan_launch), a row being a query of
+// one of row_heads query heads; every wave attends 32 rows and fetches its share of each unit from the scratch area into LDS.  KLO: the
+// keys are quantized (they come as two fp16 numbers).
 //
-// Five LDS buffers and two units per trip: while units u and u + 1 are being used, unit u + 2 is already there and units
+// 8 waves, alone on their compute unit: five LDS buffers and two units per trip: while units u and u + 1 are being used, unit u + 2 is already there and units
 // u + 3 and u + 4 are on their way; one barrier per trip.  With the next unit present, a wave issues the score products
 // of unit u + 1 in the same stretch of code as the softmax of unit u (matrix and vector instructions that do not depend
 // on each other), instead of waiting for each product's result in turn.
-constexpr int kBuffers = 5;
+// 4 waves, two such work-groups per compute unit: three buffers and one unit per trip; while one work-group waits for its unit, the
+// other goes on.  (Their 256 registers leave none for the window's offsets, which are kept in LDS over the loop.)
+__host__ __device__ constexpr int tile_buffers(int waves) { return waves == 8 ? 5 : 3; }
+constexpr size_t attention_lds(int waves) { return tile_buffers(waves) * sizeof(Tiles) + (waves == 4 ? 64 * 4 * kQT * sizeof(float) : 0); }
+static_assert(2 * attention_lds(4) <= 160 * 1024, "two work-groups of four waves per compute unit");
 
-// What one work-group attends to: piece `index` of the `count` pieces that the packed units of query tile `tile` are cut
-// into (the fp16 window goes with the last one); slot: where its partial results go (count > 1).
-struct Piece { int tile, index, count, slot; };
+// What one work-group attends to: the rows from row0 on of the heads from `head` on, and of the `count` pieces that the packed units of
+// their tile (256 rows) are cut into piece `index` (the fp16 window goes with the last one); slot: where the partial results of the
+// tile's piece go (count > 1).
+struct Piece { int tile, row0, head, index, count, slot; };
 
 // How the tiles of a query head are cut into pieces (plan_pieces).  One word per tile, the tiles with the longest pieces
 // first: tile | pieces << 8 | pieces in front of it << 16 (whole words: the kernel reads them through the scalar unit).
@@ -820,8 +833,8 @@ __device__ __forceinline__ int piece_partials(uint32_t entry)
 
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
 // kLoCompact); CUT: the tile may be cut (else pc.tile alone counts).
-template <int LO, bool CUT>
-__device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, int jq, const Piece &pc)
+template <int LO, bool CUT, int WAVES, bool PACKED>
+__device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, const Piece &pc)
 {
     constexpr bool KLO = LO != kLoNone;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -829,30 +842,30 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     const int n = lane & 15, rq = lane >> 4;
     const int gq = a.Hq / a.Hkv;
     const int bh = a.bh0 + local;
-    const int head = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + jq;   // b * Hq + query head
+    const int head0 = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + pc.head;  // b * Hq + first query head
     const int T = 32 * a.n_blocks + a.n_res;
     const int p0 = T - a.n_q;                                    // absolute position of query 0
-    const int i0 = pc.tile * kQB;
-    const int ilast = (i0 + kQB < a.n_q ? i0 + kQB : a.n_q) - 1;
-    const int units = (p0 + ilast) / 32 + 1;                     // units the work-group walks through
-    const int iw = i0 + kQW * wave;                              // first query of this wave
-    const int wlast = iw < a.n_q ? (p0 + (iw + kQW - 1 < a.n_q ? iw + kQW - 1 : a.n_q - 1)) / 32 : -1;
-    const int wmin = p0 + iw;                                    // position of the wave's first query
-    const int open_units = iw < a.n_q ? (wmin + 1) / 32 : 0;     // units [0, open_units) lie before it: no mask needed
+    const int hp = PACKED ? a.row_heads : 1, rows = a.n_q * hp;      // row r: query r / hp of head head0 + r % hp
+    auto query_of = [&](int r) { return PACKED ? row_query(a, r) : r; };
+    const int rlast = (pc.row0 + kQW * WAVES < rows ? pc.row0 + kQW * WAVES : rows) - 1;
+    const int units = (p0 + query_of(rlast)) / 32 + 1;                // units the work-group walks through
+    const int rw = pc.row0 + kQW * wave;                         // first row of this wave
+    const int wlast = rw < rows ? (p0 + query_of(rw + kQW - 1 < rows ? rw + kQW - 1 : rows - 1)) / 32 : -1;
+    const int open_units = rw < rows ? (p0 + query_of(rw) + 1) / 32 : 0;   // units [0, open_units) lie before the wave's first query: no mask needed
     const float c = a.scale_log2e;
-    const float inv_c = 1.0f / c;
+    const float inv_c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, 1.0f / c)));
 
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     Tiles *L = reinterpret_cast<Tiles *>(lds_raw);
 
-    // queries of this lane: iq[qt] = iw + 16 qt + n; past the end the last query is repeated and never stored
+    // rows of this lane: rw + 16 qt + n; past the end the last row is repeated and never stored
     int qpos[kQT];
     half8 Qf[kQT][4], Qlo[kQT];
 #pragma unroll
     for (int qt = 0; qt < kQT; qt++) {
-        const int i = iw + 16 * qt + n, ic = i < a.n_q ? i : a.n_q - 1;
+        const int r = rw + 16 * qt + n, rc = r < rows ? r : rows - 1, ic = query_of(rc);
         qpos[qt] = p0 + ic;
-        const uint16_t *row = a.q + ((size_t)head * a.n_q + ic) * kD;
+        const uint16_t *row = a.q + ((size_t)(head0 + rc - ic * hp) * a.n_q + ic) * kD;
 #pragma unroll
         for (int step = 0; step < 4; step++) Qf[qt][step] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(row + 32 * step + 8 * rq));
         if constexpr (LO == kLoCompact) {
@@ -869,7 +882,9 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     // Packed keys come with their channel's centre taken off (prefill_dequantize), which lowers every packed score of a
     // query by q . centre; the scores of the window's fp16 rows are lowered by the same amount here, so that the softmax
     // sees all of a query's scores moved alike.  woff = minus that amount in the exponent's units.
+    // (Four waves keep it in LDS over the loop, which leaves no registers for it.)
     float woff[kQT];
+    float *kept = reinterpret_cast<float *>(lds_raw + tile_buffers(WAVES) * sizeof(Tiles)) + tid;
 #pragma unroll
     for (int qt = 0; qt < kQT; qt++) woff[qt] = 0.0f;
     if constexpr (KLO) {
@@ -890,6 +905,10 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
                 woff[qt] = -c * dot;
             }
         }
+        if constexpr (WAVES == 4) {
+#pragma unroll
+            for (int qt = 0; qt < kQT; qt++) kept[64 * WAVES * qt] = woff[qt];
+        }
     }
 
     float4v O[8][kQT];
@@ -905,20 +924,30 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     // ---- packed units [ub, nb): the tile's, or a piece of them.  Unit u lives in buffer (u - ub) % 5.  Per trip: the wave issues its fetches of units u + 3 and
     // u + 4 (into the buffers of units u - 2 and u - 1, which everybody left at the last barrier), uses units u and u + 1
     // (taking the scores of the following unit ahead each time), then waits until its fetches have landed, and the
-    // barrier makes everybody's visible.  Past the end the last unit is fetched again, into a buffer nobody reads.
-    const int nbt = a.n_blocks < units ? a.n_blocks : units;     // the tile's
+    // barrier makes everybody's visible.
+    const int nbt = a.n_blocks < units ? a.n_blocks : units;     // the work-group's
     int ub = 0, nb = nbt;
     if constexpr (CUT) {
-        ub = nbt * pc.index / pc.count;
-        nb = nbt * (pc.index + 1) / pc.count;
+        int all = nbt;
+        if constexpr (WAVES == 4) {
+            // (the tile's rows may reach further than the work-group's: only its last piece ends earlier here)
+            const int tlast = ((pc.tile + 1) * kQB < rows ? (pc.tile + 1) * kQB : rows) - 1, tunits = (p0 + query_of(tlast)) / 32 + 1;
+            all = a.n_blocks < tunits ? a.n_blocks : tunits;
+        }
+        ub = all * pc.index / pc.count;
+        nb = all * (pc.index + 1) / pc.count;
+        if constexpr (WAVES == 4) nb = nb < nbt ? nb : nbt;
     }
     if (nb > ub) {
         const uint8_t *mine = a.scratch + (size_t)local * a.n_blocks * sizeof(Tiles);
-        const int last = nb - 1;
-        auto unit_at = [&](int u) { return mine + (size_t)(u < last ? u : last) * sizeof(Tiles); };
-        fetch_unit<LO>(unit_at(ub), L[0], wave, lane);
-        fetch_unit<LO>(unit_at(ub + 1), L[1], wave, lane);
-        fetch_unit<LO>(unit_at(ub + 2), L[2], wave, lane);
+        auto fetch = [&](int u, Tiles &to) {
+            // 4 waves wait for every unit: none is fetched past the end.  8 waves, whose loop is a little slower with the condition (0.3 %), fetch
+            // the last one again, into a buffer nobody reads.
+            if (WAVES == 4 ? u < nb : true) fetch_unit<LO, WAVES>(mine + (size_t)(u < nb ? u : nb - 1) * sizeof(Tiles), to, wave, lane);
+        };
+        fetch(ub, L[0]);
+        fetch(ub + 1, L[1]);
+        if constexpr (WAVES == 8) fetch(ub + 2, L[2]);
         // The queries are first used under a condition; without this the compiler would keep their loads on its list
         // of pending ones inside the loop and wait there for everything in flight, the fetches just issued included.
 #pragma unroll
@@ -929,7 +958,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 #pragma unroll
             for (int qt = 0; qt < kQT; qt++) asm volatile("" ::"v"(Qlo[qt]));
         }
-        wait_fetches();                                         // the first three units are there
+        wait_fetches();                                         // the first units are there
         __syncthreads();
         float4v S[2][kQT], Sn[2][kQT];
         // base[qt]: what the scores waiting in S / Sn are relative to (KLO only: the reference as it stood when their
@@ -988,23 +1017,42 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
                 calm = ahead && u + 2 < nb && u + 2 <= wlast && u + 1 < open_units && !(KLO && moved) && !unit_exceeds<KLO>(Sout, inv_c, m);
             }
         };
-        auto after = [](int x) { return x + 1 < kBuffers ? x + 1 : 0; };
+        auto after = [](int x) { return x + 1 < tile_buffers(WAVES) ? x + 1 : 0; };
         int b0 = 0;                                              // buffer of unit u
-        for (int u = ub; u < nb; u += 2) {
-            const int b1 = after(b0), b2 = after(b1), b3 = after(b2), b4 = after(b3);
-            fetch_unit<LO>(unit_at(u + 3), L[b3], wave, lane);  // buffers of units u - 2 and u - 1: all are done with them
-            fetch_unit<LO>(unit_at(u + 4), L[b4], wave, lane);
-            step(u, L[b0], L[b1], S, Sn);
-            if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S);
-            wait_fetches();                                     // units u + 3 and u + 4 are there
-            __syncthreads();
-            b0 = b2;
+        if constexpr (WAVES == 8) {
+            for (int u = ub; u < nb; u += 2) {
+                const int b1 = after(b0), b2 = after(b1), b3 = after(b2), b4 = after(b3);
+                fetch(u + 3, L[b3]);                            // buffers of units u - 2 and u - 1: all are done with them
+                fetch(u + 4, L[b4]);
+                step(u, L[b0], L[b1], S, Sn);
+                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S);
+                wait_fetches();                                 // units u + 3 and u + 4 are there
+                __syncthreads();
+                b0 = b2;
+            }
+        } else {
+            for (int u = ub; u < nb; u += 2) {
+                const int b1 = after(b0), b2 = after(b1);
+                fetch(u + 2, L[b2]);                            // buffer of unit u - 1
+                step(u, L[b0], L[b1], S, Sn);
+                wait_fetches();                                 // unit u + 2 is there
+                __syncthreads();
+                fetch(u + 3, L[b0]);
+                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S);
+                wait_fetches();
+                __syncthreads();
+                b0 = b2;
+            }
         }
     }
     // ---- chunks of the fp16 window (with the tile's last piece), staged by the first four waves straight from the ring
     const int uend = !CUT || pc.index + 1 == pc.count ? units : nbt;
+    if constexpr (KLO && WAVES == 4) {
+#pragma unroll
+        for (int qt = 0; qt < kQT; qt++) woff[qt] = kept[64 * WAVES * qt];
+    }
     for (int u = nbt; u < uend; u++) {
-        if (wave < kStagers) stage_window(a, bh, u, T, tid, L[0]);
+        if (WAVES == kStagers || wave < kStagers) stage_window(a, bh, u, T, tid, L[0]);
         __syncthreads();
         if (u <= wlast) {
             float4v S[2][kQT];
@@ -1027,16 +1075,18 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
         float l = lsum[qt];
         l += xor_lanes(l, 16);
         l += xor_lanes(l, 32);
-        const int i = iw + 16 * qt + n;
-        if (CUT && i < a.n_q && pc.count > 1) {
-            // a piece: un-normalised outputs and (reference, sum) of the query, for prefill_merge
-            float *o = a.part_o + (size_t)(pc.slot * kQB + (i - i0)) * kD;
-            if (rq == 0) *reinterpret_cast<float2 *>(a.part_ml + (size_t)(pc.slot * kQB + (i - i0)) * 2) = make_float2(m[qt], l);
+        const int r = rw + 16 * qt + n;
+        if (CUT && r < rows && pc.count > 1) {
+            // a piece: un-normalised outputs and (reference, sum) of the row, for prefill_merge
+            const size_t at = (size_t)pc.slot * kQB + (r - pc.tile * kQB);
+            float *o = a.part_o + at * kD;
+            if (rq == 0) *reinterpret_cast<float2 *>(a.part_ml + at * 2) = make_float2(m[qt], l);
 #pragma unroll
             for (int ct = 0; ct < 8; ct++) *reinterpret_cast<float4v *>(o + 16 * ct + 4 * rq) = O[ct][qt];
-        } else if (i < a.n_q) {
+        } else if (r < rows) {
             const float inv = 1.0f / l;
-            uint16_t *row = a.out + ((size_t)head * a.n_q + i) * kD;
+            const int i = query_of(r);
+            uint16_t *row = a.out + ((size_t)(head0 + r - i * hp) * a.n_q + i) * kD;
 #pragma unroll
             for (int ct = 0; ct < 8; ct++)
                 __builtin_nontemporal_store(u32x2{pack2(O[ct][qt][0] * inv, O[ct][qt][1] * inv), pack2(O[ct][qt][2] * inv, O[ct][qt][3] * inv)},
@@ -1048,59 +1098,82 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 // KQ: the layer's keys are quantized.  Each cache of such a layer is attended in the form its selection record names
 // (without records: low parts of all channels).
 //
-// PT: PieceTable, or WholeTiles where the units are too few for a cut: reading the table and dividing by piece counts that are all 1
+// PT: PieceTable, or WholeTiles (whole tiles, 4 waves): reading the table and dividing by piece counts that are all 1
 // costs a work-group about 0.14 us, which shows in short prompts (call of one layer with / without: 32 sequences of 22
 // tokens, 32 / 8 heads 15.6 / 15.1 us, of 33 tokens, 28 / 4 heads 21.0 / 20.4 us).  Long prompts of whole tiles keep the kernel
 // that knows the table: its loop is compiled a little better (4 x 8192 tokens 2436 us; without 2454).
-template <bool KQ, class PT>
-__global__ __launch_bounds__(64 * kWaves, 1) void prefill_attention(PrefillArgs a, PT pt)
+// PACKED: rows of several query heads (PrefillArgs::row_heads).
+template <bool KQ, class PT, int WAVES, bool PACKED>
+__device__ __forceinline__ void attend_group(const PrefillArgs &a, const PT &pt)
 {
     constexpr bool CUT = std::is_same<PT, PieceTable>::value;
-    const int tiles = (a.n_q + kQB - 1) / kQB;
-    int pieces = tiles;                                          // work-groups per query head
-    if constexpr (CUT) pieces = pt.pieces ? pt.pieces : tiles;
-    const int gq = a.Hq / a.Hkv;
+    constexpr int kRows = kQW * WAVES;
+    const int hp = PACKED ? a.row_heads : 1;                     // a cache's query heads are taken hp at a time
+    const int rows = a.n_q * hp, heads = PACKED ? a.row_groups : a.Hq / a.Hkv;
+    const int tiles = CUT ? (rows + kQB - 1) / kQB : 0;
+    const int parts = CUT && rows > kRows ? kQB / kRows : 1;     // work-groups of a piece
+    int groups = (rows + kRows - 1) / kRows;                     // work-groups per cache and `heads`
+    if constexpr (CUT) groups = pt.pieces ? pt.pieces * parts : groups;
     // Work-groups go to the 8 XCDs in turn by their index, and each XCD has an L2 of its own: all query heads and
     // query tiles that read one (batch, kv head) cache are given to one XCD (when the count divides), so that its
     // units are fetched from memory once and then served by that L2.  Otherwise the pieces of all heads start in the order
     // of their length, and as many neighbouring heads as possible share an XCD.
-    int local, jq, rank;                                         // cache within this launch, query head within its group, order
-    const int heads = a.n_bh * gq;
+    int local, jh, rank;                                         // cache within this launch, heads within its group, order
+    const bool across = WAVES == 4 && !CUT && a.order != kByCache, paired = WAVES == 4 && !CUT && a.order == kPaired;
     if (a.n_bh % 8 == 0) {
-        const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3, per = gq * pieces;
-        local = 8 * (k / per) + xcd;
-        jq = (k % per) % gq;
-        rank = (k % per) / gq;
-    } else {
-        int head = blockIdx.x % heads;
-        rank = blockIdx.x / heads;
-        if (heads % 8 == 0) head = (head & 7) * (heads >> 3) + (head >> 3);
-        local = head / gq;
-        jq = head % gq;
-    }
-    Piece pc = {tiles - 1 - rank, 0, 1, 0};                      // the longest rows start first
-    if constexpr (CUT) {
-        if (pt.pieces) {
-            uint32_t w = pt.entry[0];
-            int before = 0;                                      // partial results of the tiles in front of this one
-            for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= rank; r++) {
-                before += piece_partials(w);
-                w = pt.entry[r];
-            }
-            pc.tile = (int)(w & 255u);
-            pc.index = rank - (int)(w >> 16);
-            pc.count = (int)((w >> 8) & 255u);
-            pc.slot = (local * gq + jq) * pt.partials + before + pc.index;
+        const int xcd = blockIdx.x & 7, per = heads * groups;
+        int k = blockIdx.x >> 3;
+        if (across) {
+            const int caches = a.n_bh >> 3, first = kCUs / 8;
+            if (paired && k >= first) k = per * caches - 1 - (k - first);
+            rank = k / (heads * caches);
+            local = 8 * ((k % (heads * caches)) / heads) + xcd;
+            jh = k % heads;
+        } else {
+            local = 8 * (k / per) + xcd;
+            jh = (k % per) % heads;
+            rank = (k % per) / heads;
         }
+    } else {
+        const int all = a.n_bh * heads;
+        int k = blockIdx.x;
+        if (paired && k >= kCUs) k = all * groups - 1 - (k - kCUs);
+        int head = k % all;
+        rank = k / all;
+        if (all % 8 == 0) head = (head & 7) * (all >> 3) + (head >> 3);
+        local = head / heads;
+        jh = head % heads;
+    }
+    Piece pc = {kRows * (groups - 1 - rank) / kQB, kRows * (groups - 1 - rank), jh * hp, 0, 1, 0};      // the longest rows start first
+    if constexpr (CUT) if (pt.pieces) {
+        const int order = rank / parts;
+        uint32_t w = pt.entry[0];
+        int before = 0;                                          // partial results of the tiles in front of this one
+        for (int r = 1; r < tiles && (int)(pt.entry[r] >> 16) <= order; r++) {
+            before += piece_partials(w);
+            w = pt.entry[r];
+        }
+        pc.tile = (int)(w & 255u);
+        pc.row0 = pc.tile * kQB + (rank % parts) * kRows;
+        if (WAVES == 4 && pc.row0 >= rows) return;               // the tile's second half is empty
+        pc.index = order - (int)(w >> 16);
+        pc.count = (int)((w >> 8) & 255u);
+        pc.slot = (local * heads + jh) * pt.partials + before + pc.index;
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact, CUT>(a, rec, local, jq, pc);
-        else attend<kLoAll, CUT>(a, rec, local, jq, pc);
+        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact, CUT, WAVES, PACKED>(a, rec, local, pc);
+        else attend<kLoAll, CUT, WAVES, PACKED>(a, rec, local, pc);
     } else {
-        attend<kLoNone, CUT>(a, nullptr, local, jq, pc);
+        attend<kLoNone, CUT, WAVES, PACKED>(a, nullptr, local, pc);
     }
 }
+
+template <bool KQ, class PT>
+__global__ __launch_bounds__(64 * 4, 2) void prefill_attention(PrefillArgs a, PT pt) { attend_group<KQ, PT, 4, true>(a, pt); }
+
+template <bool KQ, bool PACKED>
+__global__ __launch_bounds__(64 * 8, 1) void prefill_attend_long(PrefillArgs a, PieceTable pt) { attend_group<KQ, PieceTable, 8, PACKED>(a, pt); }
 
 // ---- pass 3, only behind a pass 2 whose tiles were cut: merges the pieces of every tile that has more than one.  32 lanes
 // per query row, 16 bytes per lane and piece, up to eight pieces in flight.  Bound by the traffic of the partial results.
@@ -1111,12 +1184,12 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
     const uint32_t w = pt.entry[blockIdx.y];
     const int tile = (int)(w & 255u), count = (int)((w >> 8) & 255u);
     const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 5), lane = threadIdx.x & 31;
-    const int i = tile * kQB + row;
+    const int r = tile * kQB + row, hp = a.row_heads, i = row_query(a, r);
     if (count < 2 || i >= a.n_q) return;
     int before = 0;
-    for (int r = 0; r < (int)blockIdx.y; r++) before += piece_partials(pt.entry[r]);
-    const int head = blockIdx.z;                                 // query head of the launch: local * gq + jq
-    const int gq = a.Hq / a.Hkv, bh = a.bh0 + head / gq;
+    for (int k = 0; k < (int)blockIdx.y; k++) before += piece_partials(pt.entry[k]);
+    const int head = blockIdx.z;                                 // local * (heads of the group / row_heads) + which of them
+    const int gq = a.Hq / a.Hkv, heads = a.row_groups, local = head / heads, bh = a.bh0 + local;
     const size_t row0 = ((size_t)head * pt.partials + before) * kQB + row;
     const float *po = a.part_o + row0 * kD + 4 * lane, *pm = a.part_ml + row0 * 2;
     float M = -INFINITY, Lsum = 0.0f;
@@ -1145,13 +1218,13 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
         M = Mn;
     }
     const float inv = 1.0f / Lsum;
-    uint16_t *out = a.out + ((size_t)((bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + head % gq) * a.n_q + i) * kD + 4 * lane;
+    uint16_t *out = a.out + ((size_t)((bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + (head - local * heads) * hp + r - i * hp) * a.n_q + i) * kD + 4 * lane;
     __builtin_nontemporal_store(u32x2{pack2(O[0] * inv, O[1] * inv), pack2(O[2] * inv, O[3] * inv)}, reinterpret_cast<u32x2 *>(out));
 }
 
 // ---- how many pieces each tile is cut into (host).
 //
-// A compute unit holds one attention work-group (its five tile buffers fill the LDS), so a launch of few tiles leaves the
+// A compute unit holds one attention work-group of 8 waves (its five tile buffers fill the LDS) or two of 4, so a launch of few tiles leaves the
 // chip idle, and one whose longest tiles take longer than an even share of all units waits for them.  The plan compares
 // the uncut launch with cuts of the one to four longest tiles only and with cuts into pieces of 1/2, 1/3 .. 1/16 of the
 // longest tile, each by the time its pieces take when the compute units pick them up longest first.  In units of 32 tokens:
@@ -1168,12 +1241,12 @@ constexpr int kMinPiece = 12;            // units: more than a tile's diagonal a
                                          // tile sees the whole first unit of its last piece (softmax_unit relies on it)
 constexpr int kLeastCut = 2 * kMinPiece; // units of a cache that can be cut
 
-struct Tiling { int tiles, n_blocks, p0, n_q; };
+struct Tiling { int tiles, n_blocks, p0, n_q, hp, waves; };
 
 int tile_units(const Tiling &g, int tile)
 {
-    const int last = (tile + 1) * kQB < g.n_q ? (tile + 1) * kQB - 1 : g.n_q - 1;
-    const int units = (g.p0 + last) / 32 + 1;
+    const int rows = g.n_q * g.hp, last = (tile + 1) * kQB < rows ? (tile + 1) * kQB - 1 : rows - 1;
+    const int units = (g.p0 + last / g.hp) / 32 + 1;
     return g.n_blocks < units ? g.n_blocks : units;
 }
 
@@ -1183,9 +1256,19 @@ int tile_pieces(int units, int length)
     return want < 1 || most < 1 ? 1 : want < most ? want : most;
 }
 
-// Fills t for pieces of at most `length` units; returns the time by the rule above for `heads` query heads.
+// What a unit takes a work-group, in percent of the unit above: fewer rows than fill a work-group of 8 waves take less, down to the latency
+// of its chain; one of 4 waves has 128 rows and shares its compute unit, unless there are no more of them than compute units.
+int unit_cost(int waves, int rows, bool alone)
+{
+    if (waves == 8) return rows <= 64 ? 50 : rows <= 128 ? 65 : rows <= 192 ? 85 : 100;
+    return !alone ? 100 : rows <= 64 ? 55 : 75;
+}
+
+// Fills t for pieces of at most `length` units; returns the time by the rule above for `heads` query heads, in percent of a unit.
+// (A single tile that is not full: unit_cost, and that much less of partial results.)
 long long cut(const Tiling &g, int heads, int length, PieceTable &t)
 {
+    const int rows = g.tiles > 1 ? kQB : g.n_q * g.hp, places = g.waves == 4 && rows <= kQB / 2 ? 2 * kCUs : kCUs;
     // tiles by falling length of their pieces
     int len[kMaxCutTiles], num[kMaxCutTiles], id[kMaxCutTiles];
     for (int i = 0; i < g.tiles; i++) {
@@ -1203,16 +1286,18 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
     }
     t.pieces = pieces;
     t.partials = partials;
+    const bool alone = (long long)pieces * heads * (rows <= kQB / 2 ? 1 : 2) <= kCUs;
+    const int unit = g.tiles > 1 ? 100 : unit_cost(g.waves, rows, alone);
     // compute units grouped by when they are free, soonest first; equal pieces go to whole groups at a time
     struct { long long free; int count; } cu[kMaxCutTiles + 2];
     int groups = 1;
-    cu[0] = {0, kCUs};
+    cu[0] = {0, places};
     for (int r = 0; r < g.tiles; r++) {
         long long left = (long long)num[r] * heads;
-        const int cost = len[r] + kPieceCost;
-        const long long rounds = left / kCUs;                    // whole rounds over all compute units
+        const int cost = len[r] * unit + 100 * kPieceCost;
+        const long long rounds = left / places;                  // whole rounds over all compute units
         for (int i = 0; i < groups; i++) cu[i].free += rounds * cost;
-        left -= rounds * kCUs;
+        left -= rounds * places;
         while (left > 0) {
             const int take = left < cu[0].count ? (int)left : cu[0].count;
             const long long until = cu[0].free + cost;
@@ -1230,42 +1315,129 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
             }
         }
     }
-    return cu[groups - 1].free + (partials ? kMergeCost + (long long)partials * heads / kPartialsPerUnit : 0);
+    return cu[groups - 1].free + (partials ? 100 * kMergeCost + 100LL * partials * heads * rows / (kQB * kPartialsPerUnit) : 0);
 }
 
-// slots: partial results the scratch area has room for
-PieceTable plan_pieces(const Tiling &g, int heads, int slots)
+// slots: partial results the scratch area has room for; least: the time by the rule above (0: not a case for pieces)
+PieceTable plan_pieces(const Tiling &g, int heads, int slots, long long &least)
 {
     PieceTable best;
     best.pieces = best.partials = 0;
+    least = 0;
     // (with three work-groups and more for every compute unit the longest tiles start early enough)
     if (g.tiles > kMaxCutTiles || g.n_blocks < kLeastCut || (long long)heads * g.tiles >= 3 * kCUs || slots < 2) return best;
     const int longest = tile_units(g, g.tiles - 1);
     PieceTable t;
-    long long least = cut(g, heads, longest, t);
+    least = cut(g, heads, longest, t);
     auto consider = [&](int length) {
         if (length < kMinPiece || length >= longest) return;
         const long long time = cut(g, heads, length, t);
         if ((long long)t.partials * heads <= slots && time < least) { least = time; best = t; }
     };
     for (int k = 1; k <= 4 && k < g.tiles; k++) consider(tile_units(g, g.tiles - 1 - k));
-    for (int parts = 2; parts <= 16 && longest / parts >= kMinPiece; parts++) consider((longest + parts - 1) / parts);
+    // (so few tiles that 16 pieces of each do not fill the chip: up to 64)
+    const int most = (long long)heads * g.tiles * 16 < 2 * kCUs ? 64 : 16;
+    for (int parts = 2; parts <= most && longest / parts >= kMinPiece; parts++) consider((longest + parts - 1) / parts);
     return best;
 }
 
-PieceTable plan_pieces(const PrefillArgs &a)
+// How a launch is divided.
+struct LaunchPlan {
+    PieceTable pt;
+    int waves, row_heads, order;
+};
+
+// The two forms of the attention kernel: work-groups of 8 waves and 256 rows, one per compute unit, or of 4 waves and 128 rows,
+// two per compute unit.  The latter fetch every unit twice as often, but have the finer grain: the chip is filled by half as
+// many rows, of two work-groups on a compute unit one goes on while the other waits, and a long one that is left alone
+// speeds up.  A row of a work-group is a query of one of row_heads query heads.  Taken together, the heads of a group let 128
+// rows end on the same or the next unit, so that hardly a wave waits for the others' last units, and few queries fill a work-group.
+//
+// - Whole tiles, 4 waves, all heads of the group together: caches of up to kShortCache units, unless pieces take less time (whole_time,
+//   looked at where the rows are half of what fills the chip).  Up to two work-groups per compute unit start together, the longest
+//   with the shortest.  Measured (us a call of one K4V4 or K4V2 layer with selection and dequantization, 8 waves of one head / 4
+//   waves of the group): one prompt of 2027 tokens, 32 / 8 heads 87 / 76, 5000 tokens 290 / 269, 6000 tokens 390 / 367, 7000 tokens
+//   480 / 483, 8192 tokens 619 / 637; four of 1024 tokens 129 / 114, eight of 500 tokens 165 / 136, four of 6000 tokens 1410 / 1399,
+//   one of 300 tokens 37 / 34; 28 / 4 heads, two of 6000 tokens 621 / 602; 8 / 2 heads, one of 4000 tokens: 89 in pieces / 127.
+//   (An XCD's L2 holds the 20 KiB units of one cache up to about there.)
+// - Tiles cut into pieces: 4 waves where they leave out an empty half of a tile or many of the units are some query's last ones
+//   (300 queries over 4000, 8000, 16000 tokens 36 / 34, 54 / 52, 94 / 91; 8 / 2 heads, a prompt of 8000 tokens 212 / 209), else 8 waves
+//   (512 queries over 8000 tokens 111 / 114, over 24576 281 / 295).
+// - Else whole tiles and 8 waves.
+constexpr int kShortCache = 192;
+constexpr int kShortPieces = 256;
+constexpr int kFewUnits = 8;
+
+// Time of whole tiles in work-groups of 4 waves, as `cut` has it (100: a unit of two work-groups on a compute unit); one that has its
+// compute unit for itself takes 0.75 per unit.  (The two rules name the faster one for 18 shapes on both sides of the line.)
+long long whole_time(const PrefillArgs &a)
 {
-    const Tiling tiling = {(a.n_q + kQB - 1) / kQB, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q};
-    return plan_pieces(tiling, a.n_bh * (a.Hq / a.Hkv), a.part_slots);
+    const int gq = a.Hq / a.Hkv, p0 = 32 * a.n_blocks + a.n_res - a.n_q, rows = a.n_q * gq, per = kQB / 2, tiles = (rows + per - 1) / per;
+    auto units = [&](long long place) {                          // of the place-th longest work-group
+        const int t = tiles - 1 - (int)(place / a.n_bh), last = (t + 1) * per < rows ? (t + 1) * per - 1 : rows - 1, u = (p0 + last / gq) / 32 + 1;
+        return (long long)(a.n_blocks < u ? a.n_blocks : u);
+    };
+    const long long n = (long long)tiles * a.n_bh;
+    const long long fixed = 100 * (kPieceCost + (a.n_bh % 8 == 0 ? 2 : 4));
+    if (n <= kCUs) return units(0) * 75 + fixed;
+    const long long uneven = units(0) * 75 + units(n - 1) * 25, even = 100 * units(kCUs);
+    return (uneven > even ? uneven : even) + fixed;
+}
+
+long long rows_of(const PrefillArgs &a, int row_heads) { return (long long)a.n_q * row_heads; }
+
+LaunchPlan plan_launch(const PrefillArgs &a)
+{
+    LaunchPlan p;
+    const int gq = a.Hq / a.Hkv, heads = a.n_bh * gq, tiles = (a.n_q + kQB - 1) / kQB;
+    const bool brief = a.n_blocks <= kShortCache;
+    const long long work = (long long)heads * tiles;
+    p.pt.pieces = p.pt.partials = 0;
+    if (!brief || work < kCUs) {
+        // the heads by themselves, or as many together as fit a tile; 8 waves or 4
+        const int last = a.n_q - (tiles - 1) * kQB;              // rows of the last tile
+        const bool prompt = a.n_blocks <= kShortPieces && 2 * a.n_q >= 32 * a.n_blocks;
+        long long least = 0;
+        for (int hp = 1; hp <= gq && (hp == 1 || (long long)a.n_q * hp <= kQB); hp++)
+            for (int waves = 8; waves >= 4 && gq % hp == 0; waves -= 4) {
+                const bool four = hp > 1 || prompt || (a.n_bh % 8 == 0 && tiles <= 2 && last <= kQB / 2);
+                if (waves == 4 ? !four : tiles > 1 && four) continue;                 // (several tiles: the one or the other)
+                const Tiling tiling = {(a.n_q * hp + kQB - 1) / kQB, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q, hp, waves};
+                long long time;
+                const PieceTable t = plan_pieces(tiling, heads / hp, a.part_slots / hp, time);   // (as many records as with every head by itself)
+                if (!t.pieces || (p.pt.pieces && time >= least)) continue;
+                least = time;
+                p.pt = t;
+                p.waves = waves;
+                p.row_heads = hp;
+            }
+        if (brief && work >= kCUs / 2 && p.pt.pieces && whole_time(a) < least) p.pt.pieces = p.pt.partials = 0;
+    }
+    if (p.pt.pieces) {
+        p.order = kByCache;
+    } else {
+        p.waves = brief ? 4 : 8;
+        // (Caches of a few units, where the heads by themselves leave no compute unit with two work-groups: those have fewer rows each. Two
+        // sequences of 54 tokens, 32 / 8 heads, 4 layers: 96 us, 100 with the heads together; one of 300 tokens, 2 layers 65 / 67, of 500 84 / 82.)
+        const bool few = a.n_blocks <= kFewUnits && (long long)heads * ((a.n_q + kQB / 2 - 1) / (kQB / 2)) <= kCUs;
+        p.row_heads = brief && !few && (long long)a.n_q * gq * gq < (1LL << 30) ? gq : 1;    // (row numbers: see row_query)
+        for (int hp = 2; !brief && work >= 3 * kCUs && hp <= gq; hp++)
+            if (gq % hp == 0 && (long long)a.n_q * hp <= kQB) p.row_heads = hp;
+        // The work-groups of an XCD cache by cache, or all by length while its caches fit its L2: the longest of the last cache
+        // would start late (24 caches of 1114 tokens, per-token keys: 4 layers 506 us by cache).
+        const long long groups = a.n_bh * ((rows_of(a, p.row_heads) + kQB / 2 - 1) / (kQB / 2)) * (gq / p.row_heads);
+        p.order = !brief ? kByCache : groups <= 2 * kCUs ? kPaired : (long long)a.n_bh * a.n_blocks <= 8 * kShortCache ? kByLength : kByCache;
+    }
+    return p;
 }
 
 }  // namespace
 
 int prefill_tile_pieces(const PrefillArgs &a, int tile)
 {
-    const PieceTable t = plan_pieces(a);
-    for (int r = 0; t.pieces && r < (a.n_q + kQB - 1) / kQB; r++)
-        if ((int)(t.entry[r] & 255u) == tile) return (int)((t.entry[r] >> 8) & 255u);
+    const LaunchPlan p = plan_launch(a);
+    for (int r = 0; p.pt.pieces && r < (a.n_q * p.row_heads + kQB - 1) / kQB; r++)
+        if ((int)(p.pt.entry[r] & 255u) == tile) return (int)((p.pt.entry[r] >> 8) & 255u);
     return 1;
 }
 
@@ -1290,12 +1462,19 @@ hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
+hipError_t launch_prefill_attention(const PrefillArgs &a0, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
-    const long long tiles = (a.n_q + kQB - 1) / kQB;
-    const int heads = a.n_bh * (a.Hq / a.Hkv);                   // query heads of the launch
-    const PieceTable pt = plan_pieces(a);
-    const long long groups = (pt.pieces ? pt.pieces : tiles) * heads;
+    const LaunchPlan plan = plan_launch(a0);
+    const PieceTable &pt = plan.pt;
+    PrefillArgs a = a0;
+    a.row_heads = plan.row_heads;
+    a.row_groups = a.Hq / a.Hkv / plan.row_heads;
+    a.row_magic = (uint32_t)(((1ULL << 32) + plan.row_heads - 1) / plan.row_heads);   // (of one head: not used)
+    a.order = plan.order;
+    const long long rows = (long long)a.n_q * a.row_heads;
+    const int heads = a.n_bh * a.row_groups, per = kQW * plan.waves;
+    const int tiles = (int)((rows + kQB - 1) / kQB);
+    const long long groups = heads * (pt.pieces ? (long long)pt.pieces * (rows > per ? kQB / per : 1) : (rows + per - 1) / per);
     if (groups < 1 || groups > 0x7fffffffLL || a.n_bh < 1 || a.n_bh > 65535) return hipErrorInvalidConfiguration;
     const bool kq = a.lv.kbits < 16, vq = a.lv.vbits < 16;
     // selection records only exist where launch_prefill_select could write them
@@ -1316,9 +1495,9 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // pass 2 (kBuffers tile buffers: more LDS than a kernel may declare statically)
-    const dim3 grid((unsigned)groups), block(64 * kWaves);
-    const size_t lds = kBuffers * sizeof(Tiles);
+    // pass 2 (more LDS than a kernel may declare statically)
+    const dim3 grid((unsigned)groups), block(64 * plan.waves);
+    const size_t lds = attention_lds(plan.waves);
     auto attend_launch = [&](auto kernel, auto table) -> hipError_t {
         // the larger dynamic LDS size is asked for at every launch of either kernel, on whichever device is current:
         // a host-side setting, negligible next to a launch of milliseconds, and no process-wide state to keep
@@ -1329,9 +1508,12 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEven
         else hipLaunchKernelGGL(kernel, grid, block, lds, s, a, table);
         return hipGetLastError();
     };
-    if (a.n_blocks < kLeastCut)
-        return kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
-    const hipError_t e = kq ? attend_launch(prefill_attention<true, PieceTable>, pt) : attend_launch(prefill_attention<false, PieceTable>, pt);
+    hipError_t e;
+    if (plan.waves == 4 && !pt.pieces)
+        e = kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
+    else if (plan.waves == 4) e = kq ? attend_launch(prefill_attention<true, PieceTable>, pt) : attend_launch(prefill_attention<false, PieceTable>, pt);
+    else if (plan.row_heads > 1) e = kq ? attend_launch(prefill_attend_long<true, true>, pt) : attend_launch(prefill_attend_long<false, true>, pt);
+    else e = kq ? attend_launch(prefill_attend_long<true, false>, pt) : attend_launch(prefill_attend_long<false, false>, pt);
     if (e != hipSuccess || !pt.pieces) return e;
     // pass 3
     const dim3 mgrid(kQB / kMergeRows, (unsigned)tiles, (unsigned)heads), mblock(32 * kMergeRows);
