@@ -253,7 +253,7 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
         a.copy_pos0 = a.copy_pos1 = a.copy_groups = 0;
         a.tickets = ws_tickets(c);
         a.ticket_stride = ticket_stride();
-        a.counters = tickets_per_cache(c) <= kvq::kMaxTickets ? tickets_per_cache(c) : 0;
+        a.counters = kvq::kMaxTickets;
         // The same launch fills the ring, unless a new token's slot still holds a token that this launch quantizes: slots are
         // positions modulo RC, so the first such token would be RC behind the last new one.  (Never the case in a prompt's
         // first append, which quantizes nothing from the ring, or when one token is appended.)
@@ -411,7 +411,7 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
     // it fetches in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
     const long long groups = (long long)a.B * a.Hkv * tickets_per_cache(c) * splits;
     const bool paired = variant == 2 && (splits == 1 || groups <= (a.lv.kbits + a.lv.vbits <= 8 ? 3 : 2) * kCUs);
-    const bool merged = paired && splits <= (a.Hq / a.Hkv <= 4 ? kvq::kMergeSplits : 16) && tickets_per_cache(c) <= kvq::kMaxTickets;
+    const bool merged = paired && splits <= (a.Hq / a.Hkv <= 4 ? kvq::kMergeSplits : 16) && tickets_per_cache(c) < kvq::kMaxTickets;     // (the last counter is not the decode kernel's)
     a.tickets = merged ? ws_tickets(c) : nullptr;
     a.ticket_stride = ticket_stride();
     const bool timed = c->ev_begin && c->ev_end;

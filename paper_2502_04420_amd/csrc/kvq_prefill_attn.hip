@@ -80,7 +80,7 @@ struct Select {
     uint8_t pos[kD];          // slot (0..31) of a channel's remainders in the compact tile, 255 = none kept
     uint8_t chan[32];         // the channel of a slot
     uint32_t compact;         // 0: every channel keeps its remainder (Tiles::Klo as declared)
-    uint32_t tickets[kMaxTickets];      // not the prefill kernels': the decode kernel's arrival counters of this cache
+    uint32_t tickets[kMaxTickets];      // arrival counters of this cache: the decode kernel's, the last one prefill_select's
     float centre[kD];         // per channel: subtracted from every dequantized key of the cache before it is rounded
 };
 static_assert(sizeof(Select) == 768, "one record per cache");
@@ -602,17 +602,22 @@ __device__ __forceinline__ void output_rescale(const float (&alpha)[kQT], float4
 // (the case the per-channel grouping is made for, Section 3.2) qualify, and so do keys with a large offset on every
 // channel (the offsets are centred away); keys that are large and widely spread on many channels do not.
 constexpr float kSelectBudget = 300.0f;
-// One work-group per cache.  Bound by the latency of its loads, so as many as fit are in flight: a wave takes a block's
+// One work-group per cache, or several (below).  Bound by the latency of its loads, so as many as fit are in flight: a wave takes a block's
 // metadata (a query's row) at a time, lane = two neighbouring channels, kSelectAhead of them outstanding.  Measured per
 // launch (8 caches): 2027 tokens 15.5 -> 8.6 us, 24576 tokens 40 -> 19 us, against four blocks in flight per thread and
 // serial loops over the 128 channels at the end.
 constexpr int kSelectWaves = 16;
 constexpr int kSelectAhead = 16;
+// Long caches: up to kSelectParts work-groups share a cache's blocks; each leaves its sums in the scratch area (prefill_dequantize
+// comes later), written through to memory, and counts itself; the last one adds them up, in their order, and does the rest.
+constexpr int kSelectParts = 8;
+
+__device__ __forceinline__ void store_through(float *p, float v) { asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory"); }
 
 template <bool NARROW>
 __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs a)
 {
-    const int tid = threadIdx.x, lane = tid & 63, local = blockIdx.x, bh = a.bh0 + local;
+    const int tid = threadIdx.x, lane = tid & 63, local = blockIdx.y, bh = a.bh0 + local, parts = gridDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: so are the addresses of a wave's rows
     __shared__ __attribute__((aligned(16))) float k1[kSelectWaves][kD], k2[kSelectWaves][kD], q2[kSelectWaves][kD], w[kD];
     __shared__ int above[8][kD];
@@ -622,10 +627,25 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
     const int head0 = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq;
     const int per_head = (a.n_q + stride - 1) / stride, samples = gq * per_head;
     float sq[2] = {0.0f, 0.0f}, sk[2] = {0.0f, 0.0f}, sm[2] = {0.0f, 0.0f};
+    // the metadata of kSelectAhead blocks of this wave; the first ones go out in front of the queries, so that both share a round trip
+    const int across = kSelectWaves * parts, first = blockIdx.x * kSelectWaves + wave;      // waves of the cache, this one's number
+    u32x2 sc[kSelectAhead];                                      // (fp16 scales: one word, the other one is not used)
+    uint32_t zp[kSelectAhead];
+    auto fetch = [&](int u0) {
+#pragma unroll
+        for (int k = 0; k < kSelectAhead; k++) {
+            const int u = u0 + across * k < a.n_blocks ? u0 + across * k : u0;
+            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
+            if constexpr (NARROW) sc[k][0] = *reinterpret_cast<const uint32_t *>(meta_scales16(meta) + 2 * lane);
+            else sc[k] = *reinterpret_cast<const u32x2 *>(meta + 2 * lane);
+            zp[k] = *reinterpret_cast<const uint32_t *>(meta_zeros(meta, NARROW) + 2 * lane);
+        }
+    };
+    if (first < a.n_blocks) fetch(first);
     // at most 64 samples per head, four per wave: four heads at a time fill kSelectAhead loads (numbering the samples of all heads
     // through instead costs a division per load: 10.6 instead of 8.6 us a launch)
     static_assert(4 * kSelectWaves == 64 && kSelectAhead == 16, "four samples of four heads per wave");
-    for (int j0 = 0; j0 < gq; j0 += 4) {
+    for (int j0 = 0; j0 < gq && blockIdx.x == 0; j0 += 4) {      // (the first part takes the queries)
         uint32_t x[4][4];
 #pragma unroll
         for (int j = 0; j < 4; j++)
@@ -644,20 +664,11 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
                     sq[1] = fmaf(v1, v1, sq[1]);
                 }
     }
-    for (int u0 = wave; u0 < a.n_blocks; u0 += kSelectAhead * kSelectWaves) {
-        u32x2 sc[kSelectAhead];                                  // (fp16 scales: one word, the other one is not used)
-        uint32_t zp[kSelectAhead];
+    for (int u0 = first; u0 < a.n_blocks; u0 += kSelectAhead * across) {
+        if (u0 != first) fetch(u0);
 #pragma unroll
         for (int k = 0; k < kSelectAhead; k++) {
-            const int u = u0 + kSelectWaves * k < a.n_blocks ? u0 + kSelectWaves * k : u0;
-            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
-            if constexpr (NARROW) sc[k][0] = *reinterpret_cast<const uint32_t *>(meta_scales16(meta) + 2 * lane);
-            else sc[k] = *reinterpret_cast<const u32x2 *>(meta + 2 * lane);
-            zp[k] = *reinterpret_cast<const uint32_t *>(meta_zeros(meta, NARROW) + 2 * lane);
-        }
-#pragma unroll
-        for (int k = 0; k < kSelectAhead; k++) {
-            if (u0 + kSelectWaves * k < a.n_blocks) {
+            if (u0 + across * k < a.n_blocks) {
                 const uint32_t s0 = sc[k][0], s1 = sc[k][1];
 #pragma unroll
                 for (int e = 0; e < 2; e++) {
@@ -675,10 +686,46 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
     __syncthreads();
     Select *sel = reinterpret_cast<Select *>(a.select) + local;
     const int d = tid & (kD - 1), slice = tid >> 7;              // 8 slices of 16 channels for the ranks
+    float tm = 0.0f, tk = 0.0f, tq = 0.0f;
     if (tid < kD) {
-        float tm = 0.0f, tk = 0.0f, tq = 0.0f;
 #pragma unroll
         for (int k = 0; k < kSelectWaves; k++) { tm += k1[k][d]; tk += k2[k][d]; tq += q2[k][d]; }
+    }
+    if (parts > 1) {
+        static_assert(8 * kD == 64 * kSelectWaves && kSelectParts == 8, "a slice of threads per part");
+        float *sums = reinterpret_cast<float *>(a.scratch) + (size_t)local * parts * 3 * kD;
+        if (tid < kD) {
+            float *mine = sums + (size_t)blockIdx.x * 3 * kD + d;
+            store_through(mine, tm);
+            store_through(mine + kD, tk);
+            store_through(mine + 2 * kD, tq);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t *t = &sel->tickets[kMaxTickets - 1];
+            const bool last = (int)__hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+            if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            above[0][0] = last ? 1 : 0;
+        }
+        __syncthreads();
+        if (above[0][0] == 0) return;
+        const __amdgpu_buffer_rsrc_t all = __builtin_amdgcn_make_buffer_rsrc(sums, 0, parts * 3 * kD * (int)sizeof(float), 0x00020000);
+        if (slice < parts) {                                     // (read past the caches, as they were written)
+            const int off = (slice * 3 * kD + d) * (int)sizeof(float), row = kD * (int)sizeof(float);
+            const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(all, off, 0, 17), y = __builtin_amdgcn_raw_buffer_load_b32(all, off + row, 0, 17),
+                           z = __builtin_amdgcn_raw_buffer_load_b32(all, off + 2 * row, 0, 17);
+            k1[slice][d] = __builtin_bit_cast(float, x);
+            k2[slice][d] = __builtin_bit_cast(float, y);
+            q2[slice][d] = __builtin_bit_cast(float, z);
+        }
+        __syncthreads();
+        if (tid < kD) {
+            tm = tk = tq = 0.0f;
+            for (int k = 0; k < parts; k++) { tm += k1[k][d]; tk += k2[k][d]; tq += q2[k][d]; }
+        }
+    }
+    if (tid < kD) {
         // the channel's centre: the mean of its blocks' midpoints, as an fp16 number (the zero-points are fp16 numbers, so
         // zero-point minus centre is exact in fp32).  What counts from here on is the keys' spread about it.
         const float centre = (float)(_Float16)(tm / (float)a.n_blocks);
@@ -853,7 +900,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     const int wlast = rw < rows ? (p0 + query_of(rw + kQW - 1 < rows ? rw + kQW - 1 : rows - 1)) / 32 : -1;
     const int open_units = rw < rows ? (p0 + query_of(rw) + 1) / 32 : 0;   // units [0, open_units) lie before the wave's first query: no mask needed
     const float c = a.scale_log2e;
-    const float inv_c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, 1.0f / c)));
+    const float inv_c = 1.0f / c;
 
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     Tiles *L = reinterpret_cast<Tiles *>(lds_raw);
@@ -1452,7 +1499,12 @@ size_t prefill_ticket_offset() { return offsetof(Select, tickets); }
 hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin)
 {
     if (!a.select || a.lv.kbits >= 16 || a.lv.kpt || a.n_blocks < 1 || a.n_bh < 1) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)a.n_bh), block(64 * kSelectWaves);
+    // A second round of loads (more than kSelectAhead blocks per wave) costs more than the parts' way through memory.  us a call of one layer, 8
+    // caches, 1 / 2 / 4 / 8 work-groups each: 249 units 51 / 52 / 53 / 52, 499 units 82 / 79 / 78 / 78, 936 units 134 / 127 / 123 / 122.
+    int parts = 1;
+    if (a.n_blocks > kSelectAhead * kSelectWaves)
+        while (parts < kSelectParts && 2 * parts * a.n_bh <= kCUs && a.n_blocks > 64 * parts) parts *= 2;
+    const dim3 grid((unsigned)parts, (unsigned)a.n_bh), block(64 * kSelectWaves);
     auto launch = [&](auto kernel) {
         if (ev_begin) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev_begin, nullptr, 0, a);
         else hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
