@@ -310,6 +310,7 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
         int cap = cap_at(min_units);
         if (variant == 2) {
             // Few groups leave every compute unit one group or none, and a call takes as long as its longest group.  Measured
+            // with one pair of waves per group (two pairs halve what a group's blocks take; the lines were left where they are)
             // (8, 4 and 2 kv heads, batch 1 to 12, K4V2 and K8V8, us a call, 4 blocks per group / the other):
             // - 5 blocks, where 4 make more groups than there are compute units and 5 do not: one sequence, 8 kv heads, a window of two
             //   chunks, 264..320 groups 11.1..11.4 / 10.6..10.8, 4 kv heads 13.9 / 12.2; 50 such shapes gain 0..16 %.  Where 5
