@@ -248,6 +248,13 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
                          int32_t *splits, int32_t *units_per_split, int32_t *split_rem);
 
 /*
+ * How the matrix-core kernel of such a decode call would be launched (host only, no GPU work): *pairs pairs of waves per
+ * work-group (1 or 2), and *merges = 1 if its last work-group merges the splits (or a single split writes the outputs), 0 if a
+ * small kernel behind it does.  For tests and tuning; KVQ_EINVAL on invalid arguments.
+ */
+int kvq_debug_decode_form(const kvq_config *cfg, int32_t layer, int32_t n_tokens, int32_t forced_splits, int32_t *pairs, int32_t *merges);
+
+/*
  * How a kvq_prefill_attention call would be divided (host only, no GPU work): on a context configured with *cfg and a workspace
  * of workspace_bytes, a layer that holds n_tokens tokens, n_q queries.  Pass number `pass` (0, 1, ..) attends to *caches (batch, kv
  * head) caches, 0 when there is no such pass; in it query tile `tile` (queries 256 tile .. 256 tile + 255) is attended in

@@ -365,6 +365,47 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
     return p;
 }
 
+// How the matrix-core kernel is launched: pairs of waves per work-group; whether it writes the outputs itself (no combine launch).
+struct DecodeForm { int pairs; bool merges; };
+
+// Two pairs of waves per work-group (launch_decode_short) where the work-groups are few.  Such work-groups hold twice the waves and more
+// registers, so fewer are resident at once (kvq::paired_groups), and beyond that the second half of them waits for the first.  Measured: us a
+// call, one pair / two, or (below 2) the time with one pair over that with two; 32 / 8 heads unless said otherwise.
+// - Several splits, tiles of 4 heads: as long as all are resident.  K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups
+//   12.6 / 15.6; K8V8 256 groups 9.9 / 8.9, 544 groups 11.3 / 11.5, 1024 groups 13.7 / 17.4; K16V16 256 groups 12.2 / 10.8, 520 groups
+//   14.6 / 15.7.
+// - Several splits, tiles of 8 heads, whose records take longer to merge (28 / 4 heads): up to one work-group per compute unit 1.01..1.14;
+//   two, if the longest split has 4 units or more 1.03..1.08, with 2 or 3 0.94..1.01; more than two 0.93..1.00.
+// - A single split saves the merge launch.  Up to three work-groups per compute unit 1.03..1.6, at any length (60 to 4128 tokens) and width.
+//   Four of 4 heads: 1.03..1.25 for codes up to 8 bits per key + value element and with an fp16 tensor, 0.84..0.96 for 8-bit keys; of 8
+//   heads 0.69..1.01.  Beyond that:
+//   - blocks are streamed faster by one pair (2048 groups, 256 to 4096 tokens: K4V2 0.87..0.93, K2V2 0.78..0.84; K8V4 1024 to 4096 groups
+//     0.80..1.02; 28 / 4 heads 0.65..0.97), except by tiles of 4 heads where both tensors are as wide: fp16 0.99..1.17, K8V8
+//     from 16 blocks and six work-groups per compute unit on 1.01..1.10 (below 0.84..1.05);
+//   - of a window alone, two pairs of 4 heads share 2 chunks and more (1.02..1.17; 8-bit keys 0.93..0.98, from 4 chunks and six
+//     work-groups per compute unit on 1.02..1.15, so do 8 heads, 1.01..1.12); a single chunk is read faster by one pair (0.72..0.96).
+// The last work-group merges up to 64 splits of 4 heads (48 splits 9.6 behind a launch / 9.2) or 16 of 8 heads, whose records
+// it fetches in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
+DecodeForm decode_form(const SplitPlan &sp, int BH, int gq, int kbits, int vbits, int n_blocks, int n_res)
+{
+    const int tiles = (gq + 7) / 8, chunks = (n_res + 31) / 32;
+    const long long groups = (long long)BH * tiles * sp.splits;
+    const bool four = gq <= 4, light = four && (kbits + vbits <= 8 || kbits == 16 || vbits == 16);
+    bool paired;
+    if (sp.splits > 1) {
+        const int longest = sp.units_per_split + (sp.split_rem > 0 ? 1 : 0);
+        paired = groups <= (four ? kvq::paired_groups(kbits + vbits) : longest >= 4 ? 2 : 1) * kCUs;
+    } else if (groups <= (light ? 4 : 3) * kCUs) {
+        paired = true;
+    } else if (n_blocks > 0) {
+        paired = four && kbits == vbits && (kbits == 16 || (kbits == 8 && n_blocks >= 16 && groups >= 6 * kCUs));
+    } else {
+        paired = (light && chunks >= 2) || (chunks >= 4 && groups >= 6 * kCUs);
+    }
+    if (!paired) return {1, false};
+    return {2, sp.splits == 1 || (sp.splits <= (four ? kvq::kMergeSplits : 16) && tiles < kvq::kMaxTickets)};      // (the last counter is not the decode kernel's)
+}
+
 // Decode attention over the layer's tokens.  k_new / v_new: rows of a token that append_tokens() left out of the
 // window ring (fused append), or NULL.
 // part_o / part_ml: where the splits' partial results go, room for part_records (query row, split) records.
@@ -403,16 +444,8 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
                  (size_t)a.B * a.Hq * (size_t)splits, a.B * a.Hq, splits, part_records);
         return KVQ_ESCRATCH;
     }
-    // Two pairs of waves per work-group as long as the work-groups are all resident at once (three per compute unit for codes up to 8
-    // bits per key + value element, whose kernels leave room for that many, else two).  Measured, us a call (32 / 8 heads, one pair
-    // / two): K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups 12.6 / 15.6; K8V8 256 groups 9.9 / 8.9,
-    // 544 groups 11.3 / 11.5, 1024 groups 13.7 / 17.4; K16V16 256 groups 12.2 / 10.8, 520 groups 14.6 / 15.7.  A single split saves the
-    // merge at any number: 512 groups 11.0 / 8.0, 2048 groups 19.8 / 19.1.
-    // The last work-group merges up to 64 splits of 4 heads (48 splits 9.6 behind a launch / 9.2) or 16 of 8 heads, whose records
-    // it fetches in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
-    const long long groups = (long long)a.B * a.Hkv * tickets_per_cache(c) * splits;
-    const bool paired = variant == 2 && (splits == 1 || groups <= (a.lv.kbits + a.lv.vbits <= 8 ? 3 : 2) * kCUs);
-    const bool merged = paired && splits <= (a.Hq / a.Hkv <= 4 ? kvq::kMergeSplits : 16) && tickets_per_cache(c) < kvq::kMaxTickets;     // (the last counter is not the decode kernel's)
+    const DecodeForm form = variant == 2 ? decode_form(sp, a.B * a.Hkv, a.Hq / a.Hkv, a.lv.kbits, a.lv.vbits, a.n_blocks, a.n_res) : DecodeForm{1, false};
+    const bool paired = form.pairs > 1, merged = form.merges;
     a.tickets = merged ? ws_tickets(c) : nullptr;
     a.ticket_stride = ticket_stride();
     const bool timed = c->ev_begin && c->ev_end;
@@ -426,7 +459,7 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
         if (e == hipSuccess && timed && hipEventRecord(c->ev_end, c->stream) != hipSuccess) return launch_failed("event record", hipGetLastError());
     }
     if (e != hipSuccess) return launch_failed("decode kernel", e);
-    if (merged || (paired && splits == 1)) return KVQ_OK;
+    if (merged) return KVQ_OK;
     e = kvq::launch_combine(a, c->stream);
     if (e != hipSuccess) return launch_failed("combine kernel", e);
     return KVQ_OK;
@@ -622,6 +655,20 @@ int kvq_debug_split_plan(const kvq_config *cfg, int32_t layer, int32_t n_tokens,
     *splits = p.splits;
     *units_per_split = p.units_per_split;
     *split_rem = p.split_rem;
+    return KVQ_OK;
+}
+
+int kvq_debug_decode_form(const kvq_config *cfg, int32_t layer, int32_t n_tokens, int32_t forced_splits, int32_t *pairs, int32_t *merges)
+{
+    if (!config_ok(cfg) || layer < 0 || layer >= cfg->n_layers || n_tokens < 1 || n_tokens > cfg->max_tokens || forced_splits < 0 ||
+        forced_splits > kMaxSplits || !pairs || !merges)
+        return KVQ_EINVAL;
+    const int over = n_tokens - cfg->residual, np = over > 0 ? kvq::kG * (over / kvq::kG) : 0;
+    const int BH = cfg->batch * cfg->n_kv_heads, gq = cfg->n_q_heads / cfg->n_kv_heads, kb = cfg->kbits[layer], vb = cfg->vbits[layer];
+    const SplitPlan p = plan_splits(BH, gq, kb + vb, np / kvq::kG, n_tokens - np, forced_splits, 2);
+    const DecodeForm f = decode_form(p, BH, gq, kb, vb, np / kvq::kG, n_tokens - np);
+    *pairs = f.pairs;
+    *merges = f.merges ? 1 : 0;
     return KVQ_OK;
 }
 

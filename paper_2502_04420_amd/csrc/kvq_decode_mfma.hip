@@ -915,8 +915,7 @@ __device__ __forceinline__ void merge_pairs(const DecodeArgs &a, PairLds<GQ> (&L
 // Waves per SIMD the register allocation must leave room for: the host plans 2048 groups (4 waves per SIMD) for code
 // widths up to 8 bits per key + value element and 1024 (2) beyond; the wider instantiations may
 // use the registers that fewer resident waves leave free instead of spilling (16-bit layers: two units of rows).
-// Work-groups of two pairs: up to three per compute unit for the narrow widths, two beyond (kPairedGroups in the host plan).
-template <int KB, int VB, int PAIRS> constexpr int resident_waves() { return KB + VB <= 8 ? (PAIRS > 1 ? 3 : 4) : 2; }
+template <int KB, int VB, int PAIRS> constexpr int resident_waves() { return PAIRS > 1 ? paired_groups(KB + VB) : KB + VB <= 8 ? 4 : 2; }
 
 template <int KB, int VB, int GQ, bool NARROW, bool KPT, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) void decode_mfma(DecodeArgs a)

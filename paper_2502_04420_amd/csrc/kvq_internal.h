@@ -59,6 +59,10 @@ struct ExportArgs {
     int BH, NB, RC;
 };
 
+// Work-groups of two pairs of waves that a compute unit holds, for a layer of `width` bits per key + value element: a pair has a wave on two of the
+// four SIMDs, so it is also the waves per SIMD that the kernel's registers leave room for.
+constexpr int paired_groups(int width) { return width <= 8 ? 3 : 2; }
+
 struct DecodeArgs {
     LayerView lv;
     const uint16_t *q;     // fp16 [B][Hq][128]

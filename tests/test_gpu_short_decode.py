@@ -122,3 +122,26 @@ def test_one_pass_over_many_layers_of_single_splits(kvq_mod, oracle_mod):
     torch.cuda.synchronize()
     assert_outputs_close(out, *o.decode_attention(0, q.numpy()), "single")
     g.close()
+
+
+@pytest.mark.parametrize("batch,hq,hkv,T,kb,vb,pairs", [
+    (1024, 4, 2, 32 * 3 + 40, 4, 2, 1), (1024, 4, 2, 32 * 3 + 40, 16, 16, 2), (770, 2, 2, 32 * 16 + 37, 8, 8, 2), (520, 14, 2, 32 * 5 + 33, 8, 4, 1),
+    (3, 8, 2, 32 * 40 + 45, 4, 2, 2), (3, 8, 2, 32 * 40 + 45, 16, 4, 2),
+])
+def test_long_single_splits(kvq_mod, oracle_mod, batch, hq, hkv, T, kb, vb, pairs):
+    """One split over several blocks: of so many caches that there is one each (one pair of waves and a merge launch, or two pairs that write
+    the outputs), or forced."""
+    from paper_2502_04420_amd.binding import make_config
+    w = W.Workload("long single", 1, batch, hq, hkv, 128, T, [kb], [vb], seed=900 + kb + vb, outlier_channels=3)
+    forced = 1 if batch < 100 else 0
+    cfg, keep = make_config(1, batch, hq, hkv, 128, T, [kb], [vb])
+    p, s = ctypes.c_int32(), ctypes.c_int32()
+    lib = kvq_mod.load_library()
+    assert lib.kvq_debug_split_plan(ctypes.byref(cfg), 0, T, 2, forced, ctypes.byref(s), ctypes.byref(ctypes.c_int32()), ctypes.byref(ctypes.c_int32())) == 0
+    assert lib.kvq_debug_decode_form(ctypes.byref(cfg), 0, T, forced, ctypes.byref(p), ctypes.byref(ctypes.c_int32())) == 0
+    assert (s.value, p.value) == (1, pairs)
+    g, o = _filled(kvq_mod, oracle_mod, w)
+    g.set_decode_options(0, forced)
+    q = W.query(w, 0)
+    assert_outputs_close(g.decode_attention(0, q.cuda()), *o.decode_attention(0, q.numpy()), "K%dV%d" % (kb, vb))
+    g.close()

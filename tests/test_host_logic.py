@@ -306,3 +306,33 @@ def test_split_plan_of_short_caches(lib, batch, hq, hkv, residual, T, expected):
     s, u, r = i32(), i32(), i32()
     assert lib.kvq_debug_split_plan(ctypes.byref(cfg), 0, T, 2, 0, ctypes.byref(s), ctypes.byref(u), ctypes.byref(r)) == 0
     assert s.value == expected
+
+
+@pytest.mark.parametrize("batch,hq,hkv,kb,vb,residual,T,forced,expected", [
+    # a single split: up to three work-groups per compute unit, at any length
+    (1, 32, 8, 4, 2, 32, 4128, 1, (2, 1)), (96, 32, 8, 8, 8, 32, 1056, 1, (2, 1)), (192, 28, 4, 4, 2, 32, 288, 1, (2, 1)),
+    # four, with tiles of 4 heads and narrow or fp16 pairs
+    (128, 32, 8, 4, 2, 0, 128, 0, (2, 1)), (128, 32, 8, 16, 4, 32, 1056, 0, (2, 1)),
+    (128, 32, 8, 8, 4, 32, 288, 0, (1, 0)), (256, 28, 4, 4, 2, 32, 288, 1, (1, 0)),
+    # beyond: blocks go to one pair, except of fp16 pairs and many blocks of K8V8
+    (256, 32, 8, 4, 2, 32, 288, 0, (1, 0)), (256, 32, 8, 2, 2, 32, 4128, 0, (1, 0)), (256, 32, 8, 8, 4, 32, 1056, 0, (1, 0)),
+    (256, 32, 8, 16, 16, 32, 288, 0, (2, 1)), (256, 32, 8, 16, 4, 32, 288, 0, (1, 0)), (256, 32, 8, 8, 8, 32, 288, 0, (1, 0)), (256, 32, 8, 8, 8, 32, 1056, 0, (2, 1)),
+    (512, 28, 4, 4, 2, 32, 1000, 0, (1, 0)),
+    # a window alone: by its chunks
+    (256, 32, 8, 4, 2, 64, 60, 0, (2, 1)), (256, 32, 8, 4, 2, 32, 30, 0, (1, 0)), (256, 32, 8, 16, 16, 32, 30, 0, (1, 0)),
+    (256, 32, 8, 8, 4, 128, 90, 0, (1, 0)), (256, 32, 8, 8, 4, 128, 120, 0, (2, 1)), (128, 32, 8, 8, 4, 128, 120, 0, (1, 0)), (512, 28, 4, 8, 4, 128, 120, 0, (2, 1)),
+    # several splits: as long as all work-groups are resident
+    (1, 32, 8, 4, 2, 32, 4133, 0, (2, 1)), (4, 32, 8, 4, 2, 32, 3090, 0, (1, 0)), (8, 32, 8, 8, 8, 32, 1056, 8, (2, 1)), (8, 32, 8, 8, 8, 32, 1056, 9, (1, 0)),
+    # tiles of 8 heads
+    (18, 28, 4, 4, 2, 32, 352, 0, (2, 1)), (26, 28, 4, 4, 2, 32, 320, 0, (1, 0)), (26, 28, 4, 4, 2, 32, 416, 0, (2, 1)), (38, 28, 4, 4, 2, 32, 416, 0, (1, 0)),
+    (1, 28, 4, 4, 2, 32, 8592, 0, (2, 0)),
+])
+def test_decode_form(lib, batch, hq, hkv, kb, vb, residual, T, forced, expected):
+    """Pairs of waves per work-group of the decode kernel on either side of the lines that measurements drew, and who merges."""
+    cfg, keep = _cfg(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=40000, kbits=[kb], vbits=[vb], residual=residual)
+    p, m = ctypes.c_int32(), ctypes.c_int32()
+    assert lib.kvq_debug_decode_form(ctypes.byref(cfg), 0, T, forced, ctypes.byref(p), ctypes.byref(m)) == 0
+    assert (p.value, m.value) == expected
+    for bad in ((1, T, 0), (-1, T, 0), (0, 0, 0), (0, 40001, 0), (0, T, -1), (0, T, 129)):
+        assert lib.kvq_debug_decode_form(ctypes.byref(cfg), *bad, ctypes.byref(p), ctypes.byref(m)) == -1, bad
+    assert lib.kvq_debug_decode_form(ctypes.byref(cfg), 0, T, 0, None, ctypes.byref(m)) == -1
