@@ -415,7 +415,7 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
     const int T = c->tokens[layer];
     if (T < 1) return KVQ_ESTATE;
     const int np = packed_tokens(c, T);
-    kvq::DecodeArgs a;
+    kvq::ShortDecodeArgs a;
     a.lv = view(c, layer);
     a.q = static_cast<const uint16_t *>(q_device);
     a.out = static_cast<uint16_t *>(out_device);
@@ -452,7 +452,8 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
     hipError_t e;
     if (variant == 2) {
         // the matrix-core kernel's dispatch stamps the two events itself (its own start and end, no marker in between)
-        e = (paired ? kvq::launch_decode_short : kvq::launch_decode_mfma)(a, c->stream, timed ? c->ev_begin : nullptr, timed ? c->ev_end : nullptr);
+        const hipEvent_t begin = timed ? c->ev_begin : nullptr, end = timed ? c->ev_end : nullptr;
+        e = paired ? kvq::launch_decode_short(a, c->stream, begin, end) : kvq::launch_decode_mfma(a, c->stream, begin, end);
     } else {
         if (timed && hipEventRecord(c->ev_begin, c->stream) != hipSuccess) return launch_failed("event record", hipGetLastError());
         e = kvq::launch_decode_valu(a, c->stream);

@@ -29,6 +29,8 @@
 // single split writes the outputs, and of several splits the work-group that finishes last merges the records (merge_pairs).
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "kvq_internal.h"
 
 #ifndef KVQ_DECODE_PAIRS
@@ -868,7 +870,7 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&
 // kernel).  Measured, us a call (launches of this kernel and combine_splits with one pair / with two / merged here): 8 kv heads, K4V2, 200 tokens
 // 9.0 / 7.9 / 7.6, 1100 tokens 9.1 / 8.4 / 7.8, 4133 tokens 10.1 / 9.5 / 9.2, 60 tokens (a single split) 9.0 / 6.0.
 template <int GQ, int PAIRS>
-__device__ __forceinline__ void merge_pairs(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid, int split, int bh)
+__device__ __forceinline__ void merge_pairs(const ShortDecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid, int split, int bh)
 {
     wg_barrier();                                                // all pairs' results are in LDS
     const int head = threadIdx.x >> 5, lane = threadIdx.x & 31;
@@ -917,8 +919,10 @@ __device__ __forceinline__ void merge_pairs(const DecodeArgs &a, PairLds<GQ> (&L
 // use the registers that fewer resident waves leave free instead of spilling (16-bit layers: two units of rows).
 template <int KB, int VB, int PAIRS> constexpr int resident_waves() { return PAIRS > 1 ? paired_groups(KB + VB) : KB + VB <= 8 ? 4 : 2; }
 
+template <int PAIRS> using KernelArgs = std::conditional_t<PAIRS == 1, DecodeArgs, ShortDecodeArgs>;
+
 template <int KB, int VB, int GQ, bool NARROW, bool KPT, int PAIRS>
-__global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) void decode_mfma(DecodeArgs a)
+__global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) void decode_mfma(KernelArgs<PAIRS> a)
 {
     static_assert(GQ == 4 || GQ == 8, "rows 2j and 2j + 1 of a 16-row tile");
     constexpr bool kFast = KB < 16 && VB < 16;
@@ -1411,11 +1415,12 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 }
 
 constexpr int kPairs = KVQ_DECODE_PAIRS;
+using Args = KernelArgs<kPairs>;
 
 struct LaunchEvents { hipEvent_t begin, end; };
 
 template <int KB, int VB, bool NARROW, bool KPT>
-hipError_t launch_gq(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
+hipError_t launch_gq(const Args &a, hipStream_t s, LaunchEvents ev)
 {
     const int gq = a.Hq / a.Hkv;
     const int BH = a.B * a.Hkv;
@@ -1434,7 +1439,7 @@ hipError_t launch_gq(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
 }
 
 template <int KB, bool NARROW, bool KPT>
-hipError_t launch_vb(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
+hipError_t launch_vb(const Args &a, hipStream_t s, LaunchEvents ev)
 {
     switch (a.lv.vbits) {
     case 2: return launch_gq<KB, 2, NARROW, KPT>(a, s, ev);
@@ -1445,7 +1450,7 @@ hipError_t launch_vb(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
 }
 
 template <bool NARROW>
-hipError_t launch_kb(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
+hipError_t launch_kb(const Args &a, hipStream_t s, LaunchEvents ev)
 {
     // the key grouping only matters for quantized keys
     if (a.lv.kpt) {
@@ -1469,7 +1474,7 @@ hipError_t launch_kb(const DecodeArgs &a, hipStream_t s, LaunchEvents ev)
 #if KVQ_DECODE_PAIRS == 1
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
 #else
-hipError_t launch_decode_short(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
+hipError_t launch_decode_short(const ShortDecodeArgs &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
 #endif
 {
     if (a.B * a.Hkv > 65535) return hipErrorInvalidConfiguration;

@@ -81,8 +81,12 @@ struct DecodeArgs {
     // window ring; the kernel reads them from here and stores them into the ring for later launches.  NULL: none.
     const uint16_t *k_new, *v_new;
     int new_pos;           // absolute position of that token
-    // launch_decode_short only: its last work-group of a cache and tile of query heads merges the splits (at most kMergeSplits); one
-    // arrival counter per cache and tile, zero between calls, cache bh's at tickets + bh * ticket_stride.  NULL: launch_combine merges.
+};
+
+// launch_decode_short's: its last work-group of a cache and tile of query heads merges the splits (at most kMergeSplits); one
+// arrival counter per cache and tile, zero between calls, cache bh's at tickets + bh * ticket_stride.  NULL: launch_combine merges.
+// (A record of its own: 16 bytes more in the one that decode_mfma and combine_splits share made their calls 0.1..0.3 us longer.)
+struct ShortDecodeArgs : DecodeArgs {
     uint32_t *tickets;
     int ticket_stride;
 };
@@ -141,7 +145,7 @@ hipError_t launch_decode_valu(const DecodeArgs &a, hipStream_t s);
 hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 // the same with two pairs of waves per work-group, for launches of few work-groups; a single split or a.tickets: no
 // launch_combine behind it
-hipError_t launch_decode_short(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+hipError_t launch_decode_short(const ShortDecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 // pieces that launch_prefill_attention(a) cuts query tile `tile` into (host only; 1: it stays whole)
 int prefill_tile_pieces(const PrefillArgs &a, int tile);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache

@@ -175,3 +175,20 @@ def test_decode_check_follows_every_path_to_the_streaming_loop():
                 with pytest.raises(RuntimeError, match="hand-issued load"):
                     B.check_decode_code("\n".join(lines[:spot] + ["\tv_mov_b32_e32 v%s, 0" % r] + lines[spot:]))
     assert plants >= 4 * (3 + 3 + 3 + 2)
+
+
+def _record_bytes(asm, name):
+    """Bytes of the argument records of the kernels whose mangled name contains `name` (implicit arguments included)."""
+    return {int(n) for n in re.findall(r"\.amdhsa_kernel _Z\w*%s\w*\n(?:(?!\.end_amdhsa_kernel).*\n)*?\s*\.amdhsa_kernarg_size (\d+)" % name, asm)}
+
+
+def test_decode_launches_carry_only_their_own_arguments():
+    """What only the short-cache form of the decode kernel needs is not part of the record of the streaming form and of the merge,
+    whose calls it made longer; no kernel of a decode call asks for implicit arguments."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    assert _record_bytes(B.device_assembly("kvq_decode_mfma.hip"), "decode_mfma") == {176}
+    assert _record_bytes(B.device_assembly("kvq_decode_valu.hip"), "combine_splits") == {176}
+    assert _record_bytes(B.device_assembly("kvq_decode_short.hip"), "decode_mfma") == {192}
