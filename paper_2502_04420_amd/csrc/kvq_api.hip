@@ -170,9 +170,9 @@ float *ws_part_o(const kvq_ctx *c) { return reinterpret_cast<float *>(c->ws + c-
 float *ws_part_ml(const kvq_ctx *c) { return reinterpret_cast<float *>(c->ws + c->plan.part_ml); }
 size_t ws_part_records(const kvq_ctx *c) { return (size_t)c->cfg.batch * c->cfg.n_q_heads * kMaxSplits; }
 
-// Arrival counters of the decode kernel: in the selection records of the prefill attention, one record per cache.  A cache's
-// counters start at zero when its first block is quantized (only calls with packed blocks have more than one split) and are zero
-// again after every call.
+// Arrival counters of the decode and the channel selection kernels: in the selection records of the prefill attention, one record per
+// cache, shared by all layers.  A cache's counters start at zero when a layer's first block is quantized (only calls with packed
+// blocks count) and are zero again after every call.
 uint32_t *ws_tickets(const kvq_ctx *c) { return reinterpret_cast<uint32_t *>(c->ws + c->plan.prefill_select + kvq::prefill_ticket_offset()); }
 int ticket_stride() { return (int)(kvq::prefill_select_bytes() / sizeof(uint32_t)); }
 int tickets_per_cache(const kvq_ctx *c) { return (c->cfg.n_q_heads / c->cfg.n_kv_heads + 7) / 8; }
@@ -250,10 +250,9 @@ int append_tokens(kvq_ctx *c, int layer, const void *k_device, const void *v_dev
         a.BH = BH;
         a.NB = c->plan.NB;
         a.RC = c->plan.RC;
-        a.copy_pos0 = a.copy_pos1 = a.copy_groups = 0;
+        a.copy_pos0 = a.copy_pos1 = 0;
         a.tickets = ws_tickets(c);
         a.ticket_stride = ticket_stride();
-        a.counters = kvq::kMaxTickets;
         // The same launch fills the ring, unless a new token's slot still holds a token that this launch quantizes: slots are
         // positions modulo RC, so the first such token would be RC behind the last new one.  (Never the case in a prompt's
         // first append, which quantizes nothing from the ring, or when one token is appended.)

@@ -35,11 +35,13 @@ struct QuantArgs {
     int NB;                        // block capacity per (b, h)
     int RC;                        // ring capacity (R + G)
     int copy_pos0, copy_pos1;      // absolute positions of this append that go into the ring in the same launch (none: equal)
-    int copy_groups;               // waves per tensor that copy them (set by launch_quantize)
-    // the launch that writes a layer's first block clears the arrival counters of the decode kernel (DecodeArgs):
-    // `counters` of them at tickets + bh * ticket_stride
+    int extra_groups;              // waves per tensor in front of the blocks': copy_groups, then those that clear counters (set by launch_quantize)
+    // (behind the first 128 bytes, which are all that a block's wave reads)
+    // the launch that writes a layer's first block clears the arrival counters (kMaxTickets per cache, at tickets + bh * ticket_stride)
+    // of the decode and the channel selection kernels
     uint32_t *tickets;
-    int ticket_stride, counters;
+    int ticket_stride;
+    int copy_groups;               // waves per tensor that copy window tokens (set by launch_quantize)
 };
 
 struct ResidualCopyArgs {

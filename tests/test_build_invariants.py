@@ -192,3 +192,21 @@ def test_decode_launches_carry_only_their_own_arguments():
     assert _record_bytes(B.device_assembly("kvq_decode_mfma.hip"), "decode_mfma") == {176}
     assert _record_bytes(B.device_assembly("kvq_decode_valu.hip"), "combine_splits") == {176}
     assert _record_bytes(B.device_assembly("kvq_decode_short.hip"), "decode_mfma") == {192}
+
+
+def test_quantize_waves_read_two_lines_of_their_arguments(tmp_path):
+    """A block's wave of the quantize kernels reads the first 128 bytes of the argument record only (what the waves that copy window
+    rows or clear counters need lies behind them, and is asked for behind the branch that tells the waves apart)."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    kernels = B.kernel_bodies(B.device_assembly("kvq_quantize.hip"), "quantize_blocks")
+    assert len(kernels) == 32
+    for name, body in kernels:
+        branch = re.search(r"s_cbranch_\w+ (\.LBB\d+_\d+)", body)
+        near, far = body.split("\n" + branch.group(1) + ":")              # the other waves' code is the branch's target
+        assert branch.start() < len(near) and len(far) < len(near)
+        loads = re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", near)
+        ends = [int(off, 16) + 4 * int(n[1:] or 1) for n, off in loads]
+        assert ends and max(ends) <= 128, (name, loads)

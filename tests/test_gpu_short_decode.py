@@ -145,3 +145,17 @@ def test_long_single_splits(kvq_mod, oracle_mod, batch, hq, hkv, T, kb, vb, pair
     q = W.query(w, 0)
     assert_outputs_close(g.decode_attention(0, q.cuda()), *o.decode_attention(0, q.numpy()), "K%dV%d" % (kb, vb))
     g.close()
+
+
+@pytest.mark.parametrize("batch,hkv,T,residual", [(15, 1, 32 * 9 + 40, 32), (8, 2, 32 * 9, 0), (17, 1, 32 * 9 + 1, 0), (11, 3, 32 * 5 + 60, 32)])
+def test_counters_of_every_cache_start_at_zero(kvq_mod, oracle_mod, batch, hkv, T, residual):
+    """Numbers of caches on either side of what one clearing wave takes, with and without window rows in the same launch, on a workspace
+    full of ones: every cache's splits are merged, in the first call and in the next."""
+    w = W.Workload("counters", 1, batch, 4 * hkv, hkv, 128, T, [4], [2], seed=50 + batch, outlier_channels=3)
+    g, o = _filled(kvq_mod, oracle_mod, w, residual, stale=0xff)
+    q = W.query(w, 0)
+    out = torch.full(q.shape, float("nan"), dtype=q.dtype, device="cuda:0")
+    g.decode_attention(0, q.cuda(), out)
+    assert_outputs_close(out, *o.decode_attention(0, q.numpy()), "first")
+    assert torch.equal(out, g.decode_attention(0, q.cuda()))
+    g.close()
