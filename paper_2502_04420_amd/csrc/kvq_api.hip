@@ -370,11 +370,13 @@ struct DecodeForm { int pairs; bool merges; };
 // Two pairs of waves per work-group (launch_decode_short) where the work-groups are few.  Such work-groups hold twice the waves and more
 // registers, so fewer are resident at once (kvq::paired_groups), and beyond that the second half of them waits for the first.  Measured: us a
 // call, one pair / two, or (below 2) the time with one pair over that with two; 32 / 8 heads unless said otherwise.
-// - Several splits, tiles of 4 heads: as long as all are resident.  K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups
+// - Several splits, tiles of 4 heads: as long as all are resident (K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups
 //   12.6 / 15.6; K8V8 256 groups 9.9 / 8.9, 544 groups 11.3 / 11.5, 1024 groups 13.7 / 17.4; K16V16 256 groups 12.2 / 10.8, 520 groups
-//   14.6 / 15.7.
-// - Several splits, tiles of 8 heads, whose records take longer to merge (28 / 4 heads): up to one work-group per compute unit 1.01..1.14;
-//   two, if the longest split has 4 units or more 1.03..1.08, with 2 or 3 0.94..1.01; more than two 0.93..1.00.
+//   14.6 / 15.7); but where no split has more than 2 units, nor the window 2 chunks to share, up to one work-group per compute unit
+//   (1.01..1.12; more 0.93..1.02).
+// - Several splits, tiles of 8 heads (28 / 4 heads), whose records take longer to merge: with a window of 2 chunks and more, which the pairs share,
+//   the same (1.02..1.37).  Else up to one work-group per compute unit (1.01..1.14); two, if the longest split has 4 units or more (1.03..1.08,
+//   with 2 or 3 units 0.94..1.01; more than two 0.93..1.00).
 // - A single split saves the merge launch.  Up to three work-groups per compute unit 1.03..1.6, at any length (60 to 4128 tokens) and width.
 //   Four of 4 heads: 1.03..1.25 for codes up to 8 bits per key + value element and with an fp16 tensor, 0.84..0.96 for 8-bit keys; of 8
 //   heads 0.69..1.01.  Beyond that:
@@ -392,8 +394,8 @@ DecodeForm decode_form(const SplitPlan &sp, int BH, int gq, int kbits, int vbits
     const bool four = gq <= 4, light = four && (kbits + vbits <= 8 || kbits == 16 || vbits == 16);
     bool paired;
     if (sp.splits > 1) {
-        const int longest = sp.units_per_split + (sp.split_rem > 0 ? 1 : 0);
-        paired = groups <= (four ? kvq::paired_groups(kbits + vbits) : longest >= 4 ? 2 : 1) * kCUs;
+        const int longest = sp.units_per_split + (sp.split_rem > 0 ? 1 : 0), resident = kvq::paired_groups(kbits + vbits);
+        paired = groups <= (chunks > 1 ? resident : longest < (four ? 3 : 4) ? 1 : four ? resident : 2) * kCUs;
     } else if (groups <= (light ? 4 : 3) * kCUs) {
         paired = true;
     } else if (n_blocks > 0) {

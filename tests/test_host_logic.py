@@ -323,7 +323,9 @@ def test_split_plan_of_short_caches(lib, batch, hq, hkv, residual, T, expected):
     (256, 32, 8, 8, 4, 128, 90, 0, (1, 0)), (256, 32, 8, 8, 4, 128, 120, 0, (2, 1)), (128, 32, 8, 8, 4, 128, 120, 0, (1, 0)), (512, 28, 4, 8, 4, 128, 120, 0, (2, 1)),
     # several splits: as long as all work-groups are resident
     (1, 32, 8, 4, 2, 32, 4133, 0, (2, 1)), (4, 32, 8, 4, 2, 32, 3090, 0, (1, 0)), (8, 32, 8, 8, 8, 32, 1056, 8, (2, 1)), (8, 32, 8, 8, 8, 32, 1056, 9, (1, 0)),
+    (18, 32, 8, 4, 2, 0, 32 * 2 + 7, 0, (1, 0)), (15, 32, 8, 4, 2, 0, 32 * 2 + 7, 0, (2, 1)), (18, 32, 8, 4, 2, 32, 32 * 2 + 40, 0, (2, 1)), (18, 32, 8, 4, 2, 0, 32 * 3 + 7, 0, (2, 1)),
     # tiles of 8 heads
+    (11, 28, 4, 4, 4, 32, 1655, 0, (2, 1)), (48, 28, 4, 4, 2, 32, 32 * 12 + 40, 0, (2, 1)), (26, 28, 4, 8, 4, 32, 32 * 16 + 40, 0, (1, 0)),
     (18, 28, 4, 4, 2, 32, 352, 0, (2, 1)), (26, 28, 4, 4, 2, 32, 320, 0, (1, 0)), (26, 28, 4, 4, 2, 32, 416, 0, (2, 1)), (38, 28, 4, 4, 2, 32, 416, 0, (1, 0)),
     (1, 28, 4, 4, 2, 32, 8592, 0, (2, 0)),
 ])
