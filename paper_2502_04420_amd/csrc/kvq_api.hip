@@ -385,8 +385,9 @@ struct DecodeForm { int pairs; bool merges; };
 //     from 16 blocks and six work-groups per compute unit on 1.01..1.10 (below 0.84..1.05);
 //   - of a window alone, two pairs of 4 heads share 2 chunks and more (1.02..1.17; 8-bit keys 0.93..0.98, from 4 chunks and six
 //     work-groups per compute unit on 1.02..1.15, so do 8 heads, 1.01..1.12); a single chunk is read faster by one pair (0.72..0.96).
-// The last work-group merges up to 64 splits of 4 heads (48 splits 9.6 behind a launch / 9.2) or 16 of 8 heads, whose records
-// it fetches in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
+// The last work-group merges up to 48 splits of 4 heads, 16 records at a time (two pairs with the merge in a launch of their own / in the kernel:
+// 1 x 6059 tokens, 48 splits 10.4 / 10.1, 6955 tokens, 55 splits 10.8 / 10.9; 6 x 2 kv heads, K4V2 48 splits 11.0 / 11.0, 51 splits 11.4 / 11.8,
+// 63 splits 11.2 / 12.0, where one pair takes 11.4) or 16 of 8 heads, in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
 DecodeForm decode_form(const SplitPlan &sp, int BH, int gq, int kbits, int vbits, int n_blocks, int n_res)
 {
     const int tiles = (gq + 7) / 8, chunks = (n_res + 31) / 32;

@@ -776,7 +776,8 @@ __device__ __forceinline__ void rescale_rows(float (&oF)[GQ][4], float (&shrink)
 
 // ------------------------------------------------------------------ merge of a work-group's pairs, and of the splits
 
-static_assert(kMergeSplits == 64, "two records' maxima and sums per lane");
+constexpr int kWeights = 64;             // of a head: two records' maxima and sums per lane of a half wave
+static_assert(kMergeSplits <= kWeights, "a weight per split");
 
 // the maximum / sum over the 32 lanes of a half wave, in every lane
 __device__ __forceinline__ float half_max32(float x) { x = row_max16(x); return fmaxf(x, __shfl_xor(x, 16, 64)); }
@@ -807,9 +808,9 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&
     constexpr int kAhead = GQ == 8 ? 16 : 8;                     // records on their way per thread
     float (*sums)[kD] = reinterpret_cast<float (*)[kD]>(&Ls[0].Ak[0][0]);                   // [subset * GQ + head][channel]
     static_assert(sizeof(PairLds<GQ>) * (PAIRS - 1) >= sizeof(float) * kD * kSubsets * GQ, "the sums fit the first pairs' memory");
-    static_assert(sizeof(PairLds<GQ>) >= sizeof(float) * kSubsets * GQ * kMergeSplits, "the weights fit the last pair's");
+    static_assert(sizeof(PairLds<GQ>) >= sizeof(float) * kSubsets * GQ * kWeights, "the weights fit the last pair's");
     const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, head = half % GQ, subset = half / GQ;
-    float *weights = reinterpret_cast<float *>(&Ls[PAIRS - 1].Ak[0][0]) + half * kMergeSplits;
+    float *weights = reinterpret_cast<float *>(&Ls[PAIRS - 1].Ak[0][0]) + half * kWeights;
     const RowStream po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + qrow0 * a.splits * kD, 0, nvalid * a.splits * (int)(kD * sizeof(float)), 0x00020000);
     const RowStream pm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + qrow0 * a.splits * 2, 0, nvalid * a.splits * (int)(2 * sizeof(float)), 0x00020000);
     const int first = (head < nvalid ? head : nvalid - 1) * a.splits;

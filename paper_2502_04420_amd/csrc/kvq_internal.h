@@ -152,7 +152,7 @@ hipError_t launch_decode_short(const ShortDecodeArgs &a, hipStream_t s, hipEvent
 int prefill_tile_pieces(const PrefillArgs &a, int tile);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
-constexpr int kMergeSplits = 64; // most splits that a work-group of launch_decode_short merges
+constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges: three rounds of reads (below)
 constexpr int kMaxTickets = 23;   // arrival counters (DecodeArgs::tickets) that a selection record has room for
 size_t prefill_ticket_offset();  // where in a selection record they are: bytes that the record itself leaves unused
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache

@@ -41,7 +41,7 @@ def test_many_work_groups(kvq_mod, oracle_mod, kb, vb, gq, options):
     (4, 2, 1, 32, 0), (4, 2, 63, 32, 0), (4, 2, 200, 500, 0),        # a single split: window of 1, 2 and 7 chunks
     (4, 2, 96, 0, 1), (4, 1, 32 * 7, 32, 1),                         # blocks only; both
     (4, 2, 32 * 2 + 5, 0, 0),                                        # a pair without units
-    (4, 2, 32 * 66 + 40, 32, 64), (4, 2, 32 * 66 + 40, 32, 65),      # most splits that the last work-group merges, one more
+    (4, 2, 32 * 66 + 40, 32, 48), (4, 2, 32 * 66 + 40, 32, 49),      # most splits that the last work-group merges, one more
     (8, 1, 32 * 40 + 40, 32, 16), (8, 1, 32 * 40 + 40, 32, 17),      # the same of a tile of 8 heads
     (7, 2, 32 * 40 + 40, 128, 9),                                    # five chunks of window beside blocks
     (12, 1, 32 * 20 + 3, 32, 0),                                     # two tiles of heads, the second with 4

@@ -324,6 +324,7 @@ def test_split_plan_of_short_caches(lib, batch, hq, hkv, residual, T, expected):
     # several splits: as long as all work-groups are resident
     (1, 32, 8, 4, 2, 32, 4133, 0, (2, 1)), (4, 32, 8, 4, 2, 32, 3090, 0, (1, 0)), (8, 32, 8, 8, 8, 32, 1056, 8, (2, 1)), (8, 32, 8, 8, 8, 32, 1056, 9, (1, 0)),
     (18, 32, 8, 4, 2, 0, 32 * 2 + 7, 0, (1, 0)), (15, 32, 8, 4, 2, 0, 32 * 2 + 7, 0, (2, 1)), (18, 32, 8, 4, 2, 32, 32 * 2 + 40, 0, (2, 1)), (18, 32, 8, 4, 2, 0, 32 * 3 + 7, 0, (2, 1)),
+    (1, 8, 2, 4, 2, 32, 32 * 188 + 43, 48, (2, 1)), (1, 8, 2, 4, 2, 32, 32 * 188 + 43, 49, (2, 0)),
     # tiles of 8 heads
     (11, 28, 4, 4, 4, 32, 1655, 0, (2, 1)), (48, 28, 4, 4, 2, 32, 32 * 12 + 40, 0, (2, 1)), (26, 28, 4, 8, 4, 32, 32 * 16 + 40, 0, (1, 0)),
     (18, 28, 4, 4, 2, 32, 352, 0, (2, 1)), (26, 28, 4, 4, 2, 32, 320, 0, (1, 0)), (26, 28, 4, 4, 2, 32, 416, 0, (2, 1)), (38, 28, 4, 4, 2, 32, 416, 0, (1, 0)),
