@@ -560,7 +560,6 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
     a.lv = view(c, layer);
     a.q = static_cast<const uint16_t *>(q_device);
     a.out = static_cast<uint16_t *>(out_device);
-    a.B = c->cfg.batch;
     a.Hq = c->cfg.n_q_heads;
     a.Hkv = c->cfg.n_kv_heads;
     a.n_blocks = np / kvq::kG;
@@ -573,9 +572,8 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
     a.select = nullptr;
     a.part_o = ws_part_o(c);
     a.part_ml = a.part_o + (size_t)c->plan.prefill_slots * kvq::kQueryTile * kvq::kD;
-    a.part_slots = c->plan.prefill_slots;
     const bool timed = c->ev_begin && c->ev_end;
-    const int BH = a.B * a.Hkv;
+    const int BH = c->cfg.batch * a.Hkv;
     const int chunk = prefill_pass_caches(c->plan, BH, a.n_blocks);
     // Keys quantized per channel: one kernel in front decides for every cache which channels keep the low parts of
     // their keys (one record per cache), unless the caller wants them kept for all.
@@ -595,7 +593,7 @@ int kvq_prefill_attention(kvq_ctx *c, int32_t layer, const void *q_device, int32
         a.n_bh = BH - bh0 < chunk ? BH - bh0 : chunk;
         a.select = select ? select + (size_t)bh0 * kvq::prefill_select_bytes() : nullptr;
         const bool first = bh0 == 0 && !begun, last = bh0 + chunk >= BH;
-        const hipError_t e = kvq::launch_prefill_attention(a, c->stream, timed && first ? c->ev_begin : nullptr,
+        const hipError_t e = kvq::launch_prefill_attention(a, c->plan.prefill_slots, c->stream, timed && first ? c->ev_begin : nullptr,
                                                            timed && last ? c->ev_end : nullptr);
         if (e != hipSuccess) return launch_failed("prefill attention kernels", e);
     }
@@ -693,9 +691,8 @@ int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_
     a.n_res = n_tokens - np;
     a.n_q = n_q;
     a.n_bh = bh0 >= BH ? 0 : BH - bh0 < chunk ? (int)(BH - bh0) : chunk;
-    a.part_slots = plan.prefill_slots;
     *caches = a.n_bh;
-    *pieces = a.n_bh > 0 ? kvq::prefill_tile_pieces(a, tile) : 0;
+    *pieces = a.n_bh > 0 ? kvq::prefill_tile_pieces(a, plan.prefill_slots, tile) : 0;
     return KVQ_OK;
 }
 

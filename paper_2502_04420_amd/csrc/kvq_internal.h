@@ -95,31 +95,26 @@ struct ShortDecodeArgs : DecodeArgs {
 
 struct PrefillArgs {
     LayerView lv;
-    const uint16_t *q;     // fp16 [B][Hq][n_q][128]: the last n_q positions
-    uint16_t *out;         // fp16 [B][Hq][n_q][128]
-    int B, Hq, Hkv;
+    const uint16_t *q;     // fp16 [batch][Hq][n_q][128]: the last n_q positions
+    uint16_t *out;         // fp16 [batch][Hq][n_q][128]
+    int Hq, Hkv;
     int n_blocks;          // quantized blocks (N_p / 32)
     int n_res;             // fp16 tokens at positions [32*n_blocks, 32*n_blocks + n_res)
     int NB, RC;
     int n_q;               // 1 <= n_q <= 32*n_blocks + n_res
     float scale_log2e;     // log2(e) / sqrt(D)
-    // one launch covers the (batch, kv head) caches [bh0, bh0 + n_bh); their packed units are dequantized into
-    // scratch[n_bh][n_blocks][prefill_unit_bytes()] first
-    uint8_t *scratch;
-    int bh0, n_bh;
+    int bh0, n_bh;         // one launch covers the (batch, kv head) caches [bh0, bh0 + n_bh)
+    uint8_t *scratch;      // [n_bh][n_blocks][prefill_unit_bytes()]: their packed units, dequantized first
     // one record of prefill_select_bytes() per cache of the launch (written and read by the launch's kernels): which 32
     // key channels keep the remainders of their fp16 rounding, or that all do
     uint8_t *select;
-    // partial results of the pieces that a launch of few query tiles is cut into: part_slots records of 256 queries, each 128
-    // un-normalised outputs (part_o) and a pair (reference, sum) (part_ml)
+    // partial results of the pieces that a launch of few query tiles is cut into: records of 256 rows, each 128 un-normalised
+    // outputs (part_o) and a pair (reference, sum) (part_ml)
     float *part_o, *part_ml;
-    int part_slots;
-    // set by launch_prefill_attention
-    int row_heads;         // query heads that share a work-group's rows: row r of them is query r / row_heads of head r % row_heads
-    int row_groups;        // of a cache's query heads
-    uint32_t row_magic;    // for divisions by row_heads
-    int order;             // in which the work-groups start
 };
+// What a work-group needs before it knows its work lies in the first three 64-byte lines of its argument record, which arrive together: every
+// further line is a read from memory of its own, 0.2 to 0.5 us of every launch.
+static_assert(sizeof(PrefillArgs) == 160, "leaves 32 bytes of the third line to what the launch adds");
 
 // Work units [u0, u1) of a split: units are the quantized blocks, then the chunks of <= 32 fp16 window tokens.  The
 // blocks and the window's weight (a few virtual units behind the blocks) are dealt out evenly: units_per_split each,
@@ -148,8 +143,8 @@ hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_
 // the same with two pairs of waves per work-group, for launches of few work-groups; a single split or a.tickets: no
 // launch_combine behind it
 hipError_t launch_decode_short(const ShortDecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
-// pieces that launch_prefill_attention(a) cuts query tile `tile` into (host only; 1: it stays whole)
-int prefill_tile_pieces(const PrefillArgs &a, int tile);
+// pieces that launch_prefill_attention(a, part_slots, ..) cuts query tile `tile` into (host only; 1: it stays whole)
+int prefill_tile_pieces(const PrefillArgs &a, int part_slots, int tile);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
 constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges: three rounds of reads (below)
@@ -160,9 +155,9 @@ size_t prefill_select_bytes();   // bytes of the channel-selection record of one
 // packed, per-channel quantized keys only); ev_begin (may be null) receives the kernel's start
 hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr);
 // dequantizes the packed units of the caches [bh0, bh0 + n_bh) into the scratch area (a.select: their selection
-// records, or null: every channel keeps its low part), then attends; ev_begin / ev_end
+// records, or null: every channel keeps its low part), then attends; part_slots: records that a.part_o has room for; ev_begin / ev_end
 // (either may be null) receive the start of the first and the end of the last kernel
-hipError_t launch_prefill_attention(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+hipError_t launch_prefill_attention(const PrefillArgs &a, int part_slots, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 hipError_t launch_combine(const DecodeArgs &a, hipStream_t s);
 
 }  // namespace kvq

@@ -615,10 +615,11 @@ constexpr int kSelectParts = 8;
 __device__ __forceinline__ void store_through(float *p, float v) { asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory"); }
 
 template <bool NARROW>
-__global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs a)
+__global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs a, int parts)
 {
-    const int tid = threadIdx.x, lane = tid & 63, local = blockIdx.y, bh = a.bh0 + local, parts = gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63, local = blockIdx.y, bh = a.bh0 + local;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: so are the addresses of a wave's rows
+    asm volatile("" ::"s"(a.lv.kmeta), "s"(a.n_blocks), "s"(a.n_res), "s"(parts));      // the argument record's lines are asked for at once
     __shared__ __attribute__((aligned(16))) float k1[kSelectWaves][kD], k2[kSelectWaves][kD], q2[kSelectWaves][kD], w[kD];
     __shared__ int above[8][kD];
     __shared__ float rest[2];
@@ -835,12 +836,20 @@ __device__ __forceinline__ void wait_fetches() { asm volatile("s_waitcnt vmcnt(0
 // find a compute unit for themselves by length, then the shortest of the others first (two per compute unit: long and short together).
 enum { kByCache, kByLength, kPaired };
 
-// r / row_heads, exactly: row_magic = ceil(2^32 / row_heads), and r * row_heads < 2^32 (plan_launch sees to it).  Divided by the compiler's
+// Which queries the rows of a work-group are: row r is query r / heads of head r % heads of a group of `heads` query heads.
+struct Rows {
+    int heads;                           // query heads that share a work-group's rows
+    int groups;                          // of a cache's query heads
+    uint32_t magic;                      // for divisions by heads
+    int order;                           // in which the work-groups start
+};
+
+// r / heads, exactly: magic = ceil(2^32 / heads), and r * heads < 2^32 (plan_launch sees to it).  Divided by the compiler's
 // sequence instead a window-only prompt of packed rows takes 0.5 us longer.
-__device__ __forceinline__ int row_query(const PrefillArgs &a, int r) { return a.row_heads == 1 ? r : (int)__umulhi((uint32_t)r, a.row_magic); }
+__device__ __forceinline__ int row_query(const Rows &rw, int r) { return rw.heads == 1 ? r : (int)__umulhi((uint32_t)r, rw.magic); }
 
 // ---- pass 2: the attention itself.  A work-group has 8 waves and 256 rows or 4 waves and 128 (see plan_launch), a row being a query of
-// one of row_heads query heads; every wave attends 32 rows and fetches its share of each unit from the scratch area into LDS.  KLO: the
+// one of Rows::heads query heads; every wave attends 32 rows and fetches its share of each unit from the scratch area into LDS.  KLO: the
 // keys are quantized (they come as two fp16 numbers).
 //
 // 8 waves, alone on their compute unit: five LDS buffers and two units per trip: while units u and u + 1 are being used, unit u + 2 is already there and units
@@ -863,14 +872,14 @@ struct Piece { int tile, row0, head, index, count, slot; };
 // pieces = 0: every tile is one piece.
 constexpr int kMaxCutTiles = 128;
 constexpr int kMaxPieces = 255;          // of a tile
-struct PieceTable {
+struct PieceTable : Rows {
     int pieces;                          // of a query head
     int partials;                        // those of tiles with more than one piece: their results go through memory
     uint32_t entry[kMaxCutTiles];
 };
 
 // in place of the table where no tile can be cut
-struct WholeTiles {};
+struct WholeTiles : Rows {};
 
 __device__ __forceinline__ int piece_partials(uint32_t entry)
 {
@@ -881,7 +890,7 @@ __device__ __forceinline__ int piece_partials(uint32_t entry)
 // LO: how the low parts of the keys come (score_unit); rec: the cache's selection record or null (never null with
 // kLoCompact); CUT: the tile may be cut (else pc.tile alone counts).
 template <int LO, bool CUT, int WAVES, bool PACKED>
-__device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, int local, const Piece &pc)
+__device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of, const Select *rec, int local, const Piece &pc)
 {
     constexpr bool KLO = LO != kLoNone;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -892,13 +901,17 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     const int head0 = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq + pc.head;  // b * Hq + first query head
     const int T = 32 * a.n_blocks + a.n_res;
     const int p0 = T - a.n_q;                                    // absolute position of query 0
-    const int hp = PACKED ? a.row_heads : 1, rows = a.n_q * hp;      // row r: query r / hp of head head0 + r % hp
-    auto query_of = [&](int r) { return PACKED ? row_query(a, r) : r; };
-    const int rlast = (pc.row0 + kQW * WAVES < rows ? pc.row0 + kQW * WAVES : rows) - 1;
+    const int hp = PACKED ? rows_of.heads : 1, rows = a.n_q * hp;      // row r: query r / hp of head head0 + r % hp
+    auto query_of = [&](int r) { return PACKED ? row_query(rows_of, r) : r; };
+    // (The code that the compiler makes of the 8-wave loop depends on how the numbers in front of it are formed.  These forms give that of the kernel without
+    // rows of several heads and 4-wave work-groups; with row0 and open_units as one expression for all: 16 x 8192 tokens 9.77 instead of 9.71 ms.)
+    const int row0 = WAVES == 8 ? pc.tile * kQB : pc.row0;
+    const int rlast = (row0 + kQW * WAVES < rows ? row0 + kQW * WAVES : rows) - 1;
     const int units = (p0 + query_of(rlast)) / 32 + 1;                // units the work-group walks through
-    const int rw = pc.row0 + kQW * wave;                         // first row of this wave
+    const int rw = row0 + kQW * wave;                            // first row of this wave
     const int wlast = rw < rows ? (p0 + query_of(rw + kQW - 1 < rows ? rw + kQW - 1 : rows - 1)) / 32 : -1;
-    const int open_units = rw < rows ? (p0 + query_of(rw) + 1) / 32 : 0;   // units [0, open_units) lie before the wave's first query: no mask needed
+    const int wmin = p0 + query_of(rw);
+    const int open_units = rw < rows ? (wmin + 1) / 32 : 0;   // units [0, open_units) lie before the wave's first query: no mask needed
     const float c = a.scale_log2e;
     const float inv_c = 1.0f / c;
 
@@ -987,10 +1000,12 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
     }
     if (nb > ub) {
         const uint8_t *mine = a.scratch + (size_t)local * a.n_blocks * sizeof(Tiles);
+        const int last = nb - 1;
+        auto unit_at = [&](int u) { return mine + (size_t)(u < last ? u : last) * sizeof(Tiles); };
         auto fetch = [&](int u, Tiles &to) {
             // 4 waves wait for every unit: none is fetched past the end.  8 waves, whose loop is a little slower with the condition (0.3 %), fetch
             // the last one again, into a buffer nobody reads.
-            if (WAVES == 4 ? u < nb : true) fetch_unit<LO, WAVES>(mine + (size_t)(u < nb ? u : nb - 1) * sizeof(Tiles), to, wave, lane);
+            if (WAVES == 8 || u < nb) fetch_unit<LO, WAVES>(unit_at(u), to, wave, lane);
         };
         fetch(ub, L[0]);
         fetch(ub + 1, L[1]);
@@ -1149,24 +1164,27 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Select *rec, 
 // costs a work-group about 0.14 us, which shows in short prompts (call of one layer with / without: 32 sequences of 22
 // tokens, 32 / 8 heads 15.6 / 15.1 us, of 33 tokens, 28 / 4 heads 21.0 / 20.4 us).  Long prompts of whole tiles keep the kernel
 // that knows the table: its loop is compiled a little better (4 x 8192 tokens 2436 us; without 2454).
-// PACKED: rows of several query heads (PrefillArgs::row_heads).
+// PACKED: rows of several query heads (Rows::heads).
 template <bool KQ, class PT, int WAVES, bool PACKED>
 __device__ __forceinline__ void attend_group(const PrefillArgs &a, const PT &pt)
 {
     constexpr bool CUT = std::is_same<PT, PieceTable>::value;
     constexpr int kRows = kQW * WAVES;
-    const int hp = PACKED ? a.row_heads : 1;                     // a cache's query heads are taken hp at a time
-    const int rows = a.n_q * hp, heads = PACKED ? a.row_groups : a.Hq / a.Hkv;
+    // The first three lines of the argument record are asked for at once, instead of one behind the other as they are needed (pieces of 27 queries
+    // over 2290 tokens, 28 / 4 heads: 24.0 -> 23.5 us).  (In the 4-wave kernels it moves registers about and costs 0.5..1 %.)
+    if constexpr (WAVES == 8) asm volatile("" ::"s"(a.lv.kres), "s"(a.Hq), "s"(a.n_bh), "s"(pt.pieces));
+    const int hp = PACKED ? pt.heads : 1;                        // a cache's query heads are taken hp at a time
+    const int rows = a.n_q * hp, heads = PACKED ? pt.groups : a.Hq / a.Hkv;
     const int tiles = CUT ? (rows + kQB - 1) / kQB : 0;
     const int parts = CUT && rows > kRows ? kQB / kRows : 1;     // work-groups of a piece
-    int groups = (rows + kRows - 1) / kRows;                     // work-groups per cache and `heads`
+    int groups = WAVES == 8 ? tiles : (rows + kRows - 1) / kRows;      // work-groups per cache and `heads`
     if constexpr (CUT) groups = pt.pieces ? pt.pieces * parts : groups;
     // Work-groups go to the 8 XCDs in turn by their index, and each XCD has an L2 of its own: all query heads and
     // query tiles that read one (batch, kv head) cache are given to one XCD (when the count divides), so that its
     // units are fetched from memory once and then served by that L2.  Otherwise the pieces of all heads start in the order
     // of their length, and as many neighbouring heads as possible share an XCD.
     int local, jh, rank;                                         // cache within this launch, heads within its group, order
-    const bool across = WAVES == 4 && !CUT && a.order != kByCache, paired = WAVES == 4 && !CUT && a.order == kPaired;
+    const bool across = WAVES == 4 && !CUT && pt.order != kByCache, paired = WAVES == 4 && !CUT && pt.order == kPaired;
     if (a.n_bh % 8 == 0) {
         const int xcd = blockIdx.x & 7, per = heads * groups;
         int k = blockIdx.x >> 3;
@@ -1191,7 +1209,7 @@ __device__ __forceinline__ void attend_group(const PrefillArgs &a, const PT &pt)
         local = head / heads;
         jh = head % heads;
     }
-    Piece pc = {kRows * (groups - 1 - rank) / kQB, kRows * (groups - 1 - rank), jh * hp, 0, 1, 0};      // the longest rows start first
+    Piece pc = {WAVES == 8 ? tiles - 1 - rank : kRows * (groups - 1 - rank) / kQB, kRows * (groups - 1 - rank), jh * hp, 0, 1, 0};      // the longest rows start first
     if constexpr (CUT) if (pt.pieces) {
         const int order = rank / parts;
         uint32_t w = pt.entry[0];
@@ -1209,10 +1227,10 @@ __device__ __forceinline__ void attend_group(const PrefillArgs &a, const PT &pt)
     }
     if constexpr (KQ) {
         const Select *rec = a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact, CUT, WAVES, PACKED>(a, rec, local, pc);
-        else attend<kLoAll, CUT, WAVES, PACKED>(a, rec, local, pc);
+        if (rec && __builtin_amdgcn_readfirstlane((int)rec->compact) != 0) attend<kLoCompact, CUT, WAVES, PACKED>(a, pt, rec, local, pc);
+        else attend<kLoAll, CUT, WAVES, PACKED>(a, pt, rec, local, pc);
     } else {
-        attend<kLoNone, CUT, WAVES, PACKED>(a, nullptr, local, pc);
+        attend<kLoNone, CUT, WAVES, PACKED>(a, pt, nullptr, local, pc);
     }
 }
 
@@ -1231,12 +1249,12 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
     const uint32_t w = pt.entry[blockIdx.y];
     const int tile = (int)(w & 255u), count = (int)((w >> 8) & 255u);
     const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 5), lane = threadIdx.x & 31;
-    const int r = tile * kQB + row, hp = a.row_heads, i = row_query(a, r);
+    const int r = tile * kQB + row, hp = pt.heads, i = row_query(pt, r);
     if (count < 2 || i >= a.n_q) return;
     int before = 0;
     for (int k = 0; k < (int)blockIdx.y; k++) before += piece_partials(pt.entry[k]);
     const int head = blockIdx.z;                                 // local * (heads of the group / row_heads) + which of them
-    const int gq = a.Hq / a.Hkv, heads = a.row_groups, local = head / heads, bh = a.bh0 + local;
+    const int gq = a.Hq / a.Hkv, heads = pt.groups, local = head / heads, bh = a.bh0 + local;
     const size_t row0 = ((size_t)head * pt.partials + before) * kQB + row;
     const float *po = a.part_o + row0 * kD + 4 * lane, *pm = a.part_ml + row0 * 2;
     float M = -INFINITY, Lsum = 0.0f;
@@ -1391,7 +1409,7 @@ PieceTable plan_pieces(const Tiling &g, int heads, int slots, long long &least)
 // How a launch is divided.
 struct LaunchPlan {
     PieceTable pt;
-    int waves, row_heads, order;
+    int waves;
 };
 
 // The two forms of the attention kernel: work-groups of 8 waves and 256 rows, one per compute unit, or of 4 waves and 128 rows,
@@ -1433,7 +1451,8 @@ long long whole_time(const PrefillArgs &a)
 
 long long rows_of(const PrefillArgs &a, int row_heads) { return (long long)a.n_q * row_heads; }
 
-LaunchPlan plan_launch(const PrefillArgs &a)
+// part_slots: partial results there is room for
+LaunchPlan plan_launch(const PrefillArgs &a, int part_slots)
 {
     LaunchPlan p;
     const int gq = a.Hq / a.Hkv, heads = a.n_bh * gq, tiles = (a.n_q + kQB - 1) / kQB;
@@ -1451,39 +1470,41 @@ LaunchPlan plan_launch(const PrefillArgs &a)
                 if (waves == 4 ? !four : tiles > 1 && four) continue;                 // (several tiles: the one or the other)
                 const Tiling tiling = {(a.n_q * hp + kQB - 1) / kQB, a.n_blocks, 32 * a.n_blocks + a.n_res - a.n_q, a.n_q, hp, waves};
                 long long time;
-                const PieceTable t = plan_pieces(tiling, heads / hp, a.part_slots / hp, time);   // (as many records as with every head by itself)
+                const PieceTable t = plan_pieces(tiling, heads / hp, part_slots / hp, time);   // (as many records as with every head by itself)
                 if (!t.pieces || (p.pt.pieces && time >= least)) continue;
                 least = time;
                 p.pt = t;
                 p.waves = waves;
-                p.row_heads = hp;
+                p.pt.heads = hp;
             }
         if (brief && work >= kCUs / 2 && p.pt.pieces && whole_time(a) < least) p.pt.pieces = p.pt.partials = 0;
     }
     if (p.pt.pieces) {
-        p.order = kByCache;
+        p.pt.order = kByCache;
     } else {
         p.waves = brief ? 4 : 8;
         // (Caches of a few units, where the heads by themselves leave no compute unit with two work-groups: those have fewer rows each. Two
         // sequences of 54 tokens, 32 / 8 heads, 4 layers: 96 us, 100 with the heads together; one of 300 tokens, 2 layers 65 / 67, of 500 84 / 82.)
         const bool few = a.n_blocks <= kFewUnits && (long long)heads * ((a.n_q + kQB / 2 - 1) / (kQB / 2)) <= kCUs;
-        p.row_heads = brief && !few && (long long)a.n_q * gq * gq < (1LL << 30) ? gq : 1;    // (row numbers: see row_query)
+        p.pt.heads = brief && !few && (long long)a.n_q * gq * gq < (1LL << 30) ? gq : 1;    // (row numbers: see row_query)
         for (int hp = 2; !brief && work >= 3 * kCUs && hp <= gq; hp++)
-            if (gq % hp == 0 && (long long)a.n_q * hp <= kQB) p.row_heads = hp;
+            if (gq % hp == 0 && (long long)a.n_q * hp <= kQB) p.pt.heads = hp;
         // The work-groups of an XCD cache by cache, or all by length while its caches fit its L2: the longest of the last cache
         // would start late (24 caches of 1114 tokens, per-token keys: 4 layers 506 us by cache).
-        const long long groups = a.n_bh * ((rows_of(a, p.row_heads) + kQB / 2 - 1) / (kQB / 2)) * (gq / p.row_heads);
-        p.order = !brief ? kByCache : groups <= 2 * kCUs ? kPaired : (long long)a.n_bh * a.n_blocks <= 8 * kShortCache ? kByLength : kByCache;
+        const long long groups = a.n_bh * ((rows_of(a, p.pt.heads) + kQB / 2 - 1) / (kQB / 2)) * (gq / p.pt.heads);
+        p.pt.order = !brief ? kByCache : groups <= 2 * kCUs ? kPaired : (long long)a.n_bh * a.n_blocks <= 8 * kShortCache ? kByLength : kByCache;
     }
+    p.pt.groups = gq / p.pt.heads;
+    p.pt.magic = (uint32_t)(((1ULL << 32) + p.pt.heads - 1) / p.pt.heads);      // (of one head: not used)
     return p;
 }
 
 }  // namespace
 
-int prefill_tile_pieces(const PrefillArgs &a, int tile)
+int prefill_tile_pieces(const PrefillArgs &a, int part_slots, int tile)
 {
-    const LaunchPlan p = plan_launch(a);
-    for (int r = 0; p.pt.pieces && r < (a.n_q * p.row_heads + kQB - 1) / kQB; r++)
+    const LaunchPlan p = plan_launch(a, part_slots);
+    for (int r = 0; p.pt.pieces && r < (a.n_q * p.pt.heads + kQB - 1) / kQB; r++)
         if ((int)(p.pt.entry[r] & 255u) == tile) return (int)((p.pt.entry[r] >> 8) & 255u);
     return 1;
 }
@@ -1506,25 +1527,20 @@ hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t
         while (parts < kSelectParts && 2 * parts * a.n_bh <= kCUs && a.n_blocks > 64 * parts) parts *= 2;
     const dim3 grid((unsigned)parts, (unsigned)a.n_bh), block(64 * kSelectWaves);
     auto launch = [&](auto kernel) {
-        if (ev_begin) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev_begin, nullptr, 0, a);
-        else hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
+        if (ev_begin) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev_begin, nullptr, 0, a, parts);
+        else hipLaunchKernelGGL(kernel, grid, block, 0, s, a, parts);
     };
     if (a.lv.narrow) launch(prefill_select<true>);
     else launch(prefill_select<false>);
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_attention(const PrefillArgs &a0, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
+hipError_t launch_prefill_attention(const PrefillArgs &a, int part_slots, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
-    const LaunchPlan plan = plan_launch(a0);
+    const LaunchPlan plan = plan_launch(a, part_slots);
     const PieceTable &pt = plan.pt;
-    PrefillArgs a = a0;
-    a.row_heads = plan.row_heads;
-    a.row_groups = a.Hq / a.Hkv / plan.row_heads;
-    a.row_magic = (uint32_t)(((1ULL << 32) + plan.row_heads - 1) / plan.row_heads);   // (of one head: not used)
-    a.order = plan.order;
-    const long long rows = (long long)a.n_q * a.row_heads;
-    const int heads = a.n_bh * a.row_groups, per = kQW * plan.waves;
+    const long long rows = (long long)a.n_q * pt.heads;
+    const int heads = a.n_bh * pt.groups, per = kQW * plan.waves;
     const int tiles = (int)((rows + kQB - 1) / kQB);
     const long long groups = heads * (pt.pieces ? (long long)pt.pieces * (rows > per ? kQB / per : 1) : (rows + per - 1) / per);
     if (groups < 1 || groups > 0x7fffffffLL || a.n_bh < 1 || a.n_bh > 65535) return hipErrorInvalidConfiguration;
@@ -1562,9 +1578,9 @@ hipError_t launch_prefill_attention(const PrefillArgs &a0, hipStream_t s, hipEve
     };
     hipError_t e;
     if (plan.waves == 4 && !pt.pieces)
-        e = kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{});
+        e = kq ? attend_launch(prefill_attention<true, WholeTiles>, WholeTiles{pt}) : attend_launch(prefill_attention<false, WholeTiles>, WholeTiles{pt});
     else if (plan.waves == 4) e = kq ? attend_launch(prefill_attention<true, PieceTable>, pt) : attend_launch(prefill_attention<false, PieceTable>, pt);
-    else if (plan.row_heads > 1) e = kq ? attend_launch(prefill_attend_long<true, true>, pt) : attend_launch(prefill_attend_long<false, true>, pt);
+    else if (pt.heads > 1) e = kq ? attend_launch(prefill_attend_long<true, true>, pt) : attend_launch(prefill_attend_long<false, true>, pt);
     else e = kq ? attend_launch(prefill_attend_long<true, false>, pt) : attend_launch(prefill_attend_long<false, false>, pt);
     if (e != hipSuccess || !pt.pieces) return e;
     // pass 3

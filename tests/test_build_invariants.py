@@ -210,3 +210,21 @@ def test_quantize_waves_read_two_lines_of_their_arguments(tmp_path):
         loads = re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", near)
         ends = [int(off, 16) + 4 * int(n[1:] or 1) for n, off in loads]
         assert ends and max(ends) <= 128, (name, loads)
+
+
+def test_prefill_launches_ask_for_their_arguments_at_once():
+    """The kernels of a prefill call share an argument record of two and a half 64-byte lines, without implicit arguments, and what a
+    launch adds to it begins on the third; the 8-wave attention kernels and the channel selection wait for them once, in front
+    of their first branch."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    asm = B.device_assembly("kvq_prefill_attn.hip")
+    assert _record_bytes(asm, "prefill_dequantize") == {160}
+    assert _record_bytes(asm, "prefill_select") == {164}
+    assert _record_bytes(asm, "prefill_attention") | _record_bytes(asm, "prefill_attend_long") | _record_bytes(asm, "prefill_merge") == {176, 160 + 24 + 4 * 128}
+    kernels = B.kernel_bodies(asm, "prefill_attend_long") + B.kernel_bodies(asm, "prefill_select")
+    assert len(kernels) == 6
+    for name, body in kernels:
+        assert body.split("s_cbranch", 1)[0].count("lgkmcnt(0)") == 1, name
