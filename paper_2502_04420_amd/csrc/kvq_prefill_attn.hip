@@ -602,15 +602,17 @@ __device__ __forceinline__ void output_rescale(const float (&alpha)[kQT], float4
 // (the case the per-channel grouping is made for, Section 3.2) qualify, and so do keys with a large offset on every
 // channel (the offsets are centred away); keys that are large and widely spread on many channels do not.
 constexpr float kSelectBudget = 300.0f;
-// One work-group per cache, or several (below).  Bound by the latency of its loads, so as many as fit are in flight: a wave takes a block's
-// metadata (a query's row) at a time, lane = two neighbouring channels, kSelectAhead of them outstanding.  Measured per
-// launch (8 caches): 2027 tokens 15.5 -> 8.6 us, 24576 tokens 40 -> 19 us, against four blocks in flight per thread and
-// serial loops over the 128 channels at the end.
+// One work-group per cache, or several (below).  Bound by the latency of its loads: a wave takes a block's metadata (a query's row) at a time,
+// lane = two neighbouring channels, 16 query rows and kSelectAhead blocks outstanding.  Four blocks per wave (64 per work-group) do: with 16,
+// whose code is twice as long and read from memory by every launch, and with the blocks asked for in front of the queries, a launch took 7.8 instead
+// of 7.2 us at 2027 tokens, 9.3 instead of 8.6 at 8275 (113 queries, which then waited for the blocks); a call of 4 layers of 2290 tokens
+// 181.7 -> 176.3 us, of 2027 350.8 -> 343.8.
 constexpr int kSelectWaves = 16;
-constexpr int kSelectAhead = 16;
+constexpr int kSelectAhead = 4;
 // Long caches: up to kSelectParts work-groups share a cache's blocks; each leaves its sums in the scratch area (prefill_dequantize
 // comes later), written through to memory, and counts itself; the last one adds them up, in their order, and does the rest.
 constexpr int kSelectParts = 8;
+constexpr int kSelectWhole = 256;        // units of a cache that one work-group takes
 
 __device__ __forceinline__ void store_through(float *p, float v) { asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory"); }
 
@@ -628,26 +630,11 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
     const int head0 = (bh / a.Hkv) * a.Hq + (bh % a.Hkv) * gq;
     const int per_head = (a.n_q + stride - 1) / stride, samples = gq * per_head;
     float sq[2] = {0.0f, 0.0f}, sk[2] = {0.0f, 0.0f}, sm[2] = {0.0f, 0.0f};
-    // the metadata of kSelectAhead blocks of this wave; the first ones go out in front of the queries, so that both share a round trip
-    const int across = kSelectWaves * parts, first = blockIdx.x * kSelectWaves + wave;      // waves of the cache, this one's number
-    u32x2 sc[kSelectAhead];                                      // (fp16 scales: one word, the other one is not used)
-    uint32_t zp[kSelectAhead];
-    auto fetch = [&](int u0) {
-#pragma unroll
-        for (int k = 0; k < kSelectAhead; k++) {
-            const int u = u0 + across * k < a.n_blocks ? u0 + across * k : u0;
-            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
-            if constexpr (NARROW) sc[k][0] = *reinterpret_cast<const uint32_t *>(meta_scales16(meta) + 2 * lane);
-            else sc[k] = *reinterpret_cast<const u32x2 *>(meta + 2 * lane);
-            zp[k] = *reinterpret_cast<const uint32_t *>(meta_zeros(meta, NARROW) + 2 * lane);
-        }
-    };
-    if (first < a.n_blocks) fetch(first);
-    // at most 64 samples per head, four per wave: four heads at a time fill kSelectAhead loads (numbering the samples of all heads
-    // through instead costs a division per load: 10.6 instead of 8.6 us a launch)
-    static_assert(4 * kSelectWaves == 64 && kSelectAhead == 16, "four samples of four heads per wave");
-    for (int j0 = 0; j0 < gq && blockIdx.x == 0; j0 += 4) {      // (the first part takes the queries)
-        uint32_t x[4][4];
+    // Queries of four heads, four samples of each per wave: at most 64 samples per head (numbering the samples of all heads through instead
+    // costs a division per load: 10.6 instead of 8.6 us a launch).
+    static_assert(4 * kSelectWaves == 64, "four samples of a head per wave");
+    uint32_t x[4][4];
+    auto ask = [&](int j0) {
 #pragma unroll
         for (int j = 0; j < 4; j++)
 #pragma unroll
@@ -655,6 +642,8 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
                 const int jc = j0 + j < gq ? j0 + j : gq - 1, i = wave + kSelectWaves * k < per_head ? wave + kSelectWaves * k : 0;
                 x[j][k] = *reinterpret_cast<const uint32_t *>(a.q + ((size_t)(head0 + jc) * a.n_q + (size_t)i * stride) * kD + 2 * lane);
             }
+    };
+    auto take = [&](int j0) {
 #pragma unroll
         for (int j = 0; j < 4; j++)
 #pragma unroll
@@ -664,6 +653,30 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
                     sq[0] = fmaf(v0, v0, sq[0]);
                     sq[1] = fmaf(v1, v1, sq[1]);
                 }
+    };
+    const int across = kSelectWaves * parts, first = blockIdx.x * kSelectWaves + wave;      // waves of the cache, this one's number
+    u32x2 sc[kSelectAhead];                                      // (fp16 scales: one word, the other one is not used)
+    uint32_t zp[kSelectAhead];
+    auto fetch = [&](int u0) {                                   // (past the end: block 0)
+#pragma unroll
+        for (int k = 0; k < kSelectAhead; k++) {
+            const int u = u0 + across * k < a.n_blocks ? u0 + across * k : 0;
+            const float *meta = a.lv.kmeta + ((size_t)bh * a.NB + u) * meta_words(NARROW);
+            if constexpr (NARROW) sc[k][0] = *reinterpret_cast<const uint32_t *>(meta_scales16(meta) + 2 * lane);
+            else sc[k] = *reinterpret_cast<const u32x2 *>(meta + 2 * lane);
+            zp[k] = *reinterpret_cast<const uint32_t *>(meta_zeros(meta, NARROW) + 2 * lane);
+        }
+    };
+    // The first part takes the queries.  Their loads go out first and those of the first blocks right behind, so that both share a round trip
+    // and the queries are waited for without the blocks.
+    if (blockIdx.x == 0) ask(0);
+    fetch(first);
+    if (blockIdx.x == 0) {
+        take(0);
+        for (int j0 = 4; j0 < gq; j0 += 4) {
+            ask(j0);
+            take(j0);
+        }
     }
     for (int u0 = first; u0 < a.n_blocks; u0 += kSelectAhead * across) {
         if (u0 != first) fetch(u0);
@@ -1520,11 +1533,11 @@ size_t prefill_ticket_offset() { return offsetof(Select, tickets); }
 hipError_t launch_prefill_select(const PrefillArgs &a, hipStream_t s, hipEvent_t ev_begin)
 {
     if (!a.select || a.lv.kbits >= 16 || a.lv.kpt || a.n_blocks < 1 || a.n_bh < 1) return hipErrorInvalidValue;
-    // A second round of loads (more than kSelectAhead blocks per wave) costs more than the parts' way through memory.  us a call of one layer, 8
+    // Several rounds of loads cost more than the parts' way through memory.  us a call of one layer, 8
     // caches, 1 / 2 / 4 / 8 work-groups each: 249 units 51 / 52 / 53 / 52, 499 units 82 / 79 / 78 / 78, 936 units 134 / 127 / 123 / 122.
     int parts = 1;
-    if (a.n_blocks > kSelectAhead * kSelectWaves)
-        while (parts < kSelectParts && 2 * parts * a.n_bh <= kCUs && a.n_blocks > 64 * parts) parts *= 2;
+    if (a.n_blocks > kSelectWhole)
+        while (parts < kSelectParts && 2 * parts * a.n_bh <= kCUs) parts *= 2;
     const dim3 grid((unsigned)parts, (unsigned)a.n_bh), block(64 * kSelectWaves);
     auto launch = [&](auto kernel) {
         if (ev_begin) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev_begin, nullptr, 0, a, parts);

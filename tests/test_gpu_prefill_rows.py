@@ -80,3 +80,20 @@ def test_long_caches_against_decode_steps(kvq_mod, T, n_q, batch, hq, hkv):
         ref = g.decode_attention(0, q[:, :, n_q - 1 - back].contiguous()).double().cpu().numpy()
         assert np.linalg.norm(out[:, :, n_q - 1 - back] - ref) <= 1.5e-3 * np.linalg.norm(ref), back
     g.close()
+
+
+@pytest.mark.parametrize("batch,hq,hkv,units,n_q,meta16", [
+    (5, 5, 1, 257, 3, False), (3, 4, 2, 300, 3, True),              # 8 work-groups per cache; heads in two rounds
+    (33, 2, 1, 290, 2, False), (33, 1, 1, 257, 1, True),            # 4
+    (65, 1, 1, 258, 2, True),                                       # 2
+    (129, 1, 1, 257, 1, False),                                     # 1: more than one round of loads
+    (2, 12, 2, 256, 70, False), (2, 4, 2, 65, 5, True), (1, 4, 2, 64, 64, False), (1, 3, 1, 3, 4, True),   # 1: whole rounds, one unit more, few units
+])
+def test_selection_by_several_work_groups(kvq_mod, oracle_mod, batch, hq, hkv, units, n_q, meta16):
+    """Channel selection of caches on either side of the line to several work-groups per cache: keys with large channels and an
+    offset on every channel, which only come out right if every unit counts once in the centres."""
+    w = W.Workload("parts", 1, batch, hq, hkv, 128, 32 * units + 33, [4], [4], seed=1400 + batch + units, outlier_channels=4, outlier_scale=12.0, key_bias_std=6.0)
+    out, o64, g, o, q = _run(kvq_mod, oracle_mod, w, n_q, meta=kvq_mod.META_FP16 if meta16 else None)
+    assert_prefill_close(out, o64, "%d caches of %d units" % (batch * hkv, units))
+    assert torch.equal(out, g.prefill_attention(0, q.cuda()))
+    g.close()
