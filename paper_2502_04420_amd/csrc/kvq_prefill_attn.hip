@@ -1342,11 +1342,15 @@ int unit_cost(int waves, int rows, bool alone)
     return !alone ? 100 : rows <= 64 ? 55 : 75;
 }
 
-// Fills t for pieces of at most `length` units; returns the time by the rule above for `heads` query heads, in percent of a unit.
-// (A single tile that is not full: unit_cost, and that much less of partial results.)
+// Behind a cut: the launch that merges and the partial results of `partials` pieces of up to `rows` rows.
+long long merge_time(int partials, int heads, int rows)
+{
+    return partials ? 100 * kMergeCost + 100LL * partials * heads * rows / (kQB * kPartialsPerUnit) : 0;
+}
+
+// Fills t for pieces of at most `length` units of several tiles; returns the time by the rule above for `heads` query heads, in percent of a unit.
 long long cut(const Tiling &g, int heads, int length, PieceTable &t)
 {
-    const int rows = g.tiles > 1 ? kQB : g.n_q * g.hp, places = g.waves == 4 && rows <= kQB / 2 ? 2 * kCUs : kCUs;
     // tiles by falling length of their pieces
     int len[kMaxCutTiles], num[kMaxCutTiles], id[kMaxCutTiles];
     for (int i = 0; i < g.tiles; i++) {
@@ -1364,18 +1368,16 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
     }
     t.pieces = pieces;
     t.partials = partials;
-    const bool alone = (long long)pieces * heads * (rows <= kQB / 2 ? 1 : 2) <= kCUs;
-    const int unit = g.tiles > 1 ? 100 : unit_cost(g.waves, rows, alone);
     // compute units grouped by when they are free, soonest first; equal pieces go to whole groups at a time
     struct { long long free; int count; } cu[kMaxCutTiles + 2];
     int groups = 1;
-    cu[0] = {0, places};
+    cu[0] = {0, kCUs};
     for (int r = 0; r < g.tiles; r++) {
         long long left = (long long)num[r] * heads;
-        const int cost = len[r] * unit + 100 * kPieceCost;
-        const long long rounds = left / places;                  // whole rounds over all compute units
+        const int cost = 100 * (len[r] + kPieceCost);
+        const long long rounds = left / kCUs;                    // whole rounds over all compute units
         for (int i = 0; i < groups; i++) cu[i].free += rounds * cost;
-        left -= rounds * places;
+        left -= rounds * kCUs;
         while (left > 0) {
             const int take = left < cu[0].count ? (int)left : cu[0].count;
             const long long until = cu[0].free + cost;
@@ -1393,7 +1395,17 @@ long long cut(const Tiling &g, int heads, int length, PieceTable &t)
             }
         }
     }
-    return cu[groups - 1].free + (partials ? 100 * kMergeCost + 100LL * partials * heads * rows / (kQB * kPartialsPerUnit) : 0);
+    return cu[groups - 1].free + merge_time(partials, heads, kQB);
+}
+
+// Time of a single tile of `units` units in `count` pieces, which may have fewer rows than a work-group has room for (unit_cost, and that
+// much less of partial results): its pieces are all alike, so the compute units take them in rounds.
+long long single_tile_time(const Tiling &g, int heads, int units, int count)
+{
+    const int rows = g.n_q * g.hp, places = g.waves == 4 && rows <= kQB / 2 ? 2 * kCUs : kCUs, each = (units + count - 1) / count;
+    const unsigned pieces = (unsigned)(count * heads);           // (fewer than 255 * 3 * kCUs)
+    const int unit = unit_cost(g.waves, rows, pieces * (rows <= kQB / 2 ? 1 : 2) <= (unsigned)kCUs);
+    return (long long)((pieces + places - 1) / places) * (each * unit + 100 * kPieceCost) + merge_time(count > 1 ? count : 0, heads, rows);
 }
 
 // slots: partial results the scratch area has room for; least: the time by the rule above (0: not a case for pieces)
@@ -1405,6 +1417,27 @@ PieceTable plan_pieces(const Tiling &g, int heads, int slots, long long &least)
     // (with three work-groups and more for every compute unit the longest tiles start early enough)
     if (g.tiles > kMaxCutTiles || g.n_blocks < kLeastCut || (long long)heads * g.tiles >= 3 * kCUs || slots < 2) return best;
     const int longest = tile_units(g, g.tiles - 1);
+    // (so few tiles that 16 pieces of each do not fill the chip: up to 64)
+    const int most = (long long)heads * g.tiles * 16 < 2 * kCUs ? 64 : 16;
+    if (g.tiles == 1) {
+        // Several such searches decide about a launch of a few tens of us (plan_launch), so each count of pieces is looked at once, up
+        // to the most there is room for, and by a formula: 120 heads on one cache 29 us a plan with `cut` for every length, 0.8 now.
+        int chosen = 1;
+        least = single_tile_time(g, heads, longest, 1);
+        for (int parts = 2, before = 1; parts <= most && longest / parts >= kMinPiece; parts++) {
+            const int count = tile_pieces(longest, (longest + parts - 1) / parts);
+            if (count == before) continue;
+            before = count;
+            if (count * heads > slots) break;
+            const long long time = single_tile_time(g, heads, longest, count);
+            if (time < least) { least = time; chosen = count; }
+        }
+        if (chosen > 1) {
+            best.entry[0] = (uint32_t)(chosen << 8);
+            best.pieces = best.partials = chosen;
+        }
+        return best;
+    }
     PieceTable t;
     least = cut(g, heads, longest, t);
     auto consider = [&](int length) {
@@ -1413,8 +1446,6 @@ PieceTable plan_pieces(const Tiling &g, int heads, int slots, long long &least)
         if ((long long)t.partials * heads <= slots && time < least) { least = time; best = t; }
     };
     for (int k = 1; k <= 4 && k < g.tiles; k++) consider(tile_units(g, g.tiles - 1 - k));
-    // (so few tiles that 16 pieces of each do not fill the chip: up to 64)
-    const int most = (long long)heads * g.tiles * 16 < 2 * kCUs ? 64 : 16;
     for (int parts = 2; parts <= most && longest / parts >= kMinPiece; parts++) consider((longest + parts - 1) / parts);
     return best;
 }

@@ -3,6 +3,7 @@ argument validation returns the documented codes without touching a GPU, and the
 import ctypes
 import os
 import re
+import time
 
 import pytest
 
@@ -179,6 +180,28 @@ def test_prefill_plan_covers_every_tile_within_the_slots(lib, batch, hq, hkv, re
         assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), need, *bad, ctypes.byref(c), ctypes.byref(n)) == -1, bad
     assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), need, T, 5, 0, 0, None, ctypes.byref(n)) == -1
     assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), least - 1, T, 5, 0, 0, ctypes.byref(c), ctypes.byref(n)) == -4
+
+
+def test_prefill_plan_is_quick_next_to_the_launch_it_divides(lib):
+    """Few queries over a long cache: calls of some tens of us, in a loop over the layers, whose plan compares many numbers of pieces
+    for every number of heads that share a work-group.  Each plan may take 10 us here (1 to 3 measured; the search took 21 to 38)."""
+    i32 = ctypes.c_int32
+    c, n = i32(), i32()
+    for hq, T, n_q, pieces in ((24, 32000, 8, 21), (120, 32000, 8, 4), (120, 32000, 2, 4)):
+        cfg, keep = _cfg(n_layers=1, batch=1, n_q_heads=hq, n_kv_heads=1, max_tokens=T, kbits=[4], vbits=[2])
+        need = lib.kvq_workspace_bytes(ctypes.byref(cfg))
+
+        def least(tokens, queries):
+            best = 1.0
+            for _ in range(300):
+                t = time.perf_counter()
+                lib.kvq_debug_prefill_plan(ctypes.byref(cfg), need, tokens, queries, 0, 0, ctypes.byref(c), ctypes.byref(n))
+                best = min(best, time.perf_counter() - t)
+            return best * 1e6
+
+        call = least(5, 1)                      # (nothing to divide)
+        assert least(T, n_q) - call < 10.0, (hq, n_q)
+        assert n.value == pieces
 
 
 def test_library_load_brings_torch_first():
