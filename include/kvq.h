@@ -20,7 +20,11 @@
  *     workspace; the library only keeps a small host-side context.
  *   - All GPU work is enqueued on the HIP stream given to kvq_configure (a hipStream_t
  *     passed as void*, NULL = the default stream).  No call synchronises the device.
- *   - Calls on one context are not thread-safe; serialise them.
+ *   - Calls on one context are not thread-safe; serialise them.  Their GPU work must not overlap either: it shares the workspace, and
+ *     decode and prefill attention count arrivals in words of it that every call finds at zero and leaves at zero.  Replays of
+ *     captured graphs count as calls: keep them on one stream or order them with events.  Work that was cut short or overlapped can
+ *     leave such a word off zero, and later calls then merge too early or not at all; the append that quantizes
+ *     a layer's first group clears them all (kvq_reset of a layer and append again).
  *   - fp16 means IEEE binary16.  All sequences of the batch have the same length.
  *   - Functions returning int return KVQ_OK (0) or a negative kvq_status.  Argument, state and
  *     capacity errors are found before anything is enqueued.  KVQ_ELAUNCH means the HIP runtime
@@ -147,7 +151,7 @@ int kvq_decode_attention(kvq_ctx *ctx, int32_t layer, const void *q_device, void
  * per call: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, same kernels, same result as kvq_decode_attention (bit for bit:
  * the token-range splits are planned the same way).  The difference is where the splits'
- * partial results live: not in the caller's workspace but in an array built into the library's
+ * partial results live (the arrival counters stay in the workspace): not in the caller's workspace but in an array built into the library's
  * device image, 16384 records of (128 outputs, maximum, sum) = 8.1 MiB, which every GPU the
  * library runs on holds from its first use until the process ends.  The call allocates and frees
  * nothing on host or device; on its first use on a GPU (with that GPU current) it looks up the
@@ -158,9 +162,10 @@ int kvq_decode_attention(kvq_ctx *ctx, int32_t layer, const void *q_device, void
  *   n_kv_heads)), so a shape fits at every length if batch * n_q_heads times that is no more than 16384: with up to 292
  *   caches always for at most 7 query heads per kv head, for 8 where batch * n_kv_heads divides 2048.  Splits forced
  *   through kvq_set_decode_options may not fit.
- *   All contexts and streams on one GPU share that GPU's array.  Nothing in it has to start at
+ *   All contexts and streams on one GPU share that GPU's array.  Nothing in the array has to start at
  *   zero (each call writes every record it later reads), but two such calls that overlap in time
- *   on one GPU race on it: keep them on one stream or order them yourself.
+ *   on one GPU race on it: keep them on one stream or order them yourself.  (Of one context no two calls may overlap, see
+ *   Conventions.)
  */
 int kvq_decode_attention_noalloc(kvq_ctx *ctx, int32_t layer, const void *q_device, void *out_device);
 
