@@ -271,6 +271,15 @@ int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_
                            int32_t *caches, int32_t *pieces);
 
 /*
+ * The form in which pass `pass` of such a prefill-attention call would be launched (host only, no GPU work; arguments and errors
+ * as above): work-groups of *waves waves (8, which take 256 rows, or 4, which take 128), a row being a query of one of *row_heads
+ * query heads, and *order in which whole tiles start: 0 cache by cache, the longest of each first (pieces always), 1 all of an
+ * XCD by length, 2 the longest together with the shortest.  All 0 when there is no such pass.
+ */
+int kvq_debug_prefill_form(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t *waves,
+                           int32_t *row_heads, int32_t *order);
+
+/*
  * Tuning knobs (optional).  variant: 0 = choose automatically, 1 = vector-ALU kernel,
  * 2 = matrix-core kernel.  splits: 0 = automatic, else the number of token-range splits
  * per (batch, kv head) used to fill the GPU (at most 128).  Returns KVQ_EINVAL for unknown

@@ -15,7 +15,7 @@ _LIB_PATH = os.path.join(_HERE, "libkvq.so")
 _lib = None
 
 EXPORTED = [
-    "kvq_workspace_bytes", "kvq_configure", "kvq_quantize_append", "kvq_decode_attention", "kvq_decode_attention_noalloc", "kvq_debug_split_plan", "kvq_debug_decode_form", "kvq_debug_prefill_plan", "kvq_append_decode_attention", "kvq_prefill_attention",
+    "kvq_workspace_bytes", "kvq_configure", "kvq_quantize_append", "kvq_decode_attention", "kvq_decode_attention_noalloc", "kvq_debug_split_plan", "kvq_debug_decode_form", "kvq_debug_prefill_plan", "kvq_debug_prefill_form", "kvq_append_decode_attention", "kvq_prefill_attention",
     "kvq_layer_tokens", "kvq_reset", "kvq_debug_export", "kvq_set_decode_options", "kvq_set_prefill_options", "kvq_set_kernel_events", "kvq_destroy", "kvq_strerror",
     "kvq_last_error",
 ]
@@ -74,6 +74,8 @@ def load_library():
     lib.kvq_debug_decode_form.argtypes = [POINTER(_Config)] + [c_int32] * 3 + [POINTER(c_int32)] * 2
     lib.kvq_debug_prefill_plan.restype = c_int32
     lib.kvq_debug_prefill_plan.argtypes = [POINTER(_Config), c_size_t] + [c_int32] * 4 + [POINTER(c_int32)] * 2
+    lib.kvq_debug_prefill_form.restype = c_int32
+    lib.kvq_debug_prefill_form.argtypes = [POINTER(_Config), c_size_t] + [c_int32] * 3 + [POINTER(c_int32)] * 3
     lib.kvq_set_decode_options.restype = c_int32
     lib.kvq_set_decode_options.argtypes = [c_void_p, c_int32, c_int32]
     lib.kvq_set_prefill_options.restype = c_int32

@@ -673,26 +673,55 @@ int kvq_debug_decode_form(const kvq_config *cfg, int32_t layer, int32_t n_tokens
     return KVQ_OK;
 }
 
-int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t tile,
-                           int32_t *caches, int32_t *pieces)
+namespace {
+
+// Pass `pass` of a prefill-attention call, as kvq_debug_prefill_plan and _form look at it (a.n_bh = 0: there is no such pass).
+int debug_prefill_pass(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, kvq::PrefillArgs &a, int &slots)
 {
-    if (!config_ok(cfg) || n_tokens < 1 || n_tokens > cfg->max_tokens || n_q < 1 || n_q > n_tokens || pass < 0 || tile < 0 || tile > (n_q - 1) / kvq::kQueryTile ||
-        !caches || !pieces)
-        return KVQ_EINVAL;
+    if (!config_ok(cfg) || n_tokens < 1 || n_tokens > cfg->max_tokens || n_q < 1 || n_q > n_tokens || pass < 0) return KVQ_EINVAL;
     const Plan plan = make_plan(cfg, workspace_bytes);
     if (workspace_bytes < plan.total) return KVQ_EWORKSPACE;
     const int over = n_tokens - cfg->residual, np = over > 0 ? kvq::kG * (over / kvq::kG) : 0, BH = cfg->batch * cfg->n_kv_heads;
     const int chunk = prefill_pass_caches(plan, BH, np / kvq::kG);
     const long long bh0 = (long long)pass * chunk;
-    kvq::PrefillArgs a = {};
+    a = {};
     a.Hq = cfg->n_q_heads;
     a.Hkv = cfg->n_kv_heads;
     a.n_blocks = np / kvq::kG;
     a.n_res = n_tokens - np;
     a.n_q = n_q;
     a.n_bh = bh0 >= BH ? 0 : BH - bh0 < chunk ? (int)(BH - bh0) : chunk;
+    slots = plan.prefill_slots;
+    return KVQ_OK;
+}
+
+}  // namespace
+
+int kvq_debug_prefill_plan(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t tile,
+                           int32_t *caches, int32_t *pieces)
+{
+    if (tile < 0 || tile > (n_q - 1) / kvq::kQueryTile || !caches || !pieces) return KVQ_EINVAL;
+    kvq::PrefillArgs a;
+    int slots;
+    const int rc = debug_prefill_pass(cfg, workspace_bytes, n_tokens, n_q, pass, a, slots);
+    if (rc != KVQ_OK) return rc;
     *caches = a.n_bh;
-    *pieces = a.n_bh > 0 ? kvq::prefill_tile_pieces(a, plan.prefill_slots, tile) : 0;
+    *pieces = a.n_bh > 0 ? kvq::prefill_tile_pieces(a, slots, tile) : 0;
+    return KVQ_OK;
+}
+
+int kvq_debug_prefill_form(const kvq_config *cfg, size_t workspace_bytes, int32_t n_tokens, int32_t n_q, int32_t pass, int32_t *waves,
+                           int32_t *row_heads, int32_t *order)
+{
+    if (!waves || !row_heads || !order) return KVQ_EINVAL;
+    kvq::PrefillArgs a;
+    int slots;
+    const int rc = debug_prefill_pass(cfg, workspace_bytes, n_tokens, n_q, pass, a, slots);
+    if (rc != KVQ_OK) return rc;
+    const kvq::PrefillForm f = a.n_bh > 0 ? kvq::prefill_form(a, slots) : kvq::PrefillForm{0, 0, 0};
+    *waves = f.waves;
+    *row_heads = f.row_heads;
+    *order = f.order;
     return KVQ_OK;
 }
 

@@ -145,6 +145,9 @@ hipError_t launch_decode_mfma(const DecodeArgs &a, hipStream_t s, hipEvent_t ev_
 hipError_t launch_decode_short(const ShortDecodeArgs &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 // pieces that launch_prefill_attention(a, part_slots, ..) cuts query tile `tile` into (host only; 1: it stays whole)
 int prefill_tile_pieces(const PrefillArgs &a, int part_slots, int tile);
+// the form of launch_prefill_attention(a, part_slots, ..) (host only): waves per work-group, query heads per row group, order of whole tiles (kByCache ..)
+struct PrefillForm { int waves, row_heads, order; };
+PrefillForm prefill_form(const PrefillArgs &a, int part_slots);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
 constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges: three rounds of reads (below)

@@ -1553,6 +1553,12 @@ int prefill_tile_pieces(const PrefillArgs &a, int part_slots, int tile)
     return 1;
 }
 
+PrefillForm prefill_form(const PrefillArgs &a, int part_slots)
+{
+    const LaunchPlan p = plan_launch(a, part_slots);
+    return {p.waves, p.pt.heads, p.pt.order};
+}
+
 size_t prefill_piece_bytes() { return kQB * (kD + 2) * sizeof(float); }
 
 size_t prefill_unit_bytes() { return sizeof(Tiles); }

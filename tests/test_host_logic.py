@@ -182,6 +182,35 @@ def test_prefill_plan_covers_every_tile_within_the_slots(lib, batch, hq, hkv, re
     assert lib.kvq_debug_prefill_plan(ctypes.byref(cfg), least - 1, T, 5, 0, 0, ctypes.byref(c), ctypes.byref(n)) == -4
 
 
+@pytest.mark.parametrize("batch,hq,hkv,residual", [(1, 1, 1, 32), (1, 32, 8, 0), (2, 8, 4, 32), (3, 28, 4, 500), (17, 6, 1, 32), (40, 24, 1, 32)])
+def test_prefill_form_goes_with_the_plan(lib, batch, hq, hkv, residual):
+    """kvq_debug_prefill_form next to kvq_debug_prefill_plan: a known kernel form for every pass, heads that divide the group, and
+    several heads in a launch of pieces or of 8 waves only where their rows fit one tile."""
+    i32 = ctypes.c_int32
+    w, h, o = i32(), i32(), i32()
+    seen = set()
+    for T in (1, 33, 300, 800, 2027, 6000, 6500, 12000, 33000):
+        for room in (T, 4 * T):
+            cfg, keep = _cfg(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=room, kbits=[4], vbits=[2], residual=residual)
+            need = lib.kvq_workspace_bytes(ctypes.byref(cfg))
+            for n_q in {1, min(T, 9), min(T, 130), min(T, 400), T}:
+                passes = _prefill_passes(lib, cfg, need, T, n_q)
+                for i, (caches, row) in enumerate(passes):
+                    assert lib.kvq_debug_prefill_form(ctypes.byref(cfg), need, T, n_q, i, ctypes.byref(w), ctypes.byref(h), ctypes.byref(o)) == 0
+                    assert w.value in (4, 8) and o.value in (0, 1, 2) and h.value >= 1 and (hq // hkv) % h.value == 0
+                    pieces = max(row) > 1
+                    assert o.value == 0 or (w.value == 4 and not pieces)
+                    assert h.value == 1 or n_q * h.value <= 256 or (w.value == 4 and not pieces), (T, n_q)
+                    seen.add((w.value, h.value > 1, pieces))
+                assert lib.kvq_debug_prefill_form(ctypes.byref(cfg), need, T, n_q, len(passes), ctypes.byref(w), ctypes.byref(h), ctypes.byref(o)) == 0
+                assert (w.value, h.value, o.value) == (0, 0, 0)
+    assert len(seen) >= 3
+    for bad in ((0, 1, 0), (room + 1, 1, 0), (T, 0, 0), (T, T + 1, 0), (T, 5, -1)):
+        assert lib.kvq_debug_prefill_form(ctypes.byref(cfg), need, *bad, ctypes.byref(w), ctypes.byref(h), ctypes.byref(o)) == -1, bad
+    assert lib.kvq_debug_prefill_form(ctypes.byref(cfg), need, T, 5, 0, ctypes.byref(w), ctypes.byref(h), None) == -1
+    assert lib.kvq_debug_prefill_form(ctypes.byref(cfg), 0, T, 5, 0, ctypes.byref(w), ctypes.byref(h), ctypes.byref(o)) == -4
+
+
 def test_prefill_plan_is_quick_next_to_the_launch_it_divides(lib):
     """Few queries over a long cache: calls of some tens of us, in a loop over the layers, whose plan compares many numbers of pieces
     for every number of heads that share a work-group.  Each plan may take 10 us here (1 to 3 measured; the search took 21 to 38)."""
