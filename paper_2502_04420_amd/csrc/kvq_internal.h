@@ -22,7 +22,7 @@ struct LayerView {
 };
 
 constexpr int kCUs = 256;          // compute units of the GPU
-constexpr int kQueryTile = 256;    // queries that a work-group of the prefill attention kernel takes
+constexpr int kQueryTile = 256;    // rows (queries of one query head or of several) of a query tile of the prefill attention: one work-group of 8 waves, two of 4
 
 struct QuantArgs {
     LayerView lv;
@@ -149,9 +149,9 @@ int prefill_tile_pieces(const PrefillArgs &a, int part_slots, int tile);
 struct PrefillForm { int waves, row_heads, order; };
 PrefillForm prefill_form(const PrefillArgs &a, int part_slots);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
-size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 queries; part_o, part_ml)
+size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 rows; part_o, part_ml)
 constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges: three rounds of reads (below)
-constexpr int kMaxTickets = 23;   // arrival counters (DecodeArgs::tickets) that a selection record has room for
+constexpr int kMaxTickets = 23;   // arrival counters that a selection record has room for: the decode kernel's (ShortDecodeArgs::tickets), the last one the channel selection's
 size_t prefill_ticket_offset();  // where in a selection record they are: bytes that the record itself leaves unused
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache
 // decides for the caches [bh0, bh0 + n_bh) which key channels keep their low parts (a.select: their records; layers with
