@@ -1468,17 +1468,26 @@ struct LaunchPlan {
 //   waves of the group): one prompt of 2027 tokens, 32 / 8 heads 87 / 76, 5000 tokens 290 / 269, 6000 tokens 390 / 367, 7000 tokens
 //   480 / 483, 8192 tokens 619 / 637; four of 1024 tokens 129 / 114, eight of 500 tokens 165 / 136, four of 6000 tokens 1410 / 1399,
 //   one of 300 tokens 37 / 34; 28 / 4 heads, two of 6000 tokens 621 / 602; 8 / 2 heads, one of 4000 tokens: 89 in pieces / 127.
-//   (An XCD's L2 holds the 20 KiB units of one cache up to about there.)
-// - Tiles cut into pieces: 4 waves where they leave out an empty half of a tile or many of the units are some query's last ones
-//   (300 queries over 4000, 8000, 16000 tokens 36 / 34, 54 / 52, 94 / 91; 8 / 2 heads, a prompt of 8000 tokens 212 / 209), else 8 waves
-//   (512 queries over 8000 tokens 111 / 114, over 24576 281 / 295).
+//   (An XCD's L2 holds the 20 KiB units of one cache up to about there.)  Caches without packed units take them at any length, their window
+//   comes through registers either way (us a pass with its append): 32 / 8 heads, one prompt of 300 tokens 22.0 / 20.7, 2027 tokens 129 / 104, 4000 tokens 271 / 265, 16000
+//   tokens 3732 / 3437, four of 4000 tokens 1075 / 927; 28 / 4 heads, two of 8000 tokens 1710 / 1526; last 33 of 8000 tokens 368 / 362.
+// - Tiles cut into pieces: 4 waves where they leave out an empty half of a tile (32 / 8 heads, 300 queries over 8000 tokens 110 / 104, over 24000
+//   261 / 254) or many of the units are some query's last ones: prompts and halves of them up to kShortPieces units (8 / 2 heads, prompts of
+//   6400, 7500, 8100, 9000, 10500 tokens 146 / 141, 185 / 182, 208 / 199, 248 / 250, 298 / 304; last 3800 of 7500 tokens 148 / 145), else 8 waves
+//   (512 queries over 8000 tokens 111 / 114, over 24576 281 / 295; 450 over 8000 111 / 113).  An empty half counts where there are at
+//   most two tiles (three, 600 queries: they gain 0..4 %) and the caches divide by the 8 XCDs; with other numbers it goes either way
+//   (28 / 4 heads, 300 queries over 24000 tokens 209 / 229, three sequences of 8000 tokens 211 / 228; one of 8000 tokens 102 / 99).
 // - Else whole tiles and 8 waves.
 constexpr int kShortCache = 192;
 constexpr int kShortPieces = 256;
 constexpr int kFewUnits = 8;
 
 // Time of whole tiles in work-groups of 4 waves, as `cut` has it (100: a unit of two work-groups on a compute unit); one that has its
-// compute unit for itself takes 0.75 per unit.  (The two rules name the faster one for 18 shapes on both sides of the line.)
+// compute unit for itself takes 0.75 per unit.  Of 22 shapes around the line it names the
+// faster one or one within 1 % for 21 (us a call, pieces / whole: 32 / 8 heads, prompts of 1300 and 1790 tokens 57.0 / 56.9, 72.1 / 69.8, last 1024 of
+// 3000 and 5000 tokens 90 / 99, 125 / 151, last 1700 of 6000 196 / 196; 28 / 4 heads, prompts of 1500 and 2300 tokens 55.8 / 62.2, 86.8 / 82.1;
+// 8 / 2 heads, one prompt of 5000 tokens 108 / 148, two of 2100 and 3800 tokens 60.0 / 75.7, 126 / 119, last 2500 of 5500 160 / 169, four
+// of 1790 tokens 71.9 / 69.9), and not for four of 1100 tokens (49.8 / 52.3).
 long long whole_time(const PrefillArgs &a)
 {
     const int gq = a.Hq / a.Hkv, p0 = 32 * a.n_blocks + a.n_res - a.n_q, rows = a.n_q * gq, per = kQB / 2, tiles = (rows + per - 1) / per;
