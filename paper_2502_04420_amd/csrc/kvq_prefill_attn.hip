@@ -792,6 +792,9 @@ template <bool KQ, bool VQ>
 __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs a)
 {
     const int tid = threadIdx.x, u = blockIdx.x, local = blockIdx.y;
+    // The argument record's lines are asked for at once (RC: read along with NB, and its register is free for the next load only then).
+    // Short caches, us a launch, one line behind the other / at once: 48 work-groups 4.44 / 4.29, 80 work-groups 5.56 / 5.38.
+    asm volatile("" ::"s"(a.lv.kcode), "s"(a.lv.kbits), "s"(a.n_blocks), "s"(a.NB), "s"(a.RC), "s"(a.bh0), "s"(a.scratch));
     const int T = 32 * a.n_blocks + a.n_res;
     __shared__ __attribute__((aligned(16))) MetaSlab M[kStagers];
     __shared__ __attribute__((aligned(16))) Tiles tile;

@@ -215,7 +215,7 @@ def test_quantize_waves_read_two_lines_of_their_arguments(tmp_path):
 def test_prefill_launches_ask_for_their_arguments_at_once():
     """The kernels of a prefill call share an argument record of two and a half 64-byte lines, without implicit arguments, and what a
     launch adds to it begins on the third; the 8-wave attention kernels and the channel selection wait for them once, in front
-    of their first branch."""
+    of their first branch, and the dequantization asks for all of its lines in front of its first wait."""
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
     from paper_2502_04420_amd import build as B
@@ -228,3 +228,8 @@ def test_prefill_launches_ask_for_their_arguments_at_once():
     assert len(kernels) == 6
     for name, body in kernels:
         assert body.split("s_cbranch", 1)[0].count("lgkmcnt(0)") == 1, name
+    kernels = B.kernel_bodies(asm, "prefill_dequantize")
+    assert len(kernels) == 4
+    for name, body in kernels:                          # every line of the record is on its way at the first wait
+        loads = re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", body.split("lgkmcnt(0)", 1)[0])
+        assert {(int(off, 16) + 4 * int(n[1:] or 1) - 1) // 64 for n, off in loads} == {0, 1, 2}, (name, loads)
