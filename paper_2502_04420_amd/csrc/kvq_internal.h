@@ -35,13 +35,12 @@ struct QuantArgs {
     int NB;                        // block capacity per (b, h)
     int RC;                        // ring capacity (R + G)
     int copy_pos0, copy_pos1;      // absolute positions of this append that go into the ring in the same launch (none: equal)
-    int extra_groups;              // waves per tensor in front of the blocks': copy_groups, then those that clear counters (set by launch_quantize)
-    // (behind the first 128 bytes, which are all that a block's wave reads)
+    int extra_groups;              // waves per tensor in front of the blocks': those that copy window tokens, then those that clear counters (set by launch_quantize)
+    // (behind the first 128 bytes, which are all that a wave reads that quantizes a block or copies window tokens)
     // the launch that writes a layer's first block clears the arrival counters (kMaxTickets per cache, at tickets + bh * ticket_stride)
     // of the decode and the channel selection kernels
     uint32_t *tickets;
     int ticket_stride;
-    int copy_groups;               // waves per tensor that copy window tokens (set by launch_quantize)
 };
 
 struct ResidualCopyArgs {

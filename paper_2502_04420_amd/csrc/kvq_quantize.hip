@@ -228,7 +228,7 @@ __device__ __forceinline__ float wave_max64(float xf)
 // 16 different 16-byte bank groups.
 __device__ __forceinline__ int value_row(int ch) { return (ch & 0x70) | ((ch ^ (ch >> 3)) & 15); }
 
-// Window rows taken along by the quantize launch (QuantArgs::copy_groups): new tokens [copy_pos0, copy_pos1) of one tensor,
+// Window rows taken along by the quantize launch (QuantArgs::copy_pos0, copy_pos1): new tokens [copy_pos0, copy_pos1) of one tensor,
 // input rows -> ring slots, kCopyRows rows per wave (16 lanes per row, four rows in flight per lane).  Row numbers fit 32 bits
 // (quantize_takes_window).  The rows in flight are vector-extension values: an array of the runtime's uint4 was kept in scratch
 // memory, or in LDS by the instantiation that has none else (K16V16, 16 caches of 300 tokens: 10.4 us a launch, 4.3 so).
@@ -257,6 +257,9 @@ __device__ __forceinline__ void copy_window_rows(const QuantArgs &a, int group, 
 // a branch and some of them a further line of the argument record (2 x 4096 tokens, 8 kv heads, 2 layers with first token 49.3 -> 49.0 us without).
 constexpr int kClearCaches = 16;
 
+// waves that clear counters: in the launch that writes a layer's first block
+__host__ __device__ inline int clear_groups(int first_block, int BH) { return first_block == 0 ? (BH + kClearCaches - 1) / kClearCaches : 0; }
+
 __device__ __forceinline__ void clear_counters(const QuantArgs &a, int group, int lane)
 {
     static_assert(kMaxTickets <= 32, "two caches per store");
@@ -267,7 +270,7 @@ __device__ __forceinline__ void clear_counters(const QuantArgs &a, int group, in
     }
 }
 
-// One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values; in front of them copy_groups waves per
+// One wave per (tensor, block of 32 tokens, (b, h)); blockIdx.y = 0 keys, 1 values; in front of them waves per
 // tensor that put the tokens which stay in the window into the ring (a launch of its own for those took 4-5 us behind every
 // append: a 2027-token prompt, append and attention of 4 layers, 418 -> 409 us without it; behind 16 x 8192 tokens, append and
 // first token of 2 layers, it is lost in what the placement of the buffers does, 2.5 % of 320 us).  The statistics are
@@ -279,8 +282,11 @@ __global__ __launch_bounds__(64) void quantize_blocks(QuantArgs a)
     const int lane = threadIdx.x;
     const bool values = blockIdx.y != 0;
     if ((int)blockIdx.x < a.extra_groups) {
-        if ((int)blockIdx.x < a.copy_groups) copy_window_rows(a, blockIdx.x, values, lane);
-        else if (!values) clear_counters(a, blockIdx.x - a.copy_groups, lane);
+        // (Worked out from what the first lines of the argument record hold: read from its third line, the number of copying waves makes short
+        // launches of 16-bit blocks, which end with these waves, 0.2 us longer: 500 tokens, 2 kv heads, append and first token 11.17 / 10.86.)
+        const int copies = a.extra_groups - clear_groups(a.first_block, a.BH);
+        if ((int)blockIdx.x < copies) copy_window_rows(a, blockIdx.x, values, lane);
+        else if (!values) clear_counters(a, blockIdx.x - copies, lane);
         return;
     }
     const int item = blockIdx.x - a.extra_groups;
@@ -699,8 +705,7 @@ hipError_t launch_quantize(QuantArgs a, hipStream_t s)
     if ((long long)a.n_blocks * a.BH > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const int n_copy = a.copy_pos1 - a.copy_pos0;
     if (n_copy > 0 && !quantize_takes_window(a.n_blocks, a.BH, n_copy)) return hipErrorInvalidConfiguration;
-    a.copy_groups = n_copy > 0 ? (int)copy_groups(a.BH, n_copy) : 0;
-    a.extra_groups = a.copy_groups + (a.first_block == 0 ? (a.BH + kClearCaches - 1) / kClearCaches : 0);
+    a.extra_groups = (n_copy > 0 ? (int)copy_groups(a.BH, n_copy) : 0) + clear_groups(a.first_block, a.BH);
     return a.lv.narrow ? launch_quantize_kb<true>(a, s) : launch_quantize_kb<false>(a, s);
 }
 

@@ -210,6 +210,11 @@ def test_quantize_waves_read_two_lines_of_their_arguments(tmp_path):
         loads = re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", near)
         ends = [int(off, 16) + 4 * int(n[1:] or 1) for n, off in loads]
         assert ends and max(ends) <= 128, (name, loads)
+        # of the other waves, those that copy window rows do not wait for the third line either: it holds the counters' place only
+        first = far.index("s[0:1], 0x80")
+        assert "s_cbranch" in far[:first] and "global_load" not in far[:first] and "lgkmcnt" not in far[:first], name
+        third = [(off, n) for n, off in re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", far) if int(off, 16) >= 128]
+        assert sorted(third) == [("0x80", "x2"), ("0x88", "")], (name, third)
 
 
 def test_prefill_launches_ask_for_their_arguments_at_once():
