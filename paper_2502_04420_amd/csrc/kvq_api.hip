@@ -434,6 +434,8 @@ int decode_layer(kvq_ctx *c, int layer, const void *q_device, void *out_device, 
     a.k_new = static_cast<const uint16_t *>(k_new);
     a.v_new = static_cast<const uint16_t *>(v_new);
     a.new_pos = T - 1;
+    a.gq = a.Hq / a.Hkv;
+    a.win_slot = np % a.RC;
     const int variant = decode_variant(c);
     const SplitPlan sp = plan_splits(a.B * a.Hkv, a.Hq / a.Hkv, a.lv.kbits + a.lv.vbits, a.n_blocks, a.n_res, c->splits, variant);
     const int splits = sp.splits;

@@ -249,6 +249,48 @@ __device__ __forceinline__ void await_zero_points(u32x4 (&zb)[4])
     asm volatile("s_waitcnt vmcnt(%4)" : "+v"(zb[0]), "+v"(zb[1]), "+v"(zb[2]), "+v"(zb[3]) : "n"(N));
 }
 
+// The query rows of a tile, issued by hand like the block loads and ahead of them.  As ordinary loads, and behind branches for the heads that do
+// not exist, they cost a round trip each: the compiler waited for them before it let the first blocks be asked for (it
+// also took loads of the other role's code path to be pending), and, not knowing of the blocks' loads, waited for those too before
+// the queries could be used.  Heads that do not exist read the first head's row and are cleared afterwards.  Together with the arguments asked for at
+// once and the divisions taken out of the way to the first load (decode_mfma), us a call, before / after: 2 kv heads, 512 tokens 7.0 / 6.5; 8 kv heads,
+// 4133 tokens 9.8 / 9.1; 32 kv heads, 760 tokens 8.6 / 8.0; streaming launches 0.4 shorter (batch 16, 8192 tokens 32.5 / 32.0).
+// (key wave: two channels of every head per lane; value wave: 16 bytes of one row of the query tile)
+__device__ __forceinline__ void issue_query(uint32_t &q, const uint8_t *rows, uint32_t voff)
+{
+    asm volatile("global_load_dword %0, %1, %2" : "+v"(q) : "v"(voff), "s"(rows));
+}
+__device__ __forceinline__ void issue_query(u32x4 &q, const uint8_t *rows, uint32_t voff)
+{
+    asm volatile("global_load_dwordx4 %0, %1, %2" : "+v"(q) : "v"(voff), "s"(rows));
+}
+// N: loads issued behind the queries.  One statement for all of them: they are in registers when it is done.
+template <int N>
+__device__ __forceinline__ void await_queries(uint32_t (&q)[4])
+{
+    asm volatile("s_waitcnt vmcnt(%4)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]) : "n"(N));
+}
+template <int N>
+__device__ __forceinline__ void await_queries(uint32_t (&q)[8])
+{
+    asm volatile("s_waitcnt vmcnt(%8)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]) : "n"(N));
+}
+template <int N>
+__device__ __forceinline__ void await_queries(u32x4 (&q)[1])
+{
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(q[0]) : "n"(N));
+}
+template <int N>
+__device__ __forceinline__ void await_queries(u32x4 (&q)[2])
+{
+    asm volatile("s_waitcnt vmcnt(%2)" : "+v"(q[0]), "+v"(q[1]) : "n"(N));
+}
+template <int N>
+__device__ __forceinline__ void await_queries(u32x4 (&q)[4])
+{
+    asm volatile("s_waitcnt vmcnt(%4)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]) : "n"(N));
+}
+
 // Wait until at most N vector memory operations of this wave are outstanding; r's registers are operands, so every
 // use of the block comes after the wait.
 template <int N, int BITS>
@@ -571,7 +613,8 @@ __device__ __forceinline__ WindowChunk window_chunk(const DecodeArgs &a, bool va
     w.nt = left < 32 ? left : 32;
     w.ring = (values ? a.lv.vres : a.lv.kres) + (size_t)bh * a.RC * kD;
     w.RC = a.RC;
-    w.slot0 = pos0 % a.RC;
+    w.slot0 = a.win_slot + chunk * 32;                           // (the window is shorter than the ring)
+    w.slot0 = w.slot0 >= a.RC ? w.slot0 - a.RC : w.slot0;
     w.new_row = fresh && a.new_pos == pos0 + w.nt - 1 ? fresh + (size_t)bh * kD : nullptr;
     return w;
 }
@@ -938,12 +981,14 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
     const int n = lane & 15, rq = lane >> 4;
+    // The record's lines are asked for at once, here (each is a read from memory of its own; where the compiler asks for an argument when
+    // it is first needed, they follow one another), and nothing on the way to the first loads divides.
+    asm volatile("" ::"s"(a.lv.kcode), "s"(a.lv.kmeta), "s"(a.lv.vcode), "s"(a.lv.vmeta), "s"(a.lv.bexp), "s"(a.q), "s"(a.gq), "s"(a.n_blocks), "s"(a.n_res),
+                 "s"(a.NB), "s"(a.splits), "s"(a.units_per_split), "s"(a.split_rem), "s"(a.scale_log2e), "s"(a.win_slot));
     const int split = blockIdx.x, bh = blockIdx.y;
-    const int b = bh / a.Hkv, h = bh % a.Hkv;
-    const int gq_total = a.Hq / a.Hkv;
     const int head0 = blockIdx.z * GQ;
-    const int nvalid = gq_total - head0 < GQ ? gq_total - head0 : GQ;
-    const size_t qrow0 = (size_t)b * a.Hq + (size_t)h * gq_total + head0;
+    const int nvalid = a.gq - head0 < GQ ? a.gq - head0 : GQ;
+    const size_t qrow0 = (size_t)bh * a.gq + head0;
     // wave 0 / wave 1 take the key / value role in even work-groups and the other way round in odd ones,
     // so that both kinds of wave land on every SIMD
     const int pair = PAIRS > 1 ? wave >> 1 : 0;
@@ -964,19 +1009,21 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     if constexpr (PAIRS > 1) {
         // the window's chunks go to the last pairs (to all, where there are no blocks), the blocks to those in front: a chunk
         // takes as long as two blocks or three, and the window's split has few blocks or none
-        const int wp = blocks == 0 ? PAIRS : chunks < PAIRS - 1 ? chunks : PAIRS - 1, bp = PAIRS - wp;
-        const int most_b = bp ? (blocks + bp - 1) / bp : 0, most_c = wp ? (chunks + wp - 1) / wp : 0;
-        steps = most_b > most_c ? most_b : most_c;
-        if (pair < bp) {
-            const int b0 = blocks * pair / bp, b1 = blocks * (pair + 1) / bp;
-            u0 += b0;
-            blocks = b1 - b0;
-            chunks = 0;
+        static_assert(PAIRS == 2, "all units to both pairs, or the window to one and the blocks to the other");
+        if (blocks == 0 || chunks == 0) {
+            const int units = blocks + chunks, lower = units >> 1, mine = pair ? units - lower : lower, first = pair ? lower : 0;
+            steps = units - lower;
+            if (chunks == 0) {
+                u0 += first;
+                blocks = mine;
+            } else {
+                first_chunk = first;
+                chunks = mine;
+            }
         } else {
-            const int i = pair - bp;
-            first_chunk = chunks * i / wp;
-            chunks = chunks * (i + 1) / wp - first_chunk;
-            blocks = 0;
+            steps = blocks > chunks ? blocks : chunks;
+            if (pair == 0) chunks = 0;
+            else blocks = 0;
         }
     }
     const int n1 = kFast ? blocks : 0, n2p = kFast ? 0 : blocks;      // the blocks of phase 1, of phase 2
@@ -985,13 +1032,15 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     // cache block number of the i-th phase-1 unit (0 <= i < n1).
     // Every group starts its sweep at a different place of its range and wraps around: groups advance at the
     // same pace, and with equal phases their addresses would keep falling on the same memory channels.
-    const int rot = n1 > 0 ? (int)(((uint32_t)bh * 40503u + (uint32_t)split * 9973u) % (uint32_t)n1) : 0;
+    // (a fraction of the range, in 2^-32: the steps between neighbouring caches and splits are far from any small fraction)
+    const uint32_t phase = ((uint32_t)bh * 40503u + (uint32_t)split * 9973u) << 16;
+    const int rot = (int)__umulhi(phase, (uint32_t)n1);
     auto blk1 = [&](int i) {
         const int r = i + rot;
         return u0 + (r < n1 ? r : r - n1);
     };
     // cache block number of the i-th of phase 2's blocks (16-bit tensors), with the same rotation
-    const int rot2 = n2p > 0 ? (int)(((uint32_t)bh * 40503u + (uint32_t)split * 9973u) % (uint32_t)n2p) : 0;
+    const int rot2 = (int)__umulhi(phase, (uint32_t)n2p);
     auto blk2 = [&](int i) {
         const int r = i + rot2;
         return u0 + (r < n2p ? r : r - n2p);
@@ -1008,6 +1057,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     Q.nvalid = nvalid;
     Q.c = a.scale_log2e;
     Q.Aq = &aq_lds[0][0];
+    const uint8_t *queries = reinterpret_cast<const uint8_t *>(a.q + qrow0 * kD);       // of the tile's first head
 
     if (key_wave) {
         // =========================================================== key wave
@@ -1015,8 +1065,10 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         uint32_t qw[GQ];
 #pragma unroll
         for (int j = 0; j < GQ; j++) {
+            const uint32_t off = (uint32_t)((j < nvalid ? j : 0) * (kD * 2) + 4 * lane);
             qw[j] = 0;
-            if (j < nvalid) qw[j] = *reinterpret_cast<const uint32_t *>(a.q + (qrow0 + j) * kD + 2 * lane);
+            if constexpr (kFast) issue_query(qw[j], queries, off);
+            else qw[j] = *reinterpret_cast<const uint32_t *>(queries + off);
         }
         const BlockStream KS = block_stream(a.lv, false, blk0, a.n_blocks, lane, NARROW);
         uint32_t kexp = 0;                               // exponent words of the chunk's blocks, one per lane
@@ -1045,6 +1097,15 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 #pragma unroll
             for (int d = 0; d < DK - 1; d++) issue_block<KB, NARROW, !kZB>(KS, d < n1, blk1c(d), kr[d]);
         }
+        {
+            // A-tile rows of heads that do not exist are never written: they must read as zero
+            const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
+            for (int i = lane; i < (16 - row0) * (kD + 8) / 8; i += 64)
+                reinterpret_cast<uint4 *>(&L.Ak[row0][0])[i] = make_uint4(0, 0, 0, 0);
+        }
+        if constexpr (kFast) await_queries<1 + (kZB ? 4 : 0) + (DK - 1) * NLK>(qw);
+#pragma unroll
+        for (int j = 1; j < GQ; j++) qw[j] = j < nvalid ? qw[j] : 0u;
         {
             // queries divided by a power of two that brings the largest to [0.5, 1).  Per-channel keys: with the softmax
             // constant folded in, for the q * s operand.  Per-token keys: the raw fp16 queries, scaled exactly.
@@ -1096,12 +1157,6 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                     Q.q2[j][1] = ldexpf(qraw[j][1], -qexp) * w1;
                     Q.q16[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(Q.q2[j][0], Q.q2[j][1]));
                 }
-            }
-            {
-                // A-tile rows of heads that do not exist are never written: they must read as zero
-                const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
-                for (int i = lane; i < (16 - row0) * (kD + 8) / 8; i += 64)
-                    reinterpret_cast<uint4 *>(&L.Ak[row0][0])[i] = make_uint4(0, 0, 0, 0);
             }
         }
         // fp16 rows this wave starts with: a group without packed blocks asks for them here, one with packed blocks behind
@@ -1231,12 +1286,17 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         // =========================================================== value wave (one unit behind the key wave)
         // rows 2j and 2j + 1 of the exact-fp16 query tile (16 rows x 256 bytes); rows of absent heads are zero.
         // The loads are issued in the order in which their results are needed: queries, then the first blocks.
-        uint4 qx[4];
+        // (16-byte pieces of rows 4 pass + rq; with two pairs of waves, each value wave has half of the passes)
+        constexpr int kPasses = GQ / 2 / PAIRS;
+        const int pass0 = PAIRS > 1 ? pair * kPasses : 0;
+        u32x4 qx[kPasses];
 #pragma unroll
-        for (int pass = 0; pass < 4; pass++) {
-            const int jr = (4 * pass + rq) >> 1;
-            qx[pass] = make_uint4(0, 0, 0, 0);
-            if (jr < nvalid) qx[pass] = *reinterpret_cast<const uint4 *>(a.q + (qrow0 + jr) * kD + 8 * n);
+        for (int p = 0; p < kPasses; p++) {
+            const int jr = (4 * (pass0 + p) + rq) >> 1;
+            const uint32_t off = (uint32_t)((jr < nvalid ? jr : 0) * (kD * 2) + 16 * n);
+            qx[p] = u32x4{0u, 0u, 0u, 0u};
+            if constexpr (kFast) issue_query(qx[p], queries, off);
+            else qx[p] = *reinterpret_cast<const u32x4 *>(queries + off);
         }
         const BlockStream VS = block_stream(a.lv, true, blk0, a.n_blocks, lane, NARROW);
         uint32_t vexp = 0;
@@ -1251,15 +1311,21 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         ValueRows rows;                                 // (as in the key wave)
         u32x2 fresh;
         if constexpr (VB == 16) fetch_unit(a.lv.vcode + blk0 * block_code_bytes(16), n2p > 0, n2p > 0 ? blk2(0) : 0, lane, rows);
-        if (PAIRS == 1 || pair == 0) {
-#pragma unroll
-            for (int pass = 0; pass < 4; pass++) *reinterpret_cast<uint4 *>(&aq_lds[4 * pass + rq][8 * n]) = qx[pass];
-        }
         {
+            // rows of heads that do not exist: lane row rq clears those of its channel group
             const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
-            const int per = (16 - row0) * (32 + 8) / 8;              // 16-byte pieces of the unused rows per channel group
-            for (int i = lane; i < 4 * per; i += 64)
-                reinterpret_cast<uint4 *>(&L.Av[i / per].at[row0][0])[i % per] = make_uint4(0, 0, 0, 0);
+            for (int i = n; i < (16 - row0) * (32 + 8) / 8; i += 16)
+                reinterpret_cast<uint4 *>(&L.Av[rq].at[row0][0])[i] = make_uint4(0, 0, 0, 0);
+            if constexpr (GQ == 4) {
+#pragma unroll
+                for (int p = 0; p < kPasses; p++) *reinterpret_cast<uint4 *>(&aq_lds[8 + 4 * (pass0 + p) + rq][8 * n]) = make_uint4(0, 0, 0, 0);
+            }
+        }
+        if constexpr (kFast) await_queries<1 + (DV - 1) * block_loads<VB>()>(qx);
+#pragma unroll
+        for (int p = 0; p < kPasses; p++) {
+            const int row = 4 * (pass0 + p) + rq;
+            *reinterpret_cast<u32x4 *>(&aq_lds[row][8 * n]) = (row >> 1) < nvalid ? qx[p] : u32x4{0u, 0u, 0u, 0u};
         }
         Q.vw0 = code_weight_inv<VB < 16 ? VB : 8>((2 * n) & 7);
         Q.vw1 = code_weight_inv<VB < 16 ? VB : 8>((2 * n + 1) & 7);
@@ -1402,6 +1468,9 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             }
             wave_lds_sync();
         }
+        // Nothing of the compiler's is pending here (vmcnt(0), the other counters as they are: free).  Said for the compiler: it lays the key wave's
+        // code out behind this one and takes the way there for a possible one, and would wait there, among the hand-issued loads, for loads of here.
+        __builtin_amdgcn_s_waitcnt(0x0F70);
         if constexpr (PAIRS == 1) {
 #pragma unroll
             for (int j = 0; j < GQ; j++)

@@ -78,10 +78,12 @@ struct DecodeArgs {
     int units_per_split;   // work units per split: the last split_rem splits take one more.  Units are the quantized blocks, then
     int split_rem;         // (owned by the last split, counted as a few units) the fp16 window
     float scale_log2e;     // log2(e) / sqrt(D)
+    int gq;                // Hq / Hkv
     // fused append of one token per sequence (matrix-core kernel only): its fp16 rows [B*Hkv][128], not yet in the
     // window ring; the kernel reads them from here and stores them into the ring for later launches.  NULL: none.
     const uint16_t *k_new, *v_new;
     int new_pos;           // absolute position of that token
+    int win_slot;          // ring slot of the window's first token: 32*n_blocks mod RC
 };
 
 // launch_decode_short's: its last work-group of a cache and tile of query heads merges the splits (at most kMergeSplits); one

@@ -58,7 +58,7 @@ class _Op:
             w = re.match(r"s_waitcnt\s+vmcnt\((\d+)\)$", t)
             if w:
                 self.waits.append(int(w.group(1)))
-            elif t.startswith("buffer_load"):
+            elif t.startswith(("buffer_load", "global_load")):
                 self.loads.append(_bits(_VGPR, t.split(",")[0]))
         parts = text.split(None, 1)
         self.op = parts[0] if parts else ""
