@@ -40,6 +40,8 @@
 namespace kvq {
 namespace {
 
+constexpr int kPairs = KVQ_DECODE_PAIRS;
+
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -159,6 +161,12 @@ struct BlockStream {
 // The loop issues its loads unconditionally (so that the number of loads behind a block is a constant); past the end of
 // the group's range they go through a resource with no bytes in range: every load through it is out of range, touches
 // no memory and returns zero.
+// (`code` and `meta` are emptied in place, once and for the rest of the sweep: copies would cost four scalar moves per resource and step.)
+__device__ __forceinline__ void end_unless(bool real, BlockStream &S)
+{
+    S.code[2] = real ? S.code[2] : 0;
+    S.meta[2] = real ? S.meta[2] : 0;
+}
 // r, or r with no bytes in range: one scalar select
 __device__ __forceinline__ i32x4 pick(bool real, const i32x4 &r)
 {
@@ -212,10 +220,9 @@ template <int BITS, bool LOADZ = true> constexpr int block_loads() { return BITS
 // kept in the caches at the expense of anything else (measured: 2-7 % shorter calls, most for the 8-bit pair).
 // LOADZ = false: without the zero-points (the key wave fetches those of sixteen blocks at a time, issue_zero_points).
 template <int BITS, bool NARROW, bool LOADZ = true>
-__device__ __forceinline__ void issue_block(const BlockStream &S0, bool real, int blk, CodeRegs<BITS> &r)
+__device__ __forceinline__ void issue_block(const BlockStream &S, int blk, CodeRegs<BITS> &r)
 {
     static_assert(BITS < 16, "packed blocks only");
-    struct { i32x4 code, meta; uint32_t l16, l8, l4; } S = {pick(real, S0.code), pick(real, S0.meta), S0.l16, S0.l8, S0.l4};
     const int coff = blk * block_code_bytes(BITS), moff = blk * 4 * meta_words(NARROW);
     asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen nt" : "+v"(r.q[0]) : "v"(S.l16), "s"(S.code), "s"(coff));
     if constexpr (BITS >= 4) asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:1024 nt" : "+v"(r.q[BITS >= 4 ? 1 : 0]) : "v"(S.l16), "s"(S.code), "s"(coff));
@@ -252,17 +259,13 @@ __device__ __forceinline__ void await_zero_points(u32x4 (&zb)[4])
 // The query rows of a tile, issued by hand like the block loads and ahead of them.  As ordinary loads, and behind branches for the heads that do
 // not exist, they cost a round trip each: the compiler waited for them before it let the first blocks be asked for (it
 // also took loads of the other role's code path to be pending), and, not knowing of the blocks' loads, waited for those too before
-// the queries could be used.  Heads that do not exist read the first head's row and are cleared afterwards.  Together with the arguments asked for at
+// the queries could be used.  Heads that do not exist read the first head's row.  Together with the arguments asked for at
 // once and the divisions taken out of the way to the first load (decode_mfma), us a call, before / after: 2 kv heads, 512 tokens 7.0 / 6.5; 8 kv heads,
 // 4133 tokens 9.8 / 9.1; 32 kv heads, 760 tokens 8.6 / 8.0; streaming launches 0.4 shorter (batch 16, 8192 tokens 32.5 / 32.0).
-// (key wave: two channels of every head per lane; value wave: 16 bytes of one row of the query tile)
+// (Two channels of every head per lane.  Only the key wave needs them.)
 __device__ __forceinline__ void issue_query(uint32_t &q, const uint8_t *rows, uint32_t voff)
 {
     asm volatile("global_load_dword %0, %1, %2" : "+v"(q) : "v"(voff), "s"(rows));
-}
-__device__ __forceinline__ void issue_query(u32x4 &q, const uint8_t *rows, uint32_t voff)
-{
-    asm volatile("global_load_dwordx4 %0, %1, %2" : "+v"(q) : "v"(voff), "s"(rows));
 }
 // N: loads issued behind the queries.  One statement for all of them: they are in registers when it is done.
 template <int N>
@@ -275,22 +278,6 @@ __device__ __forceinline__ void await_queries(uint32_t (&q)[8])
 {
     asm volatile("s_waitcnt vmcnt(%8)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]) : "n"(N));
 }
-template <int N>
-__device__ __forceinline__ void await_queries(u32x4 (&q)[1])
-{
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(q[0]) : "n"(N));
-}
-template <int N>
-__device__ __forceinline__ void await_queries(u32x4 (&q)[2])
-{
-    asm volatile("s_waitcnt vmcnt(%2)" : "+v"(q[0]), "+v"(q[1]) : "n"(N));
-}
-template <int N>
-__device__ __forceinline__ void await_queries(u32x4 (&q)[4])
-{
-    asm volatile("s_waitcnt vmcnt(%4)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]) : "n"(N));
-}
-
 // Wait until at most N vector memory operations of this wave are outstanding; r's registers are operands, so every
 // use of the block comes after the wait.
 template <int N, int BITS>
@@ -311,23 +298,23 @@ __device__ __forceinline__ void await_block(CodeRegs<BITS> &r)
     await_loads<(DEPTH - 1) * block_loads<BITS>(), BITS>(r);
 }
 
-// The same wait with one of two counts, N + EXTRA when `more_behind` (EXTRA further loads were issued behind the
+// The same wait with one of two counts, N + EXTRA in step `first` (where EXTRA further loads were issued behind the
 // block's own) and N otherwise.  One statement with the branch inside: two statements on two code paths would make
 // the compiler merge two versions of registers that loads are still writing.
 template <int N, int EXTRA, int BITS>
-__device__ __forceinline__ void await_loads_either(CodeRegs<BITS> &r, int more_behind)
+__device__ __forceinline__ void await_loads_either(CodeRegs<BITS> &r, int step, int first)
 {
     static_assert(BITS == 2 || BITS == 4 || BITS == 8, "packed blocks only");
-#define KVQ_EITHER "s_cmp_eq_u32 %[mb], 0\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(%[hi])\n\ts_branch 2f\n1:\n\ts_waitcnt vmcnt(%[lo])\n2:"
+#define KVQ_EITHER "s_cmp_lg_u32 %[at], %[first]\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(%[hi])\n\ts_branch 2f\n1:\n\ts_waitcnt vmcnt(%[lo])\n2:"
     if constexpr (BITS == 8)
         asm volatile(KVQ_EITHER : "+v"(r.q[0]), "+v"(r.q[BITS == 8 ? 1 : 0]), "+v"(r.q[BITS == 8 ? 2 : 0]), "+v"(r.q[BITS == 8 ? 3 : 0]), "+v"(r.s2), "+v"(r.s1), "+v"(r.z)
-                     : [mb] "s"(more_behind), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
+                     : [at] "s"(step), [first] "s"(first), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
     else if constexpr (BITS == 4)
         asm volatile(KVQ_EITHER : "+v"(r.q[0]), "+v"(r.q[BITS == 4 ? 1 : 0]), "+v"(r.s2), "+v"(r.s1), "+v"(r.z)
-                     : [mb] "s"(more_behind), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
+                     : [at] "s"(step), [first] "s"(first), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
     else
         asm volatile(KVQ_EITHER : "+v"(r.q[0]), "+v"(r.s2), "+v"(r.s1), "+v"(r.z)
-                     : [mb] "s"(more_behind), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
+                     : [at] "s"(step), [first] "s"(first), [hi] "n"(N + EXTRA), [lo] "n"(N) : "scc");
 #undef KVQ_EITHER
 }
 
@@ -340,16 +327,19 @@ __device__ __forceinline__ void drain_unused() { asm volatile("s_waitcnt vmcnt(0
 template <int BITS, bool NARROW>
 __device__ __forceinline__ void load_block_now(const BlockStream &S, int blk, CodeRegs<BITS> &r)
 {
-    issue_block<BITS, NARROW>(S, true, blk, r);
+    issue_block<BITS, NARROW>(S, blk, r);
     await_loads<0, BITS>(r);
 }
 
+// registers that a hand-issued load is going to write: any value will do, so none is moved in
+template <typename T>
+__device__ __forceinline__ void undefined(T &x) { asm volatile("" : "=v"(x)); }
 template <int BITS>
-__device__ __forceinline__ void clear_regs(CodeRegs<BITS> &r)
+__device__ __forceinline__ void undefined_regs(CodeRegs<BITS> &r)
 {
 #pragma unroll
-    for (int c = 0; c < (BITS < 16 ? BITS / 2 : 1); c++) r.q[c] = u32x4{0u, 0u, 0u, 0u};
-    r.s2 = u32x2{0u, 0u}; r.s1 = 0u; r.z = 0u;
+    for (int c = 0; c < (BITS < 16 ? BITS / 2 : 1); c++) undefined(r.q[c]);
+    undefined(r.s2); undefined(r.s1); undefined(r.z);
 }
 
 // the two scales of a loaded block as floats
@@ -361,24 +351,24 @@ __device__ __forceinline__ float2 scales_of(const CodeRegs<BITS> &r)
     return make_float2(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y));
 }
 
-// max over the 16 lanes of a DPP row (lanes that share lane >> 4), result in every lane
-__device__ __forceinline__ float row_max16(float x)
-{
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false)));   // quad_perm [1,0,3,2]
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xf, 0xf, false)));   // quad_perm [2,3,0,1]
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xf, 0xf, false)));  // row_half_mirror
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xf, 0xf, false)));  // row_mirror
-    return x;
-}
-
-__device__ __forceinline__ float row_sum16(float x)
-{
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xf, 0xf, false));
-    return x;
-}
+// Reductions over the 16 lanes of a DPP row (lanes that share lane >> 4), result in every lane: two or four values at once, whose steps fill the two
+// wait states between the write of a register and a DPP read of it.  (One at a time and by the compiler a step takes four or
+// five instructions instead of one or two, and where few waves share a SIMD a wave issues one in five cycles.)
+#define KVQ_ROW_STEP2(OP, CTRL) OP " %0, %0, %0 " CTRL " row_mask:0xf bank_mask:0xf\n\t" OP " %1, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf"
+#define KVQ_ROW_STEP4(OP, CTRL) KVQ_ROW_STEP2(OP, CTRL) "\n\t" OP " %2, %2, %2 " CTRL " row_mask:0xf bank_mask:0xf\n\t" OP " %3, %3, %3 " CTRL " row_mask:0xf bank_mask:0xf"
+#define KVQ_ROW_REDUCE2(OP) "s_nop 1\n\t" KVQ_ROW_STEP2(OP, "quad_perm:[1,0,3,2]") "\n\ts_nop 0\n\t" KVQ_ROW_STEP2(OP, "quad_perm:[2,3,0,1]") \
+                            "\n\ts_nop 0\n\t" KVQ_ROW_STEP2(OP, "row_half_mirror") "\n\ts_nop 0\n\t" KVQ_ROW_STEP2(OP, "row_mirror")
+#define KVQ_ROW_REDUCE4(OP) "s_nop 1\n\t" KVQ_ROW_STEP4(OP, "quad_perm:[1,0,3,2]") "\n\t" KVQ_ROW_STEP4(OP, "quad_perm:[2,3,0,1]") \
+                            "\n\t" KVQ_ROW_STEP4(OP, "row_half_mirror") "\n\t" KVQ_ROW_STEP4(OP, "row_mirror")
+__device__ __forceinline__ void row_max16(float &a, float &b) { asm(KVQ_ROW_REDUCE2("v_max_f32_dpp") : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void row_sum16(float &a, float &b) { asm(KVQ_ROW_REDUCE2("v_add_f32_dpp") : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void row_sum16(float &a, float &b, float &c, float &d) { asm(KVQ_ROW_REDUCE4("v_add_f32_dpp") : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+#undef KVQ_ROW_REDUCE4
+#undef KVQ_ROW_REDUCE2
+#undef KVQ_ROW_STEP4
+#undef KVQ_ROW_STEP2
+__device__ __forceinline__ float row_max16(float x) { float y = x; row_max16(x, y); return x; }
+__device__ __forceinline__ float row_sum16(float x) { float y = x; row_sum16(x, y); return x; }
 
 // A split's partial results are written through to memory as they are stored (system-scope stores): left in the
 // write-back cache they would all be written out at once when the kernel ends, in front of the merge kernel that is
@@ -417,12 +407,16 @@ template <int GQ>
 struct QueryRegs {
     float q2[GQ][2];               // scaled queries for channels 2*lane, 2*lane+1 (for q * s)
     uint32_t q16[GQ];              // the same pair rounded to fp16
-    int nvalid;                    // heads of this tile that exist (the A-tile rows of the others stay zero)
-    const _Float16 *Aq;            // LDS: exact fp16 queries as an A tile [16][kD + 8] (rows 2j and 2j + 1 = head j)
+    int nvalid;                    // heads of this tile that exist
+    // what this lane reads of an A tile: its row (16 rows, high and low parts of 8 heads; where heads are absent, rows of the last one that
+    // exists: no row has to be cleared, and the lanes of absent heads see finite values, which nobody reads)
+    int row;
+    const _Float16 *Aq;            // LDS: exact fp16 queries, the row of this lane's head (rows 2j and 2j + 1 of the A tile are equal: one is stored)
     float c, alpha_h;              // log2(e)/sqrt(D); weight of the partial scores
     float vw0, vw1;                // bit-position weights of tokens 2n, 2n+1 in the value codes
     float kappa;                   // per-token keys: weight of the partial score sums
     float qs[2][4];                // per-token keys: c * sum of q over channel group g, heads 2*rq, 2*rq + 1
+    half8 At[4];                   // per-token keys, two pairs: the A operands, the same for every block
 };
 
 template <int GQ>
@@ -458,6 +452,18 @@ __device__ __forceinline__ void priority_at_step(int i, const PrioritySteps &t)
 
 // ------------------------------------------------------------------ key wave
 
+// The four A operands of a tile (16 bytes of this lane's row, 64 bytes apart or in four tiles), asked for together: one LDS round trip, where the
+// compiler would fetch each behind the products of the one before.  (With the bookkeeping taken out of a block's path - cleared registers, resources
+// copied, a barrier, zeroed rows, re-basing of empty sums - us a call: 8 kv heads, 4133 tokens 9.1 / 8.1; a wave alone on its SIMD
+// issues one instruction in five cycles, so a hundred instructions are 0.2 us.)  Where four waves share a SIMD it may: they fill the gaps, and
+// 4-bit instantiations would spill up to nine registers.
+__device__ __forceinline__ void read_operands(half8 (&A)[4], const _Float16 *first, int stride)
+{
+#pragma unroll
+    for (int k = 0; k < 4; k++) A[k] = *reinterpret_cast<const half8 *>(first + k * stride);
+    if constexpr (kPairs > 1) asm volatile("" : "+v"(A[0]), "+v"(A[1]), "+v"(A[2]), "+v"(A[3]));
+}
+
 // scores of a quantized block: s[th][hh] for head 2*rq + hh, tokens 16*th + n
 // ZB: the zero-point terms c * sum_d q_d z_d of heads 2 rq and 2 rq + 1 come ready-made in zc (zero_point_terms) instead
 // of from the block's own zero-points.
@@ -465,7 +471,7 @@ template <int KB, int GQ, bool NARROW, bool ZB = false>
 __device__ __forceinline__ void scores_packed(const CodeRegs<KB> &blk, uint32_t bexp, const QueryRegs<GQ> &Q, PairLds<GQ> &L, int lane,
                                               float (&s)[2][2], float2 zc = make_float2(0.0f, 0.0f))
 {
-    const int n = lane & 15, rq = lane >> 4;
+    const int rq = lane >> 4;
     // lift the operand to the top of the fp16 range: the largest q*s of the block lands in [2^12, 2^14)
     const int ek = (int)(bexp & 0xffffu) - 32768;
     const float2 sc = scales_of<NARROW>(blk);
@@ -483,14 +489,15 @@ __device__ __forceinline__ void scores_packed(const CodeRegs<KB> &blk, uint32_t 
     if constexpr (!ZB) *reinterpret_cast<uint32_t *>(&L.Zk[2 * lane]) = blk.z;
     wave_lds_sync();
     float4v S0 = {0.0f, 0.0f, 0.0f, 0.0f}, S1 = S0, Z = S0;
+    half8 Aop[4];
+    read_operands(Aop, &L.Ak[Q.row][8 * rq], 32);
 #pragma unroll
     for (int cb = 0; cb < 4; cb++) {
-        const half8 Aop = *reinterpret_cast<const half8 *>(&L.Ak[n][32 * cb + 8 * rq]);
-        S0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, codes_operand<KB>(blk, cb), S0, 0, 0, 0);
-        S1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, codes_operand<KB>(blk, 4 + cb), S1, 0, 0, 0);
+        S0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop[cb], codes_operand<KB>(blk, cb), S0, 0, 0, 0);
+        S1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop[cb], codes_operand<KB>(blk, 4 + cb), S1, 0, 0, 0);
         if constexpr (!ZB) {
             const half8 Bz = *reinterpret_cast<const half8 *>(&L.Zk[32 * cb + 8 * rq]);
-            Z = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8 *>(Q.Aq + n * (kD + 8) + 32 * cb + 8 * rq), Bz, Z, 0, 0, 0);
+            Z = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8 *>(Q.Aq + 32 * cb), Bz, Z, 0, 0, 0);
         }
     }
     // this lane holds rows 4*rq + i: (high, low) of head 2*rq and (high, low) of head 2*rq + 1
@@ -511,9 +518,11 @@ __device__ __forceinline__ void zero_point_terms(const u32x4 (&zb)[4], const Que
 {
     const int n = lane & 15, rq = lane >> 4;
     float4v Z = {0.0f, 0.0f, 0.0f, 0.0f};
+    half8 Aop[4];
+    read_operands(Aop, Q.Aq, 32);
 #pragma unroll
     for (int cb = 0; cb < 4; cb++)
-        Z = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8 *>(Q.Aq + n * (kD + 8) + 32 * cb + 8 * rq),
+        Z = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop[cb],
                                                    as_half8(zb[cb][0], zb[cb][1], zb[cb][2], zb[cb][3]), Z, 0, 0, 0);
     *reinterpret_cast<float2 *>(&L.Zt[n][rq][0]) = make_float2(Q.c * Z[0], Q.c * Z[2]);
 }
@@ -534,13 +543,27 @@ __device__ __forceinline__ void scores_packed_per_token(const CodeRegs<KB> &blk,
     wave_lds_sync();
     s[0][0] = s[0][1] = s[1][0] = s[1][1] = 0.0f;
     const float4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    float sv[4][2], zv[4][2];
+    if constexpr (kPairs > 1) {
+        // (together, like the operands of read_operands)
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) {
+            sv[cb][0] = L.Mk[0][32 * cb + n]; sv[cb][1] = L.Mk[0][32 * cb + 16 + n];
+            zv[cb][0] = L.Mk[1][32 * cb + n]; zv[cb][1] = L.Mk[1][32 * cb + 16 + n];
+        }
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) asm volatile("" : "+v"(sv[cb][0]), "+v"(sv[cb][1]), "+v"(zv[cb][0]), "+v"(zv[cb][1]));
+    }
 #pragma unroll
     for (int cb = 0; cb < 4; cb++) {
-        const half8 Aop = *reinterpret_cast<const half8 *>(&L.Ak[n][32 * cb + 8 * rq]);
+        const half8 Aop = kPairs > 1 ? Q.At[cb] : *reinterpret_cast<const half8 *>(&L.Ak[Q.row][32 * cb + 8 * rq]);
         const float4v D0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, codes_operand<KB>(blk, cb), zero, 0, 0, 0);
         const float4v D1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, codes_operand<KB>(blk, 4 + cb), zero, 0, 0, 0);
-        const float s0 = L.Mk[0][32 * cb + n], s1 = L.Mk[0][32 * cb + 16 + n];
-        const float z0 = L.Mk[1][32 * cb + n], z1 = L.Mk[1][32 * cb + 16 + n];
+        if constexpr (kPairs == 1) {
+            sv[cb][0] = L.Mk[0][32 * cb + n]; sv[cb][1] = L.Mk[0][32 * cb + 16 + n];
+            zv[cb][0] = L.Mk[1][32 * cb + n]; zv[cb][1] = L.Mk[1][32 * cb + 16 + n];
+        }
+        const float s0 = sv[cb][0], s1 = sv[cb][1], z0 = zv[cb][0], z1 = zv[cb][1];
 #pragma unroll
         for (int hh = 0; hh < 2; hh++) {
             s[0][hh] = fmaf(s0, D0[2 * hh], fmaf(z0, Q.qs[hh][cb], s[0][hh]));
@@ -669,11 +692,11 @@ __device__ __forceinline__ void settle_chunk(const WindowChunk &w, int lane, Val
 template <int GQ>
 __device__ __forceinline__ void scores_rows(const KeyRows &x, int nt, const QueryRegs<GQ> &Q, int lane, float (&s)[2][2])
 {
-    const int n = lane & 15, rq = lane >> 4;
+    const int n = lane & 15;
     float4v S0 = {0.0f, 0.0f, 0.0f, 0.0f}, S1 = S0;
 #pragma unroll
     for (int cb = 0; cb < 4; cb++) {
-        const half8 Aop = *reinterpret_cast<const half8 *>(Q.Aq + n * (kD + 8) + 32 * cb + 8 * rq);
+        const half8 Aop = *reinterpret_cast<const half8 *>(Q.Aq + 32 * cb);
         S0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, __builtin_bit_cast(half8, x.lo[cb]), S0, 0, 0, 0);
         S1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, __builtin_bit_cast(half8, x.hi[cb]), S1, 0, 0, 0);
     }
@@ -690,20 +713,23 @@ __device__ __forceinline__ void scores_rows(const KeyRows &x, int nt, const Quer
 // the block) when some score exceeds it by more than 1, so numerators stay <= 2 and the fp16 output
 // operands cannot overflow.  Heads that do not exist see all-zero operands, hence finite values.
 template <int GQ>
-__device__ __forceinline__ void softmax_publish(const float (&s)[2][2], KeyState<GQ> &W, PairLds<GQ> &L, int buf, int lane)
+__device__ __forceinline__ void softmax_publish(const float (&s)[2][2], KeyState<GQ> &W, PairLds<GQ> &L, int unit, int lane)
 {
+    const int buf = unit & 1;
     const int n = lane & 15, rq = lane >> 4;
     const float mx0 = fmaxf(s[0][0], s[1][0]), mx1 = fmaxf(s[0][1], s[1][1]);
-    const bool grow = __any((mx0 > W.m[0] + 1.0f) || (mx1 > W.m[1] + 1.0f));
+    const bool grow = __builtin_amdgcn_ballot_w64((mx0 > W.m[0] + 1.0f) || (mx1 > W.m[1] + 1.0f)) != 0;
     if (grow) {
-        const float mn0 = fmaxf(W.m[0], row_max16(mx0)), mn1 = fmaxf(W.m[1], row_max16(mx1));
+        float rm0 = mx0, rm1 = mx1;
+        row_max16(rm0, rm1);
+        const float mn0 = fmaxf(W.m[0], rm0), mn1 = fmaxf(W.m[1], rm1);
         const float a0 = __builtin_amdgcn_exp2f(W.m[0] - mn0), a1 = __builtin_amdgcn_exp2f(W.m[1] - mn1);
         W.l[0] *= a0; W.l[1] *= a1;
         W.m[0] = mn0; W.m[1] = mn1;
         L.alpha[buf][2 * rq] = a0;            // the 16 lanes of a row write the same value
         L.alpha[buf][2 * rq + 1] = a1;
     }
-    if (lane == 0) L.rescale[buf][0] = grow ? 1 : 0;
+    if (lane == 0) L.rescale[buf][0] = grow && unit > 0 ? 1 : 0;       // (in front of the first unit nothing has been accumulated)
 #pragma unroll
     for (int hh = 0; hh < 2; hh++) {
         const float p0 = __builtin_amdgcn_exp2f(s[0][hh] - W.m[hh]), p1 = __builtin_amdgcn_exp2f(s[1][hh] - W.m[hh]);
@@ -764,13 +790,14 @@ __device__ __forceinline__ void output_packed(const CodeRegs<VB> &blk, uint32_t 
         W.accz[j] = fmaf(pp.x, half_lo(blk.z), fmaf(pp.y, half_hi(blk.z), W.accz[j]));
     }
     wave_lds_sync();
+    half8 Aop[4];
+    read_operands(Aop, &L.Av[0].at[Q.row][8 * rq], sizeof(L.Av[0]) / sizeof(_Float16));
 #pragma unroll
     for (int gd = 0; gd < 4; gd++) {
-        const half8 Aop = *reinterpret_cast<const half8 *>(&L.Av[gd].at[n][8 * rq]);
 #pragma unroll
         for (int c2 = 0; c2 < 2; c2++) {
             const int cblk = 2 * gd + c2;
-            W.O[cblk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, codes_operand<VB>(blk, cblk), W.O[cblk], 0, 0, 0);
+            W.O[cblk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop[gd], codes_operand<VB>(blk, cblk), W.O[cblk], 0, 0, 0);
         }
     }
 }
@@ -975,9 +1002,9 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     // tokens: two or three blocks behind are 3-5 % slower for 4- and 2-bit codes and no faster for 8-bit ones: the
     // memory system is the queue here, more requests in it only wait longer).
     constexpr int DK = 2, DV = 2;
-    // a group without blocks asks for its window rows before anything else (not where a tile of 8 heads has to make do with a
-    // quarter of a SIMD's registers: it would spill)
-    constexpr bool kEarlyRows = !(kFast && GQ == 8 && resident_waves<KB, VB, PAIRS>() == 4);
+    // a group without blocks asks for its window rows before it waits for the queries (in the streaming form behind them: that path would hold
+    // registers of the rows over the loop, which has none to spare)
+    constexpr bool kEarlyRows = !kFast || PAIRS > 1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
     const int n = lane & 15, rq = lane >> 4;
@@ -996,7 +1023,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 
     __shared__ PairLds<GQ> Ls[PAIRS];
     PairLds<GQ> &L = Ls[pair];
-    __shared__ __attribute__((aligned(16))) _Float16 aq_lds[16][kD + 8];
+    __shared__ __attribute__((aligned(16))) _Float16 aq_lds[PAIRS][GQ][kD + 8];
 
     // ---- work of this group: units [u0, u1) = quantized blocks, then chunks of <= 32 fp16 window tokens; of this pair: `blocks`
     // blocks from block u0 on, then `chunks` chunks from first_chunk on.
@@ -1045,7 +1072,8 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         const int r = i + rot2;
         return u0 + (r < n2p ? r : r - n2p);
     };
-    auto blk1c = [&](int i) { return i < n1 ? blk1(i) : 0; };     // past the range: any number, the load is an empty one
+    auto blk1c = [&](int i) { return i < n1 ? blk1(i) : u0; };    // past the range: any number, the load is an empty one
+    auto after = [&](int blk) { return blk + 1 < u0 + n1 ? blk + 1 : u0; };                // the block behind blk in the sweep
     // byte offset, in the cache's exponent array, of the word this lane holds for the chunk that starts at step c0
     auto exp_offset = [&](int c0) {
         const int i = c0 + lane;
@@ -1056,7 +1084,8 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     QueryRegs<GQ> Q;
     Q.nvalid = nvalid;
     Q.c = a.scale_log2e;
-    Q.Aq = &aq_lds[0][0];
+    Q.row = n < 2 * nvalid ? n : 2 * nvalid - 2 + (n & 1);
+    Q.Aq = &aq_lds[pair][Q.row >> 1][8 * rq];
     const uint8_t *queries = reinterpret_cast<const uint8_t *>(a.q + qrow0 * kD);       // of the tile's first head
 
     if (key_wave) {
@@ -1066,12 +1095,13 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 #pragma unroll
         for (int j = 0; j < GQ; j++) {
             const uint32_t off = (uint32_t)((j < nvalid ? j : 0) * (kD * 2) + 4 * lane);
-            qw[j] = 0;
-            if constexpr (kFast) issue_query(qw[j], queries, off);
-            else qw[j] = *reinterpret_cast<const uint32_t *>(queries + off);
+            if constexpr (kFast) {
+                undefined(qw[j]);
+                issue_query(qw[j], queries, off);
+            } else qw[j] = *reinterpret_cast<const uint32_t *>(queries + off);
         }
-        const BlockStream KS = block_stream(a.lv, false, blk0, a.n_blocks, lane, NARROW);
-        uint32_t kexp = 0;                               // exponent words of the chunk's blocks, one per lane
+        BlockStream KS = block_stream(a.lv, false, blk0, a.n_blocks, lane, NARROW);
+        uint32_t kexp;                                   // exponent words of the chunk's blocks, one per lane
         CodeRegs<KB> kr[DK];
         // per-channel keys: the zero-points do not come with the blocks but for kZChunk blocks at a time, as the operand
         // of one matrix product (zero_point_terms), which saves 4 of the 12 matrix instructions of a block's scores
@@ -1087,25 +1117,23 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         };
         if constexpr (kFast) {
 #pragma unroll
-            for (int d = 0; d < DK; d++) clear_regs(kr[d]);
+            for (int d = 0; d < DK; d++) undefined_regs(kr[d]);
+            undefined(kexp);
             issue_exponents(kexp, KS, exp_offset(0));
             if constexpr (kZB) {
 #pragma unroll
-                for (int cb = 0; cb < 4; cb++) zb[cb] = u32x4{0u, 0u, 0u, 0u};
+                for (int cb = 0; cb < 4; cb++) undefined(zb[cb]);
                 issue_zero_points(zb, KS, n1 > 0, zero_point_offset(0));
             }
 #pragma unroll
-            for (int d = 0; d < DK - 1; d++) issue_block<KB, NARROW, !kZB>(KS, d < n1, blk1c(d), kr[d]);
-        }
-        {
-            // A-tile rows of heads that do not exist are never written: they must read as zero
-            const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
-            for (int i = lane; i < (16 - row0) * (kD + 8) / 8; i += 64)
-                reinterpret_cast<uint4 *>(&L.Ak[row0][0])[i] = make_uint4(0, 0, 0, 0);
+            for (int d = 0; d < DK - 1; d++) {
+                end_unless(d < n1, KS);
+                issue_block<KB, NARROW, !kZB>(KS, blk1c(d), kr[d]);
+            }
         }
         if constexpr (kFast) await_queries<1 + (kZB ? 4 : 0) + (DK - 1) * NLK>(qw);
 #pragma unroll
-        for (int j = 1; j < GQ; j++) qw[j] = j < nvalid ? qw[j] : 0u;
+        for (int j = 0; j < GQ; j++) *reinterpret_cast<uint32_t *>(&aq_lds[pair][j][2 * lane]) = qw[j];
         {
             // queries divided by a power of two that brings the largest to [0.5, 1).  Per-channel keys: with the softmax
             // constant folded in, for the q * s operand.  Per-token keys: the raw fp16 queries, scaled exactly.
@@ -1145,6 +1173,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                     if (n == 0) qs_lds[4 * j + rq] = part * Q.c;
                 }
                 wave_lds_sync();
+                if constexpr (kPairs > 1) read_operands(Q.At, &L.Ak[Q.row][8 * rq], 32);
 #pragma unroll
                 for (int hh = 0; hh < 2; hh++)
 #pragma unroll
@@ -1163,7 +1192,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         // those (16-bit keys: a pipeline of their own)
         KeyRows rows;
         if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);
-        wg_barrier();                                   // the value wave has written the exact-fp16 query tile
+        wave_lds_sync();                                // the query tile
         KeyState<GQ> W;
 #pragma unroll
         for (int i = 0; i < 2; i++) { W.m[i] = -INFINITY; W.l[i] = 0.0f; }
@@ -1182,7 +1211,8 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             if (n1 > 0) {
                 await_exponents<(DK - 1) * NLK>(kexp);                         // the first chunk's: issued ahead of the first blocks
                 const PrioritySteps prio = priority_steps(n1);
-                __builtin_amdgcn_s_setprio(3);
+                int next = blk1c(DK - 1);
+                if constexpr (PAIRS == 1) __builtin_amdgcn_s_setprio(3);
                 for (int c0 = 0; c0 < n1; c0 += kChunk) {
                     if (c0 > 0) {
                         issue_exponents(kexp, KS, exp_offset(c0));
@@ -1206,16 +1236,18 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 #pragma unroll
                             for (int d = 0; d < DK; d++) {
                                 if (more) {
-                                    priority_at_step(i, prio);
-                                    issue_block<KB, NARROW, !kZB>(KS, i + DK - 1 < n1, blk1c(i + DK - 1), kr[(d + DK - 1) % DK]);
-                                    if constexpr (kZB) await_loads_either<(DK - 1) * NLK, 4, KB>(kr[d], __builtin_amdgcn_readfirstlane(i == z0 ? 1 : 0));
+                                    if constexpr (PAIRS == 1) priority_at_step(i, prio);
+                                    end_unless(i + DK - 1 < n1, KS);
+                                    issue_block<KB, NARROW, !kZB>(KS, next, kr[(d + DK - 1) % DK]);
+                                    next = after(next);
+                                    if constexpr (kZB) await_loads_either<(DK - 1) * NLK, 4, KB>(kr[d], i, z0);
                                     else await_block<KB, DK>(kr[d]);
                                     const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)kexp, i - c0);
                                     if constexpr (KPT) scores_packed_per_token<KB, GQ, NARROW>(kr[d], Q, L, lane, s);
                                     else if constexpr (kZB)
                                         scores_packed<KB, GQ, NARROW, true>(kr[d], ew, Q, L, lane, s, *reinterpret_cast<const float2 *>(&L.Zt[i - z0][rq][0]));
                                     else scores_packed<KB, GQ, NARROW>(kr[d], ew, Q, L, lane, s);
-                                    softmax_publish<GQ>(s, W, L, i & 1, lane);
+                                    softmax_publish<GQ>(s, W, L, i, lane);
                                     wg_barrier();
                                     more = ++i < zend;
                                 }
@@ -1223,7 +1255,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                         }
                     }
                 }
-                __builtin_amdgcn_s_setprio(0);
+                if constexpr (PAIRS == 1) __builtin_amdgcn_s_setprio(0);
                 drain();
                 if (chunks > 0) fetch_chunk(window_chunk(a, false, bh, first_chunk), lane, rows);    // (here: on no path is `rows` held over the loop)
             } else {
@@ -1239,7 +1271,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             auto step = [&](int i, const KeyRows &x, KeyRows &y) {
                 fetch_unit(base, i + 1 < n2p, blk2(i + 1), lane, y);
                 scores_rows<GQ>(x, 32, Q, lane, s);
-                softmax_publish<GQ>(s, W, L, i & 1, lane);
+                softmax_publish<GQ>(s, W, L, i, lane);
                 wg_barrier();
             };
             for (int i = 0; i < n2p; i += 2) {
@@ -1251,11 +1283,11 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             for (int i = 0; i < n2p; i++) {
                 const int u = blk2(i);
                 CodeRegs<KB> r;
-                clear_regs(r);
+                undefined_regs(r);
                 load_block_now<KB, NARROW>(KS, u, r);
                 if constexpr (KPT) scores_packed_per_token<KB, GQ, NARROW>(r, Q, L, lane, s);
                 else scores_packed<KB, GQ, NARROW>(r, a.lv.bexp[blk0 + u], Q, L, lane, s);
-                softmax_publish<GQ>(s, W, L, i & 1, lane);
+                softmax_publish<GQ>(s, W, L, i, lane);
                 wg_barrier();
             }
         }
@@ -1266,14 +1298,15 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             keep_new_row(w, lane);
             scores_rows<GQ>(rows, w.nt, Q, lane, s);
             if (i + 1 < chunks) fetch_chunk(window_chunk(a, false, bh, first_chunk + i + 1), lane, rows);
-            softmax_publish<GQ>(s, W, L, (n1 + n2p + i) & 1, lane);
+            softmax_publish<GQ>(s, W, L, n1 + n2p + i, lane);
             wg_barrier();
         }
         wg_barrier();                                   // the value wave consumes the last unit
         // ---- result of the key wave: reference max and sum per head
+        row_sum16(W.l[0], W.l[1]);
 #pragma unroll
         for (int hh = 0; hh < 2; hh++) {
-            const float lsum = row_sum16(W.l[hh]);
+            const float lsum = W.l[hh];
             const int j = 2 * rq + hh;
             if constexpr (PAIRS > 1) {
                 if (n == 0) *reinterpret_cast<float2 *>(&L.Zt[j][0][0]) = make_float2(W.m[hh], lsum);
@@ -1284,53 +1317,26 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
         }
     } else {
         // =========================================================== value wave (one unit behind the key wave)
-        // rows 2j and 2j + 1 of the exact-fp16 query tile (16 rows x 256 bytes); rows of absent heads are zero.
-        // The loads are issued in the order in which their results are needed: queries, then the first blocks.
-        // (16-byte pieces of rows 4 pass + rq; with two pairs of waves, each value wave has half of the passes)
-        constexpr int kPasses = GQ / 2 / PAIRS;
-        const int pass0 = PAIRS > 1 ? pair * kPasses : 0;
-        u32x4 qx[kPasses];
-#pragma unroll
-        for (int p = 0; p < kPasses; p++) {
-            const int jr = (4 * (pass0 + p) + rq) >> 1;
-            const uint32_t off = (uint32_t)((jr < nvalid ? jr : 0) * (kD * 2) + 16 * n);
-            qx[p] = u32x4{0u, 0u, 0u, 0u};
-            if constexpr (kFast) issue_query(qx[p], queries, off);
-            else qx[p] = *reinterpret_cast<const u32x4 *>(queries + off);
-        }
-        const BlockStream VS = block_stream(a.lv, true, blk0, a.n_blocks, lane, NARROW);
-        uint32_t vexp = 0;
+        BlockStream VS = block_stream(a.lv, true, blk0, a.n_blocks, lane, NARROW);
+        uint32_t vexp;
         CodeRegs<VB> vr[DV];
         if constexpr (kFast) {
 #pragma unroll
-            for (int d = 0; d < DV; d++) clear_regs(vr[d]);
+            for (int d = 0; d < DV; d++) undefined_regs(vr[d]);
+            undefined(vexp);
             issue_exponents(vexp, VS, exp_offset(0));
 #pragma unroll
-            for (int d = 0; d < DV - 1; d++) issue_block<VB, NARROW>(VS, d < n1, blk1c(d), vr[d]);
+            for (int d = 0; d < DV - 1; d++) {
+                end_unless(d < n1, VS);
+                issue_block<VB, NARROW>(VS, blk1c(d), vr[d]);
+            }
         }
         ValueRows rows;                                 // (as in the key wave)
         u32x2 fresh;
         if constexpr (VB == 16) fetch_unit(a.lv.vcode + blk0 * block_code_bytes(16), n2p > 0, n2p > 0 ? blk2(0) : 0, lane, rows);
-        {
-            // rows of heads that do not exist: lane row rq clears those of its channel group
-            const int row0 = 2 * (GQ == 8 ? nvalid : GQ);
-            for (int i = n; i < (16 - row0) * (32 + 8) / 8; i += 16)
-                reinterpret_cast<uint4 *>(&L.Av[rq].at[row0][0])[i] = make_uint4(0, 0, 0, 0);
-            if constexpr (GQ == 4) {
-#pragma unroll
-                for (int p = 0; p < kPasses; p++) *reinterpret_cast<uint4 *>(&aq_lds[8 + 4 * (pass0 + p) + rq][8 * n]) = make_uint4(0, 0, 0, 0);
-            }
-        }
-        if constexpr (kFast) await_queries<1 + (DV - 1) * block_loads<VB>()>(qx);
-#pragma unroll
-        for (int p = 0; p < kPasses; p++) {
-            const int row = 4 * (pass0 + p) + rq;
-            *reinterpret_cast<u32x4 *>(&aq_lds[row][8 * n]) = (row >> 1) < nvalid ? qx[p] : u32x4{0u, 0u, 0u, 0u};
-        }
         Q.vw0 = code_weight_inv<VB < 16 ? VB : 8>((2 * n) & 7);
         Q.vw1 = code_weight_inv<VB < 16 ? VB : 8>((2 * n + 1) & 7);
         if (kEarlyRows && n1 == 0 && n2p == 0 && chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
-        wg_barrier();                                   // query tile handed to the key wave
         ValueState<GQ> W;
 #pragma unroll
         for (int cblk = 0; cblk < 8; cblk++) W.O[cblk] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
@@ -1346,8 +1352,12 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             };
             if (n1 > 0) {
                 await_exponents<(DV - 1) * block_loads<VB>()>(vexp);
+                // (the first block's: nothing has to be re-based for it)
+                W.ev = (int)((uint32_t)__builtin_amdgcn_readlane((int)vexp, 0) >> 16) - 32768;
+                W.ev = W.ev > -100 ? W.ev : -100;
                 const PrioritySteps prio = priority_steps(n1);
-                __builtin_amdgcn_s_setprio(3);
+                int next = blk1c(DV - 1);
+                if constexpr (PAIRS == 1) __builtin_amdgcn_s_setprio(3);
                 for (int c0 = 0; c0 < n1; c0 += kChunk) {
                     if (c0 > 0) {
                         issue_exponents(vexp, VS, exp_offset(c0));
@@ -1359,8 +1369,10 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
 #pragma unroll
                         for (int d = 0; d < DV; d++) {
                             if (more) {
-                                priority_at_step(i, prio);
-                                issue_block<VB, NARROW>(VS, i + DV - 1 < n1, blk1c(i + DV - 1), vr[(d + DV - 1) % DV]);
+                                if constexpr (PAIRS == 1) priority_at_step(i, prio);
+                                end_unless(i + DV - 1 < n1, VS);
+                                issue_block<VB, NARROW>(VS, next, vr[(d + DV - 1) % DV]);
+                                next = after(next);
                                 await_block<VB, DV>(vr[d]);
                                 const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)vexp, i - c0);
                                 // (always true here; as a run-time test it keeps the rarely taken re-base and rescale
@@ -1375,7 +1387,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                         }
                     }
                 }
-                __builtin_amdgcn_s_setprio(0);
+                if constexpr (PAIRS == 1) __builtin_amdgcn_s_setprio(0);
                 drain();
                 if (chunks > 0) fetch_chunk(window_chunk(a, true, bh, first_chunk), lane, rows, fresh);
             } else {
@@ -1389,7 +1401,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                 const int u = blk2(i);
                 apply_rescale<GQ>(W, L, i & 1, lane);
                 CodeRegs<VB> r;
-                clear_regs(r);
+                undefined_regs(r);
                 load_block_now<VB, NARROW>(VS, u, r);
                 output_packed<VB, GQ, NARROW>(r, a.lv.bexp[blk0 + u], Q, W, L, i & 1, lane);
                 wg_barrier();
@@ -1414,10 +1426,12 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
                 }
             }
             wave_lds_sync();
+            // sum_t p_t z_tg of this lane's channel group (lane >> 4), over the 16 lanes that hold its tokens
+#pragma unroll
+            for (int j = 0; j < GQ; j += 4) row_sum16(W.accz[j], W.accz[j + 1], W.accz[j + 2], W.accz[j + 3]);
 #pragma unroll
             for (int j = 0; j < GQ; j++) {
-                // sum_t p_t z_tg of this lane's channel group (lane >> 4), over the 16 lanes that hold its tokens
-                const float az = row_sum16(W.accz[j]);
+                const float az = W.accz[j];
                 float2 *t = reinterpret_cast<float2 *>(&o_lds[j * kD + 2 * lane]);
                 *t = make_float2(t->x + az, t->y + az);
             }
@@ -1484,7 +1498,6 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     }
 }
 
-constexpr int kPairs = KVQ_DECODE_PAIRS;
 using Args = KernelArgs<kPairs>;
 
 struct LaunchEvents { hipEvent_t begin, end; };

@@ -177,16 +177,16 @@ def test_decode_check_follows_every_path_to_the_streaming_loop():
     assert plants >= 4 * (3 + 3 + 3 + 2)
 
 
-@pytest.mark.parametrize("src,pairs", [("kvq_decode_mfma.hip", 1), ("kvq_decode_short.hip", 2)])
-def test_decode_kernels_wait_for_nothing_between_queries_and_first_blocks(src, pairs):
-    """Both roles ask for their queries, then for the first blocks, and the wait for the queries leaves exactly the blocks' loads in
+@pytest.mark.parametrize("src", ["kvq_decode_mfma.hip", "kvq_decode_short.hip"])
+def test_decode_kernels_wait_for_nothing_between_queries_and_first_blocks(src):
+    """The key wave asks for its queries, then for the first blocks, and the wait for the queries leaves exactly the blocks' loads in
     flight.  A wait of the compiler's in between (it knows of none of these loads) would put a memory round trip in front of the
     blocks; a count that is one too high would let the queries be read before they are there."""
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
     from paper_2502_04420_amd import build as B
 
-    roles = 0
+    kernels = 0
     for name, body in B.kernel_bodies(B.device_assembly(src), "decode_mfma"):
         kb, vb, gq = (int(x) for x in re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)E", name).groups())
         if 16 in (kb, vb):                                               # (their queries are ordinary loads)
@@ -201,10 +201,10 @@ def test_decode_kernels_wait_for_nothing_between_queries_and_first_blocks(src, p
                 behind += 1
             elif queries and (by_hand or "vmcnt" in line) and line.startswith("s_waitcnt"):
                 assert by_hand and line == "s_waitcnt vmcnt(%d)" % behind, (name, line, behind)
-                assert queries in (gq, gq // 2 // pairs) and behind > 3, (name, queries, behind)
-                queries, behind, roles = 0, 0, roles + 1
+                assert queries == gq and behind > 3, (name, queries, behind)
+                queries, behind, kernels = 0, 0, kernels + 1
         assert queries == 0, name
-    assert roles == 2 * 3 * 3 * 2 * 2 * 2                                # roles, key and value bits, head tiles, scale precisions, key groupings
+    assert kernels == 3 * 3 * 2 * 2 * 2                                  # key and value bits, head tiles, scale precisions, key groupings
 
 
 def _record_bytes(asm, name):
