@@ -582,8 +582,8 @@ __device__ __forceinline__ void scores_packed_per_token(const CodeRegs<KB> &blk,
 
 // keys: tokens n and 16 + n, channels 32 cb + 8 rq .. + 7
 struct KeyRows { u32x4 lo[4], hi[4]; };
-// values: tokens 16 half + i, channels 4 (lane & 31) .. + 3 (half = lane >> 5): one load fetches two whole rows
-struct ValueRows { u32x2 row[16]; };
+// values: tokens 8 rq + i, channels 8 n .. + 7: one load fetches four whole rows
+struct ValueRows { u32x4 row[8]; };
 
 // One unit (32 rows of 256 bytes) of a 16-bit layer.  Issued unconditionally, past the end of a range through a resource
 // with no bytes in range (no traffic, zeros): the number of loads behind a unit is then the same on every path, and the
@@ -608,9 +608,9 @@ __device__ __forceinline__ void fetch_unit(const uint8_t *base, bool real, int u
 __device__ __forceinline__ void fetch_unit(const uint8_t *base, bool real, int unit, int lane, ValueRows &x)
 {
     const RowStream r = row_stream(base, real, unit);
-    const int off = (lane >> 5) * (16 * kD * 2) + (lane & 31) * 8;
+    const int off = (lane >> 4) * (8 * kD * 2) + (lane & 15) * 16;
 #pragma unroll
-    for (int i = 0; i < 16; i++) x.row[i] = __builtin_amdgcn_raw_buffer_load_b64(r, off + i * (kD * 2), 0, kNonTemporal);
+    for (int i = 0; i < 8; i++) x.row[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + i * (kD * 2), 0, kNonTemporal);
 }
 
 // A chunk of nt <= 32 window tokens from position pos0 on: rows of the ring of RC >= 32 slots, except for the token of a fused
@@ -663,27 +663,28 @@ __device__ __forceinline__ void fetch_chunk(const WindowChunk &w, int lane, KeyR
     }
 }
 // values: the ring's rows by 32-bit offsets; the appended row comes in `fresh` and takes its place in settle_chunk
-__device__ __forceinline__ void fetch_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x2 &fresh)
+__device__ __forceinline__ void fetch_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x4 &fresh)
 {
     const uint8_t *ring = reinterpret_cast<const uint8_t *>(w.ring);
     asm volatile("" : "+v"(lane));
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-        const int t = 16 * (lane >> 5) + i, tc = t < w.nt ? t : w.nt - 1;
+    for (int i = 0; i < 8; i++) {
+        const int t = 8 * (lane >> 4) + i, tc = t < w.nt ? t : w.nt - 1;
         int slot = w.slot0 + tc;
         slot = slot >= w.RC ? slot - w.RC : slot;
-        x.row[i] = *reinterpret_cast<const u32x2 *>(ring + (uint32_t)(slot * (kD * 2) + 8 * (lane & 31)));
+        x.row[i] = *reinterpret_cast<const u32x4 *>(ring + (uint32_t)(slot * (kD * 2) + 16 * (lane & 15)));
     }
-    fresh = *reinterpret_cast<const u32x2 *>((w.new_row ? w.new_row : w.ring + (size_t)w.slot0 * kD) + 4 * (lane & 31));
+    // (the caller's rows: fp16 alignment is all they owe)
+    __builtin_memcpy(&fresh, (w.new_row ? w.new_row : w.ring + (size_t)w.slot0 * kD) + 8 * (lane & 15), sizeof fresh);
 }
-__device__ __forceinline__ void settle_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x2 fresh)
+__device__ __forceinline__ void settle_chunk(const WindowChunk &w, int lane, ValueRows &x, u32x4 fresh)
 {
     if (w.new_row) {
         asm volatile("" : "+v"(lane));
 #pragma unroll
-        for (int i = 0; i < 16; i++) {                           // (rows past the end too: the ring's may never have been written)
-            const bool mine = 16 * (lane >> 5) + i >= w.nt - 1;
-            x.row[i] = u32x2{mine ? fresh[0] : x.row[i][0], mine ? fresh[1] : x.row[i][1]};
+        for (int i = 0; i < 8; i++) {                            // (rows past the end too: the ring's may never have been written)
+            const bool mine = 8 * (lane >> 4) + i >= w.nt - 1;
+            x.row[i] = mine ? fresh : x.row[i];
         }
     }
 }
@@ -802,45 +803,56 @@ __device__ __forceinline__ void output_packed(const CodeRegs<VB> &blk, uint32_t 
     }
 }
 
-// output contribution of 32 fp16 rows (numerators of rows past the end are zero): this lane's 4 channels over the 16 tokens
-// of its half; the halves are added at the end (add_row_outputs)
+// Output contribution of 32 fp16 rows (numerators of rows past the end are zero).  The rows are the B operand as they are, but for the order: a lane
+// has 8 channels of 8 tokens, and operand e is the 8 tokens of channel 8 n + e, one byte permutation per pair of tokens.  The numerators are the A
+// operand, read from the hand-off tile: 2^12 p as a high and a low fp16 part (p <= 2; together 22 bits of p, down to 2^-36).
+// R[e]: rows 4 rq + i as everywhere (high and low parts of heads 2 rq, 2 rq + 1), channel 8 n + e, times 2^12.
+// With vector multiply-adds instead (16 tokens x 4 channels x the heads, 256 instructions for 4 heads against 75 here) this was the
+// longest step of a short call: a chunk took the value wave 1.1 us, 0.35 now.
+constexpr float kRowLift = 4096.0f;
 template <int GQ>
-__device__ __forceinline__ void output_rows(const ValueRows &x, float (&oF)[GQ][4], const PairLds<GQ> &L, int buf, int lane)
+__device__ __forceinline__ void output_rows(const ValueRows &x, float4v (&R)[8], const QueryRegs<GQ> &Q, const PairLds<GQ> &L, int buf, int lane)
 {
-    const int half = lane >> 5;
+    const int rq = lane >> 4;
+    const float *p = &L.P[buf][Q.row >> 1][8 * rq];
+    const float4v pa = *reinterpret_cast<const float4v *>(p), pb = *reinterpret_cast<const float4v *>(p + 4);
+    const float pp[8] = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+    uint32_t a[4];
 #pragma unroll
-    for (int i0 = 0; i0 < 16; i0 += 4) {
+    for (int k = 0; k < 4; k++) {
+        uint32_t hi, lo;
+        split_pair(pp[2 * k] * kRowLift, pp[2 * k + 1] * kRowLift, hi, lo);
+        a[k] = lane & 1 ? lo : hi;
+    }
+    const half8 Aop = as_half8(a[0], a[1], a[2], a[3]);
 #pragma unroll
-        for (int j = 0; j < GQ; j++) {
-            const float4 p4 = *reinterpret_cast<const float4 *>(&L.P[buf][j][16 * half + i0]);
-            const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+    for (int e = 0; e < 8; e++) {
+        uint32_t b[4];
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const uint32_t w0 = x.row[i0 + k][0], w1 = x.row[i0 + k][1];
-                oF[j][0] = fmaf(p[k], half_lo(w0), oF[j][0]);
-                oF[j][1] = fmaf(p[k], half_hi(w0), oF[j][1]);
-                oF[j][2] = fmaf(p[k], half_lo(w1), oF[j][2]);
-                oF[j][3] = fmaf(p[k], half_hi(w1), oF[j][3]);
-            }
-            // (left alone, the compiler fetches all numerators up front, puts the sums off until after the next loads and spills)
-            asm volatile("" : "+v"(oF[j][0]), "+v"(oF[j][1]), "+v"(oF[j][2]), "+v"(oF[j][3]));
-            if (j % 4 == 3) asm volatile("" ::: "memory");
+        for (int k = 0; k < 4; k++) {
+            const uint32_t w0 = x.row[2 * k][e >> 1], w1 = x.row[2 * k + 1][e >> 1];
+            b[k] = __builtin_amdgcn_perm(w1, w0, e & 1 ? 0x07060302u : 0x05040100u);
         }
+        R[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Aop, as_half8(b[0], b[1], b[2], b[3]), R[e], 0, 0, 0);
     }
 }
 
-// shrink: what the outputs of the blocks before the rows (already out of the registers) are to be multiplied by
+// high + low parts.  A value that is infinite makes the high part infinite and the low part infinite or, where the numerator has no
+// low part, not a number: then the high part is the sum.  (Where a value is no number, both are none.)
+__device__ __forceinline__ float join_parts(float hi, float lo)
+{
+    return hi + (lo == lo ? lo : 0.0f);
+}
+
+// shrink: what the outputs of the blocks before the rows (already out of the registers) are to be multiplied by, heads 2 rq and 2 rq + 1
 template <int GQ>
-__device__ __forceinline__ void rescale_rows(float (&oF)[GQ][4], float (&shrink)[GQ], const PairLds<GQ> &L, int buf)
+__device__ __forceinline__ void rescale_rows(float4v (&R)[8], float2 &shrink, const PairLds<GQ> &L, int buf, int lane)
 {
     if (__builtin_amdgcn_readfirstlane(L.rescale[buf][0])) {
+        const float2 al = *reinterpret_cast<const float2 *>(&L.alpha[buf][2 * (lane >> 4)]);
+        shrink = make_float2(shrink.x * al.x, shrink.y * al.y);
 #pragma unroll
-        for (int j = 0; j < GQ; j++) {
-            const float aj = L.alpha[buf][j];
-            shrink[j] *= aj;
-#pragma unroll
-            for (int k = 0; k < 4; k++) oF[j][k] *= aj;
-        }
+        for (int e = 0; e < 8; e++) R[e] = float4v{R[e][0] * al.x, R[e][1] * al.x, R[e][2] * al.y, R[e][3] * al.y};
     }
 }
 
@@ -1332,7 +1344,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             }
         }
         ValueRows rows;                                 // (as in the key wave)
-        u32x2 fresh;
+        u32x4 fresh;
         if constexpr (VB == 16) fetch_unit(a.lv.vcode + blk0 * block_code_bytes(16), n2p > 0, n2p > 0 ? blk2(0) : 0, lane, rows);
         Q.vw0 = code_weight_inv<VB < 16 ? VB : 8>((2 * n) & 7);
         Q.vw1 = code_weight_inv<VB < 16 ? VB : 8>((2 * n + 1) & 7);
@@ -1437,16 +1449,17 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             }
             wave_lds_sync();
         }
-        float oF[GQ][4], shrink[GQ];                    // contributions of fp16 rows: see output_rows, rescale_rows
+        float4v R[8];                                   // contributions of fp16 rows: see output_rows, rescale_rows
+        float2 shrink = make_float2(1.0f, 1.0f);
 #pragma unroll
-        for (int j = 0; j < GQ; j++) { oF[j][0] = oF[j][1] = oF[j][2] = oF[j][3] = 0.0f; shrink[j] = 1.0f; }
+        for (int e = 0; e < 8; e++) R[e] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (VB == 16) {
             const uint8_t *base = a.lv.vcode + blk0 * block_code_bytes(16);
             ValueRows next;
             auto step = [&](int i, const ValueRows &x, ValueRows &y) {
                 fetch_unit(base, i + 1 < n2p, blk2(i + 1), lane, y);
-                rescale_rows<GQ>(oF, shrink, L, i & 1);
-                output_rows<GQ>(x, oF, L, i & 1, lane);
+                rescale_rows<GQ>(R, shrink, L, i & 1, lane);
+                output_rows<GQ>(x, R, Q, L, i & 1, lane);
                 wg_barrier();
             };
             for (int i = 0; i < n2p; i += 2) {
@@ -1461,24 +1474,30 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
             const WindowChunk w = window_chunk(a, true, bh, first_chunk + i);
             keep_new_row(w, lane);
             settle_chunk(w, lane, rows, fresh);
-            rescale_rows<GQ>(oF, shrink, L, buf);
-            output_rows<GQ>(rows, oF, L, buf, lane);
+            rescale_rows<GQ>(R, shrink, L, buf, lane);
+            output_rows<GQ>(rows, R, Q, L, buf, lane);
             if (i + 1 < chunks) fetch_chunk(window_chunk(a, true, bh, first_chunk + i + 1), lane, rows, fresh);
             wg_barrier();
         }
         // ---- result of the value wave: un-normalised output per head and channel
         if (n2 > 0) {
-            // the fp16 rows' part: the two halves of the wave hold the same channels over different tokens
+            // the fp16 rows' part: channels 8 n .. + 7 of heads 2 rq and 2 rq + 1
 #pragma unroll
-            for (int j = 0; j < GQ; j++) {
-                float r[4];
+            for (int hh = 0; hh < 2; hh++) {
+                const int j = 2 * rq + hh;
+                if (j >= GQ) continue;
+                float r[8];
 #pragma unroll
-                for (int k = 0; k < 4; k++) r[k] = oF[j][k] + __shfl_xor(oF[j][k], 32, 64);
-                if (lane < 32) {
-                    float4 *o = reinterpret_cast<float4 *>(&o_lds[j * kD + 4 * lane]);
-                    const float4 t = staged ? *o : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    *o = make_float4(fmaf(t.x, shrink[j], r[0]), fmaf(t.y, shrink[j], r[1]), fmaf(t.z, shrink[j], r[2]), fmaf(t.w, shrink[j], r[3]));
+                for (int e = 0; e < 8; e++) r[e] = (1.0f / kRowLift) * join_parts(R[e][2 * hh], R[e][2 * hh + 1]);
+                float4v *o = reinterpret_cast<float4v *>(&o_lds[j * kD + 8 * n]);
+                float4v o0 = {r[0], r[1], r[2], r[3]}, o1 = {r[4], r[5], r[6], r[7]};
+                if (staged) {
+                    const float f = hh ? shrink.y : shrink.x;
+                    o0 += f * o[0];
+                    o1 += f * o[1];
                 }
+                o[0] = o0;
+                o[1] = o1;
             }
             wave_lds_sync();
         }

@@ -1,0 +1,96 @@
+"""fp16 rows of a decode call (the window, 16-bit layers): the values go through the matrix cores, their numerators as two fp16
+parts.  Against the oracle with the bars of the parity tests, and where those parts could matter against 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import kvq_workloads as W
+from test_gpu_parity import assert_outputs_close, kvq_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _odd(x):
+    """A contiguous copy on the GPU that begins two bytes behind an aligned address."""
+    t = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+    return t.copy_(x)
+
+
+@pytest.mark.parametrize("kb,vb", [(4, 2), (8, 16), (16, 4), (16, 16)])
+@pytest.mark.parametrize("gq,hkv,batch,T,residual", [
+    (1, 2, 1, 1, 32), (4, 2, 1, 31, 32), (3, 2, 1, 33, 32),              # window only: one row, one chunk less one, two chunks
+    (5, 1, 2, 32 * 6 + 7, 128), (8, 2, 1, 32 * 5 + 31, 64), (12, 1, 1, 70, 32),
+    (4, 8, 160, 40, 32), (7, 4, 300, 32 + 9, 32),                        # more work-groups than are resident: one pair of waves each
+])
+def test_rows_and_appended_rows(kvq_mod, oracle_mod, gq, hkv, batch, T, residual, kb, vb):
+    """Every kind of row position: rows of the ring, the appended one (from the caller's tensors, at odd addresses), rows past the end."""
+    w = W.Workload("rows", 1, batch, gq * hkv, hkv, 128, T, [kb], [vb], seed=7 + T + gq, outlier_channels=3)
+    g = kvq_mod.KVQ(1, batch, gq * hkv, hkv, 128, T + 40, [kb], [vb], residual=residual)
+    g.workspace.fill_(0xff)                                              # a row that was never written reads as NaN
+    o = oracle_mod.OracleCache(1, batch, gq * hkv, hkv, 128, [kb], [vb], residual=residual)
+    K, V = W.kv_tokens(w, 0, 0, T + 2)
+    if T > 1:
+        g.quantize_append(0, _odd(K[:, :, :T - 1].contiguous()), _odd(V[:, :, :T - 1].contiguous()))
+        o.quantize_append(0, K[:, :, :T - 1].numpy().copy(), V[:, :, :T - 1].numpy().copy())
+    q = W.query(w, 0)
+    for t in range(T - 1, T + 2):
+        k, v = K[:, :, t:t + 1].contiguous(), V[:, :, t:t + 1].contiguous()
+        out = g.append_decode_attention(0, _odd(k), _odd(v), _odd(q), _odd(torch.zeros_like(q)))
+        o.quantize_append(0, k.numpy(), v.numpy())
+        assert_outputs_close(out, *o.decode_attention(0, q.numpy()), "append %d" % t)
+    assert_outputs_close(g.decode_attention(0, _odd(q)), *o.decode_attention(0, q.numpy()), "from the ring")
+    g.close()
+
+
+@pytest.mark.parametrize("vb", [4, 16])
+def test_small_numerators_count(kvq_mod, vb):
+    """One token takes nearly all of the weight and has zeros as values; the others weigh 2^-14 .. 2^-34 of it and hold values up to
+    6e4, so the outputs are made of small numerators alone, whose high parts are down to fp16 subnormals without the lift.  A numerator
+    keeps 22 bits (2^-21 of it, or 2^-37 where the two parts end): |error| <= sum_t (2^-21 p_t + 2^-36) |v_t| / l, and the fp16 rounding."""
+    T, D = 32 + 23, 128
+    g = torch.Generator().manual_seed(5)
+    q = torch.zeros(1, 4, D, dtype=torch.float16)
+    q[..., 0] = 16.0
+    K = torch.zeros(1, 1, T, D, dtype=torch.float16)
+    logit = -(14 + 20 * torch.arange(T) / T)                             # in powers of two
+    logit[7] = 0
+    K[0, 0, :, 0] = (logit * np.log(2) * np.sqrt(D) / 16).half()
+    V = (torch.rand(1, 1, T, D, generator=g) * 6e4).half()
+    V[0, 0, 7] = 0
+    cache = kvq_mod.KVQ(1, 1, 4, 1, D, 128, [16], [vb], residual=64 if vb < 16 else 0)     # all of it in the window, or one unit of a 16-bit layer and the rest
+    cache.quantize_append(0, K.cuda(), V.cuda())
+    out = cache.decode_attention(0, q.cuda()).cpu().double()
+    s = (q.double()[0] @ K.double()[0, 0].T) / np.sqrt(D)
+    p = torch.exp(s - s.amax(1, keepdim=True))
+    ref = (p @ V.double()[0, 0]) / p.sum(1, keepdim=True)
+    bound = ((2.0 ** -20 * p + 2.0 ** -36) @ V.double()[0, 0].abs()) / p.sum(1, keepdim=True) + 2.0 ** -11 * ref.abs() + 2.0 ** -24
+    assert ref.abs().min() > 1e-3 and ((out[0] - ref).abs() <= bound).all(), ((out[0] - ref).abs() / bound).max()
+    cache.close()
+
+
+@pytest.mark.parametrize("vb", [4, 16])
+@pytest.mark.parametrize("gq", [4, 7])
+def test_infinite_values_stay_infinite(kvq_mod, gq, vb):
+    """An infinite value makes its channel of the output infinite, with the value's sign, also where a numerator is one fp16 number
+    (no low part); other channels are untouched."""
+    T, D = 32 + 9, 128
+    g = torch.Generator().manual_seed(6)
+    q, K, V = (torch.randn(1, h, n, D, generator=g).half() for h, n in ((gq, 1), (1, T), (1, T)))
+    K[0, 0, 3] = 0
+    plain = None
+    for bad in (False, True):
+        if bad:
+            V[0, 0, 3, 5], V[0, 0, T - 1, 77] = float("inf"), float("-inf")
+            V[0, 0, 9, 100] = float("nan")
+        cache = kvq_mod.KVQ(1, 1, gq, 1, D, 128, [16], [vb], residual=64 if vb < 16 else 0)
+        cache.set_decode_options(0, 1)                                   # (of several splits, absent ones are merged as the first one times zero)
+        cache.quantize_append(0, K[:, :, :T - 1].contiguous().cuda(), V[:, :, :T - 1].contiguous().cuda())
+        out = cache.append_decode_attention(0, K[:, :, T - 1:].contiguous().cuda(), V[:, :, T - 1:].contiguous().cuda(), q[:, :, 0].contiguous().cuda()).cpu()
+        cache.close()
+        if not bad:
+            plain = out
+    assert (out[0, :, 5] == float("inf")).all()
+    # (rows past the end repeat the last one with weight zero: its infinity times zero is no number, as it always was)
+    assert not torch.isfinite(out[0, :, 77]).any() and torch.isnan(out[0, :, 100]).all()
+    rest = [c for c in range(D) if c not in (5, 77, 100)]
+    assert torch.equal(out[0][:, rest], plain[0][:, rest])
