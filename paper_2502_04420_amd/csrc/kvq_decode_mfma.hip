@@ -44,6 +44,7 @@ constexpr int kPairs = KVQ_DECODE_PAIRS;
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef float float2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -858,19 +859,38 @@ __device__ __forceinline__ void rescale_rows(float4v (&R)[8], float2 &shrink, co
 
 // ------------------------------------------------------------------ merge of a work-group's pairs, and of the splits
 
-constexpr int kWeights = 64;             // of a head: two records' maxima and sums per lane of a half wave
-static_assert(kMergeSplits <= kWeights, "a weight per split");
-
-// the maximum / sum over the 32 lanes of a half wave, in every lane
-__device__ __forceinline__ float half_max32(float x) { x = row_max16(x); return fmaxf(x, __shfl_xor(x, 16, 64)); }
-__device__ __forceinline__ float half_sum32(float x) { x = row_sum16(x); return x + __shfl_xor(x, 16, 64); }
+// reductions over the 32 lanes of a half wave or (LANES = 64) over the wave, in every lane: the rows of 16, then the row's neighbour and the other
+// half by the lane swaps (fed the same register twice, every lane gets its own value in one result and its partner's in the other)
+__device__ __forceinline__ u32x2 with_row_partner(float x) { const uint32_t v = __builtin_bit_cast(uint32_t, x); return __builtin_amdgcn_permlane16_swap(v, v, false, false); }
+__device__ __forceinline__ u32x2 with_half_partner(float x) { const uint32_t v = __builtin_bit_cast(uint32_t, x); return __builtin_amdgcn_permlane32_swap(v, v, false, false); }
+__device__ __forceinline__ float swap_sum(u32x2 v) { const uint32_t a = v[0], b = v[1]; return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b); }
+__device__ __forceinline__ float swap_max(u32x2 v) { const uint32_t a = v[0], b = v[1]; return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)); }
+template <int LANES>
+__device__ __forceinline__ float lanes_max(float x)
+{
+    x = swap_max(with_row_partner(row_max16(x)));
+    return LANES == 64 ? swap_max(with_half_partner(x)) : x;
+}
+template <int LANES>
+__device__ __forceinline__ float lanes_sum(float x)
+{
+    x = swap_sum(with_row_partner(row_sum16(x)));
+    return LANES == 64 ? swap_sum(with_half_partner(x)) : x;
+}
 
 __device__ __forceinline__ void store_through(float *p, float4v v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
 }
 
-// o / l as fp16 to four channels of the output row (the caller's tensor: fp16 alignment is all it owes)
+__device__ __forceinline__ void store_through(float *p, float2v v) { store_through(p, make_float2(v[0], v[1])); }
+
+// o / l as fp16 to channels of the output row (the caller's tensor: fp16 alignment is all it owes)
+__device__ __forceinline__ void store_output(uint16_t *out, float2v o, float l)
+{
+    const half2v h = {(_Float16)(o[0] / l), (_Float16)(o[1] / l)};
+    __builtin_memcpy(out, &h, sizeof h);
+}
 __device__ __forceinline__ void store_output(uint16_t *out, float4v o, float l)
 {
     const half2v h0 = {(_Float16)(o[0] / l), (_Float16)(o[1] / l)}, h1 = {(_Float16)(o[2] / l), (_Float16)(o[3] / l)};
@@ -878,108 +898,97 @@ __device__ __forceinline__ void store_output(uint16_t *out, float4v o, float l)
     __builtin_memcpy(out, &h, sizeof h);
 }
 
-// The records of all splits (at most kMergeSplits) of the tile's heads -> outputs, by the whole work-group: 32 lanes per head and
-// subset of the splits, the subsets' sums meet in LDS.  The order of all sums is fixed, whichever work-group comes last.
+// The records of all splits (at most kMergeSplits; of a tile of 8 heads, 16) of a wave's head or, in a tile of 8, two heads -> outputs.  LANES per head
+// hold the splits' maxima and sums, 32 lanes fetch a record's outputs (16 bytes each): one head is fetched two records at a
+// time, two heads one each.  Splits and heads that do not exist lie beyond the resource and read as zero.  rows: heads of this wave that exist, row: the first.  The order of all sums is fixed, whichever wave comes last.
 // The records come from work-groups on all XCDs: they are read past the caches (sc0 sc1), as they were written.
-// Bound by the latency of the reads (0.45 us), so as many as there are registers for go out at once.
+// Bound by the latency of the reads (0.45 us), so up to 32 records per head are asked for at once, without a branch per record.  One sequence of 8 kv heads,
+// 4133 tokens (27 splits), us a call, with half as many at once and sums that met in LDS behind a barrier / now: 7.9 / 7.4.
 template <int GQ, int PAIRS>
-__device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid)
+__device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t row, int rows, int lane, int wave)
 {
     constexpr int kBeyond = 17;                                  // cache policy bits: sc0, sc1
-    constexpr int kSubsets = 4 * PAIRS / GQ;
-    constexpr int kAhead = GQ == 8 ? 16 : 8;                     // records on their way per thread
-    float (*sums)[kD] = reinterpret_cast<float (*)[kD]>(&Ls[0].Ak[0][0]);                   // [subset * GQ + head][channel]
-    static_assert(sizeof(PairLds<GQ>) * (PAIRS - 1) >= sizeof(float) * kD * kSubsets * GQ, "the sums fit the first pairs' memory");
-    static_assert(sizeof(PairLds<GQ>) >= sizeof(float) * kSubsets * GQ * kWeights, "the weights fit the last pair's");
-    const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, head = half % GQ, subset = half / GQ;
-    float *weights = reinterpret_cast<float *>(&Ls[PAIRS - 1].Ak[0][0]) + half * kWeights;
-    const RowStream po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + qrow0 * a.splits * kD, 0, nvalid * a.splits * (int)(kD * sizeof(float)), 0x00020000);
-    const RowStream pm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + qrow0 * a.splits * 2, 0, nvalid * a.splits * (int)(2 * sizeof(float)), 0x00020000);
-    const int first = (head < nvalid ? head : nvalid - 1) * a.splits;
-    u32x2 ml[2];
-#pragma unroll
-    for (int k = 0; k < 2; k++) ml[k] = __builtin_amdgcn_raw_buffer_load_b64(pm, (first + (lane + 32 * k < a.splits ? lane + 32 * k : 0)) * 8, 0, kBeyond);
+    constexpr int kLanes = 256 / GQ, kSubsets = kLanes / 32, kAhead = 16;
+    static_assert(kMergeSplits <= 64 && 2 * PAIRS == 4, "a lane per split of a single head; a wave per head or two");
+    // weights by subset and round; the key waves' A tiles are no longer needed
+    float *weights = reinterpret_cast<float *>(&Ls[0].Ak[0][0]) + wave * 64;
+    static_assert(sizeof(Ls[0].Ak) >= 4 * 64 * sizeof(float), "the weights fit");
+    const int sl = lane & (kLanes - 1), subset = kLanes == 64 ? lane >> 5 : 0, head = kLanes == 32 ? lane >> 5 : 0;
+    const RowStream po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + row * a.splits * kD, 0, rows * a.splits * (int)(kD * sizeof(float)), 0x00020000);
+    const RowStream pm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + row * a.splits * 2, 0, rows * a.splits * (int)(2 * sizeof(float)), 0x00020000);
+    const u32x2 ml = __builtin_amdgcn_raw_buffer_load_b64(pm, (head * a.splits + sl) * 8, 0, kBeyond);
     u32x4 x[kAhead];
+    const int off = (head * a.splits + subset) * (int)(kD * sizeof(float)) + 16 * (lane & 31);
     auto fetch = [&](int s0) {
 #pragma unroll
-        for (int k = 0; k < kAhead; k++) {
-            const int sp = s0 + subset + kSubsets * k;
-            x[k] = __builtin_amdgcn_raw_buffer_load_b128(po, (first + (sp < a.splits ? sp : 0)) * (int)(kD * sizeof(float)) + 16 * lane, 0, kBeyond);
-        }
+        for (int k = 0; k < kAhead; k++) x[k] = __builtin_amdgcn_raw_buffer_load_b128(po, off + s0 * (int)(kD * sizeof(float)), kSubsets * k * (int)(kD * sizeof(float)), kBeyond);
     };
     fetch(0);
-    float m[2], l[2];
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-        const uint32_t mw = ml[k][0], lw = ml[k][1];
-        m[k] = lane + 32 * k < a.splits ? __builtin_bit_cast(float, mw) : -INFINITY;
-        l[k] = __builtin_bit_cast(float, lw);
-    }
-    const float M = half_max32(fmaxf(m[0], m[1]));
-    float sum = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-        const float f = m[k] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m[k] - M);       // (no such split: weight zero)
-        weights[lane + 32 * k] = f;
-        sum = fmaf(f, l[k], sum);
-    }
-    sum = half_sum32(sum);
+    const uint32_t mw = ml[0], lw = ml[1];
+    const float m = sl < a.splits ? __builtin_bit_cast(float, mw) : -INFINITY, l = __builtin_bit_cast(float, lw);
+    const float M = lanes_max<kLanes>(m);
+    const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);         // (no such split: weight zero)
+    weights[kLanes == 64 ? 32 * (lane & 1) + (lane >> 1) : lane] = f;
+    const float sum = lanes_sum<kLanes>(sl < a.splits ? f * l : 0.0f);
     wave_lds_sync();
     float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
+    const float *w = weights + 32 * (lane >> 5);
     for (int s0 = 0; s0 < a.splits; s0 += kSubsets * kAhead) {
         if (s0 > 0) fetch(s0);
+        float4v wk[kAhead / 4];
+#pragma unroll
+        for (int k = 0; k < kAhead / 4; k++) wk[k] = *reinterpret_cast<const float4v *>(w + s0 / kSubsets + 4 * k);
 #pragma unroll
         for (int k = 0; k < kAhead; k++) {
-            const int sp = s0 + subset + kSubsets * k;
-            const float f = sp < a.splits ? weights[sp] : 0.0f;
             const uint32_t w0 = x[k][0], w1 = x[k][1], w2 = x[k][2], w3 = x[k][3];
-            O += f * float4v{__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1), __builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)};
+            O += wk[k / 4][k % 4] * float4v{__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1), __builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)};
         }
     }
-    *reinterpret_cast<float4v *>(&sums[half][4 * lane]) = O;
-    wg_barrier();
-    if (subset == 0 && head < nvalid) {
+    if constexpr (kSubsets == 2) {
 #pragma unroll
-        for (int k = 1; k < kSubsets; k++) O += *reinterpret_cast<const float4v *>(&sums[k * GQ + head][4 * lane]);
-        store_output(a.out + (qrow0 + head) * kD + 4 * lane, O, sum);
+        for (int i = 0; i < 4; i++) O[i] = swap_sum(with_half_partner(O[i]));
     }
+    if (head < rows) store_output(a.out + (row + head) * kD + 4 * (lane & 31), O, sum);
 }
 
-// The pairs' results, from LDS, to the record of the split (or, with a single split, to the outputs).  With arrival counters the
+// The pairs' results, from LDS, to the record of the split (or, with a single split, to the outputs).  A wave has a head or, in a tile of 8, two, merged here and, by
+// the last work-group, in merge_splits.  With arrival counters the
 // work-group that is the last of its cache and tile to count itself merges the splits: it waits for nobody.  A record is written
 // through to memory and its stores are complete before the work-group counts itself, the counter is in memory too (device
 // scope), and the last one reads past the caches, so it sees every record.  It leaves the counter at zero for the next call.
-// Stores, count and reads are one memory round trip each (0.6, 0.4, 0.45 us) and take the place of a launch (2.6 us from kernel to
-// kernel).  Measured, us a call (launches of this kernel and combine_splits with one pair / with two / merged here): 8 kv heads, K4V2, 200 tokens
-// 9.0 / 7.9 / 7.6, 1100 tokens 9.1 / 8.4 / 7.8, 4133 tokens 10.1 / 9.5 / 9.2, 60 tokens (a single split) 9.0 / 6.0.
+// Stores, count and reads are one memory round trip each (0.4, 0.4, 0.45 us) and take the place of a launch (2.6 us from kernel to
+// kernel).  (Every wave counting for itself saves the two barriers and costs more than they do in counts of the same word: 27 splits 8.2 / 8.0.)
 template <int GQ, int PAIRS>
-__device__ __forceinline__ void merge_pairs(const ShortDecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid, int split, int bh)
+__device__ __forceinline__ void merge_pairs(const ShortDecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t qrow0, int nvalid, int split, int bh, int lane, int wave)
 {
     wg_barrier();                                                // all pairs' results are in LDS
-    const int head = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    constexpr int kLanes = 256 / GQ, kVec = kD / kLanes;         // lanes per head, channels per lane
+    typedef float vec __attribute__((ext_vector_type(kVec)));
+    const int first = wave * (64 / kLanes), head = first + (kLanes == 32 ? lane >> 5 : 0), c0 = kVec * (lane & (kLanes - 1));
+    const bool any = first < nvalid;                             // of the wave's heads, one exists
+    const size_t row = qrow0 + head;
+    float m[PAIRS], l[PAIRS], M = -INFINITY, L = 0.0f;
+#pragma unroll
+    for (int p = 0; p < PAIRS; p++) {
+        const float2 ml = *reinterpret_cast<const float2 *>(&Ls[p].Zt[head][0][0]);
+        m[p] = ml.x;
+        l[p] = ml.y;
+        M = fmaxf(M, ml.x);
+    }
+    vec O = 0.0f;
+#pragma unroll
+    for (int p = 0; p < PAIRS; p++) {
+        if (m[p] == -INFINITY) continue;                         // a pair without units: nothing of it is in LDS
+        const float f = __builtin_amdgcn_exp2f(m[p] - M);
+        L = fmaf(f, l[p], L);
+        O += f * *reinterpret_cast<const vec *>(reinterpret_cast<const float *>(&Ls[p].Av[0].at[0][0]) + head * kD + c0);
+    }
     if (head < nvalid) {
-        float m[PAIRS], l[PAIRS], M = -INFINITY, L = 0.0f;
-#pragma unroll
-        for (int p = 0; p < PAIRS; p++) {
-            const float2 ml = *reinterpret_cast<const float2 *>(&Ls[p].Zt[head][0][0]);
-            m[p] = ml.x;
-            l[p] = ml.y;
-            M = fmaxf(M, ml.x);
-        }
-        float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int p = 0; p < PAIRS; p++) {
-            if (m[p] == -INFINITY) continue;                     // a pair without units: nothing of it is in LDS
-            const float f = __builtin_amdgcn_exp2f(m[p] - M);
-            L = fmaf(f, l[p], L);
-            O += f * *reinterpret_cast<const float4v *>(reinterpret_cast<const float *>(&Ls[p].Av[0].at[0][0]) + head * kD + 4 * lane);
-        }
-        const size_t row = qrow0 + head;
         if (a.splits == 1) {
-            store_output(a.out + row * kD + 4 * lane, O, L);
+            store_output(a.out + row * kD + c0, O, L);
         } else {
-            store_through(a.part_o + (row * a.splits + split) * kD + 4 * lane, O);
-            if (lane == 0) store_through(a.part_ml + (row * a.splits + split) * 2, make_float2(M, L));
+            store_through(a.part_o + (row * a.splits + split) * kD + c0, O);
+            if (c0 == 0) store_through(a.part_ml + (row * a.splits + split) * 2, make_float2(M, L));
         }
     }
     if (a.splits == 1 || !a.tickets) return;
@@ -992,7 +1001,8 @@ __device__ __forceinline__ void merge_pairs(const ShortDecodeArgs &a, PairLds<GQ
         Ls[0].rescale[0][0] = last ? 1 : 0;
     }
     wg_barrier();
-    if (__builtin_amdgcn_readfirstlane(Ls[0].rescale[0][0])) merge_splits<GQ, PAIRS>(a, Ls, qrow0, nvalid);
+    if (any && __builtin_amdgcn_readfirstlane(Ls[0].rescale[0][0]))
+        merge_splits<GQ, PAIRS>(a, Ls, qrow0 + first, kLanes == 32 && first + 1 < nvalid ? 2 : 1, lane, wave);
 }
 
 // ------------------------------------------------------------------ kernel
@@ -1513,7 +1523,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     }
     if constexpr (PAIRS > 1) {
         for (int i = n1 + n2; i < steps; i++) wg_barrier();      // pairs with fewer units
-        merge_pairs<GQ, PAIRS>(a, Ls, qrow0, nvalid, split, bh);
+        merge_pairs<GQ, PAIRS>(a, Ls, qrow0, nvalid, split, bh, lane, wave);
     }
 }
 
