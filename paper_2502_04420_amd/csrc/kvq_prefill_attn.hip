@@ -543,18 +543,21 @@ __device__ __forceinline__ bool unit_exceeds(const float4v (&S)[2][kQT], float i
 
 // Softmax weights of a unit against the unchanged reference (no mask), dealt out in kBatches shares so that a share
 // can be issued between two batches of another unit's score products.  PRE: the scores are the exponents themselves.
-template <bool PRE, int SHARES>
+template <bool PRE, int SHARES, class Fetch>
 struct CalmSoftmax {
     const float4v (&S)[2][kQT];
     float c;
     const float (&m)[kQT];
     float (&lsum)[kQT];
     half8 (&P)[kQT];
+    const Fetch &fetch;                                         // fetch(i): the wave's i-th load of a unit to come, of Fetch::kSlots
     static constexpr int kShares = SHARES;                      // = the batches of the score products it rides with
     __device__ __forceinline__ void operator()(int share) const
     {
         typedef _Float16 half2 __attribute__((ext_vector_type(2)));
         const half2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+        for (int i = Fetch::kSlots * share / kShares; i < Fetch::kSlots * (share + 1) / kShares; i++) fetch(i);
 #pragma unroll
         for (int pair = 8 * share / kShares; pair < 8 * (share + 1) / kShares; pair++) {
             const int qt = pair >> 2, e = 2 * (pair & 3);                                       // elements e, e + 1 of query tile qt
@@ -825,25 +828,43 @@ __device__ __forceinline__ void fetch_piece(const uint8_t *piece, uint32_t lane_
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_offset), "s"(piece) : "memory", "m0");
 }
 
-// Wave `wave` of WAVES fetches the pieces wave, wave + WAVES, ... of a unit.  Of the keys' low parts: none, the whole tile, or the
-// first kLoPieces KiB of it (the compact tile).
+// Pieces of a unit that come with the keys' low parts: none, the whole tile, or the first kLoPieces KiB of it (the compact tile).
+template <int LO> constexpr int low_pieces() { return LO == kLoAll ? kTileKiB : LO == kLoCompact ? kLoPieces : 0; }
+template <int LO> constexpr int unit_pieces() { return kTileKiB + low_pieces<LO>() + kValuesKiB; }
+// loads per wave and unit, at most
+template <int LO, int WAVES> constexpr int fetch_slots() { return (unit_pieces<LO>() + WAVES - 1) / WAVES; }
+
+// The i-th of them: wave `wave` of WAVES fetches the pieces wave, wave + WAVES, ... of a unit.
+template <int LO, int WAVES>
+__device__ __forceinline__ void fetch_slot(const uint8_t *unit, Tiles &L, int wave, int lane, int i)
+{
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)reinterpret_cast<uint8_t *>(&L);
+    const int p = wave + WAVES * i;                               // the same for all lanes of the wave
+    if (p < unit_pieces<LO>()) {
+        const int off = 1024 * (p < kTileKiB + low_pieces<LO>() ? p : p - low_pieces<LO>() + kTileKiB);     // K^, low parts, then V^
+        // (eight waves have registers for a lane offset per piece, four add the piece's to the scalar address)
+        if constexpr (WAVES == 8) fetch_piece(unit, (uint32_t)(off + 16 * lane), lds + off);
+        else fetch_piece(unit + off, (uint32_t)(16 * lane), lds + off);
+    }
+}
+
 template <int LO, int WAVES>
 __device__ __forceinline__ void fetch_unit(const uint8_t *unit, Tiles &L, int wave, int lane)
 {
-    constexpr int lo_pieces = LO == kLoAll ? kTileKiB : LO == kLoCompact ? kLoPieces : 0;
-    constexpr int pieces = kTileKiB + lo_pieces + kValuesKiB;
-    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)reinterpret_cast<uint8_t *>(&L);
 #pragma unroll
-    for (int i = 0; i < (pieces + WAVES - 1) / WAVES; i++) {
-        const int p = wave + WAVES * i;                           // the same for all lanes of the wave
-        if (p < pieces) {
-            const int off = 1024 * (p < kTileKiB + lo_pieces ? p : p - lo_pieces + kTileKiB);     // K^, low parts, then V^
-            // (eight waves have registers for a lane offset per piece, four add the piece's to the scalar address)
-            if constexpr (WAVES == 8) fetch_piece(unit, (uint32_t)(off + 16 * lane), lds + off);
-            else fetch_piece(unit + off, (uint32_t)(16 * lane), lds + off);
-        }
-    }
+    for (int i = 0; i < fetch_slots<LO, WAVES>(); i++) fetch_slot<LO, WAVES>(unit, L, wave, lane, i);
 }
+
+// what a step fetches on its way
+template <int LO, int WAVES>
+struct UnitFetch {
+    const uint8_t *unit;
+    Tiles &to;
+    int wave, lane;
+    bool real;
+    static constexpr int kSlots = fetch_slots<LO, WAVES>();
+    __device__ __forceinline__ void operator()(int i) const { if (real) fetch_slot<LO, WAVES>(unit, to, wave, lane, i); }
+};
 
 // Returns once all fetches of this wave have landed in LDS.
 __device__ __forceinline__ void wait_fetches() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -1056,7 +1077,15 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
         // unit).  Whether a unit may take the calm form is decided one unit ahead, right after its scores were issued:
         // the test then sits next to the output products of the unit before, which need nothing from it.
         bool calm = false;                                       // the first unit never is: the references start at -inf
-        auto step = [&](int u, const Tiles &X0, const Tiles &X1, const float4v (&Sin)[2][kQT], float4v (&Sout)[2][kQT]) {
+        // The wave's loads of unit uf go out on the way (into Xf, which everybody left at the last barrier), one or two behind each batch of products: issued
+        // all at once behind the barrier, by all waves, they wait for each other (80 to 100 cycles each, 200..245 a unit and wave) while the matrix cores idle.
+        // us a pass, so / on the way: a 2027-token prompt, 4 layers 342 / 330, 4 x 8192 tokens 2482 / 2437, last 512 of 24576, 4 layers 1088 / 1074.
+        auto step = [&](int u, const Tiles &X0, const Tiles &X1, const float4v (&Sin)[2][kQT], float4v (&Sout)[2][kQT], int uf, Tiles &Xf) {
+            const UnitFetch<LO, WAVES> ride = {unit_at(uf), Xf, wave, lane, WAVES == 8 || uf < nb};
+            if (!(u <= wlast && calm)) {
+#pragma unroll
+                for (int i = 0; i < ride.kSlots; i++) ride(i);
+            }
             if (u <= wlast) {
                 const bool ahead = u + 1 < nb && u + 1 <= wlast;
                 half8 P[kQT];
@@ -1068,7 +1097,7 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
                     // the common case, one stretch of straight-line code: score products of the next unit next to the
                     // weights of this one against the unchanged reference (calm implies that there is a next unit, and
                     // that this unit's scores are relative to the reference as it stands: base, init are up to date)
-                    score_unit<LO>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av, CalmSoftmax<KLO, score_batches<LO>()>{Sin, c, m, lsum, P});
+                    score_unit<LO>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av, CalmSoftmax<KLO, score_batches<LO>(), UnitFetch<LO, WAVES>>{Sin, c, m, lsum, P, ride});
                 } else {
                     float bin[kQT];
 #pragma unroll
@@ -1100,10 +1129,8 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
         if constexpr (WAVES == 8) {
             for (int u = ub; u < nb; u += 2) {
                 const int b1 = after(b0), b2 = after(b1), b3 = after(b2), b4 = after(b3);
-                fetch(u + 3, L[b3]);                            // buffers of units u - 2 and u - 1: all are done with them
-                fetch(u + 4, L[b4]);
-                step(u, L[b0], L[b1], S, Sn);
-                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S);
+                step(u, L[b0], L[b1], S, Sn, u + 3, L[b3]);     // buffers of units u - 2 and u - 1: all are done with them
+                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S, u + 4, L[b4]);
                 wait_fetches();                                 // units u + 3 and u + 4 are there
                 __syncthreads();
                 b0 = b2;
@@ -1111,12 +1138,10 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
         } else {
             for (int u = ub; u < nb; u += 2) {
                 const int b1 = after(b0), b2 = after(b1);
-                fetch(u + 2, L[b2]);                            // buffer of unit u - 1
-                step(u, L[b0], L[b1], S, Sn);
+                step(u, L[b0], L[b1], S, Sn, u + 2, L[b2]);     // buffer of unit u - 1
                 wait_fetches();                                 // unit u + 2 is there
                 __syncthreads();
-                fetch(u + 3, L[b0]);
-                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S);
+                if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S, u + 3, L[b0]);
                 wait_fetches();
                 __syncthreads();
                 b0 = b2;
