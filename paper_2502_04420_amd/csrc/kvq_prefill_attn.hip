@@ -62,19 +62,22 @@ struct Tiles {
     _Float16 Vt[kD][32];                // V^[channel][value_place(channel, token)]
 };
 
+// Rows of 64 bytes without padding (the V^ rows, the rows of the compact low parts): the four pieces of 16 bytes of a row are rotated by row / 2.  An operand
+// read takes the same piece of 16 neighbouring rows for 16 lanes; a 16-byte read of a wave is served 16 lanes at a time, but not in the order of
+// the lanes.  Measured with a probe kernel, eight waves reading, bytes per cycle: rotated by row / 2 256, like a linear read and rows of 288 bytes;
+// by row / 4, by row and not at all 160, rows of 80 bytes 160.
+__host__ __device__ constexpr int rotated_piece(int row, int piece) { return (piece + (row >> 1)) & 3; }
+
 // Place of a token in the V^ row of a channel.  A lane's operand of the output product (tokens 4 rq .. + 3 and 16 + 4 rq .. + 3, the
-// rows of the scores' result tile that it holds) is one piece of 16 bytes; the four pieces of a row are rotated by
-// channel / 4, so that 16 lanes with neighbouring channels and the same rq meet 16 different groups of four banks although
-// rows follow each other without padding (64 bytes).  Before, two pieces of 8 bytes in rows of 72: half the bytes per LDS
-// cycle and a KiB more to fetch per unit (4 x 8192-token prompts 2508 -> 2477 us, a 2027-token prompt, 4 layers, 414 -> 407).
-__host__ __device__ constexpr int value_place(int channel, int t) { return 8 * ((((t >> 2) & 3) + (channel >> 2)) & 3) + 4 * (t >> 4) + (t & 3); }
+// rows of the scores' result tile that it holds) is one piece of 16 bytes.
+__host__ __device__ constexpr int value_place(int channel, int t) { return 8 * rotated_piece(channel, (t >> 2) & 3) + 4 * (t >> 4) + (t & 3); }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Which key channels of a (batch, kv head) cache keep the remainders of their fp16 rounding (prefill_select).  In the
 // compact form only the 32 selected channels do, and their remainders are stored as a tile [token][slot] of
-// kLoStride halves per row at the place of Tiles::Klo (the first 2.5 KiB of it): one batch of the score products
+// kLoStride halves per row at the place of Tiles::Klo (the first 2 KiB of it): one batch of the score products
 // instead of four.
 struct Select {
     uint8_t pos[kD];          // slot (0..31) of a channel's remainders in the compact tile, 255 = none kept
@@ -84,9 +87,9 @@ struct Select {
     float centre[kD];         // per channel: subtracted from every dequantized key of the cache before it is rounded
 };
 static_assert(sizeof(Select) == 768, "one record per cache");
-constexpr int kLoStride = 32 + 8;       // halves per row of the compact tile: 80 bytes = 20 banks, the 16-byte reads of a wave
-                                        // (16 rows x 4 pieces) fall on every bank exactly four times
-constexpr int kLoPieces = 3;            // KiB of the compact tile that are fetched (32 rows x 80 bytes = 2.5 KiB)
+constexpr int kLoStride = 32;           // halves per row of the compact tile
+constexpr int kLoPieces = 2;            // KiB of it
+__host__ __device__ constexpr int low_place(int t, int slot) { return 8 * rotated_piece(t, slot >> 3) + (slot & 7); }
 // how the keys' low parts enter the attention kernel
 constexpr int kLoNone = 0, kLoAll = 1, kLoCompact = 2;
 
@@ -289,7 +292,7 @@ __device__ __forceinline__ void store_key_codes(const LayerView &lv, Tiles &L, c
 #pragma unroll
             for (int e = 0; e < 8; e++) {
                 const uint32_t slot = ((e < 4 ? pw[0] : pw[1]) >> (8 * (e & 3))) & 255u;
-                if (slot < 32u) row[slot] = (_Float16)x[e];
+                if (slot < 32u) row[low_place(t, (int)slot)] = (_Float16)x[e];
             }
         } else {
             *reinterpret_cast<u32x4 *>(&L.Klo[t][32 * cb + 8 * kq]) = pack8(x);
@@ -395,7 +398,7 @@ __device__ __forceinline__ float xor_lanes(float x, int mask) { return __shfl_xo
 // the A operand of the output product for channel tile ct: V^T rows 16 ct + n, tokens {4 rq .. + 3, 16 + 4 rq .. + 3}
 __device__ __forceinline__ half8 value_operand(const Tiles &X, int ct, int n, int rq)
 {
-    return *reinterpret_cast<const half8 *>(&X.Vt[16 * ct + n][8 * ((rq + (n >> 2)) & 3)]);
+    return *reinterpret_cast<const half8 *>(&X.Vt[16 * ct + n][8 * rotated_piece(n, rq)]);            // (16 ct: whole turns)
 }
 
 struct NoSlice { __device__ __forceinline__ void operator()(int) const {} };
@@ -428,8 +431,8 @@ __device__ __forceinline__ void score_unit(const Tiles &X, const half8 (&Qf)[kQT
         const int step = bt & 3;
         if (LO == kLoCompact && bt >= 4) {
             const _Float16 *lo = &X.Klo[0][0];
-            A0 = *reinterpret_cast<const half8 *>(lo + n * kLoStride + 8 * rq);
-            A1 = *reinterpret_cast<const half8 *>(lo + (16 + n) * kLoStride + 8 * rq);
+            A0 = *reinterpret_cast<const half8 *>(lo + n * kLoStride + 8 * rotated_piece(n, rq));
+            A1 = *reinterpret_cast<const half8 *>(lo + (16 + n) * kLoStride + 8 * rotated_piece(n, rq));
         } else if (KLO && bt >= 4) {
             A0 = *reinterpret_cast<const half8 *>(&X.Klo[n][32 * step + 8 * rq]);
             A1 = *reinterpret_cast<const half8 *>(&X.Klo[16 + n][32 * step + 8 * rq]);
