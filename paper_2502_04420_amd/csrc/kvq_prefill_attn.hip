@@ -106,7 +106,8 @@ struct MetaSlab {
 // Registers of a unit on its way from the packed cache to the tiles.  Quantized tensor: k0 / v0 = the dwords of the thread's two code
 // groups; fp16 rows (16-bit tensor or window): k0, k1 / v0, v1 = two 16-byte row pieces.  m = this lane's 16-byte
 // piece of the wave's metadata (lanes 0..23).
-struct Stage { u32x4 k0, k1, v0, v1, m; };
+// c, pos, compact: what the thread needs of the cache's selection record (keys quantized per channel): the centres and slots of its 8 channels.
+struct Stage { u32x4 k0, k1, v0, v1, m, c0, c1; u32x2 pos; uint32_t compact; };
 
 __device__ __forceinline__ void wave_lds_sync()
 {
@@ -250,23 +251,22 @@ __device__ __forceinline__ void slab_meta8(const uint32_t *scales, const uint16_
 
 // kscale: the softmax constant log2(e) / sqrt(D), multiplied into the dequantized keys in fp32 before they are split
 // into two fp16 numbers: the attention kernel's score products then come out in the exponent's units.
-// rec: the cache's selection record or null; compact: its low parts go into the compact tile
+// st.c0, c1: the channels' centres (zero without a selection record); compact: the low parts go into the compact tile
 template <int BITS, bool KPT>
-__device__ __forceinline__ void store_key_codes(const LayerView &lv, Tiles &L, const MetaSlab &M, int tid, u32x4 c, float kscale,
-                                                const Select *rec, bool compact)
+__device__ __forceinline__ void store_key_codes(const LayerView &lv, Tiles &L, const MetaSlab &M, int tid, const Stage &st, float kscale, bool compact)
 {
+    const u32x4 c = st.k0;
     const int l = tid & 63, cb = tid >> 6, n = l & 15, kq = l >> 4;
     const bool narrow = lv.narrow != 0;
     float s[8], z[8];
     if constexpr (!KPT) {
         slab_meta8(M.ks, M.kz, narrow, 8 * kq, s, z);                          // one (s, z) per channel
-        if (rec) {
-            // the channel's centre goes off with the zero-point: a constant per channel moves every score of a query
-            // alike, which the softmax does not see (window tokens: see attend)
-            const float4 c0 = *reinterpret_cast<const float4 *>(&rec->centre[32 * cb + 8 * kq]);
-            const float4 c1 = *reinterpret_cast<const float4 *>(&rec->centre[32 * cb + 8 * kq + 4]);
-            z[0] -= c0.x; z[1] -= c0.y; z[2] -= c0.z; z[3] -= c0.w;
-            z[4] -= c1.x; z[5] -= c1.y; z[6] -= c1.z; z[7] -= c1.w;
+        // the channel's centre goes off with the zero-point: a constant per channel moves every score of a query
+        // alike, which the softmax does not see (window tokens: see attend)
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const uint32_t w = e < 4 ? st.c0[e & 3] : st.c1[e & 3];
+            z[e] -= __builtin_bit_cast(float, w);
         }
     }
 #pragma unroll
@@ -287,12 +287,13 @@ __device__ __forceinline__ void store_key_codes(const LayerView &lv, Tiles &L, c
 #pragma unroll
         for (int e = 0; e < 8; e++) x[e] -= (float)(_Float16)x[e];
         if (compact) {
-            const u32x2 pw = *reinterpret_cast<const u32x2 *>(&rec->pos[32 * cb + 8 * kq]);
-            _Float16 *row = &L.Klo[0][0] + t * kLoStride;
+            // (channels without a slot write behind the compact tile, where nothing is read: a branch per element costs more)
+            static_assert(sizeof(L.Klo) >= kLoPieces * 1024 + 256 * 2, "a place per thread behind the compact tile");
+            _Float16 *tile = &L.Klo[0][0];
 #pragma unroll
             for (int e = 0; e < 8; e++) {
-                const uint32_t slot = ((e < 4 ? pw[0] : pw[1]) >> (8 * (e & 3))) & 255u;
-                if (slot < 32u) row[low_place(t, (int)slot)] = (_Float16)x[e];
+                const uint32_t pw = e < 4 ? st.pos[0] : st.pos[1], slot = (pw >> (8 * (e & 3))) & 255u;
+                tile[slot < 32u ? t * kLoStride + low_place(t, (int)slot) : 32 * kLoStride + tid] = (_Float16)x[e];
             }
         } else {
             *reinterpret_cast<u32x4 *>(&L.Klo[t][32 * cb + 8 * kq]) = pack8(x);
@@ -323,8 +324,20 @@ __device__ __forceinline__ void store_value_codes(const LayerView &lv, Tiles &L,
 // ---- one packed unit: packed cache -> registers, registers -> tiles (LDS or the scratch area: the stores below only
 // see a reference).  KQ / VQ: the layer's keys / values are quantized (else fp16 rows in the code area).
 template <bool KQ, bool VQ>
-__device__ __forceinline__ void load_packed(const PrefillArgs &a, int bh, int u, int T, int tid, Stage &st)
+__device__ __forceinline__ void load_packed(const PrefillArgs &a, int bh, int u, int T, int tid, const Select *rec, Stage &st)
 {
+    st.c0 = st.c1 = zero4();
+    st.pos = u32x2{0u, 0u};
+    st.compact = 0;
+    if constexpr (KQ) {
+        if (rec) {
+            const int ch = 32 * (tid >> 6) + 8 * ((tid & 63) >> 4);
+            st.compact = rec->compact;
+            st.c0 = ld16(&rec->centre[ch]);
+            st.c1 = ld16(&rec->centre[ch + 4]);
+            st.pos = *reinterpret_cast<const u32x2 *>(&rec->pos[ch]);
+        }
+    }
     const size_t blk = (size_t)bh * a.NB + u;
     if constexpr (KQ) {
         st.k0 = load_key_codes(a.lv, blk, tid);
@@ -347,9 +360,8 @@ __device__ __forceinline__ void load_packed(const PrefillArgs &a, int bh, int u,
 }
 
 template <bool KQ, bool VQ>
-__device__ __forceinline__ void store_packed(const PrefillArgs &a, int tid, const Stage &st, Tiles &L, MetaSlab &M, const Select *rec)
+__device__ __forceinline__ void store_packed(const PrefillArgs &a, int tid, const Stage &st, Tiles &L, MetaSlab &M, bool compact)
 {
-    const bool compact = rec && rec->compact != 0;
     if constexpr (KQ || VQ) {
         wave_lds_sync();                                   // the slab's readers of the unit before are done
         store_meta_piece(M, tid & 63, st.m);
@@ -357,13 +369,13 @@ __device__ __forceinline__ void store_packed(const PrefillArgs &a, int tid, cons
     }
     if constexpr (KQ) {
         if (a.lv.kpt) {
-            if (a.lv.kbits == 8) store_key_codes<8, true>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
-            else if (a.lv.kbits == 4) store_key_codes<4, true>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
-            else store_key_codes<2, true>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
+            if (a.lv.kbits == 8) store_key_codes<8, true>(a.lv, L, M, tid, st, a.scale_log2e, compact);
+            else if (a.lv.kbits == 4) store_key_codes<4, true>(a.lv, L, M, tid, st, a.scale_log2e, compact);
+            else store_key_codes<2, true>(a.lv, L, M, tid, st, a.scale_log2e, compact);
         } else {
-            if (a.lv.kbits == 8) store_key_codes<8, false>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
-            else if (a.lv.kbits == 4) store_key_codes<4, false>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
-            else store_key_codes<2, false>(a.lv, L, M, tid, st.k0, a.scale_log2e, rec, compact);
+            if (a.lv.kbits == 8) store_key_codes<8, false>(a.lv, L, M, tid, st, a.scale_log2e, compact);
+            else if (a.lv.kbits == 4) store_key_codes<4, false>(a.lv, L, M, tid, st, a.scale_log2e, compact);
+            else store_key_codes<2, false>(a.lv, L, M, tid, st, a.scale_log2e, compact);
         }
     } else {
         store_key_rows(L, tid, st.k0, st.k1);
@@ -805,11 +817,13 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
     __shared__ __attribute__((aligned(16))) MetaSlab M[kStagers];
     __shared__ __attribute__((aligned(16))) Tiles tile;
     Stage st;
-    load_packed<KQ, VQ>(a, a.bh0 + local, u, T, tid, st);
+    // The selection record's share is asked for with the unit's codes: field by field where it is needed, it cost three more round trips.
     const Select *rec = KQ && a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
-    store_packed<KQ, VQ>(a, tid, st, tile, M[tid >> 6], rec);
+    load_packed<KQ, VQ>(a, a.bh0 + local, u, T, tid, rec, st);
+    const bool compact = KQ && __builtin_amdgcn_readfirstlane((int)st.compact) != 0;
+    store_packed<KQ, VQ>(a, tid, st, tile, M[tid >> 6], compact);
     __syncthreads();
-    const int lo_pieces = !KQ ? 0 : rec && rec->compact != 0 ? kLoPieces : kTileKiB;
+    const int lo_pieces = !KQ ? 0 : compact ? kLoPieces : kTileKiB;
     uint8_t *dst = a.scratch + ((size_t)local * a.n_blocks + u) * sizeof(Tiles);
     const uint8_t *src = reinterpret_cast<const uint8_t *>(&tile);
     for (int p = tid >> 6; p < kTileKiB + lo_pieces + kValuesKiB; p += kStagers) {
