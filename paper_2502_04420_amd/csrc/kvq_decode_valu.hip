@@ -301,16 +301,25 @@ __global__ __launch_bounds__(256) void decode_valu(DecodeArgs a)
     }
 }
 
+// own value and the other half wave's (fed the same register twice, the lane swap returns the two)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 with_half_partner(float x) { const uint32_t v = __builtin_bit_cast(uint32_t, x); return __builtin_amdgcn_permlane32_swap(v, v, false, false); }
+__device__ __forceinline__ float swap_sum(float x) { const u32x2 v = with_half_partner(x); const uint32_t a = v[0], b = v[1]; return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b); }
+__device__ __forceinline__ float swap_max(float x) { const u32x2 v = with_half_partner(x); const uint32_t a = v[0], b = v[1]; return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)); }
+
 // Merge the splits of one (batch, query head) by log-sum-exp and store fp16 (round to nearest even).
 // 32 lanes hold a record (16 bytes of outputs each), so a wave takes two splits at a time; W records per half wave are in
 // flight at once and one round trip fetches all of up to 2 * WAVES * W splits.  The halves of a wave are merged by a lane
 // exchange, the waves through LDS.  The order of all sums is fixed.  Bound by its launch and that round trip, hence few
 // waves and few loads per thread where there are few splits.  Measured (whole decode call, us per call, 512 threads with a
 // channel each and 8 or 16 records in turn -> this): 7 splits 11.3 -> 10.6 (batch 4, 760 tokens), 16 splits 32.9 -> 32.6
-// (batch 16, 8192 tokens), 33 splits 11.7 -> 11.1 (one sequence of 4133 tokens).
+// (batch 16, 8192 tokens), 33 splits 11.7 -> 11.1 (one sequence of 4133 tokens).  With the arguments asked for at once and lane swaps in place of
+// exchanges through the LDS: 64 splits of 28 / 4 heads, 4 layers of 8 x 32768 tokens 147.5 -> 145.0, 16 splits as above 255.9 -> 255.4 (8 layers).
 template <int WAVES, int W>
 __global__ __launch_bounds__(64 * WAVES) void combine_splits(DecodeArgs a)
 {
+    // (at once: where each is asked for when it is first needed, the records' loads wait behind a second read of the arguments)
+    asm volatile("" ::"s"(a.splits), "s"(a.part_ml), "s"(a.part_o), "s"(a.out));
     const size_t row = blockIdx.x;
     const int lane = threadIdx.x & 31, g = threadIdx.x >> 5;
     const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row * a.splits;
@@ -329,17 +338,17 @@ __global__ __launch_bounds__(64 * WAVES) void combine_splits(DecodeArgs a)
         if (g + 2 * WAVES * k >= a.splits) r[k].x = -INFINITY;   // no such split: weight zero
         M = fmaxf(M, r[k].x);
     }
-    M = fmaxf(M, __shfl_xor(M, 32, 64));                         // (-inf in a wave without splits)
+    M = swap_max(M);                         // (-inf in a wave without splits)
     float L = 0.0f;
     float4 O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
     for (int k = 0; k < W; k++) {
-        const float f = r[k].x == -INFINITY ? 0.0f : exp2f(r[k].x - M);
+        const float f = r[k].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(r[k].x - M);
         L = fmaf(r[k].y, f, L);
         O.x = fmaf(x[k].x, f, O.x); O.y = fmaf(x[k].y, f, O.y); O.z = fmaf(x[k].z, f, O.z); O.w = fmaf(x[k].w, f, O.w);
     }
-    L += __shfl_xor(L, 32, 64);
-    O.x += __shfl_xor(O.x, 32, 64); O.y += __shfl_xor(O.y, 32, 64); O.z += __shfl_xor(O.z, 32, 64); O.w += __shfl_xor(O.w, 32, 64);
+    L = swap_sum(L);
+    O = make_float4(swap_sum(O.x), swap_sum(O.y), swap_sum(O.z), swap_sum(O.w));
     if constexpr (WAVES > 1) {
         __shared__ float Mw[WAVES], Lw[WAVES];
         __shared__ __attribute__((aligned(16))) float Ow[WAVES][kD];
@@ -355,7 +364,7 @@ __global__ __launch_bounds__(64 * WAVES) void combine_splits(DecodeArgs a)
         O = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int k = 0; k < WAVES; k++) {
-            const float f = exp2f(Mw[k] - M);                    // (a wave without splits: factor 0)
+            const float f = __builtin_amdgcn_exp2f(Mw[k] - M);                    // (a wave without splits: factor 0)
             const float4 t = *reinterpret_cast<const float4 *>(&Ow[k][4 * lane]);
             L = fmaf(Lw[k], f, L);
             O.x = fmaf(t.x, f, O.x); O.y = fmaf(t.y, f, O.y); O.z = fmaf(t.z, f, O.z); O.w = fmaf(t.w, f, O.w);
