@@ -798,10 +798,10 @@ __global__ __launch_bounds__(64 * kSelectWaves) void prefill_select(PrefillArgs 
 // KQ / VQ: the layer's keys / values are quantized (else fp16 rows in the code area).
 //
 // The unit is put together in LDS and goes out as whole KiB, 16 bytes per lane at consecutive addresses: bound by the writes
-// (26 KiB per unit, 20 in the compact form; its code and metadata reads are a tenth of that).  Stored to the scratch area
+// (26 KiB per unit, 19 in the compact form; its code and metadata reads are a tenth of that).  Stored to the scratch area
 // straight from the registers that hold the values (64-byte pieces of rows, 8-byte pieces of the transposed values, 2-byte
 // low parts, row padding left out) the lines were written in parts.  Measured (K4V2, compact): 16 caches of 255 units
-// 40 -> 31.5 us, 8 caches of 767 units 60 -> 45 us (4.0 TB/s of reads and writes).
+// 40 -> 31.5 us, 8 caches of 767 units 60 -> 45 us; with 2 KiB of low parts and the selection record asked for early 28.5 and 37.5 us.
 constexpr int kTileKiB = 9, kValuesKiB = 8;
 static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * 32 == kValuesKiB * 1024 &&
               sizeof(Tiles) == (2 * kTileKiB + kValuesKiB) * 1024, "tiles of a unit are whole KiB");
@@ -1524,7 +1524,7 @@ struct LaunchPlan {
 //   waves of the group): one prompt of 2027 tokens, 32 / 8 heads 87 / 76, 5000 tokens 290 / 269, 6000 tokens 390 / 367, 7000 tokens
 //   480 / 483, 8192 tokens 619 / 637; four of 1024 tokens 129 / 114, eight of 500 tokens 165 / 136, four of 6000 tokens 1410 / 1399,
 //   one of 300 tokens 37 / 34; 28 / 4 heads, two of 6000 tokens 621 / 602; 8 / 2 heads, one of 4000 tokens: 89 in pieces / 127.
-//   (An XCD's L2 holds the 20 KiB units of one cache up to about there.)  Caches without packed units take them at any length, their window
+//   (An XCD's L2 holds the 19 KiB units of one cache up to about there.)  Caches without packed units take them at any length, their window
 //   comes through registers either way (us a pass with its append): 32 / 8 heads, one prompt of 300 tokens 22.0 / 20.7, 2027 tokens 129 / 104, 4000 tokens 271 / 265, 16000
 //   tokens 3732 / 3437, four of 4000 tokens 1075 / 927; 28 / 4 heads, two of 8000 tokens 1710 / 1526; last 33 of 8000 tokens 368 / 362.
 // - Tiles cut into pieces: 4 waves where they leave out an empty half of a tile (32 / 8 heads, 300 queries over 8000 tokens 110 / 104, over 24000
