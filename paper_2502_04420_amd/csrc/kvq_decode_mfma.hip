@@ -898,57 +898,70 @@ __device__ __forceinline__ void store_output(uint16_t *out, float4v o, float l)
     __builtin_memcpy(out, &h, sizeof h);
 }
 
-// The records of all splits (at most kMergeSplits; of a tile of 8 heads, 16) of a wave's head or, in a tile of 8, two heads -> outputs.  LANES per head
-// hold the splits' maxima and sums, 32 lanes fetch a record's outputs (16 bytes each): one head is fetched two records at a
-// time, two heads one each.  Splits and heads that do not exist lie beyond the resource and read as zero.  rows: heads of this wave that exist, row: the first.  The order of all sums is fixed, whichever wave comes last.
+// The records of all splits (at most kMergeSplits; of a tile of 8 heads, 16) of a wave's head or, in a tile of 8, two heads -> outputs.  kLanes lanes per
+// head hold the splits' maxima and sums, 32 lanes fetch a record's outputs (16 bytes each), two records of a head at a time.  rows: heads of this
+// wave that exist, row: the first.  The order of all sums is fixed, whichever work-group comes last.
+// Splits and heads that do not exist lie beyond their head's resource and read as zero: a resource per head, since behind one for both the second head's
+// records would come in place of the first head's absent ones, and an infinity among them times the weight zero is no number.
 // The records come from work-groups on all XCDs: they are read past the caches (sc0 sc1), as they were written.
-// Bound by the latency of the reads (0.45 us), so up to 32 records per head are asked for at once, without a branch per record.  One sequence of 8 kv heads,
-// 4133 tokens (27 splits), us a call, with half as many at once and sums that met in LDS behind a barrier / now: 7.9 / 7.4.
+// Bound by the latency of the reads (0.45 us), so up to 32 records of a head (16 of each of two) are asked for at once, without a branch per record.  One
+// sequence of 8 kv heads, 4133 tokens (27 splits), us a call, with half as many at once and sums that met in LDS behind a barrier / now: 7.9 / 7.4.
 template <int GQ, int PAIRS>
 __device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&Ls)[PAIRS], size_t row, int rows, int lane, int wave)
 {
     constexpr int kBeyond = 17;                                  // cache policy bits: sc0, sc1
-    constexpr int kLanes = 256 / GQ, kSubsets = kLanes / 32, kAhead = 16;
+    constexpr int kHeads = GQ / 4, kLanes = 64 / kHeads, kAhead = 16 / kHeads, kList = 32 / kHeads, kRecord = (int)(kD * sizeof(float));
     static_assert(kMergeSplits <= 64 && 2 * PAIRS == 4, "a lane per split of a single head; a wave per head or two");
-    // weights by subset and round; the key waves' A tiles are no longer needed
+    // weights by head, half wave and round; the key waves' A tiles are no longer needed
     float *weights = reinterpret_cast<float *>(&Ls[0].Ak[0][0]) + wave * 64;
     static_assert(sizeof(Ls[0].Ak) >= 4 * 64 * sizeof(float), "the weights fit");
-    const int sl = lane & (kLanes - 1), subset = kLanes == 64 ? lane >> 5 : 0, head = kLanes == 32 ? lane >> 5 : 0;
-    const RowStream po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + row * a.splits * kD, 0, rows * a.splits * (int)(kD * sizeof(float)), 0x00020000);
+    const int half = lane >> 5, sl = lane & (kLanes - 1), head = kHeads == 2 ? half : 0;
+    RowStream po[kHeads];
+#pragma unroll
+    for (int h = 0; h < kHeads; h++) po[h] = __builtin_amdgcn_make_buffer_rsrc(a.part_o + (row + h) * a.splits * kD, 0, h < rows ? a.splits * kRecord : 0, 0x00020000);
     const RowStream pm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + row * a.splits * 2, 0, rows * a.splits * (int)(2 * sizeof(float)), 0x00020000);
     const u32x2 ml = __builtin_amdgcn_raw_buffer_load_b64(pm, (head * a.splits + sl) * 8, 0, kBeyond);
-    u32x4 x[kAhead];
-    const int off = (head * a.splits + subset) * (int)(kD * sizeof(float)) + 16 * (lane & 31);
+    u32x4 x[kHeads][kAhead];
+    const int off = half * kRecord + 16 * (lane & 31);
     auto fetch = [&](int s0) {
 #pragma unroll
-        for (int k = 0; k < kAhead; k++) x[k] = __builtin_amdgcn_raw_buffer_load_b128(po, off + s0 * (int)(kD * sizeof(float)), kSubsets * k * (int)(kD * sizeof(float)), kBeyond);
+        for (int k = 0; k < kAhead; k++)
+#pragma unroll
+            for (int h = 0; h < kHeads; h++) x[h][k] = __builtin_amdgcn_raw_buffer_load_b128(po[h], off + s0 * kRecord, 2 * k * kRecord, kBeyond);
     };
     fetch(0);
     const uint32_t mw = ml[0], lw = ml[1];
     const float m = sl < a.splits ? __builtin_bit_cast(float, mw) : -INFINITY, l = __builtin_bit_cast(float, lw);
     const float M = lanes_max<kLanes>(m);
     const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);         // (no such split: weight zero)
-    weights[kLanes == 64 ? 32 * (lane & 1) + (lane >> 1) : lane] = f;
+    weights[2 * kList * head + kList * (sl & 1) + (sl >> 1)] = f;
     const float sum = lanes_sum<kLanes>(sl < a.splits ? f * l : 0.0f);
     wave_lds_sync();
-    float4v O = {0.0f, 0.0f, 0.0f, 0.0f};
-    const float *w = weights + 32 * (lane >> 5);
-    for (int s0 = 0; s0 < a.splits; s0 += kSubsets * kAhead) {
+    float4v O[kHeads] = {};
+    const float *w = weights + kList * half;
+    for (int s0 = 0; s0 < a.splits; s0 += 2 * kAhead) {
         if (s0 > 0) fetch(s0);
-        float4v wk[kAhead / 4];
+        float4v wk[kHeads][kAhead / 4];
 #pragma unroll
-        for (int k = 0; k < kAhead / 4; k++) wk[k] = *reinterpret_cast<const float4v *>(w + s0 / kSubsets + 4 * k);
+        for (int h = 0; h < kHeads; h++)
 #pragma unroll
-        for (int k = 0; k < kAhead; k++) {
-            const uint32_t w0 = x[k][0], w1 = x[k][1], w2 = x[k][2], w3 = x[k][3];
-            O += wk[k / 4][k % 4] * float4v{__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1), __builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)};
-        }
+            for (int k = 0; k < kAhead / 4; k++) wk[h][k] = *reinterpret_cast<const float4v *>(w + 2 * kList * h + s0 / 2 + 4 * k);
+#pragma unroll
+        for (int k = 0; k < kAhead; k++)
+#pragma unroll
+            for (int h = 0; h < kHeads; h++) {
+                const uint32_t w0 = x[h][k][0], w1 = x[h][k][1], w2 = x[h][k][2], w3 = x[h][k][3];
+                O[h] += wk[h][k / 4][k % 4] * float4v{__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1), __builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)};
+            }
     }
-    if constexpr (kSubsets == 2) {
+    // even and odd splits: of one head in every lane, of two the first's in the lower and the second's in the upper half wave
+    float4v sums;
 #pragma unroll
-        for (int i = 0; i < 4; i++) O[i] = swap_sum(with_half_partner(O[i]));
+    for (int i = 0; i < 4; i++) {
+        const float lower = O[0][i], upper = O[kHeads - 1][i];
+        sums[i] = swap_sum(__builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lower), __builtin_bit_cast(uint32_t, upper), false, false));
     }
-    if (head < rows) store_output(a.out + (row + head) * kD + 4 * (lane & 31), O, sum);
+    if (head < rows) store_output(a.out + (row + head) * kD + 4 * (lane & 31), sums, sum);
 }
 
 // The pairs' results, from LDS, to the record of the split (or, with a single split, to the outputs).  A wave has a head or, in a tile of 8, two, merged here and, by

@@ -83,7 +83,7 @@ def test_infinite_values_stay_infinite(kvq_mod, gq, vb):
             V[0, 0, 3, 5], V[0, 0, T - 1, 77] = float("inf"), float("-inf")
             V[0, 0, 9, 100] = float("nan")
         cache = kvq_mod.KVQ(1, 1, gq, 1, D, 128, [16], [vb], residual=64 if vb < 16 else 0)
-        cache.set_decode_options(0, 1)                                   # (of several splits, absent ones are merged as the first one times zero)
+        cache.set_decode_options(0, 1)                                   # (several: the next test)
         cache.quantize_append(0, K[:, :, :T - 1].contiguous().cuda(), V[:, :, :T - 1].contiguous().cuda())
         out = cache.append_decode_attention(0, K[:, :, T - 1:].contiguous().cuda(), V[:, :, T - 1:].contiguous().cuda(), q[:, :, 0].contiguous().cuda()).cpu()
         cache.close()
@@ -94,3 +94,25 @@ def test_infinite_values_stay_infinite(kvq_mod, gq, vb):
     assert not torch.isfinite(out[0, :, 77]).any() and torch.isnan(out[0, :, 100]).all()
     rest = [c for c in range(D) if c not in (5, 77, 100)]
     assert torch.equal(out[0][:, rest], plain[0][:, rest])
+
+
+@pytest.mark.parametrize("vb", [4, 16])
+@pytest.mark.parametrize("gq", [3, 5, 7, 8, 12])
+def test_infinite_values_stay_infinite_in_merged_splits(kvq_mod, gq, vb):
+    """Several splits, merged by the last work-group: an infinity in one split's record reaches every head's output as it is, from 2
+    splits to as many as are merged that way, and nothing of it reaches another head's record or another channel."""
+    T, D = 32 * 17 + 9, 128
+    g = torch.Generator().manual_seed(6)
+    q, K, V = (torch.randn(1, h, n, D, generator=g).half().cuda() for h, n in ((gq, 1), (1, T), (1, T)))
+    rest = [c for c in range(D) if c != 5]
+    for splits in list(range(2, 10)) + [15, 16, 17]:
+        outs = []
+        for value in (1.0, float("-inf")):
+            V[0, 0, T - 3, 5] = value                                    # (in the window: the last split's)
+            cache = kvq_mod.KVQ(1, 1, gq, 1, D, T, [16], [vb], residual=32 if vb < 16 else 0)
+            cache.set_decode_options(0, splits)
+            cache.quantize_append(0, K, V)
+            outs.append(cache.decode_attention(0, q[:, :, 0].contiguous()).cpu())
+            cache.close()
+        assert (outs[1][0, :, 5] == float("-inf")).all(), (splits, outs[1][0, :, 5])
+        assert torch.equal(outs[0][0][:, rest], outs[1][0][:, rest]), splits
