@@ -261,7 +261,7 @@ __device__ __forceinline__ void await_zero_points(u32x4 (&zb)[4])
 // not exist, they cost a round trip each: the compiler waited for them before it let the first blocks be asked for (it
 // also took loads of the other role's code path to be pending), and, not knowing of the blocks' loads, waited for those too before
 // the queries could be used.  Heads that do not exist read the first head's row.  Together with the arguments asked for at
-// once and the divisions taken out of the way to the first load (decode_mfma), us a call, before / after: 2 kv heads, 512 tokens 7.0 / 6.5; 8 kv heads,
+// once and all divisions but one taken out of the way to the first load (decode_mfma), us a call, before / after: 2 kv heads, 512 tokens 7.0 / 6.5; 8 kv heads,
 // 4133 tokens 9.8 / 9.1; 32 kv heads, 760 tokens 8.6 / 8.0; streaming launches 0.4 shorter (batch 16, 8192 tokens 32.5 / 32.0).
 // (Two channels of every head per lane.  Only the key wave needs them.)
 __device__ __forceinline__ void issue_query(uint32_t &q, const uint8_t *rows, uint32_t voff)
@@ -1044,7 +1044,7 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
     const int n = lane & 15, rq = lane >> 4;
     // The record's lines are asked for at once, here (each is a read from memory of its own; where the compiler asks for an argument when
-    // it is first needed, they follow one another), and nothing on the way to the first loads divides.
+    // it is first needed, they follow one another), and of divisions only the one by the blocks of the range is on the way to the first loads.
     asm volatile("" ::"s"(a.lv.kcode), "s"(a.lv.kmeta), "s"(a.lv.vcode), "s"(a.lv.vmeta), "s"(a.lv.bexp), "s"(a.q), "s"(a.gq), "s"(a.n_blocks), "s"(a.n_res),
                  "s"(a.NB), "s"(a.splits), "s"(a.units_per_split), "s"(a.split_rem), "s"(a.scale_log2e), "s"(a.win_slot));
     const int split = blockIdx.x, bh = blockIdx.y;
@@ -1094,15 +1094,18 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     // cache block number of the i-th phase-1 unit (0 <= i < n1).
     // Every group starts its sweep at a different place of its range and wraps around: groups advance at the
     // same pace, and with equal phases their addresses would keep falling on the same memory channels.
-    // (a fraction of the range, in 2^-32: the steps between neighbouring caches and splits are far from any small fraction)
-    const uint32_t phase = ((uint32_t)bh * 40503u + (uint32_t)split * 9973u) << 16;
-    const int rot = (int)__umulhi(phase, (uint32_t)n1);
+    // (The start decides the order of all sums and how the operands round against the running maximum.  As the upper half of a product with the blocks,
+    // without a division, the same outputs are 5e-5 to 1e-4 of their size elsewhere, no closer to 64 bits and no further; it saves 0.3..1 %: us a
+    // pass, so / with the remainder: 16 layers of 4133 tokens 120.5 / 121.7, 4 layers of 16 x 4096 tokens K8V8 119.4 / 121.2, 8 layers of 16 x 8192
+    // 256.5 / 257.3.)
+    const uint32_t phase = (uint32_t)bh * 40503u + (uint32_t)split * 9973u;
+    const int rot = n1 > 0 ? (int)(phase % (uint32_t)n1) : 0;
     auto blk1 = [&](int i) {
         const int r = i + rot;
         return u0 + (r < n1 ? r : r - n1);
     };
     // cache block number of the i-th of phase 2's blocks (16-bit tensors), with the same rotation
-    const int rot2 = (int)__umulhi(phase, (uint32_t)n2p);
+    const int rot2 = n2p > 0 ? (int)(phase % (uint32_t)n2p) : 0;
     auto blk2 = [&](int i) {
         const int r = i + rot2;
         return u0 + (r < n2p ? r : r - n2p);

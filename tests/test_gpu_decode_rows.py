@@ -1,5 +1,8 @@
 """fp16 rows of a decode call (the window, 16-bit layers): the values go through the matrix cores, their numerators as two fp16
-parts.  Against the oracle with the bars of the parity tests, and where those parts could matter against 64 bits."""
+parts.  Against the oracle with the bars of the parity tests, and where those parts could matter against 64 bits.  And the order in which a
+call takes its blocks."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -116,3 +119,30 @@ def test_infinite_values_stay_infinite_in_merged_splits(kvq_mod, gq, vb):
             cache.close()
         assert (outs[1][0, :, 5] == float("-inf")).all(), (splits, outs[1][0, :, 5])
         assert torch.equal(outs[0][0][:, rest], outs[1][0][:, rest]), splits
+
+
+SWEEPS = {"short": (1, 8, 2, 4133, 4, 2), "streaming": (64, 8, 2, 2000, 4, 4), "tiles of 8": (16, 14, 2, 3000, 8, 2), "half": (2, 8, 2, 3000, 16, 16)}
+
+
+def sweep_outputs(module, batch, hq, hkv, T, kb, vb):
+    """Outputs of one layer's decode attention, of the last sequence."""
+    g = torch.Generator().manual_seed(9)
+    K, V, q = (torch.randn(n, 128, generator=g).half().cuda() for n in (hkv * T, hkv * T, hq))
+    cache = module.KVQ(1, batch, hq, hkv, 128, T, [kb], [vb])
+    # every sequence is the same one, its tokens rolled by another 131
+    roll = lambda x: torch.stack([torch.roll(x.view(hkv, T, 128), 131 * b, 1) for b in range(batch)])     # noqa: E731
+    cache.quantize_append(0, roll(K), roll(V))
+    out = cache.decode_attention(0, q.view(1, hq, 128).expand(batch, hq, 128).contiguous())
+    cache.close()
+    return out[-1].cpu().numpy()
+
+
+@pytest.mark.parametrize("name", list(SWEEPS))
+def test_sweeps_start_where_they_did(kvq_mod, name):
+    """A pair of waves starts its sweep at block (40503 * cache + 9973 * split) mod blocks.  The start decides the order of all sums and, with the running
+    maximum, how the operands round, so another one moves the outputs by 5e-5 to 1e-4 of their size, as far from 64 bits as before but not what they were.
+    Against outputs of that order kept in a file: sums that only differ in their own last bits turn the rounding of one output in several
+    hundred (2-norm: 2^-11 of the value, so 1e-5 where one in a thousand turns)."""
+    kept = np.load(os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "decode_sweep_outputs.npz"))
+    want, got = kept[name].astype(np.float64), sweep_outputs(kvq_mod, *SWEEPS[name]).astype(np.float64)
+    assert np.linalg.norm(got - want) <= 2e-5 * np.linalg.norm(want), np.linalg.norm(got - want) / np.linalg.norm(want)
