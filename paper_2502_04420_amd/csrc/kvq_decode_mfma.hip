@@ -115,17 +115,8 @@ __device__ __forceinline__ float code_weight_inv(int e)
     return 1.0f;
 }
 
-// split two fp32 values into fp16 high parts and fp16 low parts (hi + lo = r to about 2^-21; the
-// operands are kept near the top of the fp16 range, so the low parts are normal numbers too)
-__device__ __forceinline__ void split_pair(float r0, float r1, uint32_t &hi, uint32_t &lo)
-{
-    const half2v h = __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(r0, r1));
-    const float d0 = r0 - (float)h[0], d1 = r1 - (float)h[1];
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(d0, d1));
-}
-
-// The same for two products a0 b0, a1 b1 whose factors are also at hand rounded to fp16 (a16, b16: pairs).  The
+// Split two products a0 b0, a1 b1, whose factors are also at hand rounded to fp16 (a16, b16: pairs), into fp16 high parts and fp16 low parts (the
+// operands are kept near the top of the fp16 range, so the low parts are normal numbers too).  The
 // high parts are the packed fp16 product of the rounded factors (one instruction for both; off the true product by
 // less than 2^-9 of it), the low parts what is missing from the true products, each one mixed-precision
 // multiply-add.  hi + lo = a b to about 2^-20: four instructions instead of six.
@@ -806,11 +797,15 @@ __device__ __forceinline__ void output_packed(const CodeRegs<VB> &blk, uint32_t 
 
 // Output contribution of 32 fp16 rows (numerators of rows past the end are zero).  The rows are the B operand as they are, but for the order: a lane
 // has 8 channels of 8 tokens, and operand e is the 8 tokens of channel 8 n + e, one byte permutation per pair of tokens.  The numerators are the A
-// operand, read from the hand-off tile: 2^12 p as a high and a low fp16 part (p <= 2; together 22 bits of p, down to 2^-36).
-// R[e]: rows 4 rq + i as everywhere (high and low parts of heads 2 rq, 2 rq + 1), channel 8 n + e, times 2^12.
-// With vector multiply-adds instead (16 tokens x 4 channels x the heads, 256 instructions for 4 heads against 75 here) this was the
-// longest step of a short call: a chunk took the value wave 1.1 us, 0.35 now.
-constexpr float kRowLift = 4096.0f;
+// operand, read from the hand-off tile: 2^12 p as an fp16 number and, 2^14 times as large, what that leaves, the nearest fp16 number too (p <= 2).  Together they
+// are p to a unit of its 24th bit for p >= 2^-22 and to 2^-47 below that.  The high part is the nearest number to 2^12 p + 2^-24 and so never zero (the low
+// part makes up for it): an infinite value stays infinite under any weight.
+// R[e]: rows 4 rq + i as everywhere (high and low parts of heads 2 rq, 2 rq + 1), channel 8 n + e, times 2^12 (low parts 2^26).
+// With vector multiply-adds instead (16 tokens x 4 channels x the heads, 256 instructions for 4 heads against about 75 here) this was the
+// longest step of a short call: a chunk took the value wave 1.1 us, 0.35 now.  (Parts cut off instead of rounded, with 2^-12 of the low one's factor: 22 bits
+// of p, nothing below 2^-36, and an infinite value under such a weight was lost.  us a call, so / now: one sequence of 1000 fp16 tokens 6.00 / 6.08, 733 tokens
+// with a window of five chunks 7.1 / 7.2, 8 x 4519 fp16 tokens 29.7 / 29.75.)
+constexpr float kRowLift = 4096.0f, kLowLift = 16384.0f, kLeastHalf = 1.0f / (1 << 24);      // (the last: the smallest fp16 number)
 template <int GQ>
 __device__ __forceinline__ void output_rows(const ValueRows &x, float4v (&R)[8], const QueryRegs<GQ> &Q, const PairLds<GQ> &L, int buf, int lane)
 {
@@ -818,12 +813,15 @@ __device__ __forceinline__ void output_rows(const ValueRows &x, float4v (&R)[8],
     const float *p = &L.P[buf][Q.row >> 1][8 * rq];
     const float4v pa = *reinterpret_cast<const float4v *>(p), pb = *reinterpret_cast<const float4v *>(p + 4);
     const float pp[8] = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+    // (even lanes hold rows of high parts, odd lanes of low parts: the same instructions with other factors)
+    const float of_high = lane & 1 ? -kLowLift : 1.0f, of_p = lane & 1 ? kRowLift * kLowLift : 0.0f;
     uint32_t a[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-        uint32_t hi, lo;
-        split_pair(pp[2 * k] * kRowLift, pp[2 * k + 1] * kRowLift, hi, lo);
-        a[k] = lane & 1 ? lo : hi;
+        const float p0 = pp[2 * k], p1 = pp[2 * k + 1];
+        const half2v h = {(_Float16)fmaf(p0, kRowLift, kLeastHalf), (_Float16)fmaf(p1, kRowLift, kLeastHalf)};
+        const half2v part = {(_Float16)fmaf((float)h[0], of_high, p0 * of_p), (_Float16)fmaf((float)h[1], of_high, p1 * of_p)};
+        a[k] = __builtin_bit_cast(uint32_t, part);
     }
     const half8 Aop = as_half8(a[0], a[1], a[2], a[3]);
 #pragma unroll
@@ -838,11 +836,12 @@ __device__ __forceinline__ void output_rows(const ValueRows &x, float4v (&R)[8],
     }
 }
 
-// high + low parts.  A value that is infinite makes the high part infinite and the low part infinite or, where the numerator has no
+// high + low parts.  An infinite value makes the high part infinite and the low part infinite with either sign or, where the numerator has no
 // low part, not a number: then the high part is the sum.  (Where a value is no number, both are none.)
 __device__ __forceinline__ float join_parts(float hi, float lo)
 {
-    return hi + (lo == lo ? lo : 0.0f);
+    const float sum = fmaf(lo, 1.0f / kLowLift, hi);
+    return sum == sum ? sum : hi;
 }
 
 // shrink: what the outputs of the blocks before the rows (already out of the registers) are to be multiplied by, heads 2 rq and 2 rq + 1

@@ -49,7 +49,7 @@ def test_rows_and_appended_rows(kvq_mod, oracle_mod, gq, hkv, batch, T, residual
 def test_small_numerators_count(kvq_mod, vb):
     """One token takes nearly all of the weight and has zeros as values; the others weigh 2^-14 .. 2^-34 of it and hold values up to
     6e4, so the outputs are made of small numerators alone, whose high parts are down to fp16 subnormals without the lift.  A numerator
-    keeps 22 bits (2^-21 of it, or 2^-37 where the two parts end): |error| <= sum_t (2^-21 p_t + 2^-36) |v_t| / l, and the fp16 rounding."""
+    keeps 24 bits, or 2^-47 where its two parts end; |error| <= sum_t (2^-20 p_t + 2^-47) |v_t| / l, and the fp16 rounding."""
     T, D = 32 + 23, 128
     g = torch.Generator().manual_seed(5)
     q = torch.zeros(1, 4, D, dtype=torch.float16)
@@ -66,7 +66,7 @@ def test_small_numerators_count(kvq_mod, vb):
     s = (q.double()[0] @ K.double()[0, 0].T) / np.sqrt(D)
     p = torch.exp(s - s.amax(1, keepdim=True))
     ref = (p @ V.double()[0, 0]) / p.sum(1, keepdim=True)
-    bound = ((2.0 ** -20 * p + 2.0 ** -36) @ V.double()[0, 0].abs()) / p.sum(1, keepdim=True) + 2.0 ** -11 * ref.abs() + 2.0 ** -24
+    bound = ((2.0 ** -20 * p + 2.0 ** -47) @ V.double()[0, 0].abs()) / p.sum(1, keepdim=True) + 2.0 ** -11 * ref.abs() + 2.0 ** -24
     assert ref.abs().min() > 1e-3 and ((out[0] - ref).abs() <= bound).all(), ((out[0] - ref).abs() / bound).max()
     cache.close()
 
@@ -93,7 +93,7 @@ def test_infinite_values_stay_infinite(kvq_mod, gq, vb):
         if not bad:
             plain = out
     assert (out[0, :, 5] == float("inf")).all()
-    # (rows past the end repeat the last one with weight zero: its infinity times zero is no number, as it always was)
+    # (rows past the end repeat the last one with weight zero, and its infinity times zero is no number, but for the high parts, which are never zero)
     assert not torch.isfinite(out[0, :, 77]).any() and torch.isnan(out[0, :, 100]).all()
     rest = [c for c in range(D) if c not in (5, 77, 100)]
     assert torch.equal(out[0][:, rest], plain[0][:, rest])
@@ -119,6 +119,59 @@ def test_infinite_values_stay_infinite_in_merged_splits(kvq_mod, gq, vb):
             cache.close()
         assert (outs[1][0, :, 5] == float("-inf")).all(), (splits, outs[1][0, :, 5])
         assert torch.equal(outs[0][0][:, rest], outs[1][0][:, rest]), splits
+
+
+@pytest.mark.parametrize("vb", [4, 16])
+@pytest.mark.parametrize("gq", [1, 4, 7])
+def test_numerators_far_below_the_largest(kvq_mod, gq, vb):
+    """One token takes nearly all of the weight and has zeros as values; the others weigh 2^-37 to 2^-39 of it and hold values of
+    3e4 to 6e4, so each output is a few 2^-18: a numerator keeps 2^-47 where its bits end, and |error| <= sum_t 2^-47 |v_t| / l,
+    half of the outputs' spacing (fp16 subnormals: 2^-24), and 2^-18 of the sum (scores of 39 in fp32, exponentiated)."""
+    T, D = 32 + 31, 128
+    g = torch.Generator().manual_seed(8)
+    q = torch.zeros(1, gq, D, dtype=torch.float16)
+    q[..., 0] = 32.0
+    K = torch.zeros(1, 1, T, D, dtype=torch.float16)
+    logit = -(37 + 2 * torch.arange(T) / T)                              # in powers of two
+    logit[7] = 0
+    K[0, 0, :, 0] = (logit * np.log(2) * np.sqrt(D) / 32).half()
+    V = (3e4 * (1 + torch.rand(1, 1, T, D, generator=g))).half()
+    V[0, 0, 7] = 0
+    cache = kvq_mod.KVQ(1, 1, gq, 1, D, 128, [16], [vb], residual=64 if vb < 16 else 0)     # all of it in the window, or one unit of a 16-bit layer and the rest
+    cache.set_decode_options(0, 1)
+    cache.quantize_append(0, K.cuda(), V.cuda())
+    out = cache.decode_attention(0, q.cuda()).cpu().double()
+    cache.close()
+    s = (q.double()[0] @ K.double()[0, 0].T) / np.sqrt(D)
+    p = torch.exp(s - s.amax(1, keepdim=True))
+    ref = (p @ V.double()[0, 0]) / p.sum(1, keepdim=True)
+    bound = (2.0 ** -47 * V.double()[0, 0].abs().sum(0)) / p.sum(1, keepdim=True) + 2.0 ** -25 + 2.0 ** -18 * ref.abs()
+    assert ref.min() > 2.0 ** -19 and ((out[0] - ref).abs() <= bound).all(), ((out[0] - ref).abs() / bound).max()
+
+
+@pytest.mark.parametrize("vb", [4, 16])
+@pytest.mark.parametrize("power", [-3, -25, -38, -50, -80])
+def test_infinite_values_under_small_weights(kvq_mod, power, vb):
+    """An infinite value under a weight of 2^power of the largest: infinite, with the value's sign, next to another infinite one under a large weight,
+    and where a chunk of rows follows another.  Infinities of both signs, or a value that is no number, give no number."""
+    T, D, gq = 32 + 29, 128, 4
+    q = torch.zeros(1, gq, D, dtype=torch.float16)
+    q[..., 0] = 64.0
+    K = torch.zeros(1, 1, T, D, dtype=torch.float16)
+    small = [5, 40]
+    K[0, 0, small, 0] = power * np.log(2) * np.sqrt(D) / 64
+    V = torch.ones(1, 1, T, D, dtype=torch.float16)
+    V[0, 0, 5, 1], V[0, 0, 40, 2], V[0, 0, 5, 3], V[0, 0, 11, 3] = float("inf"), float("-inf"), float("inf"), float("inf")
+    V[0, 0, 40, 4], V[0, 0, 11, 4], V[0, 0, 5, 5], V[0, 0, 40, 5], V[0, 0, 5, 6] = float("-inf"), float("-inf"), float("inf"), float("-inf"), float("nan")
+    cache = kvq_mod.KVQ(1, 1, gq, 1, D, 128, [16], [vb], residual=64 if vb < 16 else 0)
+    cache.set_decode_options(0, 1)
+    cache.quantize_append(0, K.cuda(), V.cuda())
+    out = cache.decode_attention(0, q.cuda()).cpu()[0]
+    cache.close()
+    inf = float("inf")
+    for channel, value in ((1, inf), (2, -inf), (3, inf), (4, -inf)):
+        assert (out[:, channel] == value).all(), (channel, out[:, channel])
+    assert torch.isnan(out[:, 5:7]).all() and torch.isfinite(out[:, 7:]).all() and torch.isfinite(out[:, 0]).all()
 
 
 SWEEPS = {"short": (1, 8, 2, 4133, 4, 2), "streaming": (64, 8, 2, 2000, 4, 4), "tiles of 8": (16, 14, 2, 3000, 8, 2), "half": (2, 8, 2, 3000, 16, 16)}
