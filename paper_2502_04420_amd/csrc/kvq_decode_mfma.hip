@@ -902,6 +902,8 @@ __device__ __forceinline__ void store_output(uint16_t *out, float4v o, float l)
 // wave that exist, row: the first.  The order of all sums is fixed, whichever work-group comes last.
 // Splits and heads that do not exist lie beyond their head's resource and read as zero: a resource per head, since behind one for both the second head's
 // records would come in place of the first head's absent ones, and an infinity among them times the weight zero is no number.
+// A record's place is in the vector offset, which is checked against the resource as it is (as a scalar offset it would be taken off the resource's
+// size first, which is smaller where records are absent).
 // The records come from work-groups on all XCDs: they are read past the caches (sc0 sc1), as they were written.
 // Bound by the latency of the reads (0.45 us), so up to 32 records of a head (16 of each of two) are asked for at once, without a branch per record.  One
 // sequence of 8 kv heads, 4133 tokens (27 splits), us a call, with half as many at once and sums that met in LDS behind a barrier / now: 7.9 / 7.4.
@@ -926,7 +928,7 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, PairLds<GQ> (&
 #pragma unroll
         for (int k = 0; k < kAhead; k++)
 #pragma unroll
-            for (int h = 0; h < kHeads; h++) x[h][k] = __builtin_amdgcn_raw_buffer_load_b128(po[h], off + s0 * kRecord, 2 * k * kRecord, kBeyond);
+            for (int h = 0; h < kHeads; h++) x[h][k] = __builtin_amdgcn_raw_buffer_load_b128(po[h], off + (s0 + 2 * k) * kRecord, 0, kBeyond);
     };
     fetch(0);
     const uint32_t mw = ml[0], lw = ml[1];

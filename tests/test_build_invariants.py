@@ -207,6 +207,21 @@ def test_decode_kernels_wait_for_nothing_between_queries_and_first_blocks(src):
     assert kernels == 3 * 3 * 2 * 2 * 2                                  # key and value bits, head tiles, scale precisions, key groupings
 
 
+def test_merge_of_the_splits_reads_at_checked_offsets():
+    """The work-group that merges asks for a fixed number of records and has the absent ones read as zero: their place must be in the offset that
+    the buffer resource checks, so the loads past the caches (the merge's, all of them) have no scalar offset."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    from paper_2502_04420_amd import build as B
+
+    kernels = B.kernel_bodies(B.device_assembly("kvq_decode_short.hip"), "decode_mfma")
+    assert kernels
+    for name, body in kernels:
+        loads = re.findall(r"buffer_load_dwordx[24] \S+ (\S+), (s\[[0-9:]+\]), (\S+) offen( offset:\d+)? sc0 sc1", body)
+        assert len(loads) >= 17 and len(loads) == len(re.findall(r"buffer_load\w* [^\n]*sc0 sc1", body)), (name, len(loads))
+        assert {x[2] for x in loads} == {"0"}, name
+
+
 def _record_bytes(asm, name):
     """Bytes of the argument records of the kernels whose mangled name contains `name` (implicit arguments included)."""
     return {int(n) for n in re.findall(r"\.amdhsa_kernel _Z\w*%s\w*\n(?:(?!\.end_amdhsa_kernel).*\n)*?\s*\.amdhsa_kernarg_size (\d+)" % name, asm)}
