@@ -66,11 +66,20 @@ struct Tiles {
 // read takes the same piece of 16 neighbouring rows for 16 lanes; a 16-byte read of a wave is served 16 lanes at a time, but not in the order of
 // the lanes.  Measured with a probe kernel, eight waves reading, bytes per cycle: rotated by row / 2 256, like a linear read and rows of 288 bytes;
 // by row / 4, by row and not at all 160, rows of 80 bytes 160.
-__host__ __device__ constexpr int rotated_piece(int row, int piece) { return (piece + (row >> 1)) & 3; }
+__host__ __device__ constexpr int rotated_piece(int row, int piece, int shift = 1) { return (piece + (row >> shift)) & 3; }
 
-// Place of a token in the V^ row of a channel.  A lane's operand of the output product (tokens 4 rq .. + 3 and 16 + 4 rq .. + 3, the
+// Place of a token in the V^ row of a channel, rotated by channel >> shift.  A lane's operand of the output product (tokens 4 rq .. + 3 and 16 + 4 rq .. + 3, the
 // rows of the scores' result tile that it holds) is one piece of 16 bytes.
-__host__ __device__ constexpr int value_place(int channel, int t) { return 8 * rotated_piece(channel, (t >> 2) & 3) + 4 * (t >> 4) + (t & 3); }
+__host__ __device__ constexpr int value_place(int channel, int t, int shift) { return 8 * rotated_piece(channel, (t >> 2) & 3, shift) + 4 * (t >> 4) + (t & 3); }
+
+// fp16 keys in work-groups of 4 waves: rotated by channel / 4, and a step's fetches go out at its top.  The step is short there (no low parts, four
+// batches) and ends with a wait for the unit that it fetches, and the transposed stores of a value row meet two piece addresses per lane instead
+// of four.  us a pass, K16V16, rotated by / 2 and fetched between the products / so: 32 / 8 heads, four prompts of 2000 tokens 209.6 / 201.6, one
+// of 190 15.25 / 15.10, four of 4000 631 / 650, last 300 of 8000 85.3 / 83.6; 28 / 4 heads, one of 1000 35.4 / 34.8; 8 / 2 heads, one of 6000 118.4 / 112.9, of
+// 2500 39.9 / 38.6; 99 such calls lie between 0.97 and 1.05, without a line between them.  Work-groups of 8 waves wait once in two units and gain: last 512 of
+// 24576 240.5 / 246, 8 / 2 heads, one prompt of 9000 tokens 215.5 / 220.
+constexpr bool half_keys_of_4(bool quantized, int waves) { return !quantized && waves == 4; }
+constexpr int value_shift(bool quantized, int waves) { return half_keys_of_4(quantized, waves) ? 2 : 1; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -160,6 +169,7 @@ __device__ __forceinline__ u32x4 load_value_row_piece(const uint16_t *base, int 
     return ld16(base + (size_t)(ring ? pc % ring : pc) * kD + 8 * c16);
 }
 
+template <int SHIFT>
 __device__ __forceinline__ void store_value_piece(Tiles &L, int idx, u32x4 x, int pos0, int T)
 {
     const int t = idx & 31, c16 = idx >> 5;
@@ -167,7 +177,7 @@ __device__ __forceinline__ void store_value_piece(Tiles &L, int idx, u32x4 x, in
 #pragma unroll
     for (int e = 0; e < 8; e++) {
         const uint32_t w = x[e >> 1];
-        L.Vt[8 * c16 + e][value_place(8 * c16 + e, t)] = __builtin_bit_cast(_Float16, (uint16_t)(live ? ((e & 1) ? w >> 16 : w & 0xffffu) : 0u));
+        L.Vt[8 * c16 + e][value_place(8 * c16 + e, t, SHIFT)] = __builtin_bit_cast(_Float16, (uint16_t)(live ? ((e & 1) ? w >> 16 : w & 0xffffu) : 0u));
     }
 }
 
@@ -301,7 +311,7 @@ __device__ __forceinline__ void store_key_codes(const LayerView &lv, Tiles &L, c
     }
 }
 
-template <int BITS>
+template <int BITS, int SHIFT>
 __device__ __forceinline__ void store_value_codes(const LayerView &lv, Tiles &L, const MetaSlab &M, int tid, u32x4 c)
 {
     const int l = tid & 63, g = tid >> 6, n = l & 15, kq = l >> 4;
@@ -316,8 +326,8 @@ __device__ __forceinline__ void store_value_codes(const LayerView &lv, Tiles &L,
         for (int e = 0; e < 8; e++) x[e] = fmaf(code_of<BITS>(w0, w1, mm, e), s[e], z[e]);
         const u32x4 h = pack8(x);
         const int ch = 16 * (2 * g + mm) + n;
-        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq)]) = make_uint2(h[0], h[1]);
-        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq + 4)]) = make_uint2(h[2], h[3]);
+        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq, SHIFT)]) = make_uint2(h[0], h[1]);
+        *reinterpret_cast<uint2 *>(&L.Vt[ch][value_place(ch, 8 * kq + 4, SHIFT)]) = make_uint2(h[2], h[3]);
     }
 }
 
@@ -359,7 +369,7 @@ __device__ __forceinline__ void load_packed(const PrefillArgs &a, int bh, int u,
     else st.m = zero4();
 }
 
-template <bool KQ, bool VQ>
+template <bool KQ, bool VQ, int SHIFT>
 __device__ __forceinline__ void store_packed(const PrefillArgs &a, int tid, const Stage &st, Tiles &L, MetaSlab &M, bool compact)
 {
     if constexpr (KQ || VQ) {
@@ -381,24 +391,25 @@ __device__ __forceinline__ void store_packed(const PrefillArgs &a, int tid, cons
         store_key_rows(L, tid, st.k0, st.k1);
     }
     if constexpr (VQ) {
-        if (a.lv.vbits == 8) store_value_codes<8>(a.lv, L, M, tid, st.v0);
-        else if (a.lv.vbits == 4) store_value_codes<4>(a.lv, L, M, tid, st.v0);
-        else store_value_codes<2>(a.lv, L, M, tid, st.v0);
+        if (a.lv.vbits == 8) store_value_codes<8, SHIFT>(a.lv, L, M, tid, st.v0);
+        else if (a.lv.vbits == 4) store_value_codes<4, SHIFT>(a.lv, L, M, tid, st.v0);
+        else store_value_codes<2, SHIFT>(a.lv, L, M, tid, st.v0);
     } else {
-        store_value_piece(L, tid, st.v0, 0, 32);
-        store_value_piece(L, tid + 256, st.v1, 0, 32);
+        store_value_piece<SHIFT>(L, tid, st.v0, 0, 32);
+        store_value_piece<SHIFT>(L, tid + 256, st.v1, 0, 32);
     }
 }
 
 // ---- one chunk of the fp16 window, ring -> LDS tiles (at most two chunks per work-group: staged without overlap)
+template <int SHIFT>
 __device__ __forceinline__ void stage_window(const PrefillArgs &a, int bh, int u, int T, int tid, Tiles &L)
 {
     const uint16_t *krows = a.lv.kres + (size_t)bh * a.RC * kD, *vrows = a.lv.vres + (size_t)bh * a.RC * kD;
     const u32x4 k0 = load_row_piece(krows, a.RC, 32 * u, T, tid), k1 = load_row_piece(krows, a.RC, 32 * u, T, tid + 256);
     const u32x4 v0 = load_value_row_piece(vrows, a.RC, 32 * u, T, tid), v1 = load_value_row_piece(vrows, a.RC, 32 * u, T, tid + 256);
     store_key_rows(L, tid, live_piece(k0, 32 * u, T, tid), live_piece(k1, 32 * u, T, tid + 256));
-    store_value_piece(L, tid, v0, 32 * u, T);
-    store_value_piece(L, tid + 256, v1, 32 * u, T);
+    store_value_piece<SHIFT>(L, tid, v0, 32 * u, T);
+    store_value_piece<SHIFT>(L, tid + 256, v1, 32 * u, T);
 }
 
 __device__ __forceinline__ float xor_lanes(float x, int mask) { return __shfl_xor(x, mask, 64); }
@@ -408,9 +419,10 @@ __device__ __forceinline__ float xor_lanes(float x, int mask) { return __shfl_xo
 // S^T = K^ Q^T: rows = tokens 16 tt + 4 rq + r, column = query n of tile qt.  KLO: quantized keys, whose fp16 rounding
 // remainders are multiplied as well.
 // the A operand of the output product for channel tile ct: V^T rows 16 ct + n, tokens {4 rq .. + 3, 16 + 4 rq .. + 3}
+template <int SHIFT>
 __device__ __forceinline__ half8 value_operand(const Tiles &X, int ct, int n, int rq)
 {
-    return *reinterpret_cast<const half8 *>(&X.Vt[16 * ct + n][8 * rotated_piece(n, rq)]);            // (16 ct: whole turns)
+    return *reinterpret_cast<const half8 *>(&X.Vt[16 * ct + n][8 * rotated_piece(n, rq, SHIFT)]);            // (16 ct: whole turns)
 }
 
 struct NoSlice { __device__ __forceinline__ void operator()(int) const {} };
@@ -420,7 +432,7 @@ template <int LO> constexpr int score_batches() { return LO == kLoAll ? 8 : LO =
 
 // LO: how the low parts of quantized keys come (none: fp16 rows; all channels: Tiles::Klo; compact: the tile of the 32
 // selected channels, against Qlo = the queries' values at those channels).
-template <int LO, class Slice = NoSlice>
+template <int LO, int SHIFT, class Slice = NoSlice>
 __device__ __forceinline__ void score_unit(const Tiles &X, const half8 (&Qf)[kQT][4], const half8 (&Qlo)[kQT], float4v (&S)[2][kQT],
                                            int n, int rq, const float4v (&init)[kQT], const Tiles *Xv = nullptr, half8 *Av = nullptr,
                                            Slice slice = Slice())
@@ -463,7 +475,7 @@ __device__ __forceinline__ void score_unit(const Tiles &X, const half8 (&Qf)[kQT
         if (bt + kAhead < kBatches) fetch(bt + kAhead, A0[bt + kAhead], A1[bt + kAhead]);
         if (Xv && bt >= kVFirst && bt < kVFirst + 2) {
 #pragma unroll
-            for (int k = 0; k < 4; k++) Av[4 * (bt - kVFirst) + k] = value_operand(*Xv, 4 * (bt - kVFirst) + k, n, rq);
+            for (int k = 0; k < 4; k++) Av[4 * (bt - kVFirst) + k] = value_operand<SHIFT>(*Xv, 4 * (bt - kVFirst) + k, n, rq);
         }
         asm volatile("" ::: "memory");
         const int step = bt & 3;
@@ -806,8 +818,9 @@ constexpr int kTileKiB = 9, kValuesKiB = 8;
 static_assert(sizeof(_Float16) * 32 * kKStride == kTileKiB * 1024 && sizeof(_Float16) * kD * 32 == kValuesKiB * 1024 &&
               sizeof(Tiles) == (2 * kTileKiB + kValuesKiB) * 1024, "tiles of a unit are whole KiB");
 
-template <bool KQ, bool VQ>
-__global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs a)
+// SHIFT: the value rows' rotation that the attention kernel behind it reads (value_shift).
+template <bool KQ, bool VQ, int SHIFT>
+__device__ __forceinline__ void dequantize_unit(const PrefillArgs &a)
 {
     const int tid = threadIdx.x, u = blockIdx.x, local = blockIdx.y;
     // The argument record's lines are asked for at once (RC: read along with NB, and its register is free for the next load only then).
@@ -821,7 +834,7 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
     const Select *rec = KQ && a.select ? reinterpret_cast<const Select *>(a.select) + local : nullptr;
     load_packed<KQ, VQ>(a, a.bh0 + local, u, T, tid, rec, st);
     const bool compact = KQ && __builtin_amdgcn_readfirstlane((int)st.compact) != 0;
-    store_packed<KQ, VQ>(a, tid, st, tile, M[tid >> 6], compact);
+    store_packed<KQ, VQ, SHIFT>(a, tid, st, tile, M[tid >> 6], compact);
     __syncthreads();
     const int lo_pieces = !KQ ? 0 : compact ? kLoPieces : kTileKiB;
     uint8_t *dst = a.scratch + ((size_t)local * a.n_blocks + u) * sizeof(Tiles);
@@ -831,6 +844,13 @@ __global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs 
         *reinterpret_cast<u32x4 *>(dst + off) = *reinterpret_cast<const u32x4 *>(src + off);
     }
 }
+
+template <bool KQ, bool VQ>
+__global__ __launch_bounds__(64 * kStagers) void prefill_dequantize(PrefillArgs a) { dequantize_unit<KQ, VQ, value_shift(KQ, 8)>(a); }
+
+// the same in front of half_keys_of_4
+template <bool VQ>
+__global__ __launch_bounds__(64 * kStagers) void units_of_half_keys(PrefillArgs a) { dequantize_unit<false, VQ, value_shift(false, 4)>(a); }
 
 // A unit goes from the scratch area into an LDS buffer without passing through registers: a wave issues
 // global-to-LDS loads of 1 KiB each (64 lanes x 16 bytes, which land at consecutive LDS addresses from the base
@@ -872,7 +892,11 @@ __device__ __forceinline__ void fetch_unit(const uint8_t *unit, Tiles &L, int wa
     for (int i = 0; i < fetch_slots<LO, WAVES>(); i++) fetch_slot<LO, WAVES>(unit, L, wave, lane, i);
 }
 
-// what a step fetches on its way
+// what a step fetches on its way, or nothing
+struct NoFetch {
+    static constexpr int kSlots = 0;
+    __device__ __forceinline__ void operator()(int) const {}
+};
 template <int LO, int WAVES>
 struct UnitFetch {
     const uint8_t *unit;
@@ -947,6 +971,8 @@ template <int LO, bool CUT, int WAVES, bool PACKED>
 __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of, const Select *rec, int local, const Piece &pc)
 {
     constexpr bool KLO = LO != kLoNone;
+    constexpr int kShift = value_shift(KLO, WAVES);
+    constexpr bool kRide = !half_keys_of_4(KLO, WAVES);          // a step's fetches go out between its products
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, rq = lane >> 4;
@@ -1100,17 +1126,17 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
             }
         };
         set_base();
-        if (ub <= wlast) score_unit<LO>(L[0], Qf, Qlo, S, n, rq, init);
+        if (ub <= wlast) score_unit<LO, kShift>(L[0], Qf, Qlo, S, n, rq, init);
         // one unit: its scores come in Sin, those of the next unit leave in Sout (the two arrays swap roles from unit to
         // unit).  Whether a unit may take the calm form is decided one unit ahead, right after its scores were issued:
         // the test then sits next to the output products of the unit before, which need nothing from it.
         bool calm = false;                                       // the first unit never is: the references start at -inf
         // The wave's loads of unit uf go out on the way (into Xf, which everybody left at the last barrier), one or two behind each batch of products: issued
         // all at once behind the barrier, by all waves, they wait for each other (80 to 100 cycles each, 200..245 a unit and wave) while the matrix cores idle.
-        // us a pass, so / on the way: a 2027-token prompt, 4 layers 342 / 330, 4 x 8192 tokens 2482 / 2437, last 512 of 24576, 4 layers 1088 / 1074.
+        // (Half-precision keys in 4 waves: see half_keys_of_4.)  us a pass, so / on the way: a 2027-token prompt, 4 layers 342 / 330, 4 x 8192 tokens 2482 / 2437, last 512 of 24576, 4 layers 1088 / 1074.
         auto step = [&](int u, const Tiles &X0, const Tiles &X1, const float4v (&Sin)[2][kQT], float4v (&Sout)[2][kQT], int uf, Tiles &Xf) {
             const UnitFetch<LO, WAVES> ride = {unit_at(uf), Xf, wave, lane, WAVES == 8 || uf < nb};
-            if (!(u <= wlast && calm)) {
+            if (kRide && !(u <= wlast && calm)) {
 #pragma unroll
                 for (int i = 0; i < ride.kSlots; i++) ride(i);
             }
@@ -1125,17 +1151,18 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
                     // the common case, one stretch of straight-line code: score products of the next unit next to the
                     // weights of this one against the unchanged reference (calm implies that there is a next unit, and
                     // that this unit's scores are relative to the reference as it stands: base, init are up to date)
-                    score_unit<LO>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av, CalmSoftmax<KLO, score_batches<LO>(), UnitFetch<LO, WAVES>>{Sin, c, m, lsum, P, ride});
+                    if constexpr (kRide) score_unit<LO, kShift>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av, CalmSoftmax<KLO, score_batches<LO>(), UnitFetch<LO, WAVES>>{Sin, c, m, lsum, P, ride});
+                    else score_unit<LO, kShift>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av, CalmSoftmax<KLO, score_batches<LO>(), NoFetch>{Sin, c, m, lsum, P, NoFetch()});
                 } else {
                     float bin[kQT];
 #pragma unroll
                     for (int qt = 0; qt < kQT; qt++) bin[qt] = base[qt];
                     if (ahead) {
                         set_base();
-                        score_unit<LO>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av);
+                        score_unit<LO, kShift>(X1, Qf, Qlo, Sout, n, rq, init, &X0, Av);
                     } else {
 #pragma unroll
-                        for (int ct = 0; ct < 8; ct++) Av[ct] = value_operand(X0, ct, n, rq);
+                        for (int ct = 0; ct < 8; ct++) Av[ct] = value_operand<kShift>(X0, ct, n, rq);
                     }
                     if (u < open_units) moved = softmax_unit<false, KLO>(Sin, c, u, qpos, bin, m, lsum, P, alpha, rq);
                     else moved = softmax_unit<true, KLO>(Sin, c, u, qpos, bin, m, lsum, P, alpha, rq);
@@ -1166,9 +1193,11 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
         } else {
             for (int u = ub; u < nb; u += 2) {
                 const int b1 = after(b0), b2 = after(b1);
+                if (!kRide) fetch(u + 2, L[b2]);
                 step(u, L[b0], L[b1], S, Sn, u + 2, L[b2]);     // buffer of unit u - 1
                 wait_fetches();                                 // unit u + 2 is there
                 __syncthreads();
+                if (!kRide) fetch(u + 3, L[b0]);
                 if (u + 1 < nb) step(u + 1, L[b1], L[b2], Sn, S, u + 3, L[b0]);
                 wait_fetches();
                 __syncthreads();
@@ -1183,19 +1212,19 @@ __device__ __forceinline__ void attend(const PrefillArgs &a, const Rows &rows_of
         for (int qt = 0; qt < kQT; qt++) woff[qt] = kept[64 * WAVES * qt];
     }
     for (int u = nbt; u < uend; u++) {
-        if (WAVES == kStagers || wave < kStagers) stage_window(a, bh, u, T, tid, L[0]);
+        if (WAVES == kStagers || wave < kStagers) stage_window<kShift>(a, bh, u, T, tid, L[0]);
         __syncthreads();
         if (u <= wlast) {
             float4v S[2][kQT];
             half8 P[kQT];
             float alpha[kQT];
             const float4v none[kQT] = {};
-            score_unit<kLoNone>(L[0], Qf, Qlo, S, n, rq, none);                 // fp16 rows: raw scores
+            score_unit<kLoNone, kShift>(L[0], Qf, Qlo, S, n, rq, none);                 // fp16 rows: raw scores
             softmax_unit<true, false>(S, c, u, qpos, woff, m, lsum, P, alpha, rq);
             output_rescale(alpha, O);
             half8 Av[8];
 #pragma unroll
-            for (int ct = 0; ct < 8; ct++) Av[ct] = value_operand(L[0], ct, n, rq);
+            for (int ct = 0; ct < 8; ct++) Av[ct] = value_operand<kShift>(L[0], ct, n, rq);
             output_add(Av, P, O);
         }
         __syncthreads();
@@ -1671,7 +1700,10 @@ hipError_t launch_prefill_attention(const PrefillArgs &a, int part_slots, hipStr
             else hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
             begin = nullptr;
         };
-        if (kq && vq) launch(prefill_dequantize<true, true>);
+        if (half_keys_of_4(kq, plan.waves)) {
+            if (vq) launch(units_of_half_keys<true>);
+            else launch(units_of_half_keys<false>);
+        } else if (kq && vq) launch(prefill_dequantize<true, true>);
         else if (kq) launch(prefill_dequantize<true, false>);
         else if (vq) launch(prefill_dequantize<false, true>);
         else launch(prefill_dequantize<false, false>);

@@ -280,6 +280,8 @@ def test_prefill_launches_ask_for_their_arguments_at_once():
         assert body.split("s_cbranch", 1)[0].count("lgkmcnt(0)") == 1, name
     kernels = B.kernel_bodies(asm, "prefill_dequantize")
     assert len(kernels) == 4
+    assert _record_bytes(asm, "units_of_half_keys") == {160} and len(B.kernel_bodies(asm, "units_of_half_keys")) == 2
+    kernels += B.kernel_bodies(asm, "units_of_half_keys")
     for name, body in kernels:                          # every line of the record is on its way at the first wait
         loads = re.findall(r"s_load_dword(x\d+)? \S+ s\[0:1\], (0x[0-9a-f]+)", body.split("lgkmcnt(0)", 1)[0])
         assert {(int(off, 16) + 4 * int(n[1:] or 1) - 1) // 64 for n, off in loads} == {0, 1, 2}, (name, loads)

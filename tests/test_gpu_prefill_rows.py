@@ -124,6 +124,23 @@ def test_forms_of_the_units_in_work_groups_of_four_waves(kvq_mod, oracle_mod, fo
     g.close()
 
 
+@pytest.mark.parametrize("vb", [16, 8, 2])
+@pytest.mark.parametrize("T,n_q,batch,hq,hkv,launch", [
+    (257, 129, 2, 3, 3, [(6, 4, 1, PAIRED, 1)]), (420, 420, 4, 8, 2, [(8, 4, 4, PAIRED, 1)]),       # whole tiles, 4 waves
+    (2500, 33, 8, 14, 2, [(16, 4, 7, BY_CACHE, 4)]),                     # pieces, 4 waves
+    (1600, 385, 4, 4, 2, [(8, 8, 1, BY_CACHE, 4)]), (3000, 17, 2, 14, 2, [(4, 8, 1, BY_CACHE, 7)]),  # pieces, 8 waves: one head's rows
+    (5000, 60, 16, 8, 2, [(16, 8, 2, BY_CACHE, 8)] * 2),                 # ... several heads'
+])
+def test_half_precision_keys(kvq_mod, oracle_mod, T, n_q, batch, hq, hkv, launch, vb):
+    """Value rows of fp16-key layers lie in another order for 4 waves than for 8 (value_shift), packed values and the window's rows alike, and
+    4 waves fetch a unit at the top of a step."""
+    w = W.Workload("half keys", 1, batch, hq, hkv, 128, T, [16], [vb], seed=1350 + T + n_q, outlier_channels=3)
+    out, o64, g, o, q = _run(kvq_mod, oracle_mod, w, n_q, max_tokens=T)
+    assert forms(g, T, n_q) == launch
+    assert_prefill_close(out, o64, "V%d" % vb)
+    g.close()
+
+
 @pytest.mark.parametrize("T,n_q,batch,hq,hkv,room,form", [
     (6300, 9, 100, 8, 1, 60000, [(100, 8, 8, BY_CACHE, 1)]),             # whole tiles of several heads' queries, 8 waves
     (6300, 200, 96, 8, 2, 50000, [(128, 8, 1, BY_CACHE, 1), (64, 8, 1, BY_CACHE, 1)]),      # ... of one head
