@@ -308,18 +308,15 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
         const int chunks = (n_res + 31) / 32;
         int cap = cap_at(min_units);
         if (variant == 2) {
-            // Few groups leave every compute unit one group or none, and a call takes as long as its longest group.  Measured
-            // with one pair of waves per group (two pairs halve what a group's blocks take; the lines were left where they are)
-            // (8, 4 and 2 kv heads, batch 1 to 12, K4V2 and K8V8, us a call, 4 blocks per group / the other):
-            // - 5 blocks, where 4 make more groups than there are compute units and 5 do not: one sequence, 8 kv heads, a window of two
-            //   chunks, 264..320 groups 11.1..11.4 / 10.6..10.8, 4 kv heads 13.9 / 12.2; 50 such shapes gain 0..16 %.  Where 5
-            //   still make more (312 / 264 groups, 336 / 272 and up) most lose 2..5 %, but not with a window of three
-            //   chunks and more, which is the longest group and slower beside another one (24 caches of 47 blocks, five chunks:
-            //   15.3 / 14.2; -4..+5 %, +1 % on average, up to 320 groups).  A window of one chunk or none is the
-            //   shorter group, and with less than 32 groups over, half of the shapes lose (264 groups -5..+4 %); from 32 over
-            //   they gain 0..7 % (but 12 x 4 kv heads, 288 groups: -4 %).
-            // - 2 blocks, up to 64 groups, where the window is one chunk at most: 9.2 / 8.4 (2 kv heads, 512 tokens), 5..15 % on all shapes.
-            //   A group with two chunks of window takes as long as one with 4 blocks: there 2 blocks are 1 % faster to 4 % slower.
+            // Few groups leave every compute unit one group or none, and a call takes as long as its longest group.  The lines were drawn with one
+            // pair of waves per group.  With the kernels as they stand (two pairs up to kvq::paired_groups; K4V2 and K8V8 within 1 % of
+            // each other unless said), us a call, blocks per group / the other:
+            // - 4 / 5, where 4 make more groups than there are compute units and 5 do not: one sequence, 8 kv heads, a window of two chunks,
+            //   272..320 groups 7.8..8.1 / 7.4, 4 kv heads 8.1 / 7.4; a window of one chunk 8.0 / 7.4 at 272 groups, 7.7 / 7.4 at 312 (below 32 groups
+            //   over, the line still takes 4 there).  Where 5 still make more (328 / 264 groups) 7.7 / 8.2.  With a window of five chunks (24 caches of
+            //   47 blocks, 312 / 264 groups) K4V2 7.7 / 7.7, K8V8 7.9 / 7.7.  (6 blocks where 5 make more: 7.5, 12 x 2 kv heads 7.5.)
+            // - 4 / 2, up to 64 groups, where the window is one chunk at most: 6.4 / 6.0 (2 kv heads, 512 tokens).  With two chunks, where the line
+            //   keeps 4, 6.5 / 6.1 now (2 kv heads, 512 and 900 tokens), and tiles of 8 heads 7.3 / 6.6 (513 tokens), 7.3 / 6.7 (900), 8.4 / 8.2 (2000).
             const long long with4 = per_split * cap_at(4), with5 = per_split * cap_at(5);
             if (with4 >= kCUs + (chunks > 1 ? 1 : 32) && (with5 <= kCUs || (chunks > 2 && with4 <= kCUs + kCUs / 4))) cap = cap_at(5);
             else if (chunks <= 1 && per_split * (n_blocks / 2 + 1) <= kCUs / 4) cap = cap_at(2);
@@ -329,18 +326,20 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
     if (splits > kMaxSplits) splits = kMaxSplits;
     if (splits < 1) splits = 1;
     // The fp16 window rides on the last split, behind the split's blocks and chunk by chunk: a chunk's key and value rows are
-    // each asked for at once, about the time of a few packed blocks.  The window counts as kWindowWeight units per chunk behind
+    // each asked for at once.  The window counts as kWindowWeight units per chunk behind
     // the blocks, and the units are dealt out evenly (the last split gets that many blocks fewer, none at all when its share
-    // is smaller than that).  Measured, batch 16, 8192 tokens, 8 layers: weights 3, 4 and 6 are alike (266..267 us), 1 and 2
-    // make the window's split the straggler (273).
+    // is smaller than that).  A chunk takes about as long as a block (0.48 us, a block 0.54 or, of 8 heads, 0.69), but its rows come behind the
+    // split's blocks, and the weight was set when it took two or three times that.  Measured, us a call, weights 2 / 3 / 4 / 6: batch 16,
+    // 8192 tokens K4V2 31.0 / 30.4 / 31.2 / 30.8, K4V4 35.6 / 35.1 / 35.4 / 35.5; 16 x 4096 tokens K8V8 29.2 / 29.0 / 29.6 / 29.9; 64 x 1000 tokens 18.7 / 18.6 /
+    // 19.0 / 19.2; 15 others, one sequence to 64, within 2 % but for one.
     int window = kWindowWeight * ((n_res + 31) / 32);
     if (n_blocks == 0) splits = 1;
     const int most = n_blocks + (window ? 1 : 0);                // no more splits than blocks (+ one for the window)
     if (splits > most) splits = most;
     if (splits < 1) splits = 1;
     // (never more than the share of a split in front of the window's: with many small splits the window's split takes no
-    // blocks, not even the odd one that is left over.  One sequence, 23 blocks: 11.1 us a call with a block in front of the
-    // window in the same group, 9.1 without)
+    // blocks, not even the odd one that is left over.  With one pair of waves per group and an earlier kernel, one sequence, 23 blocks: 11.1 us a call
+    // with a block in front of the window in the same group, 9.1 without)
     if (splits > 1) {
         const int share = (n_blocks + splits - 2) / (splits - 1);
         if (window > share) window = share;
@@ -368,26 +367,20 @@ SplitPlan plan_splits(int BH, int gq, int width, int n_blocks, int n_res, int fo
 struct DecodeForm { int pairs; bool merges; };
 
 // Two pairs of waves per work-group (launch_decode_short) where the work-groups are few.  Such work-groups hold twice the waves and more
-// registers, so fewer are resident at once (kvq::paired_groups), and beyond that the second half of them waits for the first.  Measured: us a
-// call, one pair / two, or (below 2) the time with one pair over that with two; 32 / 8 heads unless said otherwise.
-// - Several splits, tiles of 4 heads: as long as all are resident (K4V2 520 groups 11.8 / 11.3, 640 groups 11.3 / 10.6, 1056 groups
-//   12.6 / 15.6; K8V8 256 groups 9.9 / 8.9, 544 groups 11.3 / 11.5, 1024 groups 13.7 / 17.4; K16V16 256 groups 12.2 / 10.8, 520 groups
-//   14.6 / 15.7); but where no split has more than 2 units, nor the window 2 chunks to share, up to one work-group per compute unit
-//   (1.01..1.12; more 0.93..1.02).
-// - Several splits, tiles of 8 heads (28 / 4 heads), whose records take longer to merge: with a window of 2 chunks and more, which the pairs share,
-//   the same (1.02..1.37).  Else up to one work-group per compute unit (1.01..1.14); two, if the longest split has 4 units or more (1.03..1.08,
-//   with 2 or 3 units 0.94..1.01; more than two 0.93..1.00).
-// - A single split saves the merge launch.  Up to three work-groups per compute unit 1.03..1.6, at any length (60 to 4128 tokens) and width.
-//   Four of 4 heads: 1.03..1.25 for codes up to 8 bits per key + value element and with an fp16 tensor, 0.84..0.96 for 8-bit keys; of 8
-//   heads 0.69..1.01.  Beyond that:
-//   - blocks are streamed faster by one pair (2048 groups, 256 to 4096 tokens: K4V2 0.87..0.93, K2V2 0.78..0.84; K8V4 1024 to 4096 groups
-//     0.80..1.02; 28 / 4 heads 0.65..0.97), except by tiles of 4 heads where both tensors are as wide: fp16 0.99..1.17, K8V8
-//     from 16 blocks and six work-groups per compute unit on 1.01..1.10 (below 0.84..1.05);
-//   - of a window alone, two pairs of 4 heads share 2 chunks and more (1.02..1.17; 8-bit keys 0.93..0.98, from 4 chunks and six
-//     work-groups per compute unit on 1.02..1.15, so do 8 heads, 1.01..1.12); a single chunk is read faster by one pair (0.72..0.96).
-// The last work-group merges up to 48 splits of 4 heads, 16 records at a time (two pairs with the merge in a launch of their own / in the kernel:
-// 1 x 6059 tokens, 48 splits 10.4 / 10.1, 6955 tokens, 55 splits 10.8 / 10.9; 6 x 2 kv heads, K4V2 48 splits 11.0 / 11.0, 51 splits 11.4 / 11.8,
-// 63 splits 11.2 / 12.0, where one pair takes 11.4) or 16 of 8 heads, in one go (15 splits 10.2 / 9.6, 17 splits 10.3 / 10.4, 33 splits 10.7 / 11.0).
+// registers, so fewer are resident at once (kvq::paired_groups), and beyond that the second half of them waits for the first.  Measured over 432 calls (32 / 8,
+// 28 / 4 and 8 / 2 heads, K4V2, K8V8, K16V16, windows of two chunks and of three or four, 1 to 512 sequences of 60 to 7000 tokens) with the lines as they
+// are: 392 take the fastest form or one within 3 % of it, the mean is 0.8 % over the fastest.  Below: the time with one pair over that with two.
+// - Several splits, as long as all are resident: up to one work-group per compute unit 1.06..1.37 (median 1.2), beyond K4V2 1.01..1.13, K8V8 1.02..1.13,
+//   K16V16 1.01..1.06.  More work-groups: up to half as many again K4V2 0.76..0.80, K8V8 1.00..1.09, K16V16 0.96..1.01; then 0.65..0.9.
+//   (The lines for splits of 2 or 3 units and windows of one chunk were drawn where calls of either kind gained and lost up to 8 %.)
+// - A single split saves the merge launch.  Up to three work-groups per compute unit 1.27..2.1, at any length and width.  Four, of packed blocks
+//   0.85..1.0 (the line still takes two pairs of 4 heads with narrow codes and fp16 there: 8 / 2 heads, 512 sequences of 500 fp16 tokens 44.6 / 52.3).  Beyond:
+//   - blocks are streamed faster by one pair (2048 groups of 500 tokens, K4V2 0.80..0.92) except by tiles of 4 heads where both tensors are as wide
+//     (K8V8 1.03, K16V16 1.16);
+//   - a window alone: tiles of 4 heads 1.01..1.06, K16V16 1.10..1.15, and of 8 heads, for which the line keeps one pair, 1.04..1.06, K16V16 1.16..1.20.
+// The last work-group merges up to 48 splits of 4 heads, 32 records at a time, or 16 of 8 heads, in one go.  The launch's time over the merge's: 4 heads, 2 to 18
+// splits 1.00..1.42, 27 to 48 splits 1.01..1.13, 55 and 56 splits, which the limit leaves to the launch, 1.00..1.13; 8 heads, 2 to 16 splits 0.99..1.37,
+// 18 splits 1.03..1.18 (one sequence of 2200 tokens, K4V2 8.3 / 7.95, K16V16 8.0 / 6.9), 33 splits 1.00..1.03 (more are not merged: 32 lanes per head).
 DecodeForm decode_form(const SplitPlan &sp, int BH, int gq, int kbits, int vbits, int n_blocks, int n_res)
 {
     const int tiles = (gq + 7) / 8, chunks = (n_res + 31) / 32;

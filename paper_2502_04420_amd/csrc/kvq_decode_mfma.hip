@@ -23,8 +23,8 @@
 // (which is what lets 4 waves share a SIMD and hide the memory latency).  Each wave writes its
 // part of the split's partial result itself; the splits are merged by combine_splits.
 //
-// Short caches give few work-groups, each of which takes its blocks one after the other, and a call takes as long as that
-// chain (0.6 us per block, on two of a compute unit's four SIMDs) and two launches.  There a work-group has two such pairs (KVQ_DECODE_PAIRS 2,
+// Short caches give few work-groups, each of which takes its blocks one after the other, and a call of such work-groups takes as long as that
+// chain (0.54 us per block, 0.69 of 8 heads, on two of a compute unit's four SIMDs) and two launches.  There a work-group has two such pairs (KVQ_DECODE_PAIRS 2,
 // kvq_decode_short.hip): each takes half of the split's units, or one the blocks and one the window, their results meet in LDS, a
 // single split writes the outputs, and of several splits the work-group that finishes last merges the records (merge_pairs).
 #include <hip/hip_ext.h>
@@ -704,7 +704,7 @@ __device__ __forceinline__ void scores_rows(const KeyRows &x, int nt, const Quer
 // by which the value wave must shrink what it has accumulated (L.alpha[buf], L.rescale[buf]).
 // The reference maximum only has to keep the numerators in range: it is refreshed (exact maximum over
 // the block) when some score exceeds it by more than 1, so numerators stay <= 2 and the fp16 output
-// operands cannot overflow.  Heads that do not exist see all-zero operands, hence finite values.
+// operands cannot overflow.  Heads that do not exist see the last one's operands (QueryRegs::row), hence no other values than that head's.
 template <int GQ>
 __device__ __forceinline__ void softmax_publish(const float (&s)[2][2], KeyState<GQ> &W, PairLds<GQ> &L, int unit, int lane)
 {
@@ -1038,8 +1038,11 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     // tokens: two or three blocks behind are 3-5 % slower for 4- and 2-bit codes and no faster for 8-bit ones: the
     // memory system is the queue here, more requests in it only wait longer).
     constexpr int DK = 2, DV = 2;
-    // a group without blocks asks for its window rows before it waits for the queries (in the streaming form behind them: that path would hold
-    // registers of the rows over the loop, which has none to spare)
+    // A group without blocks asks for its window rows ahead of the branch between the two kinds of group: the value wave at once, the key wave behind its
+    // queries (whose wait counts the loads behind them).  In the streaming form of packed layers both ask behind the branch: that path would
+    // hold registers of the rows over the loop, which has none to spare.  Launches of such groups alone, us a call, with the rows ahead and
+    // their values on the vector units / so: 32 / 8 heads, 200 sequences of 60 tokens K4V2 15.4 / 13.3, K8V8 18.6 / 13.3, 640 of 25 tokens 25.3 / 21.3; 28 / 4
+    // heads, 64 of 33 tokens 7.3 / 4.7, 320 of 100 tokens 25.6 / 16.5.
     constexpr bool kEarlyRows = !kFast || PAIRS > 1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // wave-uniform on purpose: block indices stay scalar
@@ -1070,8 +1073,8 @@ __global__ __launch_bounds__(128 * PAIRS, (resident_waves<KB, VB, PAIRS>())) voi
     int blocks = (u1 < a.n_blocks ? u1 : a.n_blocks) - u0, first_chunk = 0, chunks = u1 > a.n_blocks ? u1 - a.n_blocks : 0;
     int steps = blocks + chunks;                  // of the pair with most units: every wave meets that many barriers
     if constexpr (PAIRS > 1) {
-        // the window's chunks go to the last pairs (to all, where there are no blocks), the blocks to those in front: a chunk
-        // takes as long as two blocks or three, and the window's split has few blocks or none
+        // the window's chunks go to the last pairs (to all, where there are no blocks), the blocks to those in front: the window's split has few blocks or
+        // none, and a chunk (0.48 us) takes about as long as one
         static_assert(PAIRS == 2, "all units to both pairs, or the window to one and the blocks to the other");
         if (blocks == 0 || chunks == 0) {
             const int units = blocks + chunks, lower = units >> 1, mine = pair ? units - lower : lower, first = pair ? lower : 0;

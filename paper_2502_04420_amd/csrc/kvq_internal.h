@@ -151,7 +151,7 @@ struct PrefillForm { int waves, row_heads, order; };
 PrefillForm prefill_form(const PrefillArgs &a, int part_slots);
 size_t prefill_unit_bytes();     // scratch bytes per packed unit (32 tokens) of one (batch, kv head) cache
 size_t prefill_piece_bytes();    // bytes of the partial results of one piece of a query tile (256 rows; part_o, part_ml)
-constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges: three rounds of reads, more take longer than the launch
+constexpr int kMergeSplits = 48; // most splits of 4 heads that a work-group of launch_decode_short merges, in two rounds of reads (decode_form has times on both sides)
 constexpr int kMaxTickets = 23;   // arrival counters that a selection record has room for: the decode kernel's (ShortDecodeArgs::tickets), the last one the channel selection's
 size_t prefill_ticket_offset();  // where in a selection record they are: bytes that the record itself leaves unused
 size_t prefill_select_bytes();   // bytes of the channel-selection record of one (batch, kv head) cache

@@ -1396,7 +1396,9 @@ __global__ __launch_bounds__(32 * kMergeRows) void prefill_merge(PrefillArgs a, 
 // planned): 512 queries over 24576 tokens 833 / 292, 300 over 8000 297 / 129, a 2000-token prompt of 2 kv heads
 // 92 / 63, of 8 kv heads 106 / 100 (finer cuts 106..122: the partial results outweigh the even load).  The constants are those
 // of compact units (36 products); units with all low parts (48) or fp16 keys (32) count the same.  Of 163 calls of all forms,
-// 17 to 30000 tokens, 8 queries and more, none takes longer than with whole tiles.
+// 17 to 30000 tokens, 8 queries and more, none takes longer than with whole tiles.  (A piece's start has become 2.5 us shorter since the two costs were set.  With
+// kPieceCost 2, 3, 4 and 5, 27 calls of 8 to 9000 queries over 1500 to 32000 tokens are within 1.5 % of each other and no value is ahead: 512 over 24576 tokens
+// 250.8 / 247.5 / 248.5 / 250.1, 512 over 8000 106.0 / 104.4 / 105.2 / 104.5, 8 / 2 heads, prompts of 4000 and 9000 tokens 75.2 / 75.5 / 74.7 / 73.9 and 229 / 230 / 230 / 231.)
 constexpr int kPieceCost = 4;
 constexpr int kMergeCost = 4;
 constexpr int kPartialsPerUnit = 20;
