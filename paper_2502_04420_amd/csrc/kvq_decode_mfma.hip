@@ -798,7 +798,7 @@ __device__ __forceinline__ void output_packed(const CodeRegs<VB> &blk, uint32_t 
 // Output contribution of 32 fp16 rows (numerators of rows past the end are zero).  The rows are the B operand as they are, but for the order: a lane
 // has 8 channels of 8 tokens, and operand e is the 8 tokens of channel 8 n + e, one byte permutation per pair of tokens.  The numerators are the A
 // operand, read from the hand-off tile: 2^12 p as an fp16 number and, 2^14 times as large, what that leaves, the nearest fp16 number too (p <= 2).  Together they
-// are p to a unit of its 24th bit for p >= 2^-22 and to 2^-47 below that.  The high part is the nearest number to 2^12 p + 2^-24 and so never zero (the low
+// are p to a unit of its 24th bit (below 2^-12 two) for p >= 2^-22 and to 2^-47 below that.  The high part is the nearest number to 2^12 p + 2^-24 and so never zero (the low
 // part makes up for it): an infinite value stays infinite under any weight.
 // R[e]: rows 4 rq + i as everywhere (high and low parts of heads 2 rq, 2 rq + 1), channel 8 n + e, times 2^12 (low parts 2^26).
 // With vector multiply-adds instead (16 tokens x 4 channels x the heads, 256 instructions for 4 heads against about 75 here) this was the

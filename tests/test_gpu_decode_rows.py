@@ -174,13 +174,22 @@ def test_infinite_values_under_small_weights(kvq_mod, power, vb):
     assert torch.isnan(out[:, 5:7]).all() and torch.isfinite(out[:, 7:]).all() and torch.isfinite(out[:, 0]).all()
 
 
-SWEEPS = {"short": (1, 8, 2, 4133, 4, 2), "streaming": (64, 8, 2, 2000, 4, 4), "tiles of 8": (16, 14, 2, 3000, 8, 2), "half": (2, 8, 2, 3000, 16, 16)}
+SWEEPS = {"short": (1, 8, 2, 4133, 4, 2), "streaming": (64, 8, 2, 2000, 4, 4), "tiles of 8": (16, 14, 2, 3000, 8, 2)}
+
+
+def _bell(rows, seed):
+    """fp16 [rows, 128] of unit variance, by whole numbers: the same on every machine."""
+    with np.errstate(over="ignore"):
+        x = np.arange(rows * 128, dtype=np.uint64) + np.uint64(seed << 40)
+        for shift, factor in ((30, 0xBF58476D1CE4E5B9), (27, 0x94D049BB133111EB), (31, 0x9E3779B97F4A7C15), (29, 0xBF58476D1CE4E5B9)):
+            x = (x ^ (x >> np.uint64(shift))) * np.uint64(factor)
+    total = sum(((x >> np.uint64(16 * k)) & np.uint64(0xffff)).astype(np.int64) for k in range(4))       # of four uniform numbers
+    return torch.from_numpy(((total - 131070) / 37837.0).astype(np.float16)).view(rows, 128)
 
 
 def sweep_outputs(module, batch, hq, hkv, T, kb, vb):
     """Outputs of one layer's decode attention, of the last sequence."""
-    g = torch.Generator().manual_seed(9)
-    K, V, q = (torch.randn(n, 128, generator=g).half().cuda() for n in (hkv * T, hkv * T, hq))
+    K, V, q = _bell(hkv * T, 1).cuda(), _bell(hkv * T, 2).cuda(), _bell(hq, 3).cuda()
     cache = module.KVQ(1, batch, hq, hkv, 128, T, [kb], [vb])
     # every sequence is the same one, its tokens rolled by another 131
     roll = lambda x: torch.stack([torch.roll(x.view(hkv, T, 128), 131 * b, 1) for b in range(batch)])     # noqa: E731
