@@ -322,15 +322,18 @@ __global__ __launch_bounds__(64 * WAVES) void combine_splits(DecodeArgs a)
     asm volatile("" ::"s"(a.splits), "s"(a.part_ml), "s"(a.part_o), "s"(a.out));
     const size_t row = blockIdx.x;
     const int lane = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row * a.splits;
-    const float4 *po = reinterpret_cast<const float4 *>(a.part_o + row * a.splits * kD) + lane;
+    // splits that do not exist lie past the row's resources and read as zero (another record in their place, times the weight zero, would be no
+    // number where it holds an infinity)
+    constexpr int kRecord = (int)(kD * sizeof(float));
+    const __amdgpu_buffer_rsrc_t ml = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + row * a.splits * 2, 0, a.splits * (int)(2 * sizeof(float)), 0x00020000);
+    const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(a.part_o + row * a.splits * kD, 0, a.splits * kRecord, 0x00020000);
     float2 r[W];
     float4 x[W];
 #pragma unroll
     for (int k = 0; k < W; k++) {
-        const int sp = g + 2 * WAVES * k, spc = sp < a.splits ? sp : 0;
-        r[k] = ml[spc];
-        x[k] = po[(size_t)spc * (kD / 4)];
+        const int sp = g + 2 * WAVES * k;
+        r[k] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(ml, sp * (int)(2 * sizeof(float)), 0, 0));
+        x[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(po, sp * kRecord + 16 * lane, 0, 0));
     }
     float M = -INFINITY;
 #pragma unroll

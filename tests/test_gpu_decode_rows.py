@@ -121,6 +121,28 @@ def test_infinite_values_stay_infinite_in_merged_splits(kvq_mod, gq, vb):
         assert torch.equal(outs[0][0][:, rest], outs[1][0][:, rest]), splits
 
 
+@pytest.mark.parametrize("batch,gq,splits", [(300, 4, s) for s in (2, 3, 5, 8, 9, 13, 16, 17)] + [(1, 7, 17), (1, 8, 19), (1, 4, 49), (1, 1, 63), (2, 7, 65), (1, 7, 70)])
+def test_infinite_values_stay_infinite_where_a_launch_merges(kvq_mod, batch, gq, splits):
+    """The same for splits that a launch of their own merges: one sequence's first and last split hold an infinity each, which its outputs show in their
+    channels and nothing else does, whatever number of records the launch's threads have room for."""
+    T, D = 32 * 72 + 9 if batch < 10 else 32 * 20 + 9, 128
+    g = torch.Generator().manual_seed(7)
+    q, K, V = (torch.randn(1, h, n, D, generator=g).half().cuda().expand(batch, h, n, D).contiguous() for h, n in ((gq, 1), (1, T), (1, T)))
+    outs = []
+    for bad in (False, True):
+        if bad:
+            V[0, 0, 3, 5], V[0, 0, T - 3, 77] = float("inf"), float("-inf")
+        cache = kvq_mod.KVQ(1, batch, gq, 1, D, T, [16], [16])
+        cache.set_decode_options(0, splits)
+        cache.quantize_append(0, K, V)
+        outs.append(cache.decode_attention(0, q[:, :, 0].contiguous()).cpu())
+        cache.close()
+    plain, out = outs
+    assert (out[0, :, 5] == float("inf")).all() and (out[0, :, 77] == float("-inf")).all(), (out[0, :, 5], out[0, :, 77])
+    plain[0, :, 5], plain[0, :, 77] = float("inf"), float("-inf")
+    assert torch.equal(out, plain)
+
+
 @pytest.mark.parametrize("vb", [4, 16])
 @pytest.mark.parametrize("gq", [1, 4, 7])
 def test_numerators_far_below_the_largest(kvq_mod, gq, vb):
